@@ -330,7 +330,7 @@ __global__ __launch_bounds__(kBlock) void k_pattern_round(SigParams p) {
         // S states per thread and iteration, every load of one kind issued
         // for all of them before any value is used (the round is bound by
         // the latency of the column reads and the dependent bit gathers)
-        constexpr int S = 4;
+        constexpr int S = KC <= 8 ? 4 : 2;
         for (size_t base = static_cast<size_t>(blockIdx.x) * (S * kBlock); base < p.N;
              base += static_cast<size_t>(gridDim.x) * (S * kBlock)) {
             size_t q[S];
@@ -354,9 +354,18 @@ __global__ __launch_bounds__(kBlock) void k_pattern_round(SigParams p) {
     } else {
         for (size_t q = global_tid(); q < p.N; q += grid_stride()) {
             uint32_t label = acc_bit(p.accbits, static_cast<uint32_t>(q));
-            for (uint32_t j = 0; j < keff; ++j) {
-                const uint32_t t = p.cols[static_cast<size_t>(p.colmap[j]) * p.N + q];
-                label |= acc_bit(p.accbits, t) << (j + 1);
+            // letters in batches of 8: their targets, then the targets' bits,
+            // are loaded together
+            for (uint32_t j0 = 0; j0 < keff; j0 += 8) {
+                uint32_t t[8];
+#pragma unroll
+                for (uint32_t j = 0; j < 8; ++j)
+                    t[j] = p.cols[static_cast<size_t>(p.colmap[j0 + j < keff ? j0 + j : j0]) * p.N + q];
+#pragma unroll
+                for (uint32_t j = 0; j < 8; ++j) {
+                    const uint32_t bit = acc_bit(p.accbits, t[j]);
+                    if (j0 + j < keff) label |= bit << (j0 + j + 1);
+                }
             }
             emit(q, label);
         }
@@ -2677,6 +2686,7 @@ void launch_pattern_kernel(const RoundArgs &a, hipStream_t s) {
         case 3: launch_kernel(k_pattern_round<3>, grid, block, 0, s, sp); break;
         case 4: launch_kernel(k_pattern_round<4>, grid, block, 0, s, sp); break;
         case 8: launch_kernel(k_pattern_round<8>, grid, block, 0, s, sp); break;
+        case 16: launch_kernel(k_pattern_round<16>, grid, block, 0, s, sp); break;
         default: launch_kernel(k_pattern_round<0>, grid, block, 0, s, sp); break;
     }
 }
