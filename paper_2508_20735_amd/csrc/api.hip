@@ -189,7 +189,7 @@ struct Ctx {
     // the column list last uploaded, and the allocation it went to
     std::vector<uint32_t> colmap_on_device;
     uint64_t colmap_on_device_in = 0;
-    Buffer reach_visited, reach_qa, reach_qb, reach_flags, reach_dense, reach_orig, sub_delta,
+    Buffer reach_ctl, reach_qa, reach_qb, reach_dense, reach_orig, sub_delta,
         sub_acc, sub_block;
     Buffer sort_keys0, sort_keys1, sort_vals0, sort_vals1, sort_hist, sort_partials,
         sort_runhead, sort_m;
@@ -1259,69 +1259,79 @@ int minimise_impl(Ctx &c, uint32_t n, uint32_t k, const uint32_t *delta, const u
 int minimise_pruned(Ctx &c, uint32_t n, uint32_t k, const uint32_t *delta, const uint8_t *acc,
                     uint32_t *block_out, dfa_quotient *q, const dfa_options &o, dfa_stats *st) {
     if (o.start >= n) return fail(DFA_EINVAL, "start (%u) >= n (%u)", o.start, n);
-    const size_t words64 = (static_cast<size_t>(n) + 63) / 64;
     const size_t ntiles = (static_cast<size_t>(n) + kScanTile - 1) / kScanTile;
     DFA_TRY(c.flags.ensure(4 * sizeof(uint32_t), "flags"));
     DFA_TRY(c.scalars.ensure(16 * sizeof(uint32_t), "scalars"));
-    DFA_TRY(c.reach_visited.ensure(words64 * sizeof(unsigned long long), "visited bits"));
+    DFA_TRY(c.reach_ctl.ensure((kBfsBatch * kBfsSetWords + 1) * sizeof(uint32_t), "search counters"));
     DFA_TRY(c.reach_qa.ensure(static_cast<size_t>(n) * sizeof(uint32_t), "search queue"));
     DFA_TRY(c.reach_qb.ensure(static_cast<size_t>(n), "search marks"));
-    DFA_TRY(c.reach_flags.ensure(static_cast<size_t>(n) * sizeof(uint32_t), "reachable flags"));
     DFA_TRY(c.reach_dense.ensure(static_cast<size_t>(n) * sizeof(uint32_t), "reachable numbering"));
     DFA_TRY(c.reach_orig.ensure(static_cast<size_t>(n) * sizeof(uint32_t), "reachable states"));
     DFA_TRY(c.partials.ensure((ntiles + 1) * sizeof(uint32_t), "scan partials"));
     HIP_TRY(hipEventRecord(c.ev_p0, c.stream));
     uint32_t *err = c.flags.as<uint32_t>();
-    HIP_TRY(hipMemsetAsync(err, 0, sizeof(uint32_t), c.stream));
+    // counters of a batch of dense levels, then the queue's length
+    uint32_t *stored = c.reach_ctl.as<uint32_t>();
+    uint32_t *sizes = stored + kBfsBatch * kBfsSetWords;
+    ReachArgs ra{delta, n, k, c.reach_qb.as<uint8_t>(), c.reach_qa.as<uint32_t>(), sizes, stored,
+                 err};
+    {
+        ZeroList z{};
+        DFA_TRY(zero_add(z, c.flags, sizeof(uint32_t)));
+        DFA_TRY(zero_add(z, c.reach_qb, n));
+        launch_zero(z, c.stream);
+    }
+    // the search's kernels stop at the check's flag themselves, so the host
+    // does not wait for it before it queues them
     launch_check_targets(delta, static_cast<uint64_t>(n) * k, n, err, c.stream);
-    HIP_TRY(hipGetLastError());
-    DFA_TRY(read_back(c, err, sizeof(uint32_t)));
-    if (c.pinned[0]) return fail(DFA_EINVAL, "a transition target is >= n");
-
-    uint32_t *sizes = c.scalars.as<uint32_t>();
-    ReachArgs ra{delta, n, k, c.reach_visited.as<unsigned long long>(), c.reach_qb.as<uint8_t>(),
-                 c.reach_qa.as<uint32_t>(), sizes};
-    HIP_TRY(hipMemsetAsync(ra.visited, 0, words64 * sizeof(unsigned long long), c.stream));
-    HIP_TRY(hipMemsetAsync(ra.mark, 0, n, c.stream));
-    launch_bfs_init(ra, o.start, c.stream);
     // small frontiers: a queue expanded in one workgroup; large ones: dense
-    // levels over the marks (frontier mark f, alternating 2 / 3)
+    // levels over the marks (frontier mark f, alternating 2 / 3), queued
+    // kBfsBatch at a time
     const uint64_t cap = bfs_narrow_cap();
-    bool dense = false;
+    const bool never_dense = static_cast<uint64_t>(n) * k <= cap;
+    bool init = true, dense = false;
     uint8_t f = 2;
     for (;;) {
-        HIP_TRY(hipGetLastError());
-        if (!dense) {
-            DFA_TRY(read_back(c, sizes, sizeof(uint32_t)));
-            const uint32_t frontier = c.pinned[0];
-            if (frontier == 0) break;
-            if (static_cast<uint64_t>(frontier) * k <= cap) {
-                launch_bfs_narrow(ra, c.stream);
-                continue;
-            }
-            launch_bfs_list_to_marks(ra, frontier, f, c.stream);
-            dense = true;
+        const bool from_list = !dense;
+        if (from_list) launch_bfs_narrow(ra, o.start, init, c.stream);
+        if (!never_dense) {
+            launch_bfs_reset(ra, false, c.stream);
+            if (from_list) launch_bfs_list_to_marks(ra, f, c.stream);
+            uint8_t fl = f;
+            for (uint32_t l = 0; l < kBfsBatch; ++l, fl ^= 1)
+                launch_bfs_dense(ra, fl, fl ^ 1, l, from_list && l == 0, c.stream);
         }
-        const uint8_t nf = f == 2 ? 3 : 2;
-        launch_bfs_dense(ra, f, nf, c.stream);
         HIP_TRY(hipGetLastError());
-        DFA_TRY(read_back(c, sizes + 1, sizeof(uint32_t)));
-        const uint32_t stored = c.pinned[0];  // >= the new states; 0 iff none
-        if (stored == 0) break;
-        f = nf;
-        if (static_cast<uint64_t>(stored) * k <= cap) {
+        if (init) {
+            HIP_TRY(hipMemcpyAsync(c.pinned + kBfsBatch * kBfsSetWords + 1, err, sizeof(uint32_t),
+                                   hipMemcpyDeviceToHost, c.stream));
+        }
+        DFA_TRY(read_back(c, stored, (kBfsBatch * kBfsSetWords + 1) * sizeof(uint32_t)));
+        if (init && c.pinned[kBfsBatch * kBfsSetWords + 1])
+            return fail(DFA_EINVAL, "a transition target is >= n");
+        init = false;
+        // a narrow launch ends with an empty frontier or one that is too large
+        if (from_list && c.pinned[kBfsBatch * kBfsSetWords] == 0) break;
+        uint64_t last = 0;  // marks stored by the last level that ran (>= its new states)
+        for (uint32_t l = 0; l < kBfsBatch; ++l) {
+            last = 0;
+            for (uint32_t i = 0; i < kBfsSpread; ++i)
+                last += c.pinned[l * kBfsSetWords + i * kBfsStride];
+            f ^= 1;
+            if (last * k <= cap) break;
+        }
+        if (last == 0) break;  // no new state
+        dense = last * k > cap;
+        if (!dense) {
+            launch_bfs_reset(ra, true, c.stream);
             launch_bfs_marks_to_list(ra, f, c.stream);
-            dense = false;
         }
     }
     // dense numbering of the reachable states; m = their count
-    launch_reach_flags(ra.mark, n, c.reach_flags.as<uint32_t>(), c.stream);
-    launch_dense_leaders(c.reach_flags.as<uint32_t>(), n, c.partials.as<uint32_t>(),
-                         c.reach_dense.as<uint32_t>(), c.reach_orig.as<uint32_t>(), sizes + 2,
-                         c.stream);
+    sizes = c.scalars.as<uint32_t>();
+    launch_dense_marks(ra.mark, n, o.start, c.partials.as<uint32_t>(), c.reach_dense.as<uint32_t>(),
+                       c.reach_orig.as<uint32_t>(), sizes + 2, sizes + 3, c.stream);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(hipMemcpyAsync(sizes + 3, c.reach_dense.as<uint32_t>() + o.start, sizeof(uint32_t),
-                           hipMemcpyDeviceToDevice, c.stream));
     DFA_TRY(read_back(c, sizes + 2, 2 * sizeof(uint32_t)));
     const uint32_t m = c.pinned[0], sub_start = c.pinned[1];
     DFA_TRY(c.sub_delta.ensure(static_cast<size_t>(m) * k * sizeof(uint32_t), "sub-automaton"));
@@ -2198,10 +2208,11 @@ void for_each_buffer(Ctx &c, F &&f) {
                       &c.scalars, &c.multi, &c.active, &c.accbits, &c.counters, &c.presence,
                       &c.presence_packed, &c.lab8, &c.stage_delta, &c.stage_acc, &c.stage_block,
                       &c.stage_qdelta, &c.stage_qacc, &c.stage_delta_b, &c.stage_acc_b,
-                      &c.visited, &c.visited2, &c.front0, &c.front1, &c.parts, &c.tile_part,
+                      &c.visited, &c.visited2, &c.front0, &c.front1,
+                      &c.parts, &c.tile_part,
                       &c.seg_words, &c.batch_in, &c.batch_out, &c.new_leader, &c.moved,
-                      &c.chg, &c.single, &c.touched, &c.chg_sum, &c.reach_visited, &c.reach_qa,
-                      &c.reach_qb, &c.reach_flags, &c.reach_dense, &c.reach_orig, &c.sub_delta,
+                      &c.chg, &c.single, &c.touched, &c.chg_sum, &c.reach_ctl, &c.reach_qa,
+                      &c.reach_qb, &c.reach_dense, &c.reach_orig, &c.sub_delta,
                       &c.sub_acc, &c.sub_block, &c.sort_keys0, &c.sort_keys1, &c.sort_vals0,
                       &c.sort_vals1, &c.sort_hist, &c.sort_partials, &c.sort_runhead,
                       &c.sort_m, &c.serve_in, &c.small_jobs, &c.small_results,

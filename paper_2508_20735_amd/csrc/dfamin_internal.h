@@ -330,30 +330,42 @@ void launch_leader_move(const LeaderArgs &a, hipStream_t s);
 void launch_leader_end(const LeaderArgs &a, hipStream_t s);
 
 // ---- reachability and the reachable sub-automaton (reach_kernels.hip) ----
+// Dense levels queued per host wait, and their counters: per level a set of
+// kBfsSpread words on lines of their own (one word for every workgroup's
+// atomic serialises).
+constexpr uint32_t kBfsBatch = 8;
+constexpr uint32_t kBfsSpread = 16;
+constexpr uint32_t kBfsStride = 16;
+constexpr uint32_t kBfsSetWords = kBfsSpread * kBfsStride;
 struct ReachArgs {
     const uint32_t *delta;           // row-major n x k, targets < n (checked first)
     uint32_t n, k;
-    unsigned long long *visited;     // n/64 words, zero before the search
     uint8_t *mark;                   // n: 0 unvisited, 1 settled, 2 / 3 dense frontier
     uint32_t *qa;                    // frontier queue, n entries
-    uint32_t *sizes;                 // [0] entries in qa, [1] marks stored by a dense level
+    uint32_t *sizes;                 // [0] entries in qa
+    uint32_t *stored;                // kBfsBatch sets of marks stored by the dense levels
+    const uint32_t *err;             // a target is out of range: no kernel searches
 };
 // *err = 1 if a target is >= n.
 void launch_check_targets(const uint32_t *delta, uint64_t total, uint32_t n, uint32_t *err,
                           hipStream_t s);
-void launch_bfs_init(const ReachArgs &a, uint32_t start, hipStream_t s);
-// Expands levels in one workgroup while sizes[0] * k <= bfs_narrow_cap().
-void launch_bfs_narrow(const ReachArgs &a, hipStream_t s);
+// Expands levels in one workgroup, from `start` (init) or the listed
+// frontier, while sizes[0] * k <= bfs_narrow_cap().
+void launch_bfs_narrow(const ReachArgs &a, uint32_t start, bool init, hipStream_t s);
 uint32_t bfs_narrow_cap();
-// The count listed states of qa become the frontier mark f.
-void launch_bfs_list_to_marks(const ReachArgs &a, uint32_t count, uint8_t f, hipStream_t s);
-// One dense level: frontier f expands into nf; sizes[1] = marks stored
-// (0 iff no new state).
-void launch_bfs_dense(const ReachArgs &a, uint8_t f, uint8_t nf, hipStream_t s);
-// The states marked f settle and are listed in qa; sizes[0] = their number.
+// A listed frontier too large for the narrow kernel becomes the mark f.
+void launch_bfs_list_to_marks(const ReachArgs &a, uint8_t f, hipStream_t s);
+// Dense level `level` of a batch: frontier f expands into nf; counter set
+// `level` = marks stored (0 iff no new state).  It runs if the listed
+// frontier was too large for the narrow kernel (after_list), or the level
+// before it stored more than that; level 0 otherwise always runs.
+void launch_bfs_dense(const ReachArgs &a, uint8_t f, uint8_t nf, uint32_t level, bool after_list,
+                      hipStream_t s);
+// The states marked f settle and are listed in qa; sizes[0] (zero before) =
+// their number.
 void launch_bfs_marks_to_list(const ReachArgs &a, uint8_t f, hipStream_t s);
-// flags[q] = q if marked (reached), all ones otherwise.
-void launch_reach_flags(const uint8_t *mark, size_t n, uint32_t *flags, hipStream_t s);
+// Clears the level counters, and sizes[0] with `list`.
+void launch_bfs_reset(const ReachArgs &a, bool list, hipStream_t s);
 // sub_delta[i][a] = dense[delta[orig[i]][a]], sub_acc[i] = acc[orig[i]], i < *m_dev.
 void launch_sub_dfa(const uint32_t *delta, const uint8_t *acc, uint32_t k, const uint32_t *orig,
                     const uint32_t *dense, const uint32_t *m_dev, uint32_t m_host,
@@ -399,6 +411,12 @@ void launch_dense_leaders(const uint32_t *block, size_t N, uint32_t *partials, u
 
 // qdelta[b*k + a] = dense[block[delta[l*k + a]]], qacc[b] = acc[l] for
 // l = leader_of[b]; *qstart = dense[block[start]].  dq: n words of scratch.
+// The same numbering of the marked states (mark[q] != 0): dense[q],
+// leader_of[dense[q]] = q, *num = their count; *start_dense = dense[start].
+void launch_dense_marks(const uint8_t *mark, size_t n, uint32_t start, uint32_t *partials,
+                        uint32_t *dense, uint32_t *leader_of, uint32_t *num,
+                        uint32_t *start_dense, hipStream_t s);
+
 void launch_quotient(const uint32_t *delta, const uint8_t *acc, uint32_t k,
                      const uint32_t *block, const uint32_t *dense, const uint32_t *leader_of,
                      const uint32_t *num_blocks, uint32_t n, uint32_t start, uint32_t *dq,

@@ -7,12 +7,19 @@
 // the frontier of an even / odd level) and a frontier queue.  A frontier of
 // at most kNarrowCap / k states is expanded inside one workgroup, level after
 // level, with both queues in LDS (long thin searches, such as chains, then
-// cost no launch per level; a visited bitmap with atomics dedupes within the
+// cost no launch per level; an atomic on the mark's word dedupes within the
 // workgroup).  A larger frontier is expanded by dense levels: every state is
 // scanned, the frontier ones expand, and unvisited targets get the next
 // level's mark by plain stores (several writers store the same value), so
 // wide levels use no atomics on the visited set.  Every state is marked once,
 // so both loops end.
+//
+// The host queues a narrow launch and several dense levels at a time; each
+// decides on the device whether it still has work (the marks that the level
+// before it stored, the target check), so the host waits once per batch of
+// levels, not once per level.
+#include <algorithm>
+
 #include "device_common.h"
 
 namespace dfamin {
@@ -20,14 +27,6 @@ namespace {
 
 constexpr uint32_t kNarrowThreads = 1024;
 constexpr uint32_t kNarrowCap = 4096;  // LDS queue entries (two queues: 32 KB)
-
-// Sets t's visited bit; true if this call set it.
-__device__ __forceinline__ bool visit(unsigned long long *visited, uint32_t t) {
-    const unsigned long long bit = 1ull << (t & 63);
-    unsigned long long *w = visited + (t >> 6);
-    if (__hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit) return false;
-    return (atomicOr(w, bit) & bit) == 0;
-}
 
 // *err = 1 if some target is >= n (every later step indexes with targets).
 __global__ __launch_bounds__(kBlock) void k_check_targets(const uint32_t *__restrict__ delta,
@@ -38,25 +37,35 @@ __global__ __launch_bounds__(kBlock) void k_check_targets(const uint32_t *__rest
     wave_set_flag(err, bad);
 }
 
-__global__ void k_bfs_init(ReachArgs a, uint32_t start) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    a.visited[start >> 6] |= 1ull << (start & 63);
-    a.mark[start] = 1;
-    a.qa[0] = start;
-    a.sizes[0] = 1;
-    a.sizes[1] = 0;
+// Marks t as settled if it is unvisited; true for the one caller that did.
+// (While the narrow kernel runs, every mark is 0 or 1.)
+__device__ __forceinline__ bool settle(uint8_t *mark, uint32_t t) {
+    if (__hip_atomic_load(mark + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) return false;
+    const uint32_t sh = 8 * (t & 3);
+    uint32_t *w = reinterpret_cast<uint32_t *>(mark) + (t >> 2);
+    return ((atomicOr(w, 1u << sh) >> sh) & 0xFFu) == 0;
 }
 
 // One workgroup: expands levels while the frontier times k fits kNarrowCap,
-// then leaves the frontier in qa / sizes[0].
-__global__ __launch_bounds__(kNarrowThreads) void k_bfs_narrow(ReachArgs a) {
+// then leaves the frontier in qa / sizes[0].  The search starts at `start`
+// (init), or continues from qa.
+__global__ __launch_bounds__(kNarrowThreads) void k_bfs_narrow(ReachArgs a, uint32_t start,
+                                                               uint32_t init) {
     __shared__ uint32_t buf[2][kNarrowCap];
     __shared__ uint32_t sz[2];
+    if (*a.err) return;
     const uint32_t tx = threadIdx.x;
     const uint32_t k = a.k;
-    uint32_t s = a.sizes[0];
-    if (static_cast<uint64_t>(s) * k > kNarrowCap) return;  // the host checked; stay safe
-    for (uint32_t i = tx; i < s; i += kNarrowThreads) buf[0][i] = a.qa[i];
+    uint32_t s = init ? 1u : a.sizes[0];
+    if (!init && static_cast<uint64_t>(s) * k > kNarrowCap) return;  // the host checked; stay safe
+    if (init) {
+        if (tx == 0) {
+            buf[0][0] = start;
+            a.mark[start] = 1;
+        }
+    } else {
+        for (uint32_t i = tx; i < s; i += kNarrowThreads) buf[0][i] = a.qa[i];
+    }
     if (tx == 0) sz[0] = s;
     __syncthreads();
     uint32_t cur = 0;
@@ -71,12 +80,8 @@ __global__ __launch_bounds__(kNarrowThreads) void k_bfs_narrow(ReachArgs a) {
         for (uint32_t i = tx; i < work; i += kNarrowThreads) {
             const uint32_t q = buf[cur][i / k];
             const uint32_t t = a.delta[static_cast<size_t>(q) * k + (i % k)];
-            // at most one entry per (state, letter) pair: pos < s * k <= kNarrowCap;
-            // states settled by dense levels carry a mark, not a bit
-            if (a.mark[t] == 0 && visit(a.visited, t)) {
-                a.mark[t] = 1;
-                buf[nxt][atomicAdd(&sz[nxt], 1u)] = t;
-            }
+            // at most one entry per (state, letter) pair: pos < s * k <= kNarrowCap
+            if (settle(a.mark, t)) buf[nxt][atomicAdd(&sz[nxt], 1u)] = t;
         }
         __syncthreads();
         cur = nxt;
@@ -86,46 +91,104 @@ __global__ __launch_bounds__(kNarrowThreads) void k_bfs_narrow(ReachArgs a) {
     if (tx == 0) a.sizes[0] = s;
 }
 
-// Queue -> marks: the listed states become the frontier of a dense level.
+// Queue -> marks: the listed states become the frontier of a dense level
+// (nothing to do while the frontier still suits the narrow kernel).
 __global__ __launch_bounds__(kBlock) void k_bfs_list_to_marks(ReachArgs a, uint8_t f) {
+    if (*a.err) return;
     const uint32_t s = a.sizes[0];
+    if (static_cast<uint64_t>(s) * a.k <= kNarrowCap) return;
     for (size_t i = global_tid(); i < s; i += grid_stride()) a.mark[a.qa[i]] = f;
 }
 
 // One dense level: states marked f expand (unvisited targets get nf) and
-// settle.  sizes[1] += number of marks stored (an upper bound of the new
-// states: two lanes may store the same target; zero iff none was stored).
-__global__ __launch_bounds__(kBlock) void k_bfs_dense(ReachArgs a, uint8_t f, uint8_t nf) {
+// settle.  The level's counters receive the number of marks stored (an
+// upper bound of the new states: two lanes may store the same target; zero
+// iff none was stored).  Level j of a batch writes counter set j; it runs if
+// the level before it stored more than the narrow kernel takes (after_list:
+// if the listed frontier is that large; the first level of a batch that
+// continues dense levels always runs).
+//
+// Bound by the frontier's rows and their random mark reads (the marks fit
+// L2).  S states per thread, a word of marks at a time; the count goes out as
+// one atomic per workgroup, spread over kBfsSpread lines: one atomic per
+// wave on a single word made a level of 2^20 states 190 us (16,384 waves,
+// about 11 ns each); this one takes about 12.
+template <int KC>
+__global__ __launch_bounds__(kBlock) void k_bfs_dense(ReachArgs a, uint8_t f, uint8_t nf,
+                                                      uint32_t level, uint32_t after_list) {
+    __shared__ uint32_t part[kBlock / 64];
+    if (*a.err) return;
+    if (after_list) {
+        if (static_cast<uint64_t>(a.sizes[0]) * a.k <= kNarrowCap) return;
+    } else if (level > 0) {
+        const uint32_t *prev = a.stored + (level - 1) * kBfsSetWords;
+        uint32_t v = lane_id() < kBfsSpread ? prev[lane_id() * kBfsStride] : 0u;
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
+        if (static_cast<uint64_t>(v) * a.k <= kNarrowCap) return;  // uniform over the grid
+    }
+    constexpr int S = 4;  // states per thread: one word of marks
     uint32_t stored = 0;
-    for (size_t q = global_tid(); q < a.n; q += grid_stride()) {
-        if (a.mark[q] != f) continue;
-        const uint32_t *row = a.delta + q * a.k;
-        // letters in groups of 8: the row entries, then their marks, are
-        // loaded together before any store
-        for (uint32_t j0 = 0; j0 < a.k; j0 += 8) {
-            const uint32_t m = a.k - j0 < 8 ? a.k - j0 : 8;
-            uint32_t t[8];
-            uint8_t mk[8];
+    const size_t words = (static_cast<size_t>(a.n) + S - 1) / S;
+    for (size_t i = global_tid(); i < words; i += grid_stride()) {
+        const uint32_t m = reinterpret_cast<const uint32_t *>(a.mark)[i];
+        bool act[S];
+        bool any = false;
 #pragma unroll
-            for (uint32_t j = 0; j < 8; ++j) t[j] = j < m ? row[j0 + j] : static_cast<uint32_t>(q);
-#pragma unroll
-            for (uint32_t j = 0; j < 8; ++j) mk[j] = a.mark[t[j]];
-#pragma unroll
-            for (uint32_t j = 0; j < 8; ++j)
-                if (j < m && mk[j] == 0) {
-                    a.mark[t[j]] = nf;
-                    ++stored;
-                }
+        for (int u = 0; u < S; ++u) {
+            act[u] = ((m >> (8 * u)) & 0xFFu) == f && i * S + u < a.n;
+            any |= act[u];
         }
-        a.mark[q] = 1;
+        if (!any) continue;
+        // letters in groups of KC: the row entries of every state, then
+        // their marks, are loaded together before any store (an idle state
+        // reads its word's first active one's row again)
+        size_t q[S], busy = 0;
+#pragma unroll
+        for (int u = S - 1; u >= 0; --u)
+            if (act[u]) busy = i * S + u;
+#pragma unroll
+        for (int u = 0; u < S; ++u) q[u] = act[u] ? i * S + u : busy;
+        for (uint32_t j0 = 0; j0 < a.k; j0 += KC) {
+            uint32_t t[S][KC];
+            uint8_t mk[S][KC];
+#pragma unroll
+            for (int u = 0; u < S; ++u)
+#pragma unroll
+                for (int j = 0; j < KC; ++j)
+                    t[u][j] = a.delta[q[u] * a.k + (j0 + j < a.k ? j0 + j : j0)];
+#pragma unroll
+            for (int u = 0; u < S; ++u)
+#pragma unroll
+                for (int j = 0; j < KC; ++j) mk[u][j] = a.mark[t[u][j]];
+#pragma unroll
+            for (int u = 0; u < S; ++u)
+#pragma unroll
+                for (int j = 0; j < KC; ++j)
+                    if (act[u] && mk[u][j] == 0) {
+                        a.mark[t[u][j]] = nf;
+                        ++stored;
+                    }
+        }
+#pragma unroll
+        for (int u = 0; u < S; ++u)
+            if (act[u]) a.mark[i * S + u] = 1;
     }
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) stored += __shfl_xor(stored, d, 64);
-    if (lane_id() == 0 && stored) atomicAdd(a.sizes + 1, stored);
+    if (lane_id() == 0) part[threadIdx.x / 64] = stored;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t sum = 0;
+#pragma unroll
+        for (int w = 0; w < kBlock / 64; ++w) sum += part[w];
+        if (sum)
+            atomicAdd(a.stored + level * kBfsSetWords + (blockIdx.x % kBfsSpread) * kBfsStride, sum);
+    }
 }
 
 // Marks -> queue: the states marked f settle and are listed in qa (one
-// append atomic per wave); sizes[0] = their number.
+// append atomic per wave); sizes[0], zero on entry, = their number.
 __global__ __launch_bounds__(kBlock) void k_bfs_marks_to_list(ReachArgs a, uint8_t f) {
     const uint32_t lane = lane_id();
     for (size_t base = static_cast<size_t>(blockIdx.x) * kBlock; base < a.n;
@@ -147,19 +210,10 @@ __global__ __launch_bounds__(kBlock) void k_bfs_marks_to_list(ReachArgs a, uint8
     }
 }
 
-__global__ void k_bfs_set(uint32_t *sizes, uint32_t i0, uint32_t v0, uint32_t i1, uint32_t v1) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        sizes[i0] = v0;
-        sizes[i1] = v1;
-    }
-}
-
-// flags[q] = q for reachable q, all ones otherwise (the input of the dense
-// numbering, which numbers the states with flags[q] == q).
-__global__ __launch_bounds__(kBlock) void k_reach_flags(const uint8_t *mark, size_t n,
-                                                        uint32_t *flags) {
-    for (size_t q = global_tid(); q < n; q += grid_stride())
-        flags[q] = mark[q] ? static_cast<uint32_t>(q) : ~0u;
+// The counters of a batch of dense levels start at zero.
+__global__ __launch_bounds__(kBlock) void k_bfs_reset(ReachArgs a, uint32_t list) {
+    for (uint32_t i = threadIdx.x; i < kBfsBatch * kBfsSetWords; i += kBlock) a.stored[i] = 0;
+    if (list && threadIdx.x == 0) a.sizes[0] = 0;
 }
 
 // Sub-automaton: row i is the reachable state orig[i], targets renumbered.
@@ -207,33 +261,36 @@ void launch_check_targets(const uint32_t *delta, uint64_t total, uint32_t n, uin
                        err);
 }
 
-void launch_bfs_init(const ReachArgs &a, uint32_t start, hipStream_t s) {
-    launch_kernel(k_bfs_init, dim3(1), dim3(64), 0, s, a, start);
+void launch_bfs_narrow(const ReachArgs &a, uint32_t start, bool init, hipStream_t s) {
+    launch_kernel(k_bfs_narrow, dim3(1), dim3(kNarrowThreads), 0, s, a, start, init ? 1u : 0u);
 }
 
-void launch_bfs_narrow(const ReachArgs &a, hipStream_t s) {
-    launch_kernel(k_bfs_narrow, dim3(1), dim3(kNarrowThreads), 0, s, a);
+void launch_bfs_list_to_marks(const ReachArgs &a, uint8_t f, hipStream_t s) {
+    // the frontier's size is known on the device only: at most kNarrowCap
+    // states per letter step of the narrow kernel
+    launch_kernel(k_bfs_list_to_marks, dim3(grid_of(std::min(a.n, kNarrowCap))), dim3(kBlock), 0, s,
+                  a, f);
 }
 
-void launch_bfs_list_to_marks(const ReachArgs &a, uint32_t count, uint8_t f, hipStream_t s) {
-    launch_kernel(k_bfs_list_to_marks, dim3(grid_of(count)), dim3(kBlock), 0, s, a, f);
-}
-
-void launch_bfs_dense(const ReachArgs &a, uint8_t f, uint8_t nf, hipStream_t s) {
-    launch_kernel(k_bfs_set, dim3(1), dim3(64), 0, s, a.sizes, 1u, 0u, 1u, 0u);
-    launch_kernel(k_bfs_dense, dim3(grid_of(a.n)), dim3(kBlock), 0, s, a, f, nf);
+void launch_bfs_dense(const ReachArgs &a, uint8_t f, uint8_t nf, uint32_t level, bool after_list,
+                      hipStream_t s) {
+    const dim3 grid(grid_of((static_cast<uint64_t>(a.n) + 3) / 4, 4096)), block(kBlock);
+    const uint32_t al = after_list ? 1u : 0u;
+    if (a.k <= 2)
+        launch_kernel(k_bfs_dense<2>, grid, block, 0, s, a, f, nf, level, al);
+    else
+        launch_kernel(k_bfs_dense<4>, grid, block, 0, s, a, f, nf, level, al);
 }
 
 void launch_bfs_marks_to_list(const ReachArgs &a, uint8_t f, hipStream_t s) {
-    launch_kernel(k_bfs_set, dim3(1), dim3(64), 0, s, a.sizes, 0u, 0u, 0u, 0u);
     launch_kernel(k_bfs_marks_to_list, dim3(grid_of(a.n)), dim3(kBlock), 0, s, a, f);
 }
 
-uint32_t bfs_narrow_cap() { return kNarrowCap; }
-
-void launch_reach_flags(const uint8_t *mark, size_t n, uint32_t *flags, hipStream_t s) {
-    launch_kernel(k_reach_flags, dim3(grid_of(n)), dim3(kBlock), 0, s, mark, n, flags);
+void launch_bfs_reset(const ReachArgs &a, bool list, hipStream_t s) {
+    launch_kernel(k_bfs_reset, dim3(1), dim3(kBlock), 0, s, a, list ? 1u : 0u);
 }
+
+uint32_t bfs_narrow_cap() { return kNarrowCap; }
 
 void launch_sub_dfa(const uint32_t *delta, const uint8_t *acc, uint32_t k, const uint32_t *orig,
                     const uint32_t *dense, const uint32_t *m_dev, uint32_t m_host,

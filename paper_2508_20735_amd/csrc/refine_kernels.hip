@@ -2420,12 +2420,24 @@ __global__ __launch_bounds__(kBlock) void k_canon_apply(const uint32_t *__restri
 
 constexpr int kScanThreads = static_cast<int>(kScanTile);  // one element per thread
 
-// Per-tile leader counts: ballot of "block[q] == q" and popcount per wave.
-__global__ __launch_bounds__(kScanThreads) void k_leader_partials(const uint32_t *__restrict__ block,
-                                                                   size_t N, uint32_t *partials) {
+// The states that are numbered: the leaders of a partition, or the marked
+// states.
+struct IsLeader {
+    const uint32_t *block;
+    __device__ __forceinline__ bool operator()(size_t q) const { return block[q] == q; }
+};
+struct IsMarked {
+    const uint8_t *mark;
+    __device__ __forceinline__ bool operator()(size_t q) const { return mark[q] != 0; }
+};
+
+// Per-tile counts of the numbered states: ballot and popcount per wave.
+template <class Pick>
+__global__ __launch_bounds__(kScanThreads) void k_leader_partials(Pick pick, size_t N,
+                                                                   uint32_t *partials) {
     __shared__ uint32_t wsum[kScanThreads / 64];
     const size_t q = static_cast<size_t>(blockIdx.x) * kScanTile + threadIdx.x;
-    const bool lead = q < N && block[q] == q;
+    const bool lead = q < N && pick(q);
     const unsigned long long m = __ballot(lead);
     if (lane_id() == 0) wsum[threadIdx.x / 64] = static_cast<uint32_t>(__popcll(m));
     __syncthreads();
@@ -2478,15 +2490,16 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_partials(uint32_t *partia
 }
 
 // dense[q] for leaders: tile offset + leaders before q in the tile (ballot
-// rank within the wave + wave offsets).
-__global__ __launch_bounds__(kScanThreads) void k_leader_rank(const uint32_t *__restrict__ block,
-                                                               size_t N,
+// rank within the wave + wave offsets); *at_dense = dense[at] if at is one.
+template <class Pick>
+__global__ __launch_bounds__(kScanThreads) void k_leader_rank(Pick pick, size_t N,
                                                                const uint32_t *__restrict__ partials,
                                                                uint32_t *__restrict__ dense,
-                                                               uint32_t *__restrict__ leader_of) {
+                                                               uint32_t *__restrict__ leader_of,
+                                                               size_t at, uint32_t *at_dense) {
     __shared__ uint32_t wsum[kScanThreads / 64];
     const size_t q = static_cast<size_t>(blockIdx.x) * kScanTile + threadIdx.x;
-    const bool lead = q < N && block[q] == q;
+    const bool lead = q < N && pick(q);
     const unsigned long long m = __ballot(lead);
     const uint32_t lane = lane_id();
     if (lane == 0) wsum[threadIdx.x / 64] = static_cast<uint32_t>(__popcll(m));
@@ -2498,6 +2511,7 @@ __global__ __launch_bounds__(kScanThreads) void k_leader_rank(const uint32_t *__
         const uint32_t d = partials[blockIdx.x] + woff + static_cast<uint32_t>(__popcll(below));
         dense[q] = d;
         leader_of[d] = static_cast<uint32_t>(q);
+        if (q == at) *at_dense = d;
     }
 }
 
@@ -2933,15 +2947,31 @@ void launch_canonicalise(const uint32_t *ids, size_t N, size_t id_range, uint32_
     launch_kernel(k_canon_apply, grid, block, 0, s, ids, N, scratch_min, out);
 }
 
+namespace {
+
+template <class Pick>
+void dense_numbering(Pick pick, size_t N, uint32_t *partials, uint32_t *dense, uint32_t *leader_of,
+                     uint32_t *num, size_t at, uint32_t *at_dense, hipStream_t s) {
+    const uint32_t ntiles = static_cast<uint32_t>((N + kScanTile - 1) / kScanTile);
+    launch_kernel(k_leader_partials<Pick>, dim3(ntiles), dim3(kScanThreads), 0, s, pick, N,
+                  partials);
+    launch_kernel(k_scan_partials, dim3(1), dim3(kScanThreads), 0, s, partials, ntiles, num);
+    launch_kernel(k_leader_rank<Pick>, dim3(ntiles), dim3(kScanThreads), 0, s, pick, N, partials,
+                  dense, leader_of, at, at_dense);
+}
+
+}  // namespace
+
 void launch_dense_leaders(const uint32_t *block, size_t N, uint32_t *partials, uint32_t *dense,
                           uint32_t *leader_of, uint32_t *num_blocks, hipStream_t s) {
-    const uint32_t ntiles = static_cast<uint32_t>((N + kScanTile - 1) / kScanTile);
-    launch_kernel(k_leader_partials, dim3(ntiles), dim3(kScanThreads), 0, s, block, N,
-                       partials);
-    launch_kernel(k_scan_partials, dim3(1), dim3(kScanThreads), 0, s, partials, ntiles,
-                       num_blocks);
-    launch_kernel(k_leader_rank, dim3(ntiles), dim3(kScanThreads), 0, s, block, N, partials,
-                       dense, leader_of);
+    dense_numbering(IsLeader{block}, N, partials, dense, leader_of, num_blocks, ~static_cast<size_t>(0),
+                    nullptr, s);
+}
+
+void launch_dense_marks(const uint8_t *mark, size_t n, uint32_t start, uint32_t *partials,
+                        uint32_t *dense, uint32_t *leader_of, uint32_t *num,
+                        uint32_t *start_dense, hipStream_t s) {
+    dense_numbering(IsMarked{mark}, n, partials, dense, leader_of, num, start, start_dense, s);
 }
 
 void launch_quotient(const uint32_t *delta, const uint8_t *acc, uint32_t k,
