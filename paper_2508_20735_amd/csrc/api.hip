@@ -183,7 +183,7 @@ struct Ctx {
     dfa_tuning tune{};
     Buffer stage_delta, stage_acc, stage_block, stage_qdelta, stage_qacc, stage_delta_b,
         stage_acc_b;
-    Buffer visited, visited2, front0, front1;
+    Buffer visited, visited2, front0, front1, product_ctl;
     Buffer new_leader, moved;
     Buffer chg, single, touched, chg_sum;
     // the column list last uploaded, and the allocation it went to
@@ -1404,102 +1404,104 @@ int equivalent_impl(Ctx &c, const dfa_view &a, const dfa_view &b, int *verdict,
 }
 
 // Breadth-first exploration of the synchronous product from (start_a,
-// start_b), one level per launch.  mode 0: inclusion (refuted by p accepting,
-// q rejecting); mode 1: equivalence (refuted by exactly one accepting side).
+// start_b).  mode 0: inclusion (refuted by p accepting, q rejecting); mode 1:
+// equivalence (refuted by exactly one accepting side).  The host queues a
+// batch at a time (a narrow launch, then wide levels that stop by themselves
+// when they have no work or no room) and waits once per batch.
 int included_impl(Ctx &c, const dfa_view &a, const dfa_view &b, int *verdict, uint64_t *visited,
                   dfa_stats *st, int mode = 0) {
     const uint32_t k = a.k;
-    // reuse the flag buffer for the target checks (no refinement here)
-    DFA_TRY(c.flags.ensure((kFlagNonid + k) * sizeof(uint32_t), "flags"));
     const size_t N = static_cast<size_t>(a.n) + b.n;
-    DFA_TRY(c.cols.ensure(static_cast<size_t>(k) * N * sizeof(uint32_t), "columns"));
-    HIP_TRY(hipMemsetAsync(c.flags.p, 0, (kFlagNonid + k) * sizeof(uint32_t), c.stream));
-    HIP_TRY(hipEventRecord(c.ev_start, c.stream));
-    uint32_t *flags = c.flags.as<uint32_t>();
-    launch_ingest(a.delta, a.n, k, c.cols.as<uint32_t>(), N, 0, 0, flags + kFlagErr,
-                  flags + kFlagNonid, c.stream);
-    launch_ingest(b.delta, b.n, k, c.cols.as<uint32_t>(), N, a.n, a.n, flags + kFlagErr,
-                  flags + kFlagNonid, c.stream);
-    HIP_TRY(hipGetLastError());
-    DFA_TRY(read_back(c, flags, sizeof(uint32_t)));
-    if (c.pinned[0]) return fail(DFA_EINVAL, "a transition target is >= n");
-
     uint64_t cap = next_pow2(std::max<uint64_t>(4 * N, 4096));
+    // frontiers: at first no more than kFrontierPairs (or every pair there
+    // is); larger ones are made when a level needs them
+    constexpr uint64_t kFrontierPairs = uint64_t(1) << 20;
+    const uint64_t pairs = static_cast<uint64_t>(a.n) * b.n;
+    const uint64_t room = std::max<uint64_t>(kProductNarrowCap, std::min(pairs, kFrontierPairs));
+    DFA_TRY(c.product_ctl.ensure(sizeof(ProductCtl), "search state"));
     DFA_TRY(c.visited.ensure(cap * sizeof(unsigned long long), "visited set"));
+    DFA_TRY(c.front0.ensure(room * sizeof(unsigned long long), "frontier"));
+    DFA_TRY(c.front1.ensure(room * sizeof(unsigned long long), "frontier"));
+    HIP_TRY(hipEventRecord(c.ev_start, c.stream));
+    ProductCtl *ctl = c.product_ctl.as<ProductCtl>();
+    {
+        ZeroList z{};
+        DFA_TRY(zero_add(z, c.product_ctl, sizeof(ProductCtl)));
+        launch_zero(z, c.stream);
+    }
+    // the search's kernels stop at the check's flag themselves
+    launch_check_targets(a.delta, static_cast<uint64_t>(a.n) * k, a.n, &ctl->err, c.stream);
+    launch_check_targets(b.delta, static_cast<uint64_t>(b.n) * k, b.n, &ctl->err, c.stream);
     launch_visited_clear(c.visited.as<unsigned long long>(), cap, c.stream);
-    const unsigned long long start = (static_cast<unsigned long long>(a.start) << 32) | b.start;
-    launch_visited_insert_start(c.visited.as<unsigned long long>(), cap, start, c.stream);
-    // both frontier buffers hold at least a narrow launch's frontier
-    DFA_TRY(c.front0.ensure(kProductNarrowCap * sizeof(unsigned long long), "frontier"));
-    DFA_TRY(c.front1.ensure(kProductNarrowCap * sizeof(unsigned long long), "frontier"));
-    DFA_TRY(upload(c, c.front0.p, &start, sizeof start));
-    DFA_TRY(c.scalars.ensure(16 * sizeof(uint32_t), "scalars"));
-    uint32_t *sc = c.scalars.as<uint32_t>();
+    ProductArgs pa{a.delta, b.delta, a.accepting, b.accepting, k, mode,
+                   c.visited.as<unsigned long long>(), cap, ctl};
     Buffer *cur = &c.front0, *nxt = &c.front1;
+    launch_product_start(pa, cur->as<unsigned long long>(),
+                         (static_cast<unsigned long long>(a.start) << 32) | b.start, c.stream);
     uint64_t count = 1, fsize = 1;
     uint32_t levels = 0;
     int v = 1;
-    // levels per narrow launch: bounds the pairs one launch may add
-    constexpr uint32_t kNarrowLevels = 256;
+    constexpr uint32_t kNarrowLevels = 256;  // levels per narrow launch
+    auto frontier_room = [](const Buffer &f) { return f.cap / sizeof(unsigned long long); };
     while (fsize > 0) {
-        if (fsize * k <= kProductNarrowCap) {
-            // thin frontier: levels expanded inside one workgroup, the set
-            // sized first for every pair the launch may add (at half load)
-            const uint64_t most = count + static_cast<uint64_t>(kNarrowLevels) * kProductNarrowCap;
-            if (most * 2 > cap) {
-                const uint64_t ncap = next_pow2(most * 2);
-                DFA_TRY(c.visited2.ensure(ncap * sizeof(unsigned long long), "visited set"));
-                launch_visited_clear(c.visited2.as<unsigned long long>(), ncap, c.stream);
-                launch_rehash(c.visited.as<unsigned long long>(), cap,
-                              c.visited2.as<unsigned long long>(), ncap, c.stream);
-                std::swap(c.visited, c.visited2);
-                cap = ncap;
-            }
-            HIP_TRY(hipMemsetAsync(sc + 4, 0, 4 * sizeof(uint32_t), c.stream));
-            ProductArgs pa{a.delta, b.delta, a.accepting, b.accepting, k, mode,
-                           cur->as<unsigned long long>(), static_cast<uint32_t>(fsize), nullptr, 0,
-                           nullptr, c.visited.as<unsigned long long>(), cap, nullptr, nullptr};
-            launch_product_narrow(pa, kNarrowLevels, sc + 4, c.stream);
-            HIP_TRY(hipGetLastError());
-            DFA_TRY(read_back(c, sc + 4, 4 * sizeof(uint32_t)));
-            fsize = c.pinned[0];
-            count += c.pinned[1];
-            levels += c.pinned[2];
-            if (c.pinned[3]) {
-                v = 0;
-                break;
-            }
-            continue;
-        }
-        ++levels;
+        // room for one level at least: `next`, and the visited set at half load
         const uint64_t need = fsize * k;
         if (need >= 0xFFFFFFFFull) return fail(DFA_ENOMEM, "frontier too large");
         DFA_TRY(nxt->ensure(need * sizeof(unsigned long long), "frontier"));
         if ((count + need) * 2 > cap) {
-            const uint64_t ncap = next_pow2((count + need) * 2);
+            // (searches that outgrow the first size grow by four at least, as
+            // long as that stays small, so that a long thin search does not
+            // stop for a rehash every few levels)
+            const uint64_t ncap =
+                std::max(next_pow2((count + need) * 2),
+                         std::min<uint64_t>(cap * 4, uint64_t(1) << 22));
             DFA_TRY(c.visited2.ensure(ncap * sizeof(unsigned long long), "visited set"));
             launch_visited_clear(c.visited2.as<unsigned long long>(), ncap, c.stream);
             launch_rehash(c.visited.as<unsigned long long>(), cap,
                           c.visited2.as<unsigned long long>(), ncap, c.stream);
             std::swap(c.visited, c.visited2);
             cap = ncap;
+            pa.visited = c.visited.as<unsigned long long>();
+            pa.visited_cap = cap;
         }
-        HIP_TRY(hipMemsetAsync(sc, 0, 3 * sizeof(uint32_t), c.stream));
-        ProductArgs pa{a.delta, b.delta, a.accepting, b.accepting, k, mode,
-                       cur->as<unsigned long long>(), static_cast<uint32_t>(fsize),
-                       nxt->as<unsigned long long>(), static_cast<uint32_t>(need), sc,
-                       c.visited.as<unsigned long long>(), cap, sc + 1, sc + 2};
-        launch_product_level(pa, c.stream);
+        launch_product_reset(ctl, count, static_cast<uint32_t>(fsize), c.stream);
+        if (need <= kProductNarrowCap)
+            launch_product_narrow(pa, cur->as<unsigned long long>(), kNarrowLevels, c.stream);
+        // wide levels (none where the narrow kernel takes every level):
+        // workgroups for the frontier known here, or the 2,048 that fill the
+        // device, as a batch's later frontiers are known on the device only
+        const uint32_t groups = static_cast<uint32_t>(
+            std::min<uint64_t>(std::max<uint64_t>((fsize + kBlock - 1) / kBlock, 2048), 1u << 20));
+        const uint32_t batch = pairs <= kProductNarrowCap / k ? 0 : kProductBatch;
+        Buffer *from = cur, *to = nxt;
+        for (uint32_t l = 0; l < batch; ++l, std::swap(from, to))
+            launch_product_level(pa, from->as<unsigned long long>(), to->as<unsigned long long>(),
+                                 frontier_room(*to), l, groups, c.stream);
         HIP_TRY(hipGetLastError());
-        DFA_TRY(read_back(c, sc, 3 * sizeof(uint32_t)));
-        if (c.pinned[2]) return fail(DFA_EDEVICE, "internal: frontier overflow");
-        if (c.pinned[1]) {
+        DFA_TRY(read_back(c, ctl, sizeof(ProductCtl)));
+        ProductCtl got;
+        std::memcpy(&got, c.pinned, sizeof got);
+        if (got.err) return fail(DFA_EINVAL, "a transition target is >= n");
+        levels += got.narrow_levels;
+        count = got.count;
+        fsize = got.size[0];
+        if (got.refuted == kProductNarrowRefuted) {
             v = 0;
             break;
         }
-        fsize = c.pinned[0];
-        count += fsize;
-        std::swap(cur, nxt);
+        // the wide levels that ran, by the rule of the kernel
+        for (uint32_t l = 0; l < batch && fsize; ++l) {
+            if (fsize * k > frontier_room(*nxt) || (count + fsize * k) * 2 > cap) break;
+            ++levels;
+            if (got.refuted == l + 1) {
+                v = 0;
+                break;
+            }
+            fsize = got.size[l + 1];
+            count += fsize;
+            std::swap(cur, nxt);
+        }
+        if (!v) break;
     }
     HIP_TRY(hipEventRecord(c.ev_stop, c.stream));
     HIP_TRY(stream_sync(c));
@@ -2208,7 +2210,7 @@ void for_each_buffer(Ctx &c, F &&f) {
                       &c.scalars, &c.multi, &c.active, &c.accbits, &c.counters, &c.presence,
                       &c.presence_packed, &c.lab8, &c.stage_delta, &c.stage_acc, &c.stage_block,
                       &c.stage_qdelta, &c.stage_qacc, &c.stage_delta_b, &c.stage_acc_b,
-                      &c.visited, &c.visited2, &c.front0, &c.front1,
+                      &c.visited, &c.visited2, &c.front0, &c.front1, &c.product_ctl,
                       &c.parts, &c.tile_part,
                       &c.seg_words, &c.batch_in, &c.batch_out, &c.new_leader, &c.moved,
                       &c.chg, &c.single, &c.touched, &c.chg_sum, &c.reach_ctl, &c.reach_qa,

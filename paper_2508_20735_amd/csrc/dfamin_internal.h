@@ -455,34 +455,44 @@ void launch_small_refine(const SmallJob *jobs, uint32_t njobs, uint32_t groups, 
                          uint32_t max_rounds, uint32_t *err, hipStream_t s);
 
 // ---- product exploration (product_kernels.hip) ----
+// Device state of a search: the host queues a narrow launch and up to
+// kProductBatch levels at a time and reads this back once per batch.
+constexpr uint32_t kProductBatch = 8;
+constexpr uint32_t kProductNarrowRefuted = ~0u;
+struct ProductCtl {
+    unsigned long long count;      // pairs reached when the batch's levels start
+    uint32_t err;                  // a target is out of range: no kernel explores
+    uint32_t refuted;              // level + 1 that expanded a refuting pair (0: none), or
+                                   // kProductNarrowRefuted
+    uint32_t narrow_levels;        // levels expanded by the batch's narrow launch
+    uint32_t size[kProductBatch + 1];  // frontier of each level of the batch
+};
 struct ProductArgs {
     const uint32_t *dA, *dB;   // row-major
     const uint8_t *accA, *accB;
     uint32_t k;
     int mode;                  // 0 inclusion, 1 equivalence
-    const unsigned long long *frontier;
-    uint32_t frontier_size;
-    unsigned long long *next;  // capacity next_cap
-    uint32_t next_cap;
-    uint32_t *next_size;       // atomic counter
     unsigned long long *visited;
     uint64_t visited_cap;      // power of two
-    uint32_t *bad;             // set to 1 when a refuting pair is reached
-    uint32_t *overflow;        // set to 1 when `next` overflows
+    ProductCtl *ctl;
 };
-void launch_product_level(const ProductArgs &a, hipStream_t s);
+// A batch starts: pairs reached so far, the frontier's size; the rest zero.
+void launch_product_reset(ProductCtl *ctl, uint64_t count, uint32_t frontier_size, hipStream_t s);
+// The start pair into the (empty) visited set and the frontier.
+void launch_product_start(const ProductArgs &a, unsigned long long *frontier,
+                          unsigned long long key, hipStream_t s);
+// Level `level` of the batch, from `frontier` into `next` (next_cap pairs).
+void launch_product_level(const ProductArgs &a, const unsigned long long *frontier,
+                          unsigned long long *next, uint64_t next_cap, uint32_t level,
+                          uint32_t groups, hipStream_t s);
 // Narrow exploration inside one workgroup (LDS queues of kProductNarrowCap
-// pairs): requires frontier_size * k <= kProductNarrowCap and room in the
-// visited set for max_levels * kProductNarrowCap more pairs at half load;
-// out[0..3] = (frontier size, pairs added, levels, refuted); out[3] must be
-// zero on entry.  The frontier stays in a.frontier.
+// pairs) while the frontier times k fits them and the pairs half of the
+// visited set; the frontier stays in `frontier`, ctl->size[0].
 constexpr uint32_t kProductNarrowThreads = 1024;
 constexpr uint32_t kProductNarrowCap = 8192;
-void launch_product_narrow(const ProductArgs &a, uint32_t max_levels, uint32_t *out,
-                           hipStream_t s);
+void launch_product_narrow(const ProductArgs &a, unsigned long long *frontier,
+                           uint32_t max_levels, hipStream_t s);
 void launch_visited_clear(unsigned long long *visited, uint64_t cap, hipStream_t s);
-void launch_visited_insert_start(unsigned long long *visited, uint64_t cap,
-                                 unsigned long long key, hipStream_t s);
 void launch_rehash(const unsigned long long *old_tab, uint64_t old_cap,
                    unsigned long long *new_tab, uint64_t new_cap, hipStream_t s);
 
