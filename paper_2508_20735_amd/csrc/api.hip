@@ -203,6 +203,7 @@ struct Ctx {
     Buffer parts, tile_part, seg_words, batch_in, batch_out, tile_dead;
     Buffer small_jobs, small_results, small_ctl;  // batched small DFAs (one workgroup each)
     Buffer pb_tl, pb_src, pb_val, pb_off, pb_partials;  // edges bucketed by target slice
+    Buffer direct_cnt;                // round counters of direct rounds
     Buffer segpat_table, segpat;  // round 0 of segmented refinements by acceptance patterns
     Arena arena;  // the allocation-free context's fixed workspace (unused elsewhere)
     uint8_t *pinned_batch = nullptr;  // host staging of batched inputs/outputs
@@ -516,6 +517,12 @@ struct RefineResult {
     uint32_t N = 0;  // states refined
 };
 
+// A refinement that goes on in the general path after its first rounds: ids
+// in the block buffers, singleton bits and round state are on the device.
+struct Resume {
+    std::vector<uint32_t> colmap;  // letters that move some state
+};
+
 // Whether plain rounds have stalled, after at least 8 rounds: over the last
 // four rounds no round added more than 1/4096 of the states still to be
 // separated (large inputs), or, after 16 rounds, no more than 1/64 of them
@@ -792,8 +799,11 @@ int build_slices(Ctx &c, const uint32_t *cols, size_t N, uint32_t k_eff, const d
     return DFA_OK;
 }
 
+// With `resume`, the refinement goes on after res.ctl.round rounds (see
+// refine_direct) instead of starting.
 int refine(Ctx &c, size_t N, uint32_t k, const dfa_options &o, uint32_t check_eq, uint32_t eq_a,
-           uint32_t eq_b, bool state_ids, RefineResult &res, const SegArgs *seg = nullptr) {
+           uint32_t eq_b, bool state_ids, RefineResult &res, const SegArgs *seg = nullptr,
+           const Resume *resume = nullptr) {
     res.N = static_cast<uint32_t>(N);
     // state that starts empty, cleared in one launch queued before the
     // readback below, so that the device clears while the host waits
@@ -807,13 +817,13 @@ int refine(Ctx &c, size_t N, uint32_t k, const dfa_options &o, uint32_t check_eq
     DFA_TRY(c.chg_sum.ensure(2 * sum_words * sizeof(unsigned long long), "changed-wave summary"));
     // label rounds: the packed-label map too when k letters could use it
     // (identity letters, known after the readback, only make k_eff smaller)
-    const bool packed_possible = !seg && (k + 1) * (k + 1) <= kPackedMaxBits;
+    const bool packed_possible = !seg && !resume && (k + 1) * (k + 1) <= kPackedMaxBits;
     if (packed_possible)
         DFA_TRY(c.presence_packed.ensure(kLabelMapBytes, "label map"));
     {
         ZeroList z{};
         DFA_TRY(zero_add(z, c.table, cap * sizeof(unsigned long long)));
-        DFA_TRY(zero_add(z, c.single, words64 * sizeof(unsigned long long)));
+        if (!resume) DFA_TRY(zero_add(z, c.single, words64 * sizeof(unsigned long long)));
         DFA_TRY(zero_add(z, c.touched, 2 * words64 * sizeof(unsigned long long)));
         DFA_TRY(zero_add(z, c.chg_sum, 2 * sum_words * sizeof(unsigned long long)));
         if (packed_possible)
@@ -822,11 +832,15 @@ int refine(Ctx &c, size_t N, uint32_t k, const dfa_options &o, uint32_t check_eq
         HIP_TRY(hipGetLastError());
     }
     // target check, classes, identity letters (one readback)
-    DFA_TRY(read_back(c, c.flags.p, (kFlagNonid + k) * sizeof(uint32_t)));
-    if (c.pinned[kFlagErr]) return fail(DFA_EINVAL, "a transition target is >= n");
     std::vector<uint32_t> colmap;
-    for (uint32_t a = 0; a < k; ++a)
-        if (c.pinned[kFlagNonid + a]) colmap.push_back(a);
+    if (resume) {
+        colmap = resume->colmap;
+    } else {
+        DFA_TRY(read_back(c, c.flags.p, (kFlagNonid + k) * sizeof(uint32_t)));
+        if (c.pinned[kFlagErr]) return fail(DFA_EINVAL, "a transition target is >= n");
+        for (uint32_t a = 0; a < k; ++a)
+            if (c.pinned[kFlagNonid + a]) colmap.push_back(a);
+    }
 
     DFA_TRY(c.ctl.ensure(sizeof(RoundCtl), "round state"));
     RoundCtl *ctl = c.ctl.as<RoundCtl>();
@@ -852,7 +866,7 @@ int refine(Ctx &c, size_t N, uint32_t k, const dfa_options &o, uint32_t check_eq
     const uint32_t grouping = (o.algorithm == DFA_ALGO_SORT && !seg) ? 1u : 0u;
     // edges bucketed by target slice, for the dense rounds of the first chunk
     PbArgs pb{};
-    DFA_TRY(build_slices(c, cols, N, k_eff, o, seg != nullptr || res.tc_used, pb));
+    DFA_TRY(build_slices(c, cols, N, k_eff, o, seg != nullptr || resume || res.tc_used, pb));
     if (grouping) {
         const SortPlan pl = sort_plan(N);
         DFA_TRY(c.sort_keys0.ensure(N * sizeof(unsigned long long), "sort keys"));
@@ -867,7 +881,7 @@ int refine(Ctx &c, size_t N, uint32_t k, const dfa_options &o, uint32_t check_eq
     // label rounds need at least three rounds of budget (ids become state
     // ids in the round after them)
     // (segmented refinements keep their segment labels: no label rounds)
-    const bool budget = (o.max_rounds == 0 || o.max_rounds > 2) && !seg;
+    const bool budget = (o.max_rounds == 0 || o.max_rounds > 2) && !seg && !resume;
     const uint32_t pattern_first =
         (c.tune.label_rounds >= 1 && budget && k_eff + 1 <= kPatternMaxBits) ? 1u : 0u;
     const uint32_t packed_second =
@@ -895,8 +909,10 @@ int refine(Ctx &c, size_t N, uint32_t k, const dfa_options &o, uint32_t check_eq
                                       "pattern table"));
         DFA_TRY(c.segpat.ensure(N * sizeof(uint16_t), "patterns"));
     }
-    launch_ctl_reset(ctl, c.flags.as<uint32_t>() + kFlagClass, o.max_rounds, check_eq, eq_a, eq_b,
-                     pattern_first, packed_second, seg ? seg->init_count : nullptr, c.stream);
+    if (!resume)
+        launch_ctl_reset(ctl, c.flags.as<uint32_t>() + kFlagClass, o.max_rounds, check_eq, eq_a,
+                         eq_b, pattern_first, packed_second, seg ? seg->init_count : nullptr,
+                         c.stream);
 
     const int mode = o.loop_mode;
     uint32_t chunk = o.chunk ? o.chunk : c.tune.chunk;
@@ -904,55 +920,65 @@ int refine(Ctx &c, size_t N, uint32_t k, const dfa_options &o, uint32_t check_eq
     uint32_t last_round = 0;
     unsigned long long last_active_sum = 0;
     bool tc_failed = false;
-    res.transitions = 0;
-    res.bytes = 0;
     bool first = true;
     bool first_chunk = true;
-    for (;;) {
-        RoundArgs ra = make_round_args(c, cols, N, k_eff, cap, o.lds_stage, packed_second, seg, grouping);
-        // the dense rounds come first (the first table rounds); later chunks
-        // gather directly, so a long refinement pays nothing for the passes
-        if (first_chunk) ra.pb = pb;
-        if (segpat && first) {
-            ra.segpat_table = c.segpat_table.as<uint32_t>();
-            ra.segpat = c.segpat.as<uint16_t>();
-            ra.segpat_bits = segpat_bits;
-        }
-        if (first) {
-            // rounds 0 (and 1) run on their own: label rounds when the
-            // signatures are short enough
-            if (pattern_first) {
-                DFA_TRY(launch_kern(c, Kern::Pattern, ra, 0));
-                DFA_TRY(launch_kern(c, Kern::RoundEnd, ra, 0));
-            } else if (ra.segpat_bits) {
-                DFA_TRY(launch_kern(c, Kern::Mark, ra, 0));
-                DFA_TRY(launch_kern(c, Kern::SegPattern, ra, 0));
-                launch_seg_round(ra, c.stream);
-                DFA_TRY(launch_kern(c, Kern::RoundEnd, ra, 0));
-            } else {
-                DFA_TRY(launch_full_round(c, ra, 0));
-            }
-            if (packed_second) {
-                // through the slices when the edges are bucketed (k_eff <= 4)
-                DFA_TRY(launch_kern(c, ra.pb.nb ? Kern::PackedPb : Kern::Packed, ra, 1));
-                DFA_TRY(launch_kern(c, Kern::RoundEnd, ra, 1));
-            }
-            HIP_TRY(hipGetLastError());
-            first = false;
-        }
-        // rounds launched so far: the label rounds, then last_round onwards
-        const uint32_t next_round = std::max(last_round, res.label_rounds ? res.label_rounds : 1u);
-        DFA_TRY(run_chunk(c, ra, mode == DFA_LOOP_HOST ? 1u : chunk, mode, next_round));
-        first_chunk = false;
-        DFA_TRY(read_back(c, ctl, sizeof(RoundCtl)));
-        std::memcpy(&res.ctl, c.pinned, sizeof(RoundCtl));
-        if (c.profiling) DFA_TRY(prof_collect(c, res.ctl));
-        const uint32_t done_rounds = res.ctl.round - last_round;
-        res.transitions += static_cast<uint64_t>(done_rounds) * N * k_eff;
-        res.bytes += (res.ctl.active_sum - last_active_sum) * (8ull * k_eff + 8ull);
+    bool entered = resume == nullptr;  // false: the loop starts after a chunk
+    if (resume) {
         last_round = res.ctl.round;
         last_active_sum = res.ctl.active_sum;
-        if (res.ctl.done) break;
+        first = first_chunk = false;
+        chunk = 8;  // (the chunk that the general path would have run last)
+    } else {
+        res.transitions = 0;
+        res.bytes = 0;
+    }
+    for (;; entered = true) {
+        if (entered) {
+            RoundArgs ra = make_round_args(c, cols, N, k_eff, cap, o.lds_stage, packed_second, seg, grouping);
+            // the dense rounds come first (the first table rounds); later chunks
+            // gather directly, so a long refinement pays nothing for the passes
+            if (first_chunk) ra.pb = pb;
+            if (segpat && first) {
+                ra.segpat_table = c.segpat_table.as<uint32_t>();
+                ra.segpat = c.segpat.as<uint16_t>();
+                ra.segpat_bits = segpat_bits;
+            }
+            if (first) {
+                // rounds 0 (and 1) run on their own: label rounds when the
+                // signatures are short enough
+                if (pattern_first) {
+                    DFA_TRY(launch_kern(c, Kern::Pattern, ra, 0));
+                    DFA_TRY(launch_kern(c, Kern::RoundEnd, ra, 0));
+                } else if (ra.segpat_bits) {
+                    DFA_TRY(launch_kern(c, Kern::Mark, ra, 0));
+                    DFA_TRY(launch_kern(c, Kern::SegPattern, ra, 0));
+                    launch_seg_round(ra, c.stream);
+                    DFA_TRY(launch_kern(c, Kern::RoundEnd, ra, 0));
+                } else {
+                    DFA_TRY(launch_full_round(c, ra, 0));
+                }
+                if (packed_second) {
+                    // through the slices when the edges are bucketed (k_eff <= 4)
+                    DFA_TRY(launch_kern(c, ra.pb.nb ? Kern::PackedPb : Kern::Packed, ra, 1));
+                    DFA_TRY(launch_kern(c, Kern::RoundEnd, ra, 1));
+                }
+                HIP_TRY(hipGetLastError());
+                first = false;
+            }
+            // rounds launched so far: the label rounds, then last_round onwards
+            const uint32_t next_round = std::max(last_round, res.label_rounds ? res.label_rounds : 1u);
+            DFA_TRY(run_chunk(c, ra, mode == DFA_LOOP_HOST ? 1u : chunk, mode, next_round));
+            first_chunk = false;
+            DFA_TRY(read_back(c, ctl, sizeof(RoundCtl)));
+            std::memcpy(&res.ctl, c.pinned, sizeof(RoundCtl));
+            if (c.profiling) DFA_TRY(prof_collect(c, res.ctl));
+            const uint32_t done_rounds = res.ctl.round - last_round;
+            res.transitions += static_cast<uint64_t>(done_rounds) * N * k_eff;
+            res.bytes += (res.ctl.active_sum - last_active_sum) * (8ull * k_eff + 8ull);
+            last_round = res.ctl.round;
+            last_active_sum = res.ctl.active_sum;
+            if (res.ctl.done) break;
+        }
         // closure on demand: splitting has stalled (the chain-like regime
         // where plain rounds each split only a few blocks)
         if (o.tc_mode == DFA_TC_AUTO && !seg && !res.tc_used && !tc_failed &&
@@ -1113,13 +1139,6 @@ int refine_leader(Ctx &c, size_t N, uint32_t k, const dfa_options &o, uint32_t c
     return DFA_OK;
 }
 
-// Dispatch on the refinement algorithm of the options.
-int refine_any(Ctx &c, size_t N, uint32_t k, const dfa_options &o, uint32_t check_eq,
-               uint32_t eq_a, uint32_t eq_b, bool state_ids, RefineResult &res) {
-    if (o.algorithm == DFA_ALGO_LEADER) return refine_leader(c, N, k, o, check_eq, eq_a, eq_b, res);
-    return refine(c, N, k, o, check_eq, eq_a, eq_b, state_ids, res);
-}
-
 void fill_stats(dfa_stats *st, const RefineResult &r) {
     if (!st) return;
     st->rounds = r.ctl.round;
@@ -1160,7 +1179,9 @@ int check_batch_options(const dfa_options &o) {
     return DFA_OK;
 }
 
-int prepare_refinement(Ctx &c, size_t N, uint32_t k) {
+// Workspace of a refinement and what must start at zero there; with canon
+// also the scratch of the canonical ids (N words, already allocated).
+int prepare_refinement(Ctx &c, size_t N, uint32_t k, bool canon = false) {
     const uint32_t L = floor_log2(N);
     const size_t ncols = static_cast<size_t>(L + 1) * k;
     const size_t words64 = (N + 63) / 64;
@@ -1180,9 +1201,154 @@ int prepare_refinement(Ctx &c, size_t N, uint32_t k) {
     DFA_TRY(zero_add(z, c.accbits, words64 * sizeof(unsigned long long)));
     DFA_TRY(zero_add(z, c.counters, kSpread * kSpreadStride * sizeof(uint32_t)));
     DFA_TRY(zero_add(z, c.presence, (1u << kPatternMaxBits) / 8));
+    if (canon) DFA_TRY(zero_add(z, c.canon, N * sizeof(uint32_t)));
     launch_zero(z, c.stream);
     HIP_TRY(hipGetLastError());
     return DFA_OK;
+}
+
+// States above which a refinement takes the general path from its first
+// round (see refine_direct).
+constexpr size_t kDirectMaxStates = size_t(1) << 18;
+
+// Whether the rounds may run one launch each, straight from the inputs
+// (direct_kernels.hip): hash grouping with the default round options, no
+// closure from the start, at most kDirectMaxK letters.  Calls that choose a
+// loop driver, a chunk length, a round limit, a grouping variant or a kernel
+// tuning of the general rounds, or time its kernels, run those.
+bool direct_applies(const Ctx &c, size_t N, uint32_t k, const dfa_options &o) {
+    return N <= kDirectMaxStates && k <= kDirectMaxK && o.algorithm == DFA_ALGO_SIGNATURE &&
+           o.tc_mode != DFA_TC_ON &&
+           (o.loop_mode == DFA_LOOP_GRAPH || o.loop_mode == DFA_LOOP_CHUNK) && !o.max_rounds &&
+           !o.chunk && o.lds_stage == 2 && !c.tune.hash_bits && c.tune.label_rounds == 2 &&
+           c.tune.insert_pair && !c.profiling;
+}
+
+// The first rounds of a refinement of ordinary size, one launch each; done:
+// the refinement is decided and res is complete.  Otherwise the general path
+// goes on from round res.ctl.round (resume).
+int refine_direct(Ctx &c, const dfa_view &a, const dfa_view *b, bool canon, RefineResult &res,
+                  Resume &resume, bool &done) {
+    done = false;
+    const uint32_t k = a.k;
+    const size_t N = static_cast<size_t>(a.n) + (b ? b->n : 0);
+    const uint64_t cap = next_pow2(std::max<uint64_t>(2 * N, 1024));
+    constexpr size_t kCtlBytes = sizeof(RoundCtl) + (3 + kDirectMaxK) * sizeof(uint32_t);
+    constexpr size_t kCntBytes =
+        size_t(kDirectMaxRounds) * kDirectSpread * kDirectStride * sizeof(unsigned long long);
+    DFA_TRY(c.ctl.ensure(kCtlBytes, "round state"));
+    DFA_TRY(c.direct_cnt.ensure(kCntBytes, "round counters"));
+    DFA_TRY(c.blockA.ensure(N * sizeof(uint32_t), "blocks"));
+    DFA_TRY(c.blockB.ensure(N * sizeof(uint32_t), "blocks"));
+    DFA_TRY(c.multi.ensure((N + 1) * sizeof(uint32_t), "block marks"));
+    DFA_TRY(c.table.ensure(cap * sizeof(unsigned long long), "hash table"));
+    ZeroList z{};
+    DFA_TRY(zero_add(z, c.ctl, kCtlBytes));
+    DFA_TRY(zero_add(z, c.direct_cnt, kCntBytes));
+    DFA_TRY(zero_add(z, c.multi, N * sizeof(uint32_t)));
+    DFA_TRY(zero_add(z, c.table, cap * sizeof(unsigned long long)));
+    if (canon) DFA_TRY(zero_add(z, c.canon, N * sizeof(uint32_t)));
+    launch_zero(z, c.stream);
+    DirectArgs d{};
+    d.da = a.delta;
+    d.aa = a.accepting;
+    d.na = a.n;
+    if (b) {
+        d.db = b->delta;
+        d.ab = b->accepting;
+        d.nb = b->n;
+        d.check_eq = 1;
+        d.eq_a = a.start;
+        d.eq_b = a.n + b->start;
+    }
+    d.N = static_cast<uint32_t>(N);
+    d.k = k;
+    d.wide = k % 4 == 0 &&
+             ((reinterpret_cast<uintptr_t>(d.da) | reinterpret_cast<uintptr_t>(d.db)) & 15u) == 0;
+    d.blockA = c.blockA.as<uint32_t>();
+    d.blockB = c.blockB.as<uint32_t>();
+    d.multi = c.multi.as<uint32_t>();
+    d.table = c.table.as<unsigned long long>();
+    d.mask = cap - 1;
+    d.cnt = c.direct_cnt.as<unsigned long long>();
+    d.ctl = c.ctl.as<RoundCtl>();
+    d.flags = reinterpret_cast<uint32_t *>(d.ctl + 1);
+    // the host looks at the rounds where the general path does: after its
+    // label rounds and first chunk, then eight rounds later
+    const uint32_t labels = (k + 1) * (k + 1) <= kPackedMaxBits ? 2 : 1;
+    const uint32_t stops[2] = {labels + 4, labels + 12};
+    static_assert(2 + 12 <= kDirectMaxRounds, "a counter per round");
+    uint32_t launched = 0;
+    for (uint32_t stop : stops) {
+        while (launched < stop) launch_direct_round(d, launched++, c.stream);
+        launch_direct_end(d, launched, c.stream);
+        HIP_TRY(hipGetLastError());
+        DFA_TRY(read_back(c, c.ctl.p, kCtlBytes));
+        std::memcpy(&res.ctl, c.pinned, sizeof(RoundCtl));
+        const uint32_t *flags = c.pinned + sizeof(RoundCtl) / sizeof(uint32_t);
+        if (flags[0]) return fail(DFA_EINVAL, "a transition target is >= n");
+        resume.colmap.clear();
+        for (uint32_t j = 0; j < k; ++j)
+            if (flags[3 + j]) resume.colmap.push_back(j);
+        if (res.ctl.done) break;
+    }
+    res.N = static_cast<uint32_t>(N);
+    res.k_eff = static_cast<uint32_t>(resume.colmap.size());
+    res.transitions = static_cast<uint64_t>(res.ctl.round) * N * res.k_eff;
+    res.bytes = res.ctl.active_sum * (8ull * res.k_eff + 8ull);
+    done = res.ctl.done != 0;
+    res.final_block = ((res.ctl.round - 1) & 1u) ? d.blockA : d.blockB;
+    if (done) return DFA_OK;
+    const size_t words64 = (N + 63) / 64;
+    DFA_TRY(c.single.ensure(words64 * sizeof(unsigned long long), "singleton bits"));
+    DFA_TRY(c.active.ensure(words64 * sizeof(unsigned long long), "active masks"));
+    launch_direct_singles(d, res.ctl.round, c.single.as<unsigned long long>(),
+                          c.active.as<unsigned long long>(), c.stream);
+    HIP_TRY(hipGetLastError());
+    return DFA_OK;
+}
+
+// Refines one DFA, or the union of two (equivalence: until their start
+// states separate), by the algorithm of the options.  canon: the scratch of
+// the canonical ids is cleared too.
+int refine_any(Ctx &c, const dfa_view &a, const dfa_view *b, const dfa_options &o, bool canon,
+               RefineResult &res) {
+    const uint32_t k = a.k;
+    const size_t N = static_cast<size_t>(a.n) + (b ? b->n : 0);
+    // (a context without events, the allocation-free one, times on the host)
+    if (c.ev_start) HIP_TRY(hipEventRecord(c.ev_start, c.stream));
+    Resume resume;
+    bool resumed = false;
+    if (direct_applies(c, N, k, o)) {
+        bool done = false;
+        DFA_TRY(refine_direct(c, a, b, canon, res, resume, done));
+        if (done) return DFA_OK;
+        resumed = true;
+        canon = false;  // (cleared)
+    }
+    DFA_TRY(prepare_refinement(c, N, k, canon));
+    uint32_t *flags = c.flags.as<uint32_t>();
+    uint32_t *cols = c.cols.as<uint32_t>();
+    // (two separate target checks: A's targets < nA, B's < nB)
+    const dfa_view *parts[2] = {&a, b};
+    uint32_t off = 0;
+    for (const dfa_view *v : parts) {
+        if (!v) continue;
+        launch_ingest(v->delta, v->n, k, cols, N, off, off, flags + kFlagErr, flags + kFlagNonid,
+                      c.stream);
+        off += v->n;
+    }
+    off = 0;
+    for (const dfa_view *v : parts) {
+        if (!v || resumed) continue;
+        launch_init_blocks(v->accepting, v->n, off, c.blockA.as<uint32_t>(),
+                           c.accbits.as<unsigned long long>(), flags + kFlagClass, c.stream);
+        off += v->n;
+    }
+    HIP_TRY(hipGetLastError());
+    const uint32_t check_eq = b ? 1u : 0u, eq_a = b ? a.start : 0u, eq_b = b ? a.n + b->start : 0u;
+    if (o.algorithm == DFA_ALGO_LEADER) return refine_leader(c, N, k, o, check_eq, eq_a, eq_b, res);
+    return refine(c, N, k, o, check_eq, eq_a, eq_b, !b, res, nullptr, resumed ? &resume : nullptr);
 }
 
 int minimise_pruned(Ctx &c, uint32_t n, uint32_t k, const uint32_t *delta, const uint8_t *acc,
@@ -1191,50 +1357,57 @@ int minimise_pruned(Ctx &c, uint32_t n, uint32_t k, const uint32_t *delta, const
 int minimise_impl(Ctx &c, uint32_t n, uint32_t k, const uint32_t *delta, const uint8_t *acc,
                   uint32_t *block_out, dfa_quotient *q, const dfa_options &o, dfa_stats *st) {
     if (o.prune) return minimise_pruned(c, n, k, delta, acc, block_out, q, o, st);
-    DFA_TRY(prepare_refinement(c, n, k));
-    const size_t id_range = n;  // refine() returns state ids
-    DFA_TRY(c.canon.ensure(id_range * sizeof(uint32_t), "canonical ids"));
-    // (a context without events, the allocation-free one, times on the host)
-    if (c.ev_start) HIP_TRY(hipEventRecord(c.ev_start, c.stream));
-    uint32_t *flags = c.flags.as<uint32_t>();
-    launch_ingest(delta, n, k, c.cols.as<uint32_t>(), n, 0, 0, flags + kFlagErr, flags + kFlagNonid,
-                  c.stream);
-    launch_init_blocks(acc, n, 0, c.blockA.as<uint32_t>(), c.accbits.as<unsigned long long>(),
-                       flags + kFlagClass, c.stream);
-    HIP_TRY(hipGetLastError());
+    // (the leaders of leader rounds are canonical ids already)
+    const bool canon = o.algorithm != DFA_ALGO_LEADER;
+    if (canon || q) DFA_TRY(c.canon.ensure(static_cast<size_t>(n) * sizeof(uint32_t), "canonical ids"));
     RefineResult r;
-    int rc = refine_any(c, n, k, o, 0, 0, 0, true, r);
+    const dfa_view view{n, k, o.start, delta, acc};
+    int rc = refine_any(c, view, nullptr, o, canon, r);
     if (rc != DFA_OK) return rc;
-    launch_canonicalise(r.final_block, n, id_range, c.canon.as<uint32_t>(), block_out, c.stream);
-    if (q) {
-        DFA_TRY(c.scalars.ensure(16 * sizeof(uint32_t), "scalars"));
-        uint32_t *sc = c.scalars.as<uint32_t>();
-        if (r.ctl.prev_count == n) {
-            // every block is one state: the quotient is the input itself
-            HIP_TRY(hipMemsetD32Async(sc, n, 1, c.stream));
-            launch_quotient_identity(delta, acc, n, k, o.start, q->delta, q->accepting, sc + 1,
-                                     c.stream);
-        } else {
+    const bool discrete = r.ctl.prev_count == n;
+    if (discrete && q) {
+        launch_quotient_identity(delta, acc, n, k, block_out, q->delta, q->accepting, c.stream);
+    } else if (discrete) {
+        launch_iota(block_out, n, c.stream);
+    } else {
+        uint32_t *partials = nullptr;
+        if (q) {
             const size_t ntiles = (static_cast<size_t>(n) + kScanTile - 1) / kScanTile;
             DFA_TRY(c.partials.ensure((ntiles + 1) * sizeof(uint32_t), "scan partials"));
+            partials = c.partials.as<uint32_t>();
+        }
+        if (o.algorithm == DFA_ALGO_LEADER) {
+            // leaders are the smallest members already
+            launch_copy_u32(r.final_block, n, block_out, c.stream);
+            if (q) launch_leader_tiles(block_out, n, partials, c.stream);
+        } else {
+            launch_canonical_leaders(r.final_block, n, c.canon.as<uint32_t>(), block_out, partials,
+                                     c.stream);
+        }
+        if (q) {
+            DFA_TRY(c.scalars.ensure(16 * sizeof(uint32_t), "scalars"));
+            uint32_t *sc = c.scalars.as<uint32_t>();
             DFA_TRY(c.dense.ensure(static_cast<size_t>(n) * sizeof(uint32_t), "dense ids"));
             DFA_TRY(c.leader_of.ensure(static_cast<size_t>(n) * sizeof(uint32_t), "leaders"));
-            launch_dense_leaders(block_out, n, c.partials.as<uint32_t>(), c.dense.as<uint32_t>(),
-                                 c.leader_of.as<uint32_t>(), sc, c.stream);
             // the canonicalisation scratch is free again: it holds dq
-            launch_quotient(delta, acc, k, block_out, c.dense.as<uint32_t>(),
-                            c.leader_of.as<uint32_t>(), sc, n, o.start, c.canon.as<uint32_t>(),
-                            q->delta, q->accepting, sc + 1, c.stream);
+            launch_quotient_from_tiles(delta, acc, k, block_out, partials, n, o.start,
+                                       c.dense.as<uint32_t>(), c.leader_of.as<uint32_t>(),
+                                       c.canon.as<uint32_t>(), sc, q->delta, q->accepting, sc + 1,
+                                       c.stream);
         }
-        HIP_TRY(hipGetLastError());
     }
+    HIP_TRY(hipGetLastError());
     if (c.ev_stop) HIP_TRY(hipEventRecord(c.ev_stop, c.stream));
-    if (q) {
+    if (q && !discrete) {
         DFA_TRY(read_back(c, c.scalars.p, 2 * sizeof(uint32_t)));
         q->num_blocks = c.pinned[0];
         q->start = c.pinned[1];
     } else {
         HIP_TRY(stream_sync(c));
+        if (q) {
+            q->num_blocks = n;
+            q->start = o.start;
+        }
     }
     if (r.ctl.limit) {
         fill_stats(st, r);
@@ -1368,22 +1541,8 @@ int equivalent_impl(Ctx &c, const dfa_view &a, const dfa_view &b, int *verdict,
     if (o.equiv_method == DFA_EQ_PRODUCT) return included_impl(c, a, b, verdict, nullptr, st, 1);
     const size_t N = static_cast<size_t>(a.n) + b.n;
     if (N >= 0xFFFFFFFFull) return fail(DFA_EINVAL, "nA + nB must be < 2^32 - 1");
-    const uint32_t k = a.k;
-    DFA_TRY(prepare_refinement(c, N, k));
-    HIP_TRY(hipEventRecord(c.ev_start, c.stream));
-    uint32_t *flags = c.flags.as<uint32_t>();
-    uint32_t *cols = c.cols.as<uint32_t>();
-    // two separate target checks: A's targets < nA, B's < nB
-    launch_ingest(a.delta, a.n, k, cols, N, 0, 0, flags + kFlagErr, flags + kFlagNonid, c.stream);
-    launch_ingest(b.delta, b.n, k, cols, N, a.n, a.n, flags + kFlagErr, flags + kFlagNonid,
-                  c.stream);
-    launch_init_blocks(a.accepting, a.n, 0, c.blockA.as<uint32_t>(),
-                       c.accbits.as<unsigned long long>(), flags + kFlagClass, c.stream);
-    launch_init_blocks(b.accepting, b.n, a.n, c.blockA.as<uint32_t>(),
-                       c.accbits.as<unsigned long long>(), flags + kFlagClass, c.stream);
-    HIP_TRY(hipGetLastError());
     RefineResult r;
-    DFA_TRY(refine_any(c, N, k, o, 1, a.start, a.n + b.start, false, r));
+    DFA_TRY(refine_any(c, a, &b, o, false, r));
     HIP_TRY(hipEventRecord(c.ev_stop, c.stream));
     HIP_TRY(stream_sync(c));
     fill_stats(st, r);
@@ -2219,7 +2378,8 @@ void for_each_buffer(Ctx &c, F &&f) {
                       &c.sort_vals1, &c.sort_hist, &c.sort_partials, &c.sort_runhead,
                       &c.sort_m, &c.serve_in, &c.small_jobs, &c.small_results,
                       &c.small_ctl, &c.pb_tl, &c.pb_src, &c.pb_val, &c.pb_off,
-                      &c.pb_partials, &c.segpat_table, &c.segpat, &c.tile_dead};
+                      &c.pb_partials, &c.segpat_table, &c.segpat, &c.tile_dead,
+                      &c.direct_cnt};
     for (Buffer *b : bufs) f(*b);
 }
 

@@ -296,6 +296,35 @@ void launch_pattern_round(const RoundArgs &a, hipStream_t s);
 // (k_eff + 1)^2 <= kPackedMaxBits and lab8 written by the pattern round).
 void launch_packed_round(const RoundArgs &a, hipStream_t s);
 
+// ---- ordinary sizes: one launch per round (direct_kernels.hip) ----
+constexpr uint32_t kDirectMaxK = 16;       // letters of a direct refinement
+constexpr uint32_t kDirectMaxRounds = 16;  // rounds with a counter
+constexpr uint32_t kDirectSpread = 16;     // counters per round, one per 64-byte line
+constexpr uint32_t kDirectStride = 8;      // 8-byte words between two counters
+struct DirectArgs {
+    const uint32_t *da, *db;  // row-major; one DFA: nb == 0
+    const uint8_t *aa, *ab;
+    uint32_t na, nb, N, k;    // N = na + nb; 1 <= k <= kDirectMaxK
+    uint32_t wide;            // rows of a multiple of 4 letters, 16-byte aligned
+    uint32_t check_eq, eq_a, eq_b;
+    uint32_t *blockA, *blockB;  // round r reads A (even) or B (odd), writes the other
+    uint32_t *multi;            // zero before round 0
+    unsigned long long *table;  // zero before round 0; mask + 1 >= 2N slots
+    uint64_t mask;
+    // per round and counter: blocks after the round, refined states << 32;
+    // zero before round 0
+    unsigned long long *cnt;
+    uint32_t *flags;  // target out of range, accepting, rejecting state, letter moves a state
+    RoundCtl *ctl;
+};
+// Round r < kDirectMaxRounds (does nothing once the refinement has stopped).
+void launch_direct_round(const DirectArgs &a, uint32_t r, hipStream_t s);
+// *ctl from the counters of the rounds that ran, of `launched`.
+void launch_direct_end(const DirectArgs &a, uint32_t launched, hipStream_t s);
+// Singleton bits after `rounds` rounds; the refined-state masks are the same.
+void launch_direct_singles(const DirectArgs &a, uint32_t rounds, unsigned long long *single,
+                           unsigned long long *active, hipStream_t s);
+
 // ---- leader-based refinement (naivePR; leader_kernels.hip) ----
 //
 //   block       uint32 [N]          leader (smallest member) of q's block,
@@ -402,28 +431,38 @@ void launch_zero(const ZeroList &z, hipStream_t s);
 void launch_canonicalise(const uint32_t *ids, size_t N, size_t id_range, uint32_t *scratch_min,
                          uint32_t *out, hipStream_t s);
 
-// Dense quotient numbering of a canonical partition: dense[l] for every
-// leader l (block[l] == l) in increasing order; leader_of[b] = l;
-// *num_blocks = B.  partials needs ceil(N / kScanTile) + 1 words.
+// The same for ids < N with a scratch of N words that starts at zero; with
+// partials, also the leaders (out[q] == q) per tile of kScanTile states.
 constexpr uint32_t kScanTile = 1024;
-void launch_dense_leaders(const uint32_t *block, size_t N, uint32_t *partials, uint32_t *dense,
-                          uint32_t *leader_of, uint32_t *num_blocks, hipStream_t s);
+void launch_canonical_leaders(const uint32_t *ids, size_t N, uint32_t *scratch_max, uint32_t *out,
+                              uint32_t *partials, hipStream_t s);
+// Leaders per tile of a canonical partition.
+void launch_leader_tiles(const uint32_t *block, size_t N, uint32_t *partials, hipStream_t s);
+// out[q] = q.
+void launch_iota(uint32_t *out, size_t n, hipStream_t s);
+void launch_copy_u32(const uint32_t *in, size_t n, uint32_t *out, hipStream_t s);
 
-// qdelta[b*k + a] = dense[block[delta[l*k + a]]], qacc[b] = acc[l] for
-// l = leader_of[b]; *qstart = dense[block[start]].  dq: n words of scratch.
-// The same numbering of the marked states (mark[q] != 0): dense[q],
-// leader_of[dense[q]] = q, *num = their count; *start_dense = dense[start].
+// Dense numbering of the marked states (mark[q] != 0) in increasing order:
+// dense[q], leader_of[dense[q]] = q, *num = their count; *start_dense =
+// dense[start].  partials needs ceil(n / kScanTile) + 1 words.
 void launch_dense_marks(const uint8_t *mark, size_t n, uint32_t start, uint32_t *partials,
                         uint32_t *dense, uint32_t *leader_of, uint32_t *num,
                         uint32_t *start_dense, hipStream_t s);
 
-void launch_quotient(const uint32_t *delta, const uint8_t *acc, uint32_t k,
-                     const uint32_t *block, const uint32_t *dense, const uint32_t *leader_of,
-                     const uint32_t *num_blocks, uint32_t n, uint32_t start, uint32_t *dq,
-                     uint32_t *qdelta, uint8_t *qacc, uint32_t *qstart, hipStream_t s);
-// Quotient of a discrete partition (num_blocks == n): a copy of the input.
+// Quotient of a canonical partition from its leaders per tile (partials,
+// with room for one more word): leaders numbered in increasing order
+// (dense[l], leader_of[b] = l), *num_blocks, qdelta[b*k + a] = dense id of
+// delta(l, a), qacc[b] = acc[l] as 0/1, *qstart = dense id of start.  dq: n
+// words of scratch.
+void launch_quotient_from_tiles(const uint32_t *delta, const uint8_t *acc, uint32_t k,
+                                const uint32_t *block, uint32_t *partials, uint32_t n,
+                                uint32_t start, uint32_t *dense, uint32_t *leader_of, uint32_t *dq,
+                                uint32_t *num_blocks, uint32_t *qdelta, uint8_t *qacc,
+                                uint32_t *qstart, hipStream_t s);
+// Ids and quotient of a discrete partition (every block a single state): the
+// states themselves and a copy of the input.
 void launch_quotient_identity(const uint32_t *delta, const uint8_t *acc, uint32_t n, uint32_t k,
-                              uint32_t start, uint32_t *qdelta, uint8_t *qacc, uint32_t *qstart,
+                              uint32_t *block_out, uint32_t *qdelta, uint8_t *qacc,
                               hipStream_t s);
 
 // ---- small DFAs, one workgroup each (batch_kernels.hip) ----

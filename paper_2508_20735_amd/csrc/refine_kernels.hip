@@ -2410,6 +2410,38 @@ __global__ __launch_bounds__(kBlock) void k_canon_min(const uint32_t *__restrict
         atomicMin(mins + ids[q], static_cast<uint32_t>(q));
 }
 
+// The same in a scratch that starts at zero: the maximum of ~q.
+__global__ __launch_bounds__(kBlock) void k_canon_max(const uint32_t *__restrict__ ids, size_t N,
+                                                       uint32_t *maxs) {
+    for (size_t q = global_tid(); q < N; q += grid_stride())
+        atomicMax(maxs + ids[q], ~static_cast<uint32_t>(q));
+}
+
+// out[q] = the smallest state of q's block, and the leaders per tile (for
+// the dense numbering) when partials is given; one state per thread.
+__global__ __launch_bounds__(kScanTile) void k_canon_leaders(const uint32_t *__restrict__ ids,
+                                                             size_t N,
+                                                             const uint32_t *__restrict__ maxs,
+                                                             uint32_t *__restrict__ out,
+                                                             uint32_t *partials) {
+    __shared__ uint32_t wsum[kScanTile / 64];
+    const size_t q = static_cast<size_t>(blockIdx.x) * kScanTile + threadIdx.x;
+    uint32_t b = ~0u;
+    if (q < N) {
+        b = ~maxs[ids[q]];
+        out[q] = b;
+    }
+    if (!partials) return;
+    const unsigned long long m = __ballot(q < N && b == q);
+    if (lane_id() == 0) wsum[threadIdx.x / 64] = static_cast<uint32_t>(__popcll(m));
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t s = 0;
+        for (uint32_t w = 0; w < kScanTile / 64; ++w) s += wsum[w];
+        partials[blockIdx.x] = s;
+    }
+}
+
 __global__ __launch_bounds__(kBlock) void k_canon_apply(const uint32_t *__restrict__ ids, size_t N,
                                                          const uint32_t *__restrict__ mins,
                                                          uint32_t *__restrict__ out) {
@@ -2515,6 +2547,41 @@ __global__ __launch_bounds__(kScanThreads) void k_leader_rank(Pick pick, size_t 
     }
 }
 
+// k_leader_rank for at most kScanTile tiles, with the tile counts as they
+// are: every workgroup sums the counts before its own (the scan's launch
+// costs more than these loads); *total = their sum.
+__global__ __launch_bounds__(kScanThreads) void k_leader_rank_small(
+    const uint32_t *__restrict__ block, size_t N, const uint32_t *__restrict__ partials,
+    uint32_t ntiles, uint32_t *__restrict__ dense, uint32_t *__restrict__ leader_of,
+    uint32_t *total) {
+    __shared__ uint32_t wsum[kScanThreads / 64], psum[kScanThreads / 64];
+    const size_t q = static_cast<size_t>(blockIdx.x) * kScanTile + threadIdx.x;
+    const uint32_t lane = lane_id(), wave = threadIdx.x / 64;
+    const bool lead = q < N && block[q] == q;
+    const unsigned long long m = __ballot(lead);
+    uint32_t p = threadIdx.x < blockIdx.x && threadIdx.x < ntiles ? partials[threadIdx.x] : 0u;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) p += __shfl_xor(p, d, 64);
+    if (lane == 0) {
+        wsum[wave] = static_cast<uint32_t>(__popcll(m));
+        psum[wave] = p;
+    }
+    __syncthreads();
+    uint32_t before = 0, here = 0, own = 0;
+    for (uint32_t w = 0; w < kScanThreads / 64; ++w) {
+        before += psum[w];
+        own += w < wave ? wsum[w] : 0u;
+        here += wsum[w];
+    }
+    if (lead) {
+        const unsigned long long below = lane ? (m & ((1ull << lane) - 1ull)) : 0ull;
+        const uint32_t d = before + own + static_cast<uint32_t>(__popcll(below));
+        dense[q] = d;
+        leader_of[d] = static_cast<uint32_t>(q);
+    }
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total = before + here;
+}
+
 // dq[q] = dense id of q's block.
 __global__ __launch_bounds__(kBlock) void k_dense_of_state(const uint32_t *__restrict__ block,
                                                             const uint32_t *__restrict__ dense,
@@ -2542,18 +2609,57 @@ __global__ __launch_bounds__(kBlock) void k_quotient(const uint32_t *__restrict_
     }
 }
 
-// Discrete partition (every block a single state): the quotient is the input.
+// k_quotient without dq: the dense id through the block id.
+__global__ __launch_bounds__(kBlock) void k_quotient_small(
+    const uint32_t *__restrict__ delta, const uint8_t *__restrict__ acc, uint32_t k,
+    const uint32_t *__restrict__ block, const uint32_t *__restrict__ dense,
+    const uint32_t *__restrict__ leader_of, const uint32_t *num_blocks, uint32_t start,
+    uint32_t *__restrict__ qdelta, uint8_t *__restrict__ qacc, uint32_t *qstart) {
+    const size_t total = static_cast<size_t>(*num_blocks) * k;
+    if (global_tid() == 0) *qstart = dense[block[start]];
+    for (size_t i = global_tid(); i < total; i += grid_stride()) {
+        const size_t b = i / k;
+        const uint32_t a = static_cast<uint32_t>(i - b * k);
+        const size_t l = leader_of[b];
+        qdelta[i] = dense[block[delta[l * k + a]]];
+        if (a == 0) qacc[b] = acc[l] ? 1 : 0;
+    }
+}
+
+// Discrete partition (every block a single state): the ids are the states
+// themselves.
+__global__ __launch_bounds__(kBlock) void k_iota(uint32_t *out, size_t n) {
+    for (size_t q = global_tid(); q < n; q += grid_stride()) out[q] = static_cast<uint32_t>(q);
+}
+
+__global__ __launch_bounds__(kBlock) void k_copy_u32(const uint32_t *__restrict__ in, size_t n,
+                                                      uint32_t *__restrict__ out) {
+    for (size_t q = global_tid(); q < n; q += grid_stride()) out[q] = in[q];
+}
+
+// Discrete partition (every block a single state): the quotient is the
+// input, and the ids are the states themselves.  16 bytes at a time between
+// aligned arrays.
 __global__ __launch_bounds__(kBlock) void k_quotient_identity(const uint32_t *__restrict__ delta,
                                                                const uint8_t *__restrict__ acc,
                                                                size_t n, uint32_t k,
-                                                               uint32_t start,
+                                                               uint32_t *__restrict__ block_out,
                                                                uint32_t *__restrict__ qdelta,
-                                                               uint8_t *__restrict__ qacc,
-                                                               uint32_t *qstart) {
-    if (global_tid() == 0) *qstart = start;
+                                                               uint8_t *__restrict__ qacc) {
     const size_t total = n * k;
-    for (size_t i = global_tid(); i < total; i += grid_stride()) qdelta[i] = delta[i];
-    for (size_t q = global_tid(); q < n; q += grid_stride()) qacc[q] = acc[q] ? 1 : 0;
+    size_t done = 0;
+    if (((reinterpret_cast<uintptr_t>(delta) | reinterpret_cast<uintptr_t>(qdelta)) & 15u) == 0) {
+        const size_t quads = total / 4;
+        const uint4 *__restrict__ in = reinterpret_cast<const uint4 *>(delta);
+        uint4 *__restrict__ out = reinterpret_cast<uint4 *>(qdelta);
+        for (size_t i = global_tid(); i < quads; i += grid_stride()) out[i] = in[i];
+        done = quads * 4;
+    }
+    for (size_t i = done + global_tid(); i < total; i += grid_stride()) qdelta[i] = delta[i];
+    for (size_t q = global_tid(); q < n; q += grid_stride()) {
+        qacc[q] = acc[q] ? 1 : 0;
+        block_out[q] = static_cast<uint32_t>(q);
+    }
 }
 
 unsigned grid_for(size_t work, unsigned cap = 1u << 20) {
@@ -2962,35 +3068,72 @@ void dense_numbering(Pick pick, size_t N, uint32_t *partials, uint32_t *dense, u
 
 }  // namespace
 
-void launch_dense_leaders(const uint32_t *block, size_t N, uint32_t *partials, uint32_t *dense,
-                          uint32_t *leader_of, uint32_t *num_blocks, hipStream_t s) {
-    dense_numbering(IsLeader{block}, N, partials, dense, leader_of, num_blocks, ~static_cast<size_t>(0),
-                    nullptr, s);
-}
-
 void launch_dense_marks(const uint8_t *mark, size_t n, uint32_t start, uint32_t *partials,
                         uint32_t *dense, uint32_t *leader_of, uint32_t *num,
                         uint32_t *start_dense, hipStream_t s) {
     dense_numbering(IsMarked{mark}, n, partials, dense, leader_of, num, start, start_dense, s);
 }
 
-void launch_quotient(const uint32_t *delta, const uint8_t *acc, uint32_t k,
-                     const uint32_t *block, const uint32_t *dense, const uint32_t *leader_of,
-                     const uint32_t *num_blocks, uint32_t n, uint32_t start, uint32_t *dq,
-                     uint32_t *qdelta, uint8_t *qacc, uint32_t *qstart, hipStream_t s) {
-    launch_kernel(k_dense_of_state, dim3(grid_for(n, kDefaultGridCap)), dim3(kBlock), 0, s,
-                       block, dense, static_cast<size_t>(n), dq);
-    launch_kernel(k_quotient, dim3(grid_for(static_cast<size_t>(n) * k, kDefaultGridCap)),
-                       dim3(kBlock), 0, s, delta, acc, k, dq, leader_of, num_blocks, start, qdelta,
-                       qacc, qstart);
-}
-
 void launch_quotient_identity(const uint32_t *delta, const uint8_t *acc, uint32_t n, uint32_t k,
-                              uint32_t start, uint32_t *qdelta, uint8_t *qacc, uint32_t *qstart,
+                              uint32_t *block_out, uint32_t *qdelta, uint8_t *qacc,
                               hipStream_t s) {
     launch_kernel(k_quotient_identity,
-                       dim3(grid_for(static_cast<size_t>(n) * k, kDefaultGridCap)), dim3(kBlock),
-                       0, s, delta, acc, static_cast<size_t>(n), k, start, qdelta, qacc, qstart);
+                       dim3(grid_for(static_cast<size_t>(n) * std::max(k / 4, 1u), kDefaultGridCap)),
+                       dim3(kBlock), 0, s, delta, acc, static_cast<size_t>(n), k, block_out, qdelta,
+                       qacc);
+}
+
+void launch_iota(uint32_t *out, size_t n, hipStream_t s) {
+    launch_kernel(k_iota, dim3(grid_for(n, kDefaultGridCap)), dim3(kBlock), 0, s, out, n);
+}
+
+void launch_copy_u32(const uint32_t *in, size_t n, uint32_t *out, hipStream_t s) {
+    launch_kernel(k_copy_u32, dim3(grid_for(n, kDefaultGridCap)), dim3(kBlock), 0, s, in, n, out);
+}
+
+void launch_canonical_leaders(const uint32_t *ids, size_t N, uint32_t *scratch_max, uint32_t *out,
+                              uint32_t *partials, hipStream_t s) {
+    launch_kernel(k_canon_max, dim3(grid_for(N)), dim3(kBlock), 0, s, ids, N, scratch_max);
+    launch_kernel(k_canon_leaders, dim3(static_cast<unsigned>((N + kScanTile - 1) / kScanTile)),
+                  dim3(kScanTile), 0, s, ids, N, static_cast<const uint32_t *>(scratch_max), out,
+                  partials);
+}
+
+void launch_leader_tiles(const uint32_t *block, size_t N, uint32_t *partials, hipStream_t s) {
+    launch_kernel(k_leader_partials<IsLeader>, dim3(static_cast<unsigned>((N + kScanTile - 1) / kScanTile)),
+                  dim3(kScanThreads), 0, s, IsLeader{block}, N, partials);
+}
+
+void launch_quotient_from_tiles(const uint32_t *delta, const uint8_t *acc, uint32_t k,
+                                const uint32_t *block, uint32_t *partials, uint32_t n,
+                                uint32_t start, uint32_t *dense, uint32_t *leader_of, uint32_t *dq,
+                                uint32_t *num_blocks, uint32_t *qdelta, uint8_t *qacc,
+                                uint32_t *qstart, hipStream_t s) {
+    const uint32_t ntiles = static_cast<uint32_t>((static_cast<size_t>(n) + kScanTile - 1) / kScanTile);
+    const dim3 qgrid(grid_for(static_cast<size_t>(n) * k, kDefaultGridCap)), block_dim(kBlock);
+    // up to 2^20 states the ids stay in L2, where two dependent gathers per
+    // transition cost less than a launch; beyond, the dense id of every
+    // state is laid out first
+    if (ntiles <= kScanTile) {
+        launch_kernel(k_leader_rank_small, dim3(ntiles), dim3(kScanThreads), 0, s, block,
+                      static_cast<size_t>(n), static_cast<const uint32_t *>(partials), ntiles,
+                      dense, leader_of, num_blocks);
+        launch_kernel(k_quotient_small, qgrid, block_dim, 0, s, delta, acc, k, block,
+                      static_cast<const uint32_t *>(dense),
+                      static_cast<const uint32_t *>(leader_of),
+                      static_cast<const uint32_t *>(num_blocks), start, qdelta, qacc, qstart);
+        return;
+    }
+    launch_kernel(k_scan_partials, dim3(1), dim3(kScanThreads), 0, s, partials, ntiles,
+                  num_blocks);
+    launch_kernel(k_leader_rank<IsLeader>, dim3(ntiles), dim3(kScanThreads), 0, s, IsLeader{block},
+                  static_cast<size_t>(n), static_cast<const uint32_t *>(partials), dense, leader_of,
+                  ~static_cast<size_t>(0), static_cast<uint32_t *>(nullptr));
+    launch_kernel(k_dense_of_state, dim3(grid_for(n, kDefaultGridCap)), block_dim, 0, s, block,
+                  static_cast<const uint32_t *>(dense), static_cast<size_t>(n), dq);
+    launch_kernel(k_quotient, qgrid, block_dim, 0, s, delta, acc, k, static_cast<const uint32_t *>(dq),
+                  static_cast<const uint32_t *>(leader_of),
+                  static_cast<const uint32_t *>(num_blocks), start, qdelta, qacc, qstart);
 }
 
 }  // namespace dfamin
