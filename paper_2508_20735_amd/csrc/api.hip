@@ -515,12 +515,19 @@ struct RefineResult {
     const uint32_t *final_block = nullptr;
     uint64_t transitions = 0, bytes = 0;
     uint32_t N = 0;  // states refined
+    bool outputs_done = false;  // the canonical ids and the quotient are written too
 };
 
 // A refinement that goes on in the general path after its first rounds: ids
 // in the block buffers, singleton bits and round state are on the device.
 struct Resume {
     std::vector<uint32_t> colmap;  // letters that move some state
+};
+
+// Where a minimisation's results go (device memory).
+struct Outputs {
+    uint32_t *block;
+    dfa_quotient *q;  // or nullptr
 };
 
 // Whether plain rounds have stalled, after at least 8 rounds: over the last
@@ -1208,16 +1215,24 @@ int prepare_refinement(Ctx &c, size_t N, uint32_t k, bool canon = false) {
 }
 
 // States above which a refinement takes the general path from its first
-// round (see refine_direct).
-constexpr size_t kDirectMaxStates = size_t(1) << 18;
+// round.  The general path skips blocks whose members' successors kept their
+// ids and gathers through LDS slices from 2^20 states on, the direct one has
+// neither.  Measured on MI355X, direct against general, random DFAs of 2 to
+// 16 letters: minimisation of 2^17 states 143-167 us against 188-250, of 2^19
+// 241-380 against 257-437, of 2^21 819-986 against 564-751; equivalence with
+// a copy of one redirected transition (many rounds that change few ids),
+// union of 2^18 states 351-698 us against 394-730, of 2^19 513-886 against
+// 465-737.
+constexpr size_t kDirectMaxStates = size_t(1) << 19;
+constexpr size_t kDirectMaxUnion = size_t(1) << 18;
 
 // Whether the rounds may run one launch each, straight from the inputs
 // (direct_kernels.hip): hash grouping with the default round options, no
 // closure from the start, at most kDirectMaxK letters.  Calls that choose a
 // loop driver, a chunk length, a round limit, a grouping variant or a kernel
 // tuning of the general rounds, or time its kernels, run those.
-bool direct_applies(const Ctx &c, size_t N, uint32_t k, const dfa_options &o) {
-    return N <= kDirectMaxStates && k <= kDirectMaxK && o.algorithm == DFA_ALGO_SIGNATURE &&
+bool direct_applies(const Ctx &c, size_t N, uint32_t k, bool is_union, const dfa_options &o) {
+    return N <= (is_union ? kDirectMaxUnion : kDirectMaxStates) && k <= kDirectMaxK && o.algorithm == DFA_ALGO_SIGNATURE &&
            o.tc_mode != DFA_TC_ON &&
            (o.loop_mode == DFA_LOOP_GRAPH || o.loop_mode == DFA_LOOP_CHUNK) && !o.max_rounds &&
            !o.chunk && o.lds_stage == 2 && !c.tune.hash_bits && c.tune.label_rounds == 2 &&
@@ -1226,14 +1241,19 @@ bool direct_applies(const Ctx &c, size_t N, uint32_t k, const dfa_options &o) {
 
 // The first rounds of a refinement of ordinary size, one launch each; done:
 // the refinement is decided and res is complete.  Otherwise the general path
-// goes on from round res.ctl.round (resume).
-int refine_direct(Ctx &c, const dfa_view &a, const dfa_view *b, bool canon, RefineResult &res,
-                  Resume &resume, bool &done) {
+// goes on from round res.ctl.round (resume).  out: the canonical ids and the
+// quotient are queued behind the first rounds, before the host knows whether
+// they decided the refinement (the kernels look), so that a call that they do
+// decide waits once; res.outputs_done says so.
+int refine_direct(Ctx &c, const dfa_view &a, const dfa_view *b, bool canon, const Outputs *out,
+                  RefineResult &res, Resume &resume, bool &done) {
     done = false;
     const uint32_t k = a.k;
     const size_t N = static_cast<size_t>(a.n) + (b ? b->n : 0);
-    const uint64_t cap = next_pow2(std::max<uint64_t>(2 * N, 1024));
-    constexpr size_t kCtlBytes = sizeof(RoundCtl) + (3 + kDirectMaxK) * sizeof(uint32_t);
+    // a quarter full at most: a longer probe is one more dependent access
+    const uint64_t cap = next_pow2(std::max<uint64_t>(4 * N, 1024));
+    // round state, flags, then the quotient's size and start
+    constexpr size_t kCtlBytes = sizeof(RoundCtl) + (5 + kDirectMaxK) * sizeof(uint32_t);
     constexpr size_t kCntBytes =
         size_t(kDirectMaxRounds) * kDirectSpread * kDirectStride * sizeof(unsigned long long);
     DFA_TRY(c.ctl.ensure(kCtlBytes, "round state"));
@@ -1263,7 +1283,7 @@ int refine_direct(Ctx &c, const dfa_view &a, const dfa_view *b, bool canon, Refi
     }
     d.N = static_cast<uint32_t>(N);
     d.k = k;
-    d.wide = k % 4 == 0 &&
+    d.wide = k % 4 == 0 && k == direct_width(k) &&
              ((reinterpret_cast<uintptr_t>(d.da) | reinterpret_cast<uintptr_t>(d.db)) & 15u) == 0;
     d.blockA = c.blockA.as<uint32_t>();
     d.blockB = c.blockB.as<uint32_t>();
@@ -1282,6 +1302,19 @@ int refine_direct(Ctx &c, const dfa_view &a, const dfa_view *b, bool canon, Refi
     for (uint32_t stop : stops) {
         while (launched < stop) launch_direct_round(d, launched++, c.stream);
         launch_direct_end(d, launched, c.stream);
+        const bool queued = out && stop == stops[0];
+        if (queued) {
+            launch_direct_canonical(d, c.canon.as<uint32_t>(), out->block, c.partials.as<uint32_t>(),
+                                    c.stream);
+            if (out->q)
+                launch_quotient_from_tiles(a.delta, a.accepting, k, out->block,
+                                           c.partials.as<uint32_t>(), a.n, a.start,
+                                           c.dense.as<uint32_t>(), c.leader_of.as<uint32_t>(),
+                                           nullptr, d.flags + 3 + kDirectMaxK, out->q->delta,
+                                           out->q->accepting, d.flags + 4 + kDirectMaxK, d.ctl,
+                                           c.stream);
+            if (c.ev_stop) HIP_TRY(hipEventRecord(c.ev_stop, c.stream));
+        }
         HIP_TRY(hipGetLastError());
         DFA_TRY(read_back(c, c.ctl.p, kCtlBytes));
         std::memcpy(&res.ctl, c.pinned, sizeof(RoundCtl));
@@ -1290,7 +1323,13 @@ int refine_direct(Ctx &c, const dfa_view &a, const dfa_view *b, bool canon, Refi
         resume.colmap.clear();
         for (uint32_t j = 0; j < k; ++j)
             if (flags[3 + j]) resume.colmap.push_back(j);
-        if (res.ctl.done) break;
+        if (!res.ctl.done) continue;
+        res.outputs_done = queued;
+        if (queued && out->q) {
+            out->q->num_blocks = flags[3 + kDirectMaxK];
+            out->q->start = flags[4 + kDirectMaxK];
+        }
+        break;
     }
     res.N = static_cast<uint32_t>(N);
     res.k_eff = static_cast<uint32_t>(resume.colmap.size());
@@ -1312,16 +1351,16 @@ int refine_direct(Ctx &c, const dfa_view &a, const dfa_view *b, bool canon, Refi
 // states separate), by the algorithm of the options.  canon: the scratch of
 // the canonical ids is cleared too.
 int refine_any(Ctx &c, const dfa_view &a, const dfa_view *b, const dfa_options &o, bool canon,
-               RefineResult &res) {
+               const Outputs *out, RefineResult &res) {
     const uint32_t k = a.k;
     const size_t N = static_cast<size_t>(a.n) + (b ? b->n : 0);
     // (a context without events, the allocation-free one, times on the host)
     if (c.ev_start) HIP_TRY(hipEventRecord(c.ev_start, c.stream));
     Resume resume;
     bool resumed = false;
-    if (direct_applies(c, N, k, o)) {
+    if (direct_applies(c, N, k, b != nullptr, o)) {
         bool done = false;
-        DFA_TRY(refine_direct(c, a, b, canon, res, resume, done));
+        DFA_TRY(refine_direct(c, a, b, canon, out, res, resume, done));
         if (done) return DFA_OK;
         resumed = true;
         canon = false;  // (cleared)
@@ -1354,28 +1393,17 @@ int refine_any(Ctx &c, const dfa_view &a, const dfa_view *b, const dfa_options &
 int minimise_pruned(Ctx &c, uint32_t n, uint32_t k, const uint32_t *delta, const uint8_t *acc,
                     uint32_t *block_out, dfa_quotient *q, const dfa_options &o, dfa_stats *st);
 
-int minimise_impl(Ctx &c, uint32_t n, uint32_t k, const uint32_t *delta, const uint8_t *acc,
-                  uint32_t *block_out, dfa_quotient *q, const dfa_options &o, dfa_stats *st) {
-    if (o.prune) return minimise_pruned(c, n, k, delta, acc, block_out, q, o, st);
-    // (the leaders of leader rounds are canonical ids already)
-    const bool canon = o.algorithm != DFA_ALGO_LEADER;
-    if (canon || q) DFA_TRY(c.canon.ensure(static_cast<size_t>(n) * sizeof(uint32_t), "canonical ids"));
-    RefineResult r;
-    const dfa_view view{n, k, o.start, delta, acc};
-    int rc = refine_any(c, view, nullptr, o, canon, r);
-    if (rc != DFA_OK) return rc;
+// Canonical ids and the quotient of a finished refinement.
+int write_outputs(Ctx &c, uint32_t n, uint32_t k, const uint32_t *delta, const uint8_t *acc,
+                  uint32_t *block_out, dfa_quotient *q, const dfa_options &o,
+                  const RefineResult &r) {
     const bool discrete = r.ctl.prev_count == n;
     if (discrete && q) {
         launch_quotient_identity(delta, acc, n, k, block_out, q->delta, q->accepting, c.stream);
     } else if (discrete) {
         launch_iota(block_out, n, c.stream);
     } else {
-        uint32_t *partials = nullptr;
-        if (q) {
-            const size_t ntiles = (static_cast<size_t>(n) + kScanTile - 1) / kScanTile;
-            DFA_TRY(c.partials.ensure((ntiles + 1) * sizeof(uint32_t), "scan partials"));
-            partials = c.partials.as<uint32_t>();
-        }
+        uint32_t *partials = q ? c.partials.as<uint32_t>() : nullptr;
         if (o.algorithm == DFA_ALGO_LEADER) {
             // leaders are the smallest members already
             launch_copy_u32(r.final_block, n, block_out, c.stream);
@@ -1387,13 +1415,11 @@ int minimise_impl(Ctx &c, uint32_t n, uint32_t k, const uint32_t *delta, const u
         if (q) {
             DFA_TRY(c.scalars.ensure(16 * sizeof(uint32_t), "scalars"));
             uint32_t *sc = c.scalars.as<uint32_t>();
-            DFA_TRY(c.dense.ensure(static_cast<size_t>(n) * sizeof(uint32_t), "dense ids"));
-            DFA_TRY(c.leader_of.ensure(static_cast<size_t>(n) * sizeof(uint32_t), "leaders"));
             // the canonicalisation scratch is free again: it holds dq
             launch_quotient_from_tiles(delta, acc, k, block_out, partials, n, o.start,
                                        c.dense.as<uint32_t>(), c.leader_of.as<uint32_t>(),
                                        c.canon.as<uint32_t>(), sc, q->delta, q->accepting, sc + 1,
-                                       c.stream);
+                                       nullptr, c.stream);
         }
     }
     HIP_TRY(hipGetLastError());
@@ -1409,6 +1435,27 @@ int minimise_impl(Ctx &c, uint32_t n, uint32_t k, const uint32_t *delta, const u
             q->start = o.start;
         }
     }
+    return DFA_OK;
+}
+
+int minimise_impl(Ctx &c, uint32_t n, uint32_t k, const uint32_t *delta, const uint8_t *acc,
+                  uint32_t *block_out, dfa_quotient *q, const dfa_options &o, dfa_stats *st) {
+    if (o.prune) return minimise_pruned(c, n, k, delta, acc, block_out, q, o, st);
+    // (the leaders of leader rounds are canonical ids already)
+    const bool canon = o.algorithm != DFA_ALGO_LEADER;
+    if (canon || q) DFA_TRY(c.canon.ensure(static_cast<size_t>(n) * sizeof(uint32_t), "canonical ids"));
+    const size_t ntiles = (static_cast<size_t>(n) + kScanTile - 1) / kScanTile;
+    DFA_TRY(c.partials.ensure((ntiles + 1) * sizeof(uint32_t), "scan partials"));
+    if (q) {
+        DFA_TRY(c.dense.ensure(static_cast<size_t>(n) * sizeof(uint32_t), "dense ids"));
+        DFA_TRY(c.leader_of.ensure(static_cast<size_t>(n) * sizeof(uint32_t), "leaders"));
+    }
+    RefineResult r;
+    const dfa_view view{n, k, o.start, delta, acc};
+    const Outputs out{block_out, q};
+    int rc = refine_any(c, view, nullptr, o, canon, &out, r);
+    if (rc != DFA_OK) return rc;
+    if (!r.outputs_done) DFA_TRY(write_outputs(c, n, k, delta, acc, block_out, q, o, r));
     if (r.ctl.limit) {
         fill_stats(st, r);
         return fail(DFA_ELIMIT, "max_rounds (%u) reached before the partition was stable",
@@ -1542,7 +1589,7 @@ int equivalent_impl(Ctx &c, const dfa_view &a, const dfa_view &b, int *verdict,
     const size_t N = static_cast<size_t>(a.n) + b.n;
     if (N >= 0xFFFFFFFFull) return fail(DFA_EINVAL, "nA + nB must be < 2^32 - 1");
     RefineResult r;
-    DFA_TRY(refine_any(c, a, &b, o, false, r));
+    DFA_TRY(refine_any(c, a, &b, o, false, nullptr, r));
     HIP_TRY(hipEventRecord(c.ev_stop, c.stream));
     HIP_TRY(stream_sync(c));
     fill_stats(st, r);

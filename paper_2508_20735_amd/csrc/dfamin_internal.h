@@ -305,7 +305,7 @@ struct DirectArgs {
     const uint32_t *da, *db;  // row-major; one DFA: nb == 0
     const uint8_t *aa, *ab;
     uint32_t na, nb, N, k;    // N = na + nb; 1 <= k <= kDirectMaxK
-    uint32_t wide;            // rows of a multiple of 4 letters, 16-byte aligned
+    uint32_t wide;            // k = direct_width(k) is a multiple of 4, 16-byte aligned rows
     uint32_t check_eq, eq_a, eq_b;
     uint32_t *blockA, *blockB;  // round r reads A (even) or B (odd), writes the other
     uint32_t *multi;            // zero before round 0
@@ -317,10 +317,20 @@ struct DirectArgs {
     uint32_t *flags;  // target out of range, accepting, rejecting state, letter moves a state
     RoundCtl *ctl;
 };
+// Letters of the kernel that takes k (power of two).
+inline uint32_t direct_width(uint32_t k) {
+    uint32_t w = 1;
+    while (w < k) w <<= 1;
+    return w;
+}
 // Round r < kDirectMaxRounds (does nothing once the refinement has stopped).
 void launch_direct_round(const DirectArgs &a, uint32_t r, hipStream_t s);
 // *ctl from the counters of the rounds that ran, of `launched`.
 void launch_direct_end(const DirectArgs &a, uint32_t launched, hipStream_t s);
+// If the rounds so far decided the refinement: the canonical ids (scratch_max:
+// N words, zero before) and the leaders per tile of kScanTile states.
+void launch_direct_canonical(const DirectArgs &a, uint32_t *scratch_max, uint32_t *out,
+                             uint32_t *partials, hipStream_t s);
 // Singleton bits after `rounds` rounds; the refined-state masks are the same.
 void launch_direct_singles(const DirectArgs &a, uint32_t rounds, unsigned long long *single,
                            unsigned long long *active, hipStream_t s);
@@ -453,12 +463,12 @@ void launch_dense_marks(const uint8_t *mark, size_t n, uint32_t start, uint32_t 
 // with room for one more word): leaders numbered in increasing order
 // (dense[l], leader_of[b] = l), *num_blocks, qdelta[b*k + a] = dense id of
 // delta(l, a), qacc[b] = acc[l] as 0/1, *qstart = dense id of start.  dq: n
-// words of scratch.
+// words of scratch.  With ctl (at most kScanTile tiles): only if ctl->done.
 void launch_quotient_from_tiles(const uint32_t *delta, const uint8_t *acc, uint32_t k,
                                 const uint32_t *block, uint32_t *partials, uint32_t n,
                                 uint32_t start, uint32_t *dense, uint32_t *leader_of, uint32_t *dq,
                                 uint32_t *num_blocks, uint32_t *qdelta, uint8_t *qacc,
-                                uint32_t *qstart, hipStream_t s);
+                                uint32_t *qstart, const RoundCtl *ctl, hipStream_t s);
 // Ids and quotient of a discrete partition (every block a single state): the
 // states themselves and a copy of the input.
 void launch_quotient_identity(const uint32_t *delta, const uint8_t *acc, uint32_t n, uint32_t k,

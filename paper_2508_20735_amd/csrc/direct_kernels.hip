@@ -29,6 +29,7 @@ namespace {
 
 constexpr unsigned long long kEmptyLds = ~0ull;
 constexpr uint32_t kDirectLds = 2 * kBlock;  // LDS table slots (load <= 1/2)
+constexpr uint64_t kDirectEagerEdges = uint64_t(1) << 19;
 
 // The ids a round starts from: the acceptance of the state in the first
 // round, the last round's block ids afterwards.
@@ -45,14 +46,16 @@ struct Keys {
         return (in_b ? a.db : a.da) + static_cast<size_t>(q - off) * a.k;
     }
     // Targets of q, numbered in the union; one outside its operand becomes
-    // the operand's first state and sets `bad` (the call then fails).
+    // the operand's first state and sets `bad` (the call then fails).  With
+    // fewer letters than KC the first one fills up (a repeated key component
+    // changes no comparison, and loads without branches stay in flight
+    // together).
     __device__ __forceinline__ void targets(uint32_t q, uint32_t *t, bool &bad) const {
         uint32_t n, off;
         const uint32_t *r = row(q, n, off);
-        if (KC % 4 == 0 && a.wide) {
+        if (KC % 4 == 0 && a.wide) {  // (k == KC)
 #pragma unroll
             for (int j = 0; j < KC; j += 4) {
-                if (j >= static_cast<int>(a.k)) break;
                 const uint4 v = *reinterpret_cast<const uint4 *>(r + j);
                 t[j] = v.x;
                 t[j + 1] = v.y;
@@ -61,16 +64,14 @@ struct Keys {
             }
         } else {
 #pragma unroll
-            for (int j = 0; j < KC; ++j)
-                if (j < static_cast<int>(a.k)) t[j] = r[j];
+            for (int j = 0; j < KC; ++j) t[j] = r[j < static_cast<int>(a.k) ? j : 0];
         }
 #pragma unroll
-        for (int j = 0; j < KC; ++j)
-            if (j < static_cast<int>(a.k)) {
-                const bool out = t[j] >= n;
-                bad |= out;
-                t[j] = off + (out ? 0u : t[j]);
-            }
+        for (int j = 0; j < KC; ++j) {
+            const bool out = t[j] >= n;
+            bad |= out;
+            t[j] = off + (out ? 0u : t[j]);
+        }
     }
     __device__ __forceinline__ uint32_t id(uint32_t q) const {
         if constexpr (FIRST)
@@ -80,8 +81,7 @@ struct Keys {
     }
     __device__ __forceinline__ void ids(const uint32_t *t, uint32_t *w) const {
 #pragma unroll
-        for (int j = 0; j < KC; ++j)
-            if (j < static_cast<int>(a.k)) w[j] = id(t[j]);
+        for (int j = 0; j < KC; ++j) w[j] = id(t[j]);
     }
     // Whether state q's key is (w0, w).
     __device__ __forceinline__ bool equal(uint32_t q, uint32_t w0, const uint32_t *w) const {
@@ -92,8 +92,7 @@ struct Keys {
         ids(t, v);
         bool eq = v0 == w0;
 #pragma unroll
-        for (int j = 0; j < KC; ++j)
-            if (j < static_cast<int>(a.k)) eq &= v[j] == w[j];
+        for (int j = 0; j < KC; ++j) eq &= v[j] == w[j];
         return eq;
     }
 };
@@ -128,49 +127,57 @@ __global__ __launch_bounds__(kBlock) void k_direct_round(DirectArgs a, uint32_t 
     const uint32_t tx = threadIdx.x;
     const uint32_t *__restrict__ X = (r & 1u) ? a.blockB : a.blockA;
     uint32_t *__restrict__ Y = (r & 1u) ? a.blockA : a.blockB;
-    if constexpr (!FIRST) {
-        const uint32_t now = blocks_before(a, r), last = blocks_before(a, r - 1);
-        // (uniform over the grid)
-        if (now == 0 || now == last) return;
-        if (a.check_eq && X[a.eq_a] != X[a.eq_b]) return;
-    }
     const Keys<KC, FIRST> K{a, X};
     const uint32_t q = blockIdx.x * kBlock + tx;
     const bool valid = q < a.N;
-    const uint32_t w0 = valid ? K.id(q) : 0u;
+    const uint32_t qs = valid ? q : 0u;  // (idle lanes read the first state)
+    // Small rounds are a chain of dependent loads: everything that the round
+    // may need is loaded before the stop test, which would add its own two in
+    // front.  Larger ones test first and read the rows of refined states only
+    // (rounds of 300,007 states with 16 letters that have nothing to do: 24 us
+    // the first way, 5 the second).
+    const bool eager = FIRST || static_cast<uint64_t>(a.N) * a.k <= kDirectEagerEdges;
+    auto stopped = [&]() -> bool {  // (uniform over the grid)
+        const uint32_t now = blocks_before(a, r), last = blocks_before(a, r - 1);
+        return now == 0 || now == last || (a.check_eq && X[a.eq_a] != X[a.eq_b]);
+    };
+    if constexpr (!FIRST) {
+        if (!eager && stopped()) return;
+    }
+    const uint32_t w0 = K.id(qs);
+    uint32_t t[KC], w[KC];
+    bool bad = false;
     // a block of one member after the last round stays one (its id is the
     // state itself)
     bool act = valid;
+    if constexpr (!FIRST) act = valid && (w0 != q || a.multi[qs] == r);
+    if (eager || act) {
+        K.targets(qs, t, bad);
+        K.ids(t, w);
+    }
     if constexpr (!FIRST) {
-        if (valid && w0 == q && a.multi[q] != r) act = false;
+        if (eager && stopped()) return;
     }
     for (uint32_t i = tx; i < kDirectLds; i += kBlock) ltab[i] = kEmptyLds;
     lsize[tx] = 0;
-    uint32_t w[KC];
     uint64_t h = 0;
-    bool bad = false;
     uint32_t moves = 0;  // letters that move the state
     if (act) {
-        uint32_t t[KC];
-        K.targets(q, t, bad);
         if constexpr (FIRST) {
 #pragma unroll
-            for (int j = 0; j < KC; ++j)
-                if (j < static_cast<int>(a.k) && t[j] != q) moves |= 1u << j;
+            for (int j = 0; j < KC; ++j) moves |= t[j] != q ? 1u << j : 0u;
         }
-        K.ids(t, w);
         h = mix_step(kHashSeed, w0);
         lkey[tx * (KC + 1)] = w0;
 #pragma unroll
-        for (int j = 0; j < KC; ++j)
-            if (j < static_cast<int>(a.k)) {
-                lkey[tx * (KC + 1) + 1 + j] = w[j];
-                h = mix_step(h, w[j]);
-            }
+        for (int j = 0; j < KC; ++j) {
+            lkey[tx * (KC + 1) + 1 + j] = w[j];
+            h = mix_step(h, w[j]);
+        }
         h = mix_final(h);
     }
     if constexpr (FIRST) {
-        wave_set_flag(a.flags + 0, bad);
+        wave_set_flag(a.flags + 0, valid && bad);
         wave_set_flag(a.flags + 1, valid && w0 != 0);
         wave_set_flag(a.flags + 2, valid && w0 == 0);
 #pragma unroll
@@ -198,8 +205,7 @@ __global__ __launch_bounds__(kBlock) void k_direct_round(DirectArgs a, uint32_t 
                 const uint32_t o = static_cast<uint32_t>(e);
                 bool eq = lkey[o * (KC + 1)] == w0;
 #pragma unroll
-                for (int j = 0; j < KC; ++j)
-                    if (j < static_cast<int>(a.k)) eq &= lkey[o * (KC + 1) + 1 + j] == w[j];
+                for (int j = 0; j < KC; ++j) eq &= lkey[o * (KC + 1) + 1 + j] == w[j];
                 if (eq) {
                     lead = o;
                     break;
@@ -211,8 +217,11 @@ __global__ __launch_bounds__(kBlock) void k_direct_round(DirectArgs a, uint32_t 
     }
     __syncthreads();
     // one state per local group in the HBM table: entry = (epoch:8 | tag:24)
-    // << 32 | representative, as in the general path (load <= 1/2, so a
-    // probe always reaches an empty slot)
+    // << 32 | representative, as in the general path (the table is never more
+    // than half full, so a probe always reaches an empty slot).  Probes may
+    // read a cached, older value: a slot only changes from empty to its final
+    // value within a round, and the CAS on a stale empty one fails and
+    // returns the value stored.
     bool claimed = false;
     if (act && lead == tx) {
         const uint32_t epoch = r + 1;
@@ -220,7 +229,7 @@ __global__ __launch_bounds__(kBlock) void k_direct_round(DirectArgs a, uint32_t 
         const unsigned long long want = (static_cast<unsigned long long>(tag) << 32) | q;
         uint64_t s = h & a.mask;
         unsigned long long e =
-            __hip_atomic_load(a.table + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_load(a.table + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
         uint32_t id;
         for (;;) {
             if (static_cast<uint32_t>(e >> 56) != epoch) {
@@ -238,7 +247,7 @@ __global__ __launch_bounds__(kBlock) void k_direct_round(DirectArgs a, uint32_t 
                 break;
             }
             s = (s + 1) & a.mask;
-            e = __hip_atomic_load(a.table + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            e = __hip_atomic_load(a.table + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
         }
         gid[tx] = id;
         if (!claimed || lsize[tx]) mark_multi(a.multi, id, r + 1);
@@ -301,7 +310,8 @@ __global__ __launch_bounds__(kBlock) void k_direct_end(DirectArgs a, uint32_t la
     ctl->changing = changing;
     ctl->stable = stable;
     ctl->separated = separated;
-    ctl->done = stable | separated;
+    // (a bad target: nothing that follows may use the targets)
+    ctl->done = a.flags[0] ? 0u : stable | separated;
     ctl->limit = 0;
     ctl->max_rounds = 0;
     ctl->eq_a = a.eq_a;
@@ -334,6 +344,37 @@ __global__ __launch_bounds__(kBlock) void k_direct_singles(DirectArgs a, uint32_
     }
 }
 
+// Canonical ids of a refinement that direct rounds have decided, queued
+// behind them before the host knows (nothing to do if they have not).
+__global__ __launch_bounds__(kBlock) void k_direct_canon(DirectArgs a, uint32_t *maxs) {
+    if (!a.ctl->done) return;
+    const uint32_t *__restrict__ ids = ((a.ctl->round - 1) & 1u) ? a.blockA : a.blockB;
+    const uint32_t q = blockIdx.x * kBlock + threadIdx.x;
+    if (q < a.N) atomicMax(maxs + ids[q], ~q);
+}
+
+__global__ __launch_bounds__(kScanTile) void k_direct_leaders(DirectArgs a, const uint32_t *maxs,
+                                                              uint32_t *__restrict__ out,
+                                                              uint32_t *partials) {
+    __shared__ uint32_t wsum[kScanTile / 64];
+    if (!a.ctl->done) return;
+    const uint32_t *__restrict__ ids = ((a.ctl->round - 1) & 1u) ? a.blockA : a.blockB;
+    const uint32_t q = blockIdx.x * kScanTile + threadIdx.x;
+    uint32_t b = ~0u;
+    if (q < a.N) {
+        b = ~maxs[ids[q]];
+        out[q] = b;
+    }
+    const unsigned long long m = __ballot(q < a.N && b == q);
+    if (lane_id() == 0) wsum[threadIdx.x / 64] = static_cast<uint32_t>(__popcll(m));
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t sum = 0;
+        for (uint32_t i = 0; i < kScanTile / 64; ++i) sum += wsum[i];
+        partials[blockIdx.x] = sum;
+    }
+}
+
 template <int KC>
 void direct_round(const DirectArgs &a, uint32_t r, hipStream_t s) {
     const dim3 grid((a.N + kBlock - 1) / kBlock), block(kBlock);
@@ -346,20 +387,25 @@ void direct_round(const DirectArgs &a, uint32_t r, hipStream_t s) {
 }  // namespace
 
 void launch_direct_round(const DirectArgs &a, uint32_t r, hipStream_t s) {
-    if (a.k == 1)
-        direct_round<1>(a, r, s);
-    else if (a.k == 2)
-        direct_round<2>(a, r, s);
-    else if (a.k <= 4)
-        direct_round<4>(a, r, s);
-    else if (a.k <= 8)
-        direct_round<8>(a, r, s);
-    else
-        direct_round<16>(a, r, s);
+    switch (direct_width(a.k)) {
+        case 1: direct_round<1>(a, r, s); break;
+        case 2: direct_round<2>(a, r, s); break;
+        case 4: direct_round<4>(a, r, s); break;
+        case 8: direct_round<8>(a, r, s); break;
+        default: direct_round<16>(a, r, s); break;
+    }
 }
 
 void launch_direct_end(const DirectArgs &a, uint32_t launched, hipStream_t s) {
     launch_kernel(k_direct_end, dim3(1), dim3(kBlock), 0, s, a, launched);
+}
+
+void launch_direct_canonical(const DirectArgs &a, uint32_t *scratch_max, uint32_t *out,
+                             uint32_t *partials, hipStream_t s) {
+    launch_kernel(k_direct_canon, dim3((a.N + kBlock - 1) / kBlock), dim3(kBlock), 0, s, a,
+                  scratch_max);
+    launch_kernel(k_direct_leaders, dim3((a.N + kScanTile - 1) / kScanTile), dim3(kScanTile), 0, s,
+                  a, static_cast<const uint32_t *>(scratch_max), out, partials);
 }
 
 void launch_direct_singles(const DirectArgs &a, uint32_t rounds, unsigned long long *single,

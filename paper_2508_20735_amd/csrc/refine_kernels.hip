@@ -2553,8 +2553,9 @@ __global__ __launch_bounds__(kScanThreads) void k_leader_rank(Pick pick, size_t 
 __global__ __launch_bounds__(kScanThreads) void k_leader_rank_small(
     const uint32_t *__restrict__ block, size_t N, const uint32_t *__restrict__ partials,
     uint32_t ntiles, uint32_t *__restrict__ dense, uint32_t *__restrict__ leader_of,
-    uint32_t *total) {
+    uint32_t *total, const RoundCtl *ctl) {
     __shared__ uint32_t wsum[kScanThreads / 64], psum[kScanThreads / 64];
+    if (ctl && !ctl->done) return;
     const size_t q = static_cast<size_t>(blockIdx.x) * kScanTile + threadIdx.x;
     const uint32_t lane = lane_id(), wave = threadIdx.x / 64;
     const bool lead = q < N && block[q] == q;
@@ -2614,7 +2615,9 @@ __global__ __launch_bounds__(kBlock) void k_quotient_small(
     const uint32_t *__restrict__ delta, const uint8_t *__restrict__ acc, uint32_t k,
     const uint32_t *__restrict__ block, const uint32_t *__restrict__ dense,
     const uint32_t *__restrict__ leader_of, const uint32_t *num_blocks, uint32_t start,
-    uint32_t *__restrict__ qdelta, uint8_t *__restrict__ qacc, uint32_t *qstart) {
+    uint32_t *__restrict__ qdelta, uint8_t *__restrict__ qacc, uint32_t *qstart,
+    const RoundCtl *ctl) {
+    if (ctl && !ctl->done) return;
     const size_t total = static_cast<size_t>(*num_blocks) * k;
     if (global_tid() == 0) *qstart = dense[block[start]];
     for (size_t i = global_tid(); i < total; i += grid_stride()) {
@@ -3108,7 +3111,7 @@ void launch_quotient_from_tiles(const uint32_t *delta, const uint8_t *acc, uint3
                                 const uint32_t *block, uint32_t *partials, uint32_t n,
                                 uint32_t start, uint32_t *dense, uint32_t *leader_of, uint32_t *dq,
                                 uint32_t *num_blocks, uint32_t *qdelta, uint8_t *qacc,
-                                uint32_t *qstart, hipStream_t s) {
+                                uint32_t *qstart, const RoundCtl *ctl, hipStream_t s) {
     const uint32_t ntiles = static_cast<uint32_t>((static_cast<size_t>(n) + kScanTile - 1) / kScanTile);
     const dim3 qgrid(grid_for(static_cast<size_t>(n) * k, kDefaultGridCap)), block_dim(kBlock);
     // up to 2^20 states the ids stay in L2, where two dependent gathers per
@@ -3117,11 +3120,11 @@ void launch_quotient_from_tiles(const uint32_t *delta, const uint8_t *acc, uint3
     if (ntiles <= kScanTile) {
         launch_kernel(k_leader_rank_small, dim3(ntiles), dim3(kScanThreads), 0, s, block,
                       static_cast<size_t>(n), static_cast<const uint32_t *>(partials), ntiles,
-                      dense, leader_of, num_blocks);
+                      dense, leader_of, num_blocks, ctl);
         launch_kernel(k_quotient_small, qgrid, block_dim, 0, s, delta, acc, k, block,
                       static_cast<const uint32_t *>(dense),
                       static_cast<const uint32_t *>(leader_of),
-                      static_cast<const uint32_t *>(num_blocks), start, qdelta, qacc, qstart);
+                      static_cast<const uint32_t *>(num_blocks), start, qdelta, qacc, qstart, ctl);
         return;
     }
     launch_kernel(k_scan_partials, dim3(1), dim3(kScanThreads), 0, s, partials, ntiles,

@@ -12,7 +12,7 @@ from paper_2508_20735_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
 
-LIMIT = 1 << 18  # the largest size of the path
+LIMIT = 1 << 19  # the largest minimisation of the path
 
 
 def doubled(d):
