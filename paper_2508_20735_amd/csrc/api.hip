@@ -176,6 +176,12 @@ struct Ctx {
     int device = -1;
     hipStream_t stream = nullptr;
     hipEvent_t ev_start = nullptr, ev_stop = nullptr, ev_in = nullptr;
+    int lds_bytes = -1;          // LDS a workgroup may have (asked once)
+    int clock_khz = 0;           // rate of the device's wall clock
+    // device-pointer calls: the caller's stream, and whether its work is
+    // ordered before the library's stream yet
+    hipStream_t caller = nullptr;
+    bool joined = true;
     uint32_t *pinned = nullptr;  // host staging for small transfers
     Buffer cols, tc_cols, colmap, blockA, blockB, sig, hash, table, ctl, flags, canon, dense,
         leader_of, partials, scalars, multi, active, accbits, counters, presence, presence_packed,
@@ -355,6 +361,24 @@ int upload(Ctx &c, void *dev, const void *host, size_t bytes) {
     return DFA_OK;
 }
 
+// Orders the work already queued on the caller's stream (NULL = the legacy
+// default stream) before the library's own stream.
+int join_stream(Ctx &c, void *stream) {
+    auto s = static_cast<hipStream_t>(stream);
+    if (s == c.stream) return DFA_OK;
+    HIP_TRY(hipEventRecord(c.ev_in, s));
+    HIP_TRY(hipStreamWaitEvent(c.stream, c.ev_in, 0));
+    return DFA_OK;
+}
+
+// The same for the caller's stream of a call that has not needed it yet (a
+// refinement that one workgroup takes runs on the caller's stream itself).
+int join_caller(Ctx &c) {
+    if (c.joined) return DFA_OK;
+    c.joined = true;
+    return join_stream(c, c.caller);
+}
+
 // ---- kernel timing ----
 
 enum class Kern {
@@ -516,6 +540,7 @@ struct RefineResult {
     uint64_t transitions = 0, bytes = 0;
     uint32_t N = 0;  // states refined
     bool outputs_done = false;  // the canonical ids and the quotient are written too
+    double device_ms = -1;  // measured by the kernel, which the host has waited for (else -1)
 };
 
 // A refinement that goes on in the general path after its first rounds: ids
@@ -1239,6 +1264,50 @@ bool direct_applies(const Ctx &c, size_t N, uint32_t k, bool is_union, const dfa
            c.tune.insert_pair && !c.profiling;
 }
 
+// Rows that the kernels may read 16 bytes at a time.
+bool direct_wide(const dfa_view &a, const dfa_view *b) {
+    const uintptr_t at = reinterpret_cast<uintptr_t>(a.delta) |
+                         (b ? reinterpret_cast<uintptr_t>(b->delta) : 0);
+    return a.k % 4 == 0 && a.k == direct_width(a.k) && (at & 15u) == 0;
+}
+
+// Rounds after which the host looks (stop 0, then 1): where the general path
+// does, after its label rounds and first chunk, then eight rounds later.
+uint32_t direct_stop(uint32_t k, int stop) {
+    const uint32_t labels = (k + 1) * (k + 1) <= kPackedMaxBits ? 2 : 1;
+    return labels + (stop ? 12 : 4);
+}
+static_assert(2 + 12 <= kDirectMaxRounds, "a counter per round");
+
+// Whether a refinement that the direct rounds may take runs whole in one
+// workgroup: its transitions, ids and table fit the LDS, and at most
+// kWholeMaxStates states: beyond, one CU takes longer than the launches cost
+// (measured on MI355X, 4 letters, minimisation and equivalence with a changed
+// copy: 1,024 states 59 and 85 us against 94 and 173 with a launch per round,
+// 3,000 states 72 and 129 against 96 and 208, 8,192 states 104 and 189
+// against 100 and 183).
+constexpr size_t kWholeMaxStates = 6144;
+bool whole_applies(Ctx &c, size_t N, uint32_t k) {
+    if (N > kWholeMaxStates) return false;
+    if (c.lds_bytes < 0) {
+        int lds = 0;
+        if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, c.device) !=
+            hipSuccess) {
+            (void)hipGetLastError();
+            lds = 0;
+        }
+        if (hipDeviceGetAttribute(&c.clock_khz, hipDeviceAttributeWallClockRate, c.device) !=
+                hipSuccess ||
+            c.clock_khz <= 0) {
+            (void)hipGetLastError();
+            lds = 0;
+        }
+        c.lds_bytes = lds;
+    }
+    // (plus the kernel's own few static words)
+    return static_cast<int64_t>(whole_lds_bytes(static_cast<uint32_t>(N), k)) + 512 <= c.lds_bytes;
+}
+
 // The first rounds of a refinement of ordinary size, one launch each; done:
 // the refinement is decided and res is complete.  Otherwise the general path
 // goes on from round res.ctl.round (resume).  out: the canonical ids and the
@@ -1283,8 +1352,7 @@ int refine_direct(Ctx &c, const dfa_view &a, const dfa_view *b, bool canon, cons
     }
     d.N = static_cast<uint32_t>(N);
     d.k = k;
-    d.wide = k % 4 == 0 && k == direct_width(k) &&
-             ((reinterpret_cast<uintptr_t>(d.da) | reinterpret_cast<uintptr_t>(d.db)) & 15u) == 0;
+    d.wide = direct_wide(a, b);
     d.blockA = c.blockA.as<uint32_t>();
     d.blockB = c.blockB.as<uint32_t>();
     d.multi = c.multi.as<uint32_t>();
@@ -1293,16 +1361,12 @@ int refine_direct(Ctx &c, const dfa_view &a, const dfa_view *b, bool canon, cons
     d.cnt = c.direct_cnt.as<unsigned long long>();
     d.ctl = c.ctl.as<RoundCtl>();
     d.flags = reinterpret_cast<uint32_t *>(d.ctl + 1);
-    // the host looks at the rounds where the general path does: after its
-    // label rounds and first chunk, then eight rounds later
-    const uint32_t labels = (k + 1) * (k + 1) <= kPackedMaxBits ? 2 : 1;
-    const uint32_t stops[2] = {labels + 4, labels + 12};
-    static_assert(2 + 12 <= kDirectMaxRounds, "a counter per round");
     uint32_t launched = 0;
-    for (uint32_t stop : stops) {
+    for (int look = 0; look < 2; ++look) {
+        const uint32_t stop = direct_stop(k, look);
         while (launched < stop) launch_direct_round(d, launched++, c.stream);
         launch_direct_end(d, launched, c.stream);
-        const bool queued = out && stop == stops[0];
+        const bool queued = out && look == 0;
         if (queued) {
             launch_direct_canonical(d, c.canon.as<uint32_t>(), out->block, c.partials.as<uint32_t>(),
                                     c.stream);
@@ -1347,6 +1411,68 @@ int refine_direct(Ctx &c, const dfa_view &a, const dfa_view *b, bool canon, cons
     return DFA_OK;
 }
 
+// A refinement small enough for one workgroup's LDS; done: it is decided, res
+// is complete and the outputs are written.  Otherwise (more rounds than the
+// general path runs before it looks for a stall) another path starts anew.
+int refine_whole(Ctx &c, const dfa_view &a, const dfa_view *b, const Outputs *out,
+                 RefineResult &res, bool &done) {
+    const uint32_t k = a.k, n = a.n + (b ? b->n : 0u);
+    WholeArgs w{};
+    w.da = a.delta;
+    w.aa = a.accepting;
+    w.na = a.n;
+    if (b) {
+        w.db = b->delta;
+        w.ab = b->accepting;
+        w.nb = b->n;
+        w.eq_a = a.start;
+        w.eq_b = a.n + b->start;
+    }
+    w.k = k;
+    w.wide = direct_wide(a, b);
+    w.slots = whole_slots(n);
+    w.max_rounds = direct_stop(k, 1);
+    w.start = a.start;
+    if (out) {
+        w.block_out = out->block;
+        if (out->q) {
+            w.qdelta = out->q->delta;
+            w.qacc = out->q->accepting;
+        }
+    }
+    w.result = reinterpret_cast<WholeResult *>(c.pinned);
+    // no workspace: the kernel runs on the caller's stream, behind the work
+    // that is queued there, and times itself
+    hipStream_t s = c.joined ? c.stream : c.caller;
+    launch_whole(w, s);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(c.joined ? stream_sync(c) : hipStreamSynchronize(s));
+    WholeResult r;
+    std::memcpy(&r, c.pinned, sizeof r);
+    if (r.err) return fail(DFA_EINVAL, "a transition target is >= n");
+    done = r.done != 0;
+    if (!done) return DFA_OK;
+    res.ctl = RoundCtl{};
+    res.ctl.round = r.rounds;
+    res.ctl.changing = r.changing;
+    res.ctl.prev_count = r.blocks;
+    res.ctl.stable = r.stable;
+    res.ctl.separated = r.separated;
+    res.ctl.done = 1;
+    res.N = n;
+    res.k_eff = static_cast<uint32_t>(__builtin_popcount(r.moves & ((1u << k) - 1u)));
+    res.transitions = static_cast<uint64_t>(r.rounds) * n * res.k_eff;
+    // (every state is refined in every round)
+    res.bytes = static_cast<uint64_t>(r.rounds) * n * (8ull * res.k_eff + 8ull);
+    res.outputs_done = out != nullptr;
+    res.device_ms = static_cast<double>(r.ticks) / c.clock_khz;
+    if (out && out->q) {
+        out->q->num_blocks = r.blocks;
+        out->q->start = r.qstart;
+    }
+    return DFA_OK;
+}
+
 // Refines one DFA, or the union of two (equivalence: until their start
 // states separate), by the algorithm of the options.  canon: the scratch of
 // the canonical ids is cleared too.
@@ -1354,11 +1480,18 @@ int refine_any(Ctx &c, const dfa_view &a, const dfa_view *b, const dfa_options &
                const Outputs *out, RefineResult &res) {
     const uint32_t k = a.k;
     const size_t N = static_cast<size_t>(a.n) + (b ? b->n : 0);
-    // (a context without events, the allocation-free one, times on the host)
-    if (c.ev_start) HIP_TRY(hipEventRecord(c.ev_start, c.stream));
     Resume resume;
     bool resumed = false;
-    if (direct_applies(c, N, k, b != nullptr, o)) {
+    const bool direct = direct_applies(c, N, k, b != nullptr, o);
+    if (direct && whole_applies(c, N, k)) {
+        bool done = false;
+        DFA_TRY(refine_whole(c, a, b, out, res, done));
+        if (done) return DFA_OK;
+    }
+    DFA_TRY(join_caller(c));
+    // (a context without events, the allocation-free one, times on the host)
+    if (c.ev_start) HIP_TRY(hipEventRecord(c.ev_start, c.stream));
+    if (direct) {
         bool done = false;
         DFA_TRY(refine_direct(c, a, b, canon, out, res, resume, done));
         if (done) return DFA_OK;
@@ -1463,7 +1596,9 @@ int minimise_impl(Ctx &c, uint32_t n, uint32_t k, const uint32_t *delta, const u
     }
     if (st) {
         fill_stats(st, r);
-        if (c.ev_start && c.ev_stop) {
+        if (r.device_ms >= 0) {
+            st->device_ms = r.device_ms;
+        } else if (c.ev_start && c.ev_stop) {
             float ms = 0.f;
             HIP_TRY(hipEventElapsedTime(&ms, c.ev_start, c.ev_stop));
             st->device_ms = ms;
@@ -1479,6 +1614,7 @@ int minimise_impl(Ctx &c, uint32_t n, uint32_t k, const uint32_t *delta, const u
 int minimise_pruned(Ctx &c, uint32_t n, uint32_t k, const uint32_t *delta, const uint8_t *acc,
                     uint32_t *block_out, dfa_quotient *q, const dfa_options &o, dfa_stats *st) {
     if (o.start >= n) return fail(DFA_EINVAL, "start (%u) >= n (%u)", o.start, n);
+    DFA_TRY(join_caller(c));
     const size_t ntiles = (static_cast<size_t>(n) + kScanTile - 1) / kScanTile;
     DFA_TRY(c.flags.ensure(4 * sizeof(uint32_t), "flags"));
     DFA_TRY(c.scalars.ensure(16 * sizeof(uint32_t), "scalars"));
@@ -1590,10 +1726,14 @@ int equivalent_impl(Ctx &c, const dfa_view &a, const dfa_view &b, int *verdict,
     if (N >= 0xFFFFFFFFull) return fail(DFA_EINVAL, "nA + nB must be < 2^32 - 1");
     RefineResult r;
     DFA_TRY(refine_any(c, a, &b, o, false, nullptr, r));
-    HIP_TRY(hipEventRecord(c.ev_stop, c.stream));
-    HIP_TRY(stream_sync(c));
+    if (r.device_ms < 0) {
+        HIP_TRY(hipEventRecord(c.ev_stop, c.stream));
+        HIP_TRY(stream_sync(c));
+    }
     fill_stats(st, r);
-    if (st) {
+    if (st && r.device_ms >= 0) {
+        st->device_ms = r.device_ms;
+    } else if (st) {
         float ms = 0.f;
         HIP_TRY(hipEventElapsedTime(&ms, c.ev_start, c.ev_stop));
         st->device_ms = ms;
@@ -1616,6 +1756,7 @@ int equivalent_impl(Ctx &c, const dfa_view &a, const dfa_view &b, int *verdict,
 // when they have no work or no room) and waits once per batch.
 int included_impl(Ctx &c, const dfa_view &a, const dfa_view &b, int *verdict, uint64_t *visited,
                   dfa_stats *st, int mode = 0) {
+    DFA_TRY(join_caller(c));
     const uint32_t k = a.k;
     const size_t N = static_cast<size_t>(a.n) + b.n;
     uint64_t cap = next_pow2(std::max<uint64_t>(4 * N, 4096));
@@ -1751,16 +1892,6 @@ int check_minimise(uint32_t n, uint32_t k, const void *delta, const void *acc, c
     if (q && (!q->delta || !q->accepting)) return fail(DFA_EINVAL, "NULL quotient arrays");
     if (o.start >= n) return fail(DFA_EINVAL, "start %u >= n %u", o.start, n);
     return check_options(o);
-}
-
-// Orders the work already queued on the caller's stream (NULL = the legacy
-// default stream) before the library's own stream.
-int join_stream(Ctx &c, void *stream) {
-    auto s = static_cast<hipStream_t>(stream);
-    if (s == c.stream) return DFA_OK;
-    HIP_TRY(hipEventRecord(c.ev_in, s));
-    HIP_TRY(hipStreamWaitEvent(c.stream, c.ev_in, 0));
-    return DFA_OK;
 }
 
 double ms_since(std::chrono::steady_clock::time_point t0) {
@@ -3119,7 +3250,8 @@ int dfa_minimise_device(uint32_t n, uint32_t k, const uint32_t *delta, const uin
         DFA_TRY(get_ctx(c));
         CallScope lock(c->mu);
         DFA_TRY(init_ctx(*c));
-        DFA_TRY(join_stream(*c, stream));
+        c->caller = static_cast<hipStream_t>(stream);
+        c->joined = false;
         if (stats) std::memset(stats, 0, sizeof *stats);
         return minimise_impl(*c, n, k, delta, accepting, block_out, q_out, o, stats);
     });
@@ -3191,7 +3323,8 @@ int dfa_equivalent_device(const dfa_view *a, const dfa_view *b, int *verdict,
         DFA_TRY(get_ctx(c));
         CallScope lock(c->mu);
         DFA_TRY(init_ctx(*c));
-        DFA_TRY(join_stream(*c, stream));
+        c->caller = static_cast<hipStream_t>(stream);
+        c->joined = false;
         if (stats) std::memset(stats, 0, sizeof *stats);
         return equivalent_impl(*c, *a, *b, verdict, o, stats);
     });

@@ -335,6 +335,37 @@ void launch_direct_canonical(const DirectArgs &a, uint32_t *scratch_max, uint32_
 void launch_direct_singles(const DirectArgs &a, uint32_t rounds, unsigned long long *single,
                            unsigned long long *active, hipStream_t s);
 
+// ---- small sizes: one workgroup, one launch (whole_kernels.hip) ----
+constexpr uint32_t kWholeThreads = 1024;
+// Table slots of n states: a power of two, at least 2n.
+inline uint32_t whole_slots(uint32_t n) {
+    uint32_t t = 64;
+    while (t < 2 * n) t <<= 1;
+    return t;
+}
+struct WholeResult {
+    uint32_t err, done;  // a target out of range; stable or separated within max_rounds
+    uint32_t rounds, changing, blocks, separated, stable;
+    uint32_t moves;      // bit j: letter j moves some state
+    uint32_t qstart;
+    unsigned long long ticks;  // of the device's wall clock, start to end
+};
+struct WholeArgs {
+    const uint32_t *da, *db;  // row-major; one DFA: nb == 0
+    const uint8_t *aa, *ab;
+    uint32_t na, nb, k;       // na + nb < 2^16, k <= 16
+    uint32_t wide;            // k = direct_width(k) is a multiple of 4, 16-byte aligned rows
+    uint32_t slots;           // whole_slots(na + nb)
+    uint32_t eq_a, eq_b;      // nb > 0: ends when these states separate
+    uint32_t max_rounds, start;
+    uint32_t *block_out;      // nb == 0: canonical ids, if stable
+    uint32_t *qdelta;         // quotient, or nullptr
+    uint8_t *qacc;
+    WholeResult *result;      // page-locked host memory
+};
+uint32_t whole_lds_bytes(uint32_t n, uint32_t k);
+void launch_whole(const WholeArgs &a, hipStream_t s);
+
 // ---- leader-based refinement (naivePR; leader_kernels.hip) ----
 //
 //   block       uint32 [N]          leader (smallest member) of q's block,

@@ -1,7 +1,8 @@
-"""The one-launch-per-round path of ordinary sizes against the oracle and the
-general path (reached with loop="host"): tile edges, every letter count it
-takes, unaligned rows, unions whose operands meet inside a tile, refinements
-that go on in the general path after its last round.  Whole numbers, equal.
+"""The one-workgroup path of small sizes and the one-launch-per-round path of
+ordinary ones against the oracle and the general path (reached with
+loop="host"): tile edges, every letter count they take, unaligned rows, unions
+whose operands meet inside a tile, refinements that need more rounds than they
+run.  Whole numbers, equal.
 """
 import numpy as np
 import pytest
@@ -12,7 +13,8 @@ from paper_2508_20735_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
 
-LIMIT = 1 << 19  # the largest minimisation of the path
+WHOLE = 6144     # the largest refinement of one workgroup (2,048 x k = 16 fit its LDS too)
+LIMIT = 1 << 19  # the largest minimisation with a launch per round
 
 
 def doubled(d):
@@ -45,7 +47,8 @@ def check(d, tc="auto"):
     return res
 
 
-@pytest.mark.parametrize("n", [1, 2, 3, 63, 64, 65, 255, 256, 257, 1023, 1024, 1025, 40_000])
+@pytest.mark.parametrize("n", [1, 2, 3, 63, 64, 65, 1023, 1024, 1025, 2049, WHOLE - 1,
+                               WHOLE, WHOLE + 1, 6399, 6400, 6401, 40_000])
 @pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 8, 9, 16])
 def test_sizes_and_letters(n, k):
     check(W.random_dfa(n, k, 0.3, n * 17 + k))
@@ -93,8 +96,12 @@ def test_equivalence(n, k, change):
 
 
 def test_unaligned_rows_on_the_device():
+    for n in (3001, 7001):
+        check_unaligned(W.random_dfa(n, 4, 0.3, 9))
+
+
+def check_unaligned(d):
     import torch
-    d = W.random_dfa(3001, 4, 0.3, 9)
     flat = torch.zeros(d.n * 4 + 8, dtype=torch.int32, device="cuda:0")
     ref = oracle.hopcroft(d.delta, d.accepting)[0]
     acc = torch.from_numpy(d.accepting).cuda()
@@ -106,9 +113,10 @@ def test_unaligned_rows_on_the_device():
         assert B.equivalent_device(rows, acc, 0, rows, acc, 0)[0]
 
 
-def test_bad_targets():
-    d = W.random_dfa(2000, 4, 0.3, 10)
-    for q, a in ((0, 0), (1999, 3)):
+@pytest.mark.parametrize("n", [2000, 9000])
+def test_bad_targets(n):
+    d = W.random_dfa(n, 4, 0.3, 10)
+    for q, a in ((0, 0), (n - 1, 3)):
         bad = d.delta.copy()
         bad[q, a] = d.n
         with pytest.raises(B.DfaError) as e:
