@@ -210,6 +210,9 @@ struct Ctx {
     Buffer small_jobs, small_results, small_ctl;  // batched small DFAs (one workgroup each)
     Buffer pb_tl, pb_src, pb_val, pb_off, pb_partials;  // edges bucketed by target slice
     Buffer direct_cnt;                // round counters of direct rounds
+    Buffer segd_plan, segd_state, segd_table;  // batches, one launch per round
+    uint32_t segd_epoch = 0;          // last epoch used in segd_table (0: cleared)
+    uint64_t segd_epoch_in = 0;       // the allocation it counts in
     Buffer segpat_table, segpat;  // round 0 of segmented refinements by acceptance patterns
     Arena arena;  // the allocation-free context's fixed workspace (unused elsewhere)
     uint8_t *pinned_batch = nullptr;  // host staging of batched inputs/outputs
@@ -1319,8 +1322,9 @@ int refine_direct(Ctx &c, const dfa_view &a, const dfa_view *b, bool canon, cons
     done = false;
     const uint32_t k = a.k;
     const size_t N = static_cast<size_t>(a.n) + (b ? b->n : 0);
-    // a quarter full at most: a longer probe is one more dependent access
-    const uint64_t cap = next_pow2(std::max<uint64_t>(4 * N, 1024));
+    // up to 2^16 states a quarter full at most (a longer probe is one more
+    // dependent access of a short round), half full beyond
+    const uint64_t cap = next_pow2(std::max<uint64_t>((N <= (1u << 16) ? 4 : 2) * N, 1024));
     // round state, flags, then the quotient's size and start
     constexpr size_t kCtlBytes = sizeof(RoundCtl) + (5 + kDirectMaxK) * sizeof(uint32_t);
     constexpr size_t kCntBytes =
@@ -2033,6 +2037,167 @@ int upload_plan(Ctx &c, const std::vector<Part> &parts, uint32_t nseg, bool pair
     return DFA_OK;
 }
 
+// Result of refine_batch (host): per segment, and for the whole batch.
+struct BatchResult {
+    std::vector<uint32_t> blocks, changing;
+    std::vector<int32_t> verdicts;  // pairs
+    uint32_t rounds = 0, k_eff = 0;
+    uint64_t bytes = 0;
+    bool limit = false;
+};
+
+// Whether a batch's segments may run one launch per round: the options and
+// tuning of direct_applies, without its size limit.
+bool batch_direct_applies(const Ctx &c, const std::vector<Part> &parts, uint32_t kmax,
+                          const dfa_options &o) {
+    uint64_t tiles = 0;
+    for (const Part &p : parts) {
+        tiles += (static_cast<uint64_t>(p.n) + kBlock - 1) / kBlock;
+        if (p.n > (1u << 29)) return false;  // (a segment's slots are 32-bit)
+    }
+    return kmax <= kDirectMaxK && tiles * kBlock < 0xFFFFFFFFull &&
+           o.algorithm == DFA_ALGO_SIGNATURE && o.tc_mode != DFA_TC_ON &&
+           (o.loop_mode == DFA_LOOP_GRAPH || o.loop_mode == DFA_LOOP_CHUNK) && !o.chunk &&
+           o.lds_stage == 2 && !c.tune.hash_bits && c.tune.label_rounds == 2 &&
+           c.tune.insert_pair && !c.profiling;
+}
+
+// Refines the segments of `parts` (pairs: parts 2s and 2s + 1 together), one
+// launch per round, and queues the canonical ids to out_dev (minimisation).
+int refine_batch_direct(Ctx &c, const std::vector<Part> &parts, uint32_t nseg, bool pairs,
+                        uint32_t kmax, const dfa_options &o, uint32_t *out_dev,
+                        BatchResult &res) {
+    const uint32_t nparts = static_cast<uint32_t>(parts.size());
+    uint64_t tiles64 = 0, slots = 0;
+    for (const Part &p : parts) tiles64 += (static_cast<uint64_t>(p.n) + kBlock - 1) / kBlock;
+    const uint32_t tiles = static_cast<uint32_t>(tiles64);
+    const size_t N = static_cast<size_t>(tiles) * kBlock;
+    // the plan, built in page-locked memory and uploaded in one copy
+    const size_t segs_at = nparts * sizeof(SegdPart);
+    const size_t tiles_at = segs_at + nseg * sizeof(SegdSeg);
+    const size_t plan_bytes = tiles_at + tiles * sizeof(uint32_t);
+    const size_t state_words = 9 * static_cast<size_t>(nseg);  // cnt, classes, done, changing, blocks, verdicts
+    const size_t state_bytes = sizeof(SegdCtl) + state_words * sizeof(uint32_t);
+    DFA_TRY(ensure_pinned_batch(c, std::max(plan_bytes, state_bytes)));
+    SegdPart *hp = reinterpret_cast<SegdPart *>(c.pinned_batch);
+    SegdSeg *hs = reinterpret_cast<SegdSeg *>(c.pinned_batch + segs_at);
+    uint32_t *ht = reinterpret_cast<uint32_t *>(c.pinned_batch + tiles_at);
+    uint32_t tile = 0;
+    for (uint32_t p = 0; p < nparts; ++p) {
+        const Part &v = parts[p];
+        SegdPart &d = hp[p];
+        d.delta = v.delta;
+        d.acc = v.accepting;
+        d.n = v.n;
+        d.k = v.k;
+        d.off = tile * kBlock;
+        d.seg = v.seg;
+        d.wide = v.k % 4 == 0 && v.k == direct_width(v.k) &&
+                 (reinterpret_cast<uintptr_t>(v.delta) & 15u) == 0;
+        d.pad = 0;
+        d.out = v.out;
+        const bool second = pairs && (p & 1u);
+        SegdSeg &g = hs[v.seg];
+        if (!second) {
+            const uint64_t states = v.n + (pairs ? static_cast<uint64_t>(parts[p + 1].n) : 0);
+            const uint64_t cap = next_pow2(std::max<uint64_t>(2 * states, 64));
+            g.table = slots;
+            g.mask = static_cast<uint32_t>(cap - 1);
+            g.first_tile = tile;
+            g.eq_a = d.off + v.start;
+            g.eq_b = 0;
+            slots += cap;
+        } else {
+            g.eq_b = d.off + v.start;
+        }
+        for (uint32_t t = (v.n + kBlock - 1) / kBlock; t > 0; --t) ht[tile++] = p;
+    }
+    DFA_TRY(c.segd_plan.ensure(plan_bytes, "batch plan"));
+    DFA_TRY(c.segd_state.ensure(state_bytes, "segment state"));
+    DFA_TRY(c.blockA.ensure(N * sizeof(uint32_t), "blocks"));
+    DFA_TRY(c.blockB.ensure(N * sizeof(uint32_t), "blocks"));
+    DFA_TRY(c.multi.ensure((N + 1) * sizeof(uint32_t), "block marks"));
+    if (out_dev) DFA_TRY(c.canon.ensure(N * sizeof(uint32_t), "canonical ids"));
+    DFA_TRY(c.segd_table.ensure(slots * sizeof(unsigned long long), "segment tables"));
+    HIP_TRY(hipMemcpyAsync(c.segd_plan.p, c.pinned_batch, plan_bytes, hipMemcpyHostToDevice,
+                           c.stream));
+    auto clear_table = [&c]() -> int {
+        ZeroList z{};
+        DFA_TRY(zero_add(z, c.segd_table, c.segd_table.cap));
+        launch_zero(z, c.stream);
+        c.segd_epoch = 0;
+        c.segd_epoch_in = c.segd_table.allocation;
+        return DFA_OK;
+    };
+    if (c.segd_epoch_in != c.segd_table.allocation) DFA_TRY(clear_table());
+    {
+        ZeroList z{};
+        DFA_TRY(zero_add(z, c.segd_state, state_bytes));
+        DFA_TRY(zero_add(z, c.multi, N * sizeof(uint32_t)));
+        if (out_dev) DFA_TRY(zero_add(z, c.canon, N * sizeof(uint32_t)));
+        launch_zero(z, c.stream);
+    }
+    SegdArgs a{};
+    const uint8_t *plan = c.segd_plan.as<uint8_t>();
+    a.parts = reinterpret_cast<const SegdPart *>(plan);
+    a.segs = reinterpret_cast<const SegdSeg *>(plan + segs_at);
+    a.tile_part = reinterpret_cast<const uint32_t *>(plan + tiles_at);
+    a.tiles = tiles;
+    a.nseg = nseg;
+    a.pairs = pairs ? 1u : 0u;
+    a.blockA = c.blockA.as<uint32_t>();
+    a.blockB = c.blockB.as<uint32_t>();
+    a.multi = c.multi.as<uint32_t>();
+    a.table = c.segd_table.as<unsigned long long>();
+    a.ctl = c.segd_state.as<SegdCtl>();
+    uint32_t *w = reinterpret_cast<uint32_t *>(a.ctl + 1);
+    a.cnt = w;
+    a.classes = w + 4 * static_cast<size_t>(nseg);
+    a.done = a.classes + nseg;
+    a.changing = a.done + nseg;
+    a.blocks = a.changing + nseg;
+    int32_t *verdicts = reinterpret_cast<int32_t *>(a.blocks + nseg);
+    uint32_t launched = 0, chunk = c.tune.chunk;
+    SegdCtl got;
+    for (;;) {
+        uint32_t stop = launched + chunk;
+        if (o.max_rounds) stop = std::min(stop, o.max_rounds);
+        while (launched < stop) {
+            if (c.segd_epoch + 1 >= kSegdEpochs) DFA_TRY(clear_table());
+            launch_segd_round(a, launched++, ++c.segd_epoch, kmax > 8, c.stream);
+        }
+        const bool last = o.max_rounds && launched >= o.max_rounds;
+        launch_segd_decide(a, launched, last, c.stream);
+        HIP_TRY(hipGetLastError());
+        DFA_TRY(read_back(c, a.ctl, sizeof(SegdCtl)));
+        std::memcpy(&got, c.pinned, sizeof got);
+        if (got.err) return fail(DFA_EINVAL, "a transition target is >= n");
+        if (got.ndone == nseg) break;
+        chunk = grown_chunk(chunk, false, false);
+    }
+    if (out_dev) launch_segd_output(a, c.canon.as<uint32_t>(), out_dev, c.stream);
+    if (pairs) launch_segd_verdicts(a, verdicts, c.stream);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipMemcpyAsync(c.pinned_batch, a.ctl, state_bytes, hipMemcpyDeviceToHost, c.stream));
+    HIP_TRY(hipEventRecord(c.ev_stop, c.stream));
+    HIP_TRY(stream_sync(c));
+    const uint32_t *hw = reinterpret_cast<const uint32_t *>(c.pinned_batch + sizeof(SegdCtl));
+    const uint32_t *done = hw + 5 * static_cast<size_t>(nseg);
+    res.changing.assign(done + nseg, done + 2 * static_cast<size_t>(nseg));
+    res.blocks.assign(done + 2 * static_cast<size_t>(nseg), done + 3 * static_cast<size_t>(nseg));
+    if (pairs) {
+        const int32_t *hv = reinterpret_cast<const int32_t *>(done + 3 * static_cast<size_t>(nseg));
+        res.verdicts.assign(hv, hv + nseg);
+    }
+    for (uint32_t s = 0; s < nseg; ++s) res.rounds = std::max(res.rounds, done[s]);
+    res.k_eff = static_cast<uint32_t>(__builtin_popcount(got.moves));
+    uint64_t active = 0;
+    for (uint32_t i = 0; i < kSegdSpread; ++i) active += got.active[i * kSegdStride];
+    res.bytes = active * (8ull * res.k_eff + 8ull);
+    res.limit = got.limit != 0;
+    return DFA_OK;
+}
+
 // Refines the union described by parts; fills per-segment block counts and
 // changing rounds (host vectors).
 int refine_segments(Ctx &c, const std::vector<Part> &parts, uint32_t nseg, bool pairs,
@@ -2061,11 +2226,46 @@ int refine_segments(Ctx &c, const std::vector<Part> &parts, uint32_t nseg, bool 
     return DFA_OK;
 }
 
-void fill_batch_stats(dfa_batch_stats *st, uint32_t count, const RefineResult &r, size_t N,
+// Refines the segments of `parts` by the path that applies; ends with
+// ev_stop recorded and the stream synchronised.
+int refine_batch(Ctx &c, const std::vector<Part> &parts, uint32_t nseg, bool pairs, uint32_t kmax,
+                 const dfa_options &o, uint32_t *out_dev, BatchResult &res) {
+    if (batch_direct_applies(c, parts, kmax, o))
+        return refine_batch_direct(c, parts, nseg, pairs, kmax, o, out_dev, res);
+    RefineResult r;
+    SegArgs g{};
+    DFA_TRY(refine_segments(c, parts, nseg, pairs, kmax, o, r, g, res.blocks, res.changing));
+    const size_t N = static_cast<size_t>(parts.back().off) + parts.back().n;
+    if (pairs) {
+        res.verdicts.resize(nseg);
+        DFA_TRY(c.batch_out.ensure(nseg * sizeof(int32_t), "verdicts"));
+        launch_pair_verdicts(g, r.final_block, c.batch_out.as<int32_t>(), c.stream);
+        HIP_TRY(hipGetLastError());
+        HIP_TRY(hipMemcpyAsync(res.verdicts.data(), c.batch_out.p, nseg * sizeof(int32_t),
+                               hipMemcpyDeviceToHost, c.stream));
+    } else {
+        DFA_TRY(c.canon.ensure(N * sizeof(uint32_t), "canonical ids"));
+        // canonical ids go to the block buffer that does not hold the result
+        uint32_t *canon_ids = c.blockA.as<uint32_t>() == r.final_block ? c.blockB.as<uint32_t>()
+                                                                       : c.blockA.as<uint32_t>();
+        launch_canonicalise(r.final_block, N, N, c.canon.as<uint32_t>(), canon_ids, c.stream);
+        launch_part_output(g, N, canon_ids, out_dev, c.stream);
+        HIP_TRY(hipGetLastError());
+    }
+    HIP_TRY(hipEventRecord(c.ev_stop, c.stream));
+    HIP_TRY(stream_sync(c));
+    res.rounds = r.ctl.round;
+    res.k_eff = r.k_eff;
+    res.bytes = r.bytes;
+    res.limit = r.ctl.limit != 0;
+    return DFA_OK;
+}
+
+void fill_batch_stats(dfa_batch_stats *st, uint32_t count, const BatchResult &r, size_t N,
                       uint64_t transitions) {
     if (!st) return;
     st->count = count;
-    st->rounds = r.ctl.round;
+    st->rounds = r.rounds;
     st->k_eff = r.k_eff;
     st->states = N;
     st->transitions_refined = transitions;
@@ -2225,34 +2425,25 @@ int minimise_batch_impl(Ctx &c, uint32_t count, const dfa_view *views, uint32_t 
     }
     HIP_TRY(hipEventRecord(c.ev_start, c.stream));
     if (!small.empty()) DFA_TRY(launch_small_jobs(c, small, count, out_dev, o.max_rounds));
-    RefineResult r;
-    SegArgs g{};
-    std::vector<uint32_t> blocks, changing;
-    const size_t N = off;
+    BatchResult r;
     if (!parts.empty()) {
-        DFA_TRY(refine_segments(c, parts, static_cast<uint32_t>(parts.size()), false, kmax, o,
-                                r, g, blocks, changing));
-        DFA_TRY(c.canon.ensure(N * sizeof(uint32_t), "canonical ids"));
-        // canonical ids go to the block buffer that does not hold the result
-        uint32_t *canon_ids = c.blockA.as<uint32_t>() == r.final_block ? c.blockB.as<uint32_t>()
-                                                                       : c.blockA.as<uint32_t>();
-        launch_canonicalise(r.final_block, N, N, c.canon.as<uint32_t>(), canon_ids, c.stream);
-        launch_part_output(g, N, canon_ids, out_dev, c.stream);
-        HIP_TRY(hipGetLastError());
+        DFA_TRY(refine_batch(c, parts, static_cast<uint32_t>(parts.size()), false, kmax, o,
+                             out_dev, r));
+    } else {
+        HIP_TRY(hipEventRecord(c.ev_stop, c.stream));
+        HIP_TRY(stream_sync(c));
     }
-    HIP_TRY(hipEventRecord(c.ev_stop, c.stream));
-    HIP_TRY(stream_sync(c));
     std::vector<SmallResult> sres;
     if (!small.empty()) DFA_TRY(finish_small_jobs(c, count, sres));
     uint64_t transitions = 0, small_bytes = 0;
-    uint32_t joint_rounds = parts.empty() ? 0 : r.ctl.round;
-    bool limit = !parts.empty() && r.ctl.limit;
+    uint32_t joint_rounds = r.rounds;
+    bool limit = r.limit;
     auto record = [&](uint32_t i, uint32_t nb, uint32_t ch) {
         if (num_blocks) num_blocks[i] = nb;
         if (rounds) rounds[i] = ch + 1;
         transitions += static_cast<uint64_t>(views[i].n) * views[i].k * (ch + 1);
     };
-    for (size_t j = 0; j < parts.size(); ++j) record(large_of[j], blocks[j], changing[j]);
+    for (size_t j = 0; j < parts.size(); ++j) record(large_of[j], r.blocks[j], r.changing[j]);
     for (const SmallJob &j : small) {
         const SmallResult &sr = sres[j.index];
         record(j.index, sr.num_blocks, sr.changing);
@@ -2263,8 +2454,7 @@ int minimise_batch_impl(Ctx &c, uint32_t count, const dfa_view *views, uint32_t 
     if (st) {
         fill_batch_stats(st, count, r, total, transitions);
         st->rounds = joint_rounds;
-        if (parts.empty()) st->k_eff = 0;
-        st->algorithmic_bytes = (parts.empty() ? 0 : r.bytes) + small_bytes;
+        st->algorithmic_bytes = r.bytes + small_bytes;
         float ms = 0.f;
         HIP_TRY(hipEventElapsedTime(&ms, c.ev_start, c.ev_stop));
         st->device_ms = ms;
@@ -2325,32 +2515,25 @@ int equivalent_batch_impl(Ctx &c, uint32_t count, const dfa_view *a, const dfa_v
     }
     HIP_TRY(hipEventRecord(c.ev_start, c.stream));
     if (!small.empty()) DFA_TRY(launch_small_jobs(c, small, count, nullptr, o.max_rounds));
-    RefineResult r;
-    SegArgs g{};
-    std::vector<uint32_t> blocks, changing;
+    BatchResult r;
     const uint32_t nseg = static_cast<uint32_t>(large_of.size());
-    std::vector<int32_t> seg_verdicts(nseg);
     if (nseg) {
-        DFA_TRY(refine_segments(c, parts, nseg, true, kmax, o, r, g, blocks, changing));
-        DFA_TRY(c.batch_out.ensure(nseg * sizeof(int32_t), "verdicts"));
-        launch_pair_verdicts(g, r.final_block, c.batch_out.as<int32_t>(), c.stream);
-        HIP_TRY(hipGetLastError());
-        HIP_TRY(hipMemcpyAsync(seg_verdicts.data(), c.batch_out.p, nseg * sizeof(int32_t),
-                               hipMemcpyDeviceToHost, c.stream));
+        DFA_TRY(refine_batch(c, parts, nseg, true, kmax, o, nullptr, r));
+    } else {
+        HIP_TRY(hipEventRecord(c.ev_stop, c.stream));
+        HIP_TRY(stream_sync(c));
     }
-    HIP_TRY(hipEventRecord(c.ev_stop, c.stream));
-    HIP_TRY(stream_sync(c));
     std::vector<SmallResult> sres;
     if (!small.empty()) DFA_TRY(finish_small_jobs(c, count, sres));
     uint64_t transitions = 0, small_bytes = 0;
-    uint32_t joint_rounds = nseg ? r.ctl.round : 0;
-    bool limit = nseg && r.ctl.limit;
+    uint32_t joint_rounds = r.rounds;
+    bool limit = r.limit;
     auto record = [&](uint32_t i, int32_t verdict, uint32_t ch) {
         verdicts[i] = verdict;
         if (rounds_out) rounds_out[i] = ch + 1;
         transitions += (static_cast<uint64_t>(a[i].n) + b[i].n) * a[i].k * (ch + 1);
     };
-    for (uint32_t j = 0; j < nseg; ++j) record(large_of[j], seg_verdicts[j], changing[j]);
+    for (uint32_t j = 0; j < nseg; ++j) record(large_of[j], r.verdicts[j], r.changing[j]);
     for (const SmallJob &j : small) {
         const SmallResult &sr = sres[j.index];
         record(j.index, static_cast<int32_t>(sr.verdict), sr.changing);
@@ -2361,8 +2544,7 @@ int equivalent_batch_impl(Ctx &c, uint32_t count, const dfa_view *a, const dfa_v
     if (st) {
         fill_batch_stats(st, count, r, total, transitions);
         st->rounds = joint_rounds;
-        if (!nseg) st->k_eff = 0;
-        st->algorithmic_bytes = (nseg ? r.bytes : 0) + small_bytes;
+        st->algorithmic_bytes = r.bytes + small_bytes;
         float ms = 0.f;
         HIP_TRY(hipEventElapsedTime(&ms, c.ev_start, c.ev_stop));
         st->device_ms = ms;
@@ -2557,7 +2739,7 @@ void for_each_buffer(Ctx &c, F &&f) {
                       &c.sort_m, &c.serve_in, &c.small_jobs, &c.small_results,
                       &c.small_ctl, &c.pb_tl, &c.pb_src, &c.pb_val, &c.pb_off,
                       &c.pb_partials, &c.segpat_table, &c.segpat, &c.tile_dead,
-                      &c.direct_cnt};
+                      &c.direct_cnt, &c.segd_plan, &c.segd_state, &c.segd_table};
     for (Buffer *b : bufs) f(*b);
 }
 

@@ -366,6 +366,56 @@ struct WholeArgs {
 uint32_t whole_lds_bytes(uint32_t n, uint32_t k);
 void launch_whole(const WholeArgs &a, hipStream_t s);
 
+// ---- batches, one launch per round (segment_kernels.hip) ----
+// A DFA of the batch; its states are off .. off + n - 1 of the union, off a
+// multiple of kBlock.  Equivalence pair s is parts 2s and 2s + 1.
+struct SegdPart {
+    const uint32_t *delta;
+    const uint8_t *acc;
+    uint32_t n, k, off, seg;
+    uint32_t wide;  // k = direct_width(k) is a multiple of 4, 16-byte aligned rows
+    uint32_t pad;
+    uint64_t out;   // offset of its block ids in the output
+};
+struct SegdSeg {
+    uint64_t table;       // first slot of its table
+    uint32_t mask;        // slots - 1 (a power of two, at least twice its states)
+    uint32_t first_tile;
+    uint32_t eq_a, eq_b;  // pairs: the start states in the union
+};
+constexpr uint32_t kSegdEpochs = 1u << 20;  // epoch 0 is the cleared table's
+constexpr uint32_t kSegdSpread = 16;        // counters of refined states
+constexpr uint32_t kSegdStride = 8;         // 8-byte words between two counters
+struct SegdCtl {
+    uint32_t err, moves, ndone, limit;  // bad target, letters that move a state, decided
+                                        // segments, a segment not stable at the round limit
+    unsigned long long active[kSegdSpread * kSegdStride];  // refined states over the rounds
+};
+struct SegdArgs {
+    const SegdPart *parts;
+    const SegdSeg *segs;
+    const uint32_t *tile_part;  // part of each tile of kBlock states
+    uint32_t tiles, nseg, pairs;
+    uint32_t *blockA, *blockB;  // round r reads A (even) or B (odd), writes the other
+    uint32_t *multi;            // zero before round 0
+    unsigned long long *table;
+    // zero before round 0
+    uint32_t *cnt;       // ring of 4 x nseg: blocks after round r at r & 3
+    uint32_t *classes;   // nseg: acceptance classes present
+    uint32_t *done;      // nseg: rounds run when the segment was decided
+    uint32_t *changing;  // nseg: rounds that changed its partition
+    uint32_t *blocks;    // nseg
+    SegdCtl *ctl;
+};
+// wide_letters: some part has more than 8 letters (at most kDirectMaxK).
+void launch_segd_round(const SegdArgs &a, uint32_t r, uint32_t epoch, bool wide_letters,
+                       hipStream_t s);
+void launch_segd_decide(const SegdArgs &a, uint32_t r, bool last, hipStream_t s);
+// Canonical ids of every DFA (scratch_max: a zeroed word per state of the
+// union); verdicts of the pairs.
+void launch_segd_output(const SegdArgs &a, uint32_t *scratch_max, uint32_t *out, hipStream_t s);
+void launch_segd_verdicts(const SegdArgs &a, int32_t *verdicts, hipStream_t s);
+
 // ---- leader-based refinement (naivePR; leader_kernels.hip) ----
 //
 //   block       uint32 [N]          leader (smallest member) of q's block,
