@@ -183,6 +183,7 @@ struct Ctx {
     hipStream_t caller = nullptr;
     bool joined = true;
     uint32_t *pinned = nullptr;  // host staging for small transfers
+    HostProgress *host_progress = nullptr;  // page-locked: written by the device
     Buffer cols, tc_cols, colmap, blockA, blockB, sig, hash, table, ctl, flags, canon, dense,
         leader_of, partials, scalars, multi, active, accbits, counters, presence, presence_packed,
         lab8;
@@ -310,6 +311,9 @@ int init_ctx(Ctx &c) {
     HIP_TRY(hipEventCreateWithFlags(&c.ev_sync, hipEventBlockingSync | hipEventDisableTiming));
     HIP_TRY(hipHostMalloc(reinterpret_cast<void **>(&c.pinned), kPinnedWords * sizeof(uint32_t),
                           hipHostMallocDefault));
+    HIP_TRY(hipHostMalloc(reinterpret_cast<void **>(&c.host_progress), sizeof(HostProgress),
+                          hipHostMallocDefault));
+    std::memset(c.host_progress, 0, sizeof *c.host_progress);
     dfa_tuning_default(&c.tune);
     c.inited = true;
     return DFA_OK;
@@ -741,6 +745,62 @@ int run_chunk(Ctx &c, const RoundArgs &ra, uint32_t rounds, int mode, uint32_t f
     return DFA_OK;
 }
 
+// Queues up to `rounds` rounds one by one, kRoundsAhead ahead of the device:
+// `launched` counts the rounds queued since the refinement began, the device
+// reports the rounds that have ended, and nothing is queued once the
+// refinement has stopped.  True: it has, and ctl is its final state; the
+// stream need not be waited for (at most kRoundsAhead - 1 rounds that do
+// nothing are still queued).  Otherwise the caller reads the state back.
+constexpr uint32_t kRoundsAhead = 3;
+constexpr uint32_t kPipelinedRounds = 64;  // longer chunks are replayed from a graph
+
+template <class Launch>
+int run_pipelined(Ctx &c, uint32_t rounds, uint32_t &launched, const Launch &launch, RoundCtl &ctl,
+                  bool &done) {
+    volatile uint32_t *at = &c.host_progress->progress;
+    done = false;
+    for (uint32_t i = 0; i < rounds; ++i) {
+        for (uint32_t spins = 0;; ++spins) {
+            const uint32_t p = __atomic_load_n(at, __ATOMIC_ACQUIRE);
+            if (p & kProgressDone) {
+                done = true;
+                break;
+            }
+            if (launched < p + kRoundsAhead) break;
+            // (an idle or failed stream reports nothing more: leave the rest
+            // to the caller's synchronisation)
+            if (spins % 1024 == 1023 && hipStreamQuery(c.stream) != hipErrorNotReady) {
+                (void)hipGetLastError();
+                if (__atomic_load_n(at, __ATOMIC_ACQUIRE) == p) return DFA_OK;
+            }
+            __builtin_ia32_pause();
+        }
+        if (done) break;
+        DFA_TRY(launch(launched));
+        ++launched;
+    }
+    HIP_TRY(hipGetLastError());
+    while (!done) {  // the last rounds of the chunk
+        const uint32_t p = __atomic_load_n(at, __ATOMIC_ACQUIRE);
+        done = (p & kProgressDone) != 0;
+        if (done || p >= launched) break;
+        if (hipStreamQuery(c.stream) != hipErrorNotReady) {
+            (void)hipGetLastError();
+            done = (__atomic_load_n(at, __ATOMIC_ACQUIRE) & kProgressDone) != 0;
+            break;
+        }
+    }
+    if (done) std::memcpy(&ctl, &c.host_progress->ctl, sizeof(RoundCtl));
+    return DFA_OK;
+}
+
+// Whether a chunk is queued round by round (run_pipelined).  Server lanes
+// wait asleep, so they do not watch the device.
+bool pipelined(const Ctx &c, uint32_t rounds, int mode) {
+    return (mode == DFA_LOOP_GRAPH || mode == DFA_LOOP_CHUNK) && rounds <= kPipelinedRounds &&
+           !c.profiling && !c.blocking_sync && c.host_progress;
+}
+
 // Signature rounds over N states whose level-0 columns are in c.cols and
 // whose initial labels are in c.blockA (flags already written by the ingest
 // and init kernels).
@@ -967,6 +1027,9 @@ int refine(Ctx &c, size_t N, uint32_t k, const dfa_options &o, uint32_t check_eq
         res.transitions = 0;
         res.bytes = 0;
     }
+    // (segments: their last round's bookkeeping is read back as well)
+    const bool watch = !seg;
+    if (c.host_progress) c.host_progress->progress = last_round;
     for (;; entered = true) {
         if (entered) {
             RoundArgs ra = make_round_args(c, cols, N, k_eff, cap, o.lds_stage, packed_second, seg, grouping);
@@ -978,6 +1041,7 @@ int refine(Ctx &c, size_t N, uint32_t k, const dfa_options &o, uint32_t check_eq
                 ra.segpat = c.segpat.as<uint16_t>();
                 ra.segpat_bits = segpat_bits;
             }
+            if (watch && pipelined(c, chunk, mode)) ra.host = c.host_progress;
             if (first) {
                 // rounds 0 (and 1) run on their own: label rounds when the
                 // signatures are short enough
@@ -1002,10 +1066,21 @@ int refine(Ctx &c, size_t N, uint32_t k, const dfa_options &o, uint32_t check_eq
             }
             // rounds launched so far: the label rounds, then last_round onwards
             const uint32_t next_round = std::max(last_round, res.label_rounds ? res.label_rounds : 1u);
-            DFA_TRY(run_chunk(c, ra, mode == DFA_LOOP_HOST ? 1u : chunk, mode, next_round));
+            bool stopped = false;
+            if (watch && pipelined(c, chunk, mode)) {
+                uint32_t launched = next_round;
+                DFA_TRY(run_pipelined(
+                    c, chunk, launched,
+                    [&](uint32_t round) { return launch_full_round(c, ra, round); }, res.ctl,
+                    stopped));
+            } else {
+                DFA_TRY(run_chunk(c, ra, mode == DFA_LOOP_HOST ? 1u : chunk, mode, next_round));
+            }
             first_chunk = false;
-            DFA_TRY(read_back(c, ctl, sizeof(RoundCtl)));
-            std::memcpy(&res.ctl, c.pinned, sizeof(RoundCtl));
+            if (!stopped) {
+                DFA_TRY(read_back(c, ctl, sizeof(RoundCtl)));
+                std::memcpy(&res.ctl, c.pinned, sizeof(RoundCtl));
+            }
             if (c.profiling) DFA_TRY(prof_collect(c, res.ctl));
             const uint32_t done_rounds = res.ctl.round - last_round;
             res.transitions += static_cast<uint64_t>(done_rounds) * N * k_eff;
@@ -1123,6 +1198,7 @@ int refine_leader(Ctx &c, size_t N, uint32_t k, const dfa_options &o, uint32_t c
     res.bytes = 0;
     RoundArgs none;
     std::memset(&none, 0, sizeof none);
+    if (c.host_progress) c.host_progress->progress = 0;
     for (;;) {
         LeaderArgs la;
         std::memset(&la, 0, sizeof la);
@@ -1135,9 +1211,20 @@ int refine_leader(Ctx &c, size_t N, uint32_t k, const dfa_options &o, uint32_t c
         la.moved = c.moved.as<unsigned long long>();
         la.counters = c.counters.as<uint32_t>();
         la.ctl = ctl;
-        DFA_TRY(run_chunk(c, none, mode == DFA_LOOP_HOST ? 1u : chunk, mode, last_round, &la));
-        DFA_TRY(read_back(c, ctl, sizeof(RoundCtl)));
-        std::memcpy(&res.ctl, c.pinned, sizeof(RoundCtl));
+        bool stopped = false;
+        if (pipelined(c, chunk, mode)) {
+            la.host = c.host_progress;
+            uint32_t launched = last_round;
+            DFA_TRY(run_pipelined(
+                c, chunk, launched,
+                [&](uint32_t round) { return launch_full_round(c, la, round); }, res.ctl, stopped));
+        } else {
+            DFA_TRY(run_chunk(c, none, mode == DFA_LOOP_HOST ? 1u : chunk, mode, last_round, &la));
+        }
+        if (!stopped) {
+            DFA_TRY(read_back(c, ctl, sizeof(RoundCtl)));
+            std::memcpy(&res.ctl, c.pinned, sizeof(RoundCtl));
+        }
         if (c.profiling) DFA_TRY(prof_collect(c, res.ctl));
         const uint32_t done_rounds = res.ctl.round - last_round;
         res.transitions += static_cast<uint64_t>(done_rounds) * N * k_eff;
@@ -2769,6 +2856,8 @@ void release_ctx(Ctx &c) {
     if (c.ev_up1) (void)hipEventDestroy(c.ev_up1);
     c.ev_up0 = c.ev_up1 = nullptr;
     if (c.pinned) (void)hipHostFree(c.pinned);
+    if (c.host_progress) (void)hipHostFree(c.host_progress);
+    c.host_progress = nullptr;
     if (c.pinned_batch) (void)hipHostFree(c.pinned_batch);
     for (int i = 0; i < 2; ++i) {
         if (c.ring[i]) (void)hipHostFree(c.ring[i]);

@@ -112,6 +112,27 @@ struct ColPtrs {
     }
 };
 
+// Tells the host (page-locked memory) that rounds have ended: the number of
+// rounds, and once the refinement has stopped also the whole round state.
+// Every thread of the workgroup calls it, after ctl has been written by
+// thread 0 (behind a barrier).
+__device__ __forceinline__ void report_round(const RoundCtl *ctl, HostProgress *host) {
+    if (!host) return;
+    const bool done = ctl->done != 0;
+    if (done) {
+        constexpr uint32_t words = sizeof(RoundCtl) / sizeof(uint32_t);
+        const uint32_t *src = reinterpret_cast<const uint32_t *>(ctl);
+        uint32_t *dst = reinterpret_cast<uint32_t *>(&host->ctl);
+        for (uint32_t i = threadIdx.x; i < words; i += blockDim.x)
+            __hip_atomic_store(dst + i, src[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __threadfence_system();
+        __syncthreads();
+    }
+    if (threadIdx.x == 0)
+        __hip_atomic_store(&host->progress, ctl->round | (done ? kProgressDone : 0u),
+                           __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Marks block `id` as having two or more members after round r.
 __device__ __forceinline__ void mark_multi(uint32_t *multi, uint32_t id, uint32_t tag) {
     if (multi[id] != tag) multi[id] = tag;

@@ -84,6 +84,17 @@ struct RoundCtl {
     unsigned long long pb_rounds;       // bit r % 64: round r gathered through LDS slices
 };
 
+// What the device tells the host while rounds run, in page-locked host memory:
+// the rounds that have ended, kProgressDone with the last one, and then the
+// round state.  The host queues rounds a few ahead of it and stops when the
+// refinement has.
+constexpr uint32_t kProgressDone = 1u << 31;
+struct HostProgress {
+    uint32_t progress;
+    uint32_t pad[15];
+    RoundCtl ctl;
+};
+
 // ---- launchers (defined in refine_kernels.hip); all enqueue on `s` ----
 
 // Transpose row-major delta (n x k, targets < n) into cols[a*N + offset + q]
@@ -237,6 +248,7 @@ struct RoundArgs {
     uint32_t *segpat_table;
     uint16_t *segpat;
     uint32_t segpat_bits;
+    HostProgress *host;  // nullptr: rounds end without telling the host
 };
 // Largest pattern width (bits) and table (words) of the segmented pattern
 // round.
@@ -435,6 +447,7 @@ struct LeaderArgs {
     unsigned long long *moved;
     uint32_t *counters;  // kSpread * kSpreadStride words, zero between rounds
     RoundCtl *ctl;
+    HostProgress *host;  // nullptr: rounds end without telling the host
 };
 // Initial leaders: block[q] = smallest accepting or smallest rejecting state
 // of q's class, from the acceptance bits; lead: 2 words preset to all ones.

@@ -224,8 +224,13 @@ __global__ __launch_bounds__(kBlock) void k_leader_elect(LeaderArgs a) { leader_
 __global__ __launch_bounds__(kBlock) void k_leader_move(LeaderArgs a) { leader_move_body(a); }
 
 __global__ __launch_bounds__(kBlock) void k_leader_end(RoundCtl *ctl, const uint32_t *block,
-                                                       uint32_t *counters) {
+                                                       uint32_t *counters, HostProgress *host) {
+    const bool over = ctl->done != 0;
+    __syncthreads();  // every thread has read the flag before it is written
+    if (over) return;
     leader_end_body(ctl, block, counters);
+    __syncthreads();
+    report_round(ctl, host);
 }
 
 // Persistent loop of leader rounds: the three phases of a round separated by
@@ -282,7 +287,8 @@ void launch_leader_move(const LeaderArgs &a, hipStream_t s) {
 }
 
 void launch_leader_end(const LeaderArgs &a, hipStream_t s) {
-    launch_kernel(k_leader_end, dim3(1), dim3(kBlock), 0, s, a.ctl, a.block, a.counters);
+    launch_kernel(k_leader_end, dim3(1), dim3(kBlock), 0, s, a.ctl, a.block, a.counters,
+                  a.host);
 }
 
 void launch_leader_round(const LeaderArgs &a, hipStream_t s) {

@@ -1963,8 +1963,13 @@ __global__ __launch_bounds__(kBlock) void k_insert_lds2(InsParams p) { insert_ld
 
 __global__ __launch_bounds__(kBlock) void k_round_end(RoundCtl *ctl, const uint32_t *blockA,
                                                        const uint32_t *blockB, uint32_t *counters,
-                                                       uint32_t N) {
+                                                       uint32_t N, HostProgress *host) {
+    const bool over = ctl->done != 0;
+    __syncthreads();  // every thread has read the flag before it is written
+    if (over) return;
     round_end_body(ctl, blockA, blockB, counters, N);
+    __syncthreads();
+    report_round(ctl, host);
 }
 
 
@@ -2797,7 +2802,7 @@ void launch_ctl_resume(RoundCtl *ctl, hipStream_t s) {
 
 void launch_round_end(const RoundArgs &a, hipStream_t s) {
     launch_kernel(k_round_end, dim3(1), dim3(kBlock), 0, s, a.ctl, a.blockA, a.blockB,
-                       a.counters, static_cast<uint32_t>(a.N));
+                       a.counters, static_cast<uint32_t>(a.N), a.host);
 }
 
 void launch_pattern_kernel(const RoundArgs &a, hipStream_t s) {
