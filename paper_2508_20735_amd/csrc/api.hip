@@ -567,8 +567,9 @@ struct Outputs {
 // separated (large inputs), or, after 16 rounds, no more than 1/64 of them
 // (small ones, where the closure is cheap and the remaining rounds would
 // each split a block or two).
+constexpr uint32_t kStallRounds = 8;
 bool splitting_stalled(const RoundCtl &ctl, size_t N) {
-    if (ctl.round < 8) return false;
+    if (ctl.round < kStallRounds) return false;
     const uint64_t left = N - ctl.prev_count;
     uint64_t recent_gain = 0;
     for (uint32_t i = 1; i <= 4 && i <= ctl.round; ++i)
@@ -601,16 +602,20 @@ int build_closure(Ctx &c, size_t N, uint32_t k, std::vector<uint32_t> &colmap, u
     uint32_t *diff = nonid + ncols;
     HIP_TRY(hipMemcpyAsync(c.tc_cols.p, c.cols.p, static_cast<size_t>(k) * N * sizeof(uint32_t),
                            hipMemcpyDeviceToDevice, c.stream));
-    HIP_TRY(hipMemsetAsync(nonid + k, 0, (ncols - k) * sizeof(uint32_t), c.stream));
+    uint32_t *cols = c.tc_cols.as<uint32_t>();
     HIP_TRY(hipMemsetAsync(diff, 0, ncols * sizeof(uint32_t), c.stream));
-    for (uint32_t i = 1; i <= L; ++i)
-        launch_jump(c.tc_cols.as<uint32_t>(), N, k, i, diff, nonid, c.stream);
     if (single) {
         // on demand, mid-refinement: only the states outside singleton
-        // blocks are refined from here on, so the columns are judged on them
-        HIP_TRY(hipMemsetAsync(nonid, 0, 2 * ncols * sizeof(uint32_t), c.stream));
-        launch_column_flags(c.tc_cols.as<uint32_t>(), N, k, static_cast<uint32_t>(ncols), single,
-                            diff, nonid, c.stream);
+        // blocks are refined from here on, so the columns are judged on them,
+        // and a letter that is the identity there gets no levels
+        HIP_TRY(hipMemsetAsync(nonid, 0, ncols * sizeof(uint32_t), c.stream));
+        launch_letter_flags(cols, N, k, single, diff, c.stream);
+        for (uint32_t i = 1; i <= L; ++i)
+            launch_jump(cols, N, k, i, diff, nullptr, nullptr, c.stream);
+        launch_level_flags(cols, N, k, L, single, diff, nonid, c.stream);
+    } else {
+        HIP_TRY(hipMemsetAsync(nonid + k, 0, (ncols - k) * sizeof(uint32_t), c.stream));
+        for (uint32_t i = 1; i <= L; ++i) launch_jump(cols, N, k, i, nonid, diff, nonid, c.stream);
     }
     HIP_TRY(hipGetLastError());
     DFA_TRY(read_back(c, nonid, 2 * ncols * sizeof(uint32_t)));
@@ -637,8 +642,10 @@ int rejudge_columns(Ctx &c, size_t N, uint32_t k, uint32_t levels,
     uint32_t *nonid = c.flags.as<uint32_t>() + kFlagNonid;
     uint32_t *diff = nonid + ncols;
     HIP_TRY(hipMemsetAsync(nonid, 0, 2 * ncols * sizeof(uint32_t), c.stream));
-    launch_column_flags(c.tc_cols.as<uint32_t>(), N, k, static_cast<uint32_t>(ncols),
-                        c.single.as<unsigned long long>(), diff, nonid, c.stream);
+    // (letters without levels keep clear flags; they are not in colmap)
+    const unsigned long long *single = c.single.as<unsigned long long>();
+    launch_letter_flags(c.tc_cols.as<uint32_t>(), N, k, single, diff, c.stream);
+    launch_level_flags(c.tc_cols.as<uint32_t>(), N, k, levels, single, diff, nonid, c.stream);
     HIP_TRY(hipGetLastError());
     DFA_TRY(read_back(c, nonid, 2 * ncols * sizeof(uint32_t)));
     kept.clear();
@@ -745,52 +752,59 @@ int run_chunk(Ctx &c, const RoundArgs &ra, uint32_t rounds, int mode, uint32_t f
     return DFA_OK;
 }
 
-// Queues up to `rounds` rounds one by one, kRoundsAhead ahead of the device:
+// Queues up to `rounds` rounds one by one, two or three ahead of the device:
 // `launched` counts the rounds queued since the refinement began, the device
 // reports the rounds that have ended, and nothing is queued once the
-// refinement has stopped.  True: it has, and ctl is its final state; the
-// stream need not be waited for (at most kRoundsAhead - 1 rounds that do
-// nothing are still queued).  Otherwise the caller reads the state back.
-constexpr uint32_t kRoundsAhead = 3;
+// refinement has stopped.  known: ctl holds what the device reported, without
+// a wait for the stream: the final state if the refinement has stopped (at
+// most two rounds that do nothing are still queued), else the
+// rounds so far, after all of them (drain), with their blocks, gains and
+// refined states, or as far as they have been reported.  Not known: the
+// caller reads the state back.
+// Rounds of 2^20 states and more are longer than the host needs to queue one,
+// so two in flight keep the device busy; of the shorter ones three.
+constexpr size_t kLongRoundStates = size_t(1) << 20;
 constexpr uint32_t kPipelinedRounds = 64;  // longer chunks are replayed from a graph
 
 template <class Launch>
-int run_pipelined(Ctx &c, uint32_t rounds, uint32_t &launched, const Launch &launch, RoundCtl &ctl,
-                  bool &done) {
-    volatile uint32_t *at = &c.host_progress->progress;
-    done = false;
-    for (uint32_t i = 0; i < rounds; ++i) {
+int run_pipelined(Ctx &c, size_t N, uint32_t rounds, uint32_t &launched, bool drain,
+                  const Launch &launch, RoundCtl &ctl, bool &known) {
+    const HostProgress *host = c.host_progress;
+    const uint32_t ahead = N >= kLongRoundStates ? 2 : 3;
+    known = false;
+    // Waits until the device has ended `want` rounds or stopped; false if
+    // the stream is idle (or failed) without having reported that.
+    uint32_t p = 0;
+    auto reached = [&](uint32_t want) -> bool {
         for (uint32_t spins = 0;; ++spins) {
-            const uint32_t p = __atomic_load_n(at, __ATOMIC_ACQUIRE);
-            if (p & kProgressDone) {
-                done = true;
-                break;
-            }
-            if (launched < p + kRoundsAhead) break;
-            // (an idle or failed stream reports nothing more: leave the rest
-            // to the caller's synchronisation)
+            p = __atomic_load_n(&host->progress, __ATOMIC_ACQUIRE);
+            if ((p & kProgressDone) || p >= want) return true;
             if (spins % 1024 == 1023 && hipStreamQuery(c.stream) != hipErrorNotReady) {
                 (void)hipGetLastError();
-                if (__atomic_load_n(at, __ATOMIC_ACQUIRE) == p) return DFA_OK;
+                p = __atomic_load_n(&host->progress, __ATOMIC_ACQUIRE);
+                return (p & kProgressDone) || p >= want;
             }
             __builtin_ia32_pause();
         }
-        if (done) break;
+    };
+    for (uint32_t i = 0; i < rounds; ++i) {
+        if (launched >= ahead && !reached(launched - ahead + 1)) return DFA_OK;
+        if (p & kProgressDone) break;
         DFA_TRY(launch(launched));
         ++launched;
     }
     HIP_TRY(hipGetLastError());
-    while (!done) {  // the last rounds of the chunk
-        const uint32_t p = __atomic_load_n(at, __ATOMIC_ACQUIRE);
-        done = (p & kProgressDone) != 0;
-        if (done || p >= launched) break;
-        if (hipStreamQuery(c.stream) != hipErrorNotReady) {
-            (void)hipGetLastError();
-            done = (__atomic_load_n(at, __ATOMIC_ACQUIRE) & kProgressDone) != 0;
-            break;
-        }
+    if (drain && !(p & kProgressDone) && !reached(launched)) return DFA_OK;
+    known = true;
+    if (p & kProgressDone) {
+        std::memcpy(&ctl, &host->ctl, sizeof(RoundCtl));
+        return DFA_OK;
     }
-    if (done) std::memcpy(&ctl, &c.host_progress->ctl, sizeof(RoundCtl));
+    ctl.round = launched;
+    ctl.done = 0;
+    ctl.prev_count = host->blocks;
+    ctl.active_sum = host->active_sum;
+    std::memcpy(ctl.gain_hist, host->gain_hist, sizeof ctl.gain_hist);
     return DFA_OK;
 }
 
@@ -1036,6 +1050,9 @@ int refine(Ctx &c, size_t N, uint32_t k, const dfa_options &o, uint32_t check_eq
             // the dense rounds come first (the first table rounds); later chunks
             // gather directly, so a long refinement pays nothing for the passes
             if (first_chunk) ra.pb = pb;
+            // the states that a closure refines sit together (the rest are
+            // singletons by then)
+            ra.spread = res.tc_used;
             if (segpat && first) {
                 ra.segpat_table = c.segpat_table.as<uint32_t>();
                 ra.segpat = c.segpat.as<uint16_t>();
@@ -1066,24 +1083,31 @@ int refine(Ctx &c, size_t N, uint32_t k, const dfa_options &o, uint32_t check_eq
             }
             // rounds launched so far: the label rounds, then last_round onwards
             const uint32_t next_round = std::max(last_round, res.label_rounds ? res.label_rounds : 1u);
-            bool stopped = false;
+            bool known = false;
             if (watch && pipelined(c, chunk, mode)) {
                 uint32_t launched = next_round;
+                // the rounds need have ended only where a decision follows:
+                // the closure switched on, or its columns judged again
+                const bool drain =
+                    (o.tc_mode == DFA_TC_AUTO && !res.tc_used && !tc_failed &&
+                     launched + chunk >= kStallRounds) ||
+                    (res.tc_used && !rejudged);
                 DFA_TRY(run_pipelined(
-                    c, chunk, launched,
+                    c, N, chunk, launched, drain,
                     [&](uint32_t round) { return launch_full_round(c, ra, round); }, res.ctl,
-                    stopped));
+                    known));
             } else {
                 DFA_TRY(run_chunk(c, ra, mode == DFA_LOOP_HOST ? 1u : chunk, mode, next_round));
             }
             first_chunk = false;
-            if (!stopped) {
+            if (!known) {
                 DFA_TRY(read_back(c, ctl, sizeof(RoundCtl)));
                 std::memcpy(&res.ctl, c.pinned, sizeof(RoundCtl));
             }
             if (c.profiling) DFA_TRY(prof_collect(c, res.ctl));
-            const uint32_t done_rounds = res.ctl.round - last_round;
-            res.transitions += static_cast<uint64_t>(done_rounds) * N * k_eff;
+            // (rounds queued but not yet reported may turn out not to have run)
+            const int64_t done_rounds = static_cast<int64_t>(res.ctl.round) - last_round;
+            res.transitions += static_cast<uint64_t>(done_rounds * static_cast<int64_t>(N * k_eff));
             res.bytes += (res.ctl.active_sum - last_active_sum) * (8ull * k_eff + 8ull);
             last_round = res.ctl.round;
             last_active_sum = res.ctl.active_sum;
@@ -1211,24 +1235,27 @@ int refine_leader(Ctx &c, size_t N, uint32_t k, const dfa_options &o, uint32_t c
         la.moved = c.moved.as<unsigned long long>();
         la.counters = c.counters.as<uint32_t>();
         la.ctl = ctl;
-        bool stopped = false;
+        bool known = false;
         if (pipelined(c, chunk, mode)) {
             la.host = c.host_progress;
             uint32_t launched = last_round;
+            const bool drain = o.tc_mode == DFA_TC_AUTO && !res.tc_used && !tc_failed &&
+                               launched + chunk >= kStallRounds;
             DFA_TRY(run_pipelined(
-                c, chunk, launched,
-                [&](uint32_t round) { return launch_full_round(c, la, round); }, res.ctl, stopped));
+                c, N, chunk, launched, drain,
+                [&](uint32_t round) { return launch_full_round(c, la, round); }, res.ctl, known));
         } else {
             DFA_TRY(run_chunk(c, none, mode == DFA_LOOP_HOST ? 1u : chunk, mode, last_round, &la));
         }
-        if (!stopped) {
+        if (!known) {
             DFA_TRY(read_back(c, ctl, sizeof(RoundCtl)));
             std::memcpy(&res.ctl, c.pinned, sizeof(RoundCtl));
         }
         if (c.profiling) DFA_TRY(prof_collect(c, res.ctl));
-        const uint32_t done_rounds = res.ctl.round - last_round;
-        res.transitions += static_cast<uint64_t>(done_rounds) * N * k_eff;
-        res.bytes += static_cast<uint64_t>(done_rounds) * N * 4 +
+        // (rounds queued but not yet reported may turn out not to have run)
+        const int64_t done_rounds = static_cast<int64_t>(res.ctl.round) - last_round;
+        res.transitions += static_cast<uint64_t>(done_rounds * static_cast<int64_t>(N * k_eff));
+        res.bytes += static_cast<uint64_t>(done_rounds * static_cast<int64_t>(N * 4)) +
                      (res.ctl.active_sum - last_active_sum) * (16ull * k_eff);
         last_round = res.ctl.round;
         last_active_sum = res.ctl.active_sum;

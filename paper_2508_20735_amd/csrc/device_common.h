@@ -95,8 +95,20 @@ __device__ __forceinline__ bool rows_equal(const uint32_t *__restrict__ sig, siz
                                            size_t b) {
     const uint32_t *ra = sig + a * W;
     const uint32_t *rb = sig + b * W;
-    for (size_t i = 0; i < W; ++i)
-        if (ra[i] != rb[i]) return false;
+    // eight words at a time: their loads are in flight together
+    for (size_t i = 0; i < W; i += 8) {
+        uint32_t va[8], vb[8];
+#pragma unroll
+        for (size_t j = 0; j < 8; ++j) {
+            const size_t at = i + j < W ? i + j : W - 1;
+            va[j] = ra[at];
+            vb[j] = rb[at];
+        }
+        bool eq = true;
+#pragma unroll
+        for (size_t j = 0; j < 8; ++j) eq &= va[j] == vb[j];
+        if (!eq) return false;
+    }
     return true;
 }
 
@@ -112,10 +124,15 @@ struct ColPtrs {
     }
 };
 
-// Tells the host (page-locked memory) that rounds have ended: the number of
-// rounds, and once the refinement has stopped also the whole round state.
+// Tells the host (page-locked memory) that a round has ended: the number of
+// rounds, blocks and the round's gain, and once the refinement has stopped
+// also the whole round state.
 // Every thread of the workgroup calls it, after ctl has been written by
-// thread 0 (behind a barrier).
+// thread 0 (behind a barrier).  The stores bypass the caches, so waiting for
+// them orders them; a system-scope release would write back the XCD's L2 as
+// well, which cost 5 us a round.
+__device__ __forceinline__ void wait_for_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 __device__ __forceinline__ void report_round(const RoundCtl *ctl, HostProgress *host) {
     if (!host) return;
     const bool done = ctl->done != 0;
@@ -125,12 +142,21 @@ __device__ __forceinline__ void report_round(const RoundCtl *ctl, HostProgress *
         uint32_t *dst = reinterpret_cast<uint32_t *>(&host->ctl);
         for (uint32_t i = threadIdx.x; i < words; i += blockDim.x)
             __hip_atomic_store(dst + i, src[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        __threadfence_system();
+        wait_for_stores();
         __syncthreads();
     }
-    if (threadIdx.x == 0)
+    if (threadIdx.x == 0) {
+        const uint32_t last = (ctl->round - 1) % kActiveHist;
+        __hip_atomic_store(&host->blocks, ctl->prev_count, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(&host->active_sum, ctl->active_sum, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(&host->gain_hist[last], ctl->gain_hist[last], __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+        wait_for_stores();
         __hip_atomic_store(&host->progress, ctl->round | (done ? kProgressDone : 0u),
-                           __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
 }
 
 // Marks block `id` as having two or more members after round r.

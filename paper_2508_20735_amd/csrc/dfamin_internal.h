@@ -85,13 +85,15 @@ struct RoundCtl {
 };
 
 // What the device tells the host while rounds run, in page-locked host memory:
-// the rounds that have ended, kProgressDone with the last one, and then the
-// round state.  The host queues rounds a few ahead of it and stops when the
-// refinement has.
+// the rounds that have ended, with what the host's decisions between rounds
+// need, kProgressDone with the last one, and then the whole round state.  The
+// host queues rounds a few ahead of it and stops when the refinement has.
 constexpr uint32_t kProgressDone = 1u << 31;
 struct HostProgress {
     uint32_t progress;
-    uint32_t pad[15];
+    uint32_t blocks;                 // after the last round
+    unsigned long long active_sum;   // refined states over the rounds
+    uint32_t gain_hist[kActiveHist]; // blocks added by round r, at r % kActiveHist
     RoundCtl ctl;
 };
 
@@ -249,6 +251,7 @@ struct RoundArgs {
     uint16_t *segpat;
     uint32_t segpat_bits;
     HostProgress *host;  // nullptr: rounds end without telling the host
+    uint32_t spread;     // 1: signature tiles go round the XCDs instead of in eighths
 };
 // Largest pattern width (bits) and table (words) of the segmented pattern
 // round.
@@ -508,18 +511,21 @@ void launch_reach_expand(const uint8_t *mark, size_t n, const uint32_t *dense,
                          const uint32_t *orig, const uint32_t *sub_block, uint32_t *block_out,
                          hipStream_t s);
 
-// Pointer jumping, level i >= 1, all k letters:
+// Pointer jumping, level i >= 1, the letters whose word in `letters` is set:
 // cols[(i*k+a)*N + q] = cols[((i-1)*k+a)*N + cols[((i-1)*k+a)*N + q]];
-// diff[i*k+a] = 1 if the level differs from level i-1 somewhere,
-// nonid[i*k+a] = 1 if it is not the identity.
-// Identity / previous-level flags of ncols closure columns (k letters per
-// level) over the states whose bit in `single` is clear; diff and nonid must
-// be zero.
-void launch_column_flags(const uint32_t *cols, size_t N, uint32_t k, uint32_t ncols,
-                         const unsigned long long *single, uint32_t *diff, uint32_t *nonid,
-                         hipStream_t s);
-void launch_jump(uint32_t *cols, size_t N, uint32_t k, uint32_t level, uint32_t *diff,
-                 uint32_t *nonid, hipStream_t s);
+// with diff and nonid: diff[i*k+a] = 1 if the level differs from level i-1
+// somewhere, nonid[i*k+a] = 1 if it is not the identity.
+void launch_jump(uint32_t *cols, size_t N, uint32_t k, uint32_t level, const uint32_t *letters,
+                 uint32_t *diff, uint32_t *nonid, hipStream_t s);
+// Flags over the states whose bit in `single` is clear (all zero before):
+// letters[a] = 1 if letter a moves such a state; for the levels 0 .. `levels`
+// of the letters so marked, nonid[i*k+a] = 1 if the level moves one and
+// letters[i*k+a] = 1 (i >= 1) if it differs from level i-1 on one.
+void launch_letter_flags(const uint32_t *cols, size_t N, uint32_t k,
+                         const unsigned long long *single, uint32_t *letters, hipStream_t s);
+void launch_level_flags(const uint32_t *cols, size_t N, uint32_t k, uint32_t levels,
+                        const unsigned long long *single, uint32_t *letters, uint32_t *nonid,
+                        hipStream_t s);
 
 // Canonical renumbering: out[q] = min{ q' : ids[q'] == ids[q] } for ids <
 // id_range; scratch_min holds id_range words.

@@ -248,7 +248,17 @@ struct SigParams {
     // segmented refinements: decided tiles and their holders (else null)
     const uint8_t *tile_dead;
     const uint16_t *tile_lead;
+    uint32_t spread;  // signature tiles go round the XCDs
 };
+
+// The tiles of a signature kernel's workgroup: a contiguous eighth per XCD,
+// or (closure rounds, whose refined states sit together in a part of the
+// index space: with eighths, half of the XCDs had nothing to do) all tiles in
+// turn.
+__device__ __forceinline__ TileRange sig_tiles(const SigParams &p, size_t tile) {
+    if (!p.spread) return xcd_tiles(p.N, tile);
+    return TileRange{blockIdx.x, (p.N + tile - 1) / tile, gridDim.x};
+}
 
 // Segmented refinements: whether every kBlock-state tile of [base, base + n)
 // (base a multiple of kBlock, base < N) holds only decided segments.  Their
@@ -763,7 +773,7 @@ __device__ __forceinline__ void signature_body(const SigParams &p) {
         // their values are used
         // XCD-sliced tiles of two kBlock-state halves (a union's successor
         // ids are gathered from one operand per XCD)
-        const TileRange tr = xcd_tiles(p.N, 2 * kBlock);
+        const TileRange tr = sig_tiles(p, 2 * kBlock);
         for (size_t tile = tr.first; tile < tr.end; tile += tr.step) {
             const size_t base = tile * (2 * kBlock);
             if (tiles_dead(p.tile_dead, p.N, base, 2 * kBlock)) {
@@ -840,7 +850,7 @@ __device__ __forceinline__ void signature_body(const SigParams &p) {
                     emit_key(p, Y, q[i], w0[i], w[i], KC, W, !all && p.grouping == 0, claims);
         }
     } else {
-        const TileRange tr = xcd_tiles(p.N, kBlock);
+        const TileRange tr = sig_tiles(p, kBlock);
         for (size_t tile = tr.first; tile < tr.end; tile += tr.step) {
             if (tiles_dead(p.tile_dead, p.N, tile * kBlock, kBlock)) {
                 if (threadIdx.x == 0) leaders += dead_holders(p.tile_lead, p.N, tile * kBlock, kBlock);
@@ -920,6 +930,19 @@ constexpr uint32_t kPbScatterThreads = 2 * kBlock;
 template <int KC>
 constexpr int kPbScatterBatch = kPbBatch<KC> / 2;
 
+// atomicAdd(cnt + b, 1) for the lanes with `on`, returning each one's old
+// value; when the whole wave shares a bucket (inputs whose targets sit
+// together), one atomic instead of 64 on one word.  Every lane calls it.
+__device__ __forceinline__ uint32_t wave_bucket_add(uint32_t *cnt, uint32_t b, bool on) {
+    const uint32_t first = __builtin_amdgcn_readfirstlane(b);
+    if (__ballot(!on || b != first) == 0) {
+        uint32_t base = 0;
+        if (lane_id() == 0) base = atomicAdd(cnt + first, 64u);
+        return __builtin_amdgcn_readfirstlane(base) + lane_id();
+    }
+    return on ? atomicAdd(cnt + b, 1u) : 0u;
+}
+
 // Edge counts per (tile, bucket), tile-major: cnt[t * nb + b] is the length
 // of tile t's run in bucket b (one coalesced row per tile).
 template <int KC>
@@ -945,7 +968,7 @@ __global__ __launch_bounds__(kBlock) void k_pb_count(const uint32_t *cols, const
             for (int u = 0; u < kPbBatch<KC>; ++u)
 #pragma unroll
                 for (int a = 0; a < KC; ++a)
-                    if (tg[u][a] != ~0u) atomicAdd(hist + (tg[u][a] >> kPbSliceLog), 1u);
+                    (void)wave_bucket_add(hist, tg[u][a] >> kPbSliceLog, tg[u][a] != ~0u);
         }
         __syncthreads();
         for (uint32_t b = threadIdx.x; b < nb; b += kBlock)
@@ -1102,11 +1125,23 @@ __device__ __forceinline__ uint32_t pb_tile_run_ids(const PbArgs &pb, uint32_t t
         __syncthreads();
         uint32_t before = carry;
         for (uint32_t w = 0; w < tx / 64; ++w) before += wsum[w];
+        const uint32_t start = before + x - len;
         if (b < pb.nb) {
-            const uint32_t start = before + x - len;
             delta[b] = at - start;
             if (lpos) lpos[b] = start;
+        }
+        // short runs by their own thread; long ones (inputs whose targets sit
+        // together, chains above all) by the whole wave, run by run
+        constexpr uint32_t kLong = 64;
+        if (len <= kLong)
             for (uint32_t l = 0; l < len; ++l) rid[start + l] = static_cast<uint16_t>(b);
+        unsigned long long lng = __ballot(len > kLong);
+        while (lng) {
+            const int src = __ffsll(lng) - 1;
+            lng &= lng - 1;
+            const uint32_t rs = __shfl(start, src, 64), rl = __shfl(len, src, 64);
+            const uint32_t rb = __shfl(b, src, 64);
+            for (uint32_t l = lane_id(); l < rl; l += 64) rid[rs + l] = static_cast<uint16_t>(rb);
         }
         uint32_t total = carry;
         for (uint32_t w = 0; w < NT / 64; ++w) total += wsum[w];
@@ -1176,8 +1211,9 @@ __global__ __launch_bounds__(kPbScatterThreads) void k_pb_scatter(const uint32_t
                 const uint32_t i = i0 + u * kPbScatterThreads + tx;
 #pragma unroll
                 for (int a = 0; a < KC; ++a) {
+                    const uint32_t e =
+                        wave_bucket_add(lpos, tg[u][a] >> kPbSliceLog, tg[u][a] != ~0u);
                     if (tg[u][a] == ~0u) continue;
-                    const uint32_t e = atomicAdd(lpos + (tg[u][a] >> kPbSliceLog), 1u);
                     ltl[e] = static_cast<uint16_t>(tg[u][a] & ((1u << kPbSliceLog) - 1u));
                     lsrc[e] = static_cast<uint16_t>(i * KC + a);
                 }
@@ -2357,8 +2393,10 @@ __global__ __launch_bounds__(kBlock) void k_pair_verdicts(SegArgs g,
 
 __global__ __launch_bounds__(kBlock) void k_jump(uint32_t *__restrict__ cols, size_t N,
                                                   uint32_t k, uint32_t level,
-                                                  uint32_t *diff, uint32_t *nonid) {
+                                                  const uint32_t *letters, uint32_t *diff,
+                                                  uint32_t *nonid) {
     const uint32_t a = blockIdx.y;
+    if (!letters[a]) return;
     const uint32_t *__restrict__ prev = cols + (static_cast<size_t>(level - 1) * k + a) * N;
     uint32_t *__restrict__ cur = cols + (static_cast<size_t>(level) * k + a) * N;
     bool d = false, moves = false;
@@ -2369,31 +2407,67 @@ __global__ __launch_bounds__(kBlock) void k_jump(uint32_t *__restrict__ cols, si
         d |= t != m;
         moves |= t != q;
     }
+    if (!diff) return;
     wave_set_flag(diff + static_cast<size_t>(level) * k + a, d);
     wave_set_flag(nonid + static_cast<size_t>(level) * k + a, moves);
 }
 
 // Flags of the closure columns over the states outside singleton blocks:
-// nonid[c] when column c moves such a state, diff[c] when it differs from
-// the previous level of its letter on such a state (level 0: unused).
-// Singletons never split, so a column that is the identity, or repeats its
-// previous level, on every other state only repeats a key component there.
-__global__ __launch_bounds__(kBlock) void k_col_flags(const uint32_t *__restrict__ cols, size_t N,
-                                                      uint32_t k,
-                                                      const unsigned long long *__restrict__ single,
-                                                      uint32_t *diff, uint32_t *nonid) {
-    const uint32_t c = blockIdx.y;
-    const uint32_t *__restrict__ col = cols + static_cast<size_t>(c) * N;
-    const uint32_t *__restrict__ prev = c >= k ? cols + static_cast<size_t>(c - k) * N : col;
-    bool d = false, moves = false;
+// a level of a letter that moves such a state, or differs from the letter's
+// previous level on one.  Singletons never split, so a column that is the
+// identity, or repeats its previous level, on every other state only repeats
+// a key component there.
+__global__ __launch_bounds__(kBlock) void k_letter_flags(const uint32_t *__restrict__ cols,
+                                                         size_t N,
+                                                         const unsigned long long *__restrict__ single,
+                                                         uint32_t *letters) {
+    const uint32_t a = blockIdx.y;
+    const uint32_t *__restrict__ col = cols + static_cast<size_t>(a) * N;
+    bool moves = false;
+    for (size_t q = global_tid(); q < N; q += grid_stride())
+        if (!((single[q >> 6] >> (q & 63)) & 1ull)) moves |= col[q] != q;
+    wave_set_flag(letters + a, moves);
+}
+
+// One thread takes a state through all levels of a letter, so that every
+// column is read once (one launch row per column, which read each column
+// twice, took 324 us for 84 columns of 2^21 states, half of them refined).
+// At most 32 levels (N < 2^32): a bit per level.
+__global__ __launch_bounds__(kBlock) void k_level_flags(const uint32_t *__restrict__ cols, size_t N,
+                                                        uint32_t k, uint32_t levels,
+                                                        const unsigned long long *__restrict__ single,
+                                                        uint32_t *letters, uint32_t *nonid) {
+    const uint32_t a = blockIdx.y;
+    if (!letters[a]) return;
+    uint32_t moves = 0, differs = 0;
     for (size_t q = global_tid(); q < N; q += grid_stride()) {
         if ((single[q >> 6] >> (q & 63)) & 1ull) continue;
-        const uint32_t t = col[q];
-        d |= t != prev[q];
-        moves |= t != q;
+        const uint32_t *__restrict__ p = cols + static_cast<size_t>(a) * N + q;
+        uint32_t before = static_cast<uint32_t>(q);
+        for (uint32_t i0 = 0; i0 <= levels; i0 += 8) {
+            uint32_t t[8];
+#pragma unroll
+            for (uint32_t j = 0; j < 8; ++j)
+                t[j] = p[static_cast<size_t>(i0 + j <= levels ? i0 + j : levels) * k * N];
+#pragma unroll
+            for (uint32_t j = 0; j < 8; ++j) {
+                if (i0 + j > levels) continue;
+                moves |= t[j] != q ? 1u << (i0 + j) : 0u;
+                differs |= t[j] != before ? 1u << (i0 + j) : 0u;
+                before = t[j];
+            }
+        }
     }
-    wave_set_flag(diff + c, d);
-    wave_set_flag(nonid + c, moves);
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        moves |= __shfl_xor(moves, d, 64);
+        differs |= __shfl_xor(differs, d, 64);
+    }
+    const uint32_t i = lane_id();
+    if (i > levels) return;
+    const size_t col = static_cast<size_t>(i) * k + a;
+    if (((moves >> i) & 1u) && nonid[col] == 0u) nonid[col] = 1u;
+    if (i >= 1 && ((differs >> i) & 1u) && letters[col] == 0u) letters[col] = 1u;
 }
 
 // ---------------------------------------------------------------- canonical ids
@@ -2693,7 +2767,7 @@ SigParams sig_params(const RoundArgs &a) {
                      a.seg.nseg ? a.seg.parts : nullptr,      a.seg.nseg ? a.seg.tile_part : nullptr,
                      a.seg.nseg ? a.seg.nparts : 0u, a.pb,
                      a.seg.nseg ? a.seg.tile_dead : nullptr,
-                     a.seg.nseg ? a.seg.tile_lead : nullptr};
+                     a.seg.nseg ? a.seg.tile_lead : nullptr, a.spread};
 }
 
 // Workgroups of a round kernel whose workgroups take `tile` states at a
@@ -3032,17 +3106,23 @@ hipError_t launch_rounds_persistent(const RoundArgs &a, uint32_t rounds, hipStre
     return hipLaunchCooperativeKernel(kernel, dim3(grid), dim3(kBlock), args, 0, s);
 }
 
-void launch_column_flags(const uint32_t *cols, size_t N, uint32_t k, uint32_t ncols,
-                         const unsigned long long *single, uint32_t *diff, uint32_t *nonid,
-                         hipStream_t s) {
-    dim3 grid(grid_for(N, kDefaultGridCap / 4), ncols);
-    launch_kernel(k_col_flags, grid, dim3(kBlock), 0, s, cols, N, k, single, diff, nonid);
+void launch_letter_flags(const uint32_t *cols, size_t N, uint32_t k,
+                         const unsigned long long *single, uint32_t *letters, hipStream_t s) {
+    launch_kernel(k_letter_flags, dim3(grid_for(N, kDefaultGridCap / 4), k), dim3(kBlock), 0, s,
+                  cols, N, single, letters);
 }
 
-void launch_jump(uint32_t *cols, size_t N, uint32_t k, uint32_t level, uint32_t *diff,
-                 uint32_t *nonid, hipStream_t s) {
+void launch_level_flags(const uint32_t *cols, size_t N, uint32_t k, uint32_t levels,
+                        const unsigned long long *single, uint32_t *letters, uint32_t *nonid,
+                        hipStream_t s) {
+    launch_kernel(k_level_flags, dim3(grid_for(N, kDefaultGridCap / 4), k), dim3(kBlock), 0, s,
+                  cols, N, k, levels, single, letters, nonid);
+}
+
+void launch_jump(uint32_t *cols, size_t N, uint32_t k, uint32_t level, const uint32_t *letters,
+                 uint32_t *diff, uint32_t *nonid, hipStream_t s) {
     dim3 grid(grid_for(N, kDefaultGridCap), k);
-    launch_kernel(k_jump, grid, dim3(kBlock), 0, s, cols, N, k, level, diff, nonid);
+    launch_kernel(k_jump, grid, dim3(kBlock), 0, s, cols, N, k, level, letters, diff, nonid);
 }
 
 void launch_zero(const ZeroList &z, hipStream_t s) {
