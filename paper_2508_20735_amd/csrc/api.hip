@@ -210,6 +210,7 @@ struct Ctx {
     Buffer parts, tile_part, seg_words, batch_in, batch_out, tile_dead;
     Buffer small_jobs, small_results, small_ctl;  // batched small DFAs (one workgroup each)
     Buffer pb_tl, pb_src, pb_val, pb_off, pb_partials;  // edges bucketed by target slice
+    Buffer group_fill;  // grouping by buckets: counters and overflow flag
     Buffer direct_cnt;                // round counters of direct rounds
     Buffer segd_plan, segd_state, segd_table;  // batches, one launch per round
     uint32_t segd_epoch = 0;          // last epoch used in segd_table (0: cleared)
@@ -245,6 +246,7 @@ struct Ctx {
         uint32_t round;
         uint32_t bytes_per_state;
         uint32_t k_eff;
+        bool buckets;  // a kernel of the grouping by buckets
     };
     std::vector<Pending> pending;
     std::vector<hipEvent_t> evpool;
@@ -390,7 +392,7 @@ int join_caller(Ctx &c) {
 
 enum class Kern {
     Mark, Signature, Insert, SortGroup, RoundEnd, Pattern, Packed, LeaderElect, LeaderMove,
-    LeaderEnd, PbGather, SignaturePb, SegPattern, PackedPb
+    LeaderEnd, PbGather, SignaturePb, SegPattern, PackedPb, SignaturePart, GroupPart
 };
 
 int prof_event(Ctx &c, size_t &idx) {
@@ -418,8 +420,10 @@ uint32_t kern_bytes(Kern kind, uint32_t k_eff) {
     switch (kind) {
         case Kern::Signature: return 8 * k_eff + 4;
         case Kern::PbGather: return 4 * k_eff;
-        case Kern::SignaturePb: return 4 * k_eff + 4;
-        case Kern::Insert: return 4;
+        case Kern::SignaturePb:
+        case Kern::SignaturePart: return 4 * k_eff + 4;
+        case Kern::Insert:
+        case Kern::GroupPart: return 4;
         case Kern::Pattern:
         case Kern::Packed:
         case Kern::PackedPb:
@@ -444,6 +448,9 @@ const char *kern_name(Kern kind) {
         case Kern::SegPattern: return "k_seg_pattern";
         case Kern::PackedPb: return "k_packed_pb";
         case Kern::SignaturePb: return "k_signature_pb";
+        // (the two ways of the first table round go by the same names)
+        case Kern::SignaturePart: return "k_signature_pb";
+        case Kern::GroupPart: return "k_insert";
         default: return "k_leader_end";
     }
 }
@@ -465,6 +472,8 @@ int launch_kern(Ctx &c, Kern kind, const Args &a, uint32_t round) {
             case Kern::SegPattern: launch_seg_pattern(a, c.stream); break;
             case Kern::PackedPb: launch_packed_pb(a, c.stream); break;
             case Kern::SignaturePb: launch_signature_pb(a, c.stream); break;
+            case Kern::SignaturePart: launch_signature_part(a, c.stream); break;
+            case Kern::GroupPart: launch_group_part(a, c.stream); break;
             case Kern::Insert: launch_insert(a, c.stream); break;
             case Kern::SortGroup: launch_sort_group(a, c.stream); break;
             case Kern::RoundEnd: launch_round_end(a, c.stream); break;
@@ -483,15 +492,25 @@ int launch_kern(Ctx &c, Kern kind, const Args &a, uint32_t round) {
     if (timed) {
         DFA_TRY(prof_event(c, e1));
         HIP_TRY(hipEventRecord(c.evpool[e1], c.stream));
-        c.pending.push_back({kern_name(kind), e0, e1, round, kern_bytes(kind, a.k_eff), a.k_eff});
+        c.pending.push_back({kern_name(kind), e0, e1, round, kern_bytes(kind, a.k_eff), a.k_eff,
+                             kind == Kern::SignaturePart || kind == Kern::GroupPart});
     }
     return DFA_OK;
 }
 
-int launch_full_round(Ctx &c, const RoundArgs &a, uint32_t round) {
+int launch_full_round(Ctx &c, const RoundArgs &args, uint32_t round) {
+    RoundArgs a = args;
+    if (round != a.first_table_round) {  // buckets group that round only
+        a.pb.gbuckets = 0;
+        a.pb.gover = nullptr;
+    }
     DFA_TRY(launch_kern(c, Kern::Mark, a, round));
     if (a.pb.nb) {
         DFA_TRY(launch_kern(c, Kern::PbGather, a, round));
+        if (a.pb.gbuckets) {
+            DFA_TRY(launch_kern(c, Kern::SignaturePart, a, round));
+            DFA_TRY(launch_kern(c, Kern::GroupPart, a, round));
+        }
         DFA_TRY(launch_kern(c, Kern::SignaturePb, a, round));
     }
     DFA_TRY(launch_kern(c, Kern::Signature, a, round));
@@ -520,7 +539,12 @@ int prof_collect(Ctx &c, const RoundCtl &ctl) {
         const bool sig = std::strcmp(p.name, "k_signature") == 0;
         const bool pass = std::strcmp(p.name, "k_pb_gather") == 0 ||
                           std::strcmp(p.name, "k_signature_pb") == 0;
-        const bool did_work = !((sig && pb) || (pass && !pb));
+        // (and so do the two ways of grouping the first table round)
+        const bool part = ((ctl.part_rounds >> (p.round % 64)) & 1ull) != 0;
+        const bool grouping = std::strcmp(p.name, "k_signature_pb") == 0 ||
+                              std::strcmp(p.name, "k_insert") == 0;
+        const bool did_work =
+            !((sig && pb) || (pass && !pb) || (grouping && p.buckets != part));
         if (did_work && p.round < ctl.round && ctl.round - p.round <= kActiveHist) {
             const uint64_t refined = ctl.active_hist[p.round % kActiveHist];
             t.bytes += refined * p.bytes_per_state;
@@ -870,12 +894,45 @@ RoundArgs make_round_args(Ctx &c, const uint32_t *cols, size_t N, uint32_t k_eff
 // and init kernels).  With state_ids, a partition that ends in label ids
 // (a stable partition found by a label round) gets one more table round,
 // which keeps the partition and turns the labels into state ids.
+// Buckets for the grouping of the first table round: their entries lie in the
+// buffer of the signature rows, which that round does not write then.  A
+// context that cannot allocate keeps the table, and so does a server's lane
+// (its requests are admitted by the memory that the table takes) and a device
+// that is out of memory.
+size_t bucket_entries(size_t N, uint32_t &buckets, uint32_t &cap) {
+    buckets = static_cast<uint32_t>(next_pow2((N + kGroupMean - 1) / kGroupMean));
+    const size_t mean = (N + buckets - 1) / buckets;
+    cap = static_cast<uint32_t>(mean + mean / 4 + 512);
+    return static_cast<size_t>(buckets) * cap;
+}
+
+int make_buckets(Ctx &c, size_t N, uint32_t k_eff, PbArgs &pb) {
+    uint32_t buckets = 0, cap = 0;
+    const size_t entries = bucket_entries(N, buckets, cap);
+    if (c.arena.base || c.blocking_sync || buckets > kGroupMaxBuckets || cap >= kGroupSlots) return DFA_OK;
+    const size_t fill_bytes = (static_cast<size_t>(buckets) * kGroupStride + 2) * sizeof(uint32_t);
+    if (c.sig.ensure(entries * (k_eff + 2) * sizeof(uint32_t), "key buckets") != DFA_OK ||
+        c.group_fill.ensure(fill_bytes, "bucket counters") != DFA_OK) {
+        g_last_error.clear();
+        return c.sig.ensure(N * (k_eff + 1) * sizeof(uint32_t), "signatures");
+    }
+    ZeroList z{};
+    DFA_TRY(zero_add(z, c.group_fill, fill_bytes));
+    launch_zero(z, c.stream);
+    pb.gbuckets = buckets;
+    pb.gcap = cap;
+    pb.gent = c.sig.as<uint32_t>();
+    pb.gfill = c.group_fill.as<uint32_t>();
+    pb.gover = pb.gfill + static_cast<size_t>(buckets) * kGroupStride;
+    return DFA_OK;
+}
+
 // Buckets the edges by target slice when the refinement is large enough for
 // dense rounds to gain from gathering through LDS (dfa_tuning.slice_min_states)
 // and its signature width has a specialised kernel; pb.nb == 0 otherwise.
 // Not for segmented refinements, closure columns or the persistent loop.
 int build_slices(Ctx &c, const uint32_t *cols, size_t N, uint32_t k_eff, const dfa_options &o,
-                 bool excluded, PbArgs &pb) {
+                 bool excluded, bool group, PbArgs &pb) {
     pb = PbArgs{};
     const bool width = k_eff >= 1 && (k_eff <= 8 || k_eff == 16);
     if (excluded || !width || o.loop_mode == DFA_LOOP_PERSISTENT || !c.tune.slice_min_states ||
@@ -901,6 +958,7 @@ int build_slices(Ctx &c, const uint32_t *cols, size_t N, uint32_t k_eff, const d
     pb.bstart = pb.off + L;
     pb.nb = nb;
     pb.ntiles = ntiles;
+    if (group && (k_eff <= 4 || k_eff == 8)) DFA_TRY(make_buckets(c, N, k_eff, pb));
     uint32_t *csum = c.pb_partials.as<uint32_t>();
     launch_pb_build(cols, c.colmap.as<uint32_t>(), N, k_eff, pb, csum,
                     csum + pb_chunk_words(nb, ntiles), c.stream);
@@ -975,7 +1033,11 @@ int refine(Ctx &c, size_t N, uint32_t k, const dfa_options &o, uint32_t check_eq
     const uint32_t grouping = (o.algorithm == DFA_ALGO_SORT && !seg) ? 1u : 0u;
     // edges bucketed by target slice, for the dense rounds of the first chunk
     PbArgs pb{};
-    DFA_TRY(build_slices(c, cols, N, k_eff, o, seg != nullptr || resume || res.tc_used, pb));
+    const bool group_buckets = !grouping && !o.max_rounds && o.lds_stage == 2 &&
+                               !c.tune.hash_bits && c.tune.insert_pair &&
+                               c.tune.label_rounds == 2;
+    DFA_TRY(build_slices(c, cols, N, k_eff, o, seg != nullptr || resume || res.tc_used,
+                         group_buckets, pb));
     if (grouping) {
         const SortPlan pl = sort_plan(N);
         DFA_TRY(c.sort_keys0.ensure(N * sizeof(unsigned long long), "sort keys"));
@@ -1050,6 +1112,12 @@ int refine(Ctx &c, size_t N, uint32_t k, const dfa_options &o, uint32_t check_eq
             // the dense rounds come first (the first table rounds); later chunks
             // gather directly, so a long refinement pays nothing for the passes
             if (first_chunk) ra.pb = pb;
+            // (rounds replayed from a graph do not know their number)
+            if (mode == DFA_LOOP_GRAPH && !pipelined(c, chunk, mode) && !c.profiling) {
+                ra.pb.gbuckets = 0;
+                ra.pb.gover = nullptr;
+            }
+            ra.first_table_round = res.label_rounds;
             // the states that a closure refines sit together (the rest are
             // singletons by then)
             ra.spread = res.tc_used;
@@ -1374,7 +1442,9 @@ constexpr size_t kDirectMaxUnion = size_t(1) << 18;
 // loop driver, a chunk length, a round limit, a grouping variant or a kernel
 // tuning of the general rounds, or time its kernels, run those.
 bool direct_applies(const Ctx &c, size_t N, uint32_t k, bool is_union, const dfa_options &o) {
-    return N <= (is_union ? kDirectMaxUnion : kDirectMaxStates) && k <= kDirectMaxK && o.algorithm == DFA_ALGO_SIGNATURE &&
+    // (a tuning that wants slices below 2^20 states gets them)
+    const bool slices = c.tune.slice_min_states && N >= c.tune.slice_min_states;
+    return !slices && N <= (is_union ? kDirectMaxUnion : kDirectMaxStates) && k <= kDirectMaxK && o.algorithm == DFA_ALGO_SIGNATURE &&
            o.tc_mode != DFA_TC_ON &&
            (o.loop_mode == DFA_LOOP_GRAPH || o.loop_mode == DFA_LOOP_CHUNK) && !o.max_rounds &&
            !o.chunk && o.lds_stage == 2 && !c.tune.hash_bits && c.tune.label_rounds == 2 &&
@@ -2853,7 +2923,7 @@ void for_each_buffer(Ctx &c, F &&f) {
                       &c.sort_m, &c.serve_in, &c.small_jobs, &c.small_results,
                       &c.small_ctl, &c.pb_tl, &c.pb_src, &c.pb_val, &c.pb_off,
                       &c.pb_partials, &c.segpat_table, &c.segpat, &c.tile_dead,
-                      &c.direct_cnt, &c.segd_plan, &c.segd_state, &c.segd_table};
+                      &c.direct_cnt, &c.group_fill, &c.segd_plan, &c.segd_state, &c.segd_table};
     for (Buffer *b : bufs) f(*b);
 }
 

@@ -82,6 +82,7 @@ struct RoundCtl {
     uint32_t gain_hist[kActiveHist];    // blocks added by round r, at r % kActiveHist
     uint32_t last_claims;               // blocks formed among the refined states
     unsigned long long pb_rounds;       // bit r % 64: round r gathered through LDS slices
+    unsigned long long part_rounds;     // bit r % 64: round r grouped by buckets
 };
 
 // What the device tells the host while rounds run, in page-locked host memory:
@@ -201,7 +202,20 @@ struct PbArgs {
     uint32_t *off;     // ntiles * nb run starts in the edge list, tile-major
     uint32_t *bstart;  // nb + 1 bucket starts (the edge list is bucket-major)
     uint32_t nb, ntiles;  // nb == 0: gathers go directly to HBM
+    // the first table round grouped by buckets of the key hash (gbuckets > 0,
+    // a power of two): gcap entries of (k_eff + 2) words per bucket
+    // (key row, state), their numbers, and a flag set when one overflows
+    uint32_t gbuckets, gcap;
+    uint32_t *gent;
+    uint32_t *gfill;  // gbuckets words, kGroupStride apart
+    uint32_t *gover;
 };
+// Grouping by buckets: a bucket's entries are grouped by one workgroup in an
+// LDS table of kGroupSlots slots, so it holds on average at most kGroupMean.
+constexpr uint32_t kGroupSlots = 16384;
+constexpr uint32_t kGroupMean = 8192;
+constexpr uint32_t kGroupStride = 16;  // counters on 64-byte lines of their own
+constexpr uint32_t kGroupMaxBuckets = 1024;
 struct SortPlan {
     uint32_t sort_tiles, compact_tiles, hist_blocks, run_blocks;
     uint64_t hist_words, partial_words;
@@ -251,6 +265,7 @@ struct RoundArgs {
     uint16_t *segpat;
     uint32_t segpat_bits;
     HostProgress *host;  // nullptr: rounds end without telling the host
+    uint32_t first_table_round;  // the round that pb's buckets group
     uint32_t spread;     // 1: signature tiles go round the XCDs instead of in eighths
 };
 // Largest pattern width (bits) and table (words) of the segmented pattern
@@ -296,6 +311,12 @@ void launch_seg_round(const RoundArgs &a, hipStream_t s);
 // nothing in rounds that gather directly.
 void launch_pb_gather(const RoundArgs &a, hipStream_t s);
 void launch_signature_pb(const RoundArgs &a, hipStream_t s);
+// The first table round by buckets (pb.gbuckets > 0): the keys of every
+// source tile into the buckets of their hashes, then the buckets' grouping.
+// Both, or (a bucket overflowed) launch_signature_pb and launch_insert, which
+// follow, do the round's work.
+void launch_signature_part(const RoundArgs &a, hipStream_t s);
+void launch_group_part(const RoundArgs &a, hipStream_t s);
 // Round 1 (packed labels, k_eff <= 4) through the slices: the byte labels'
 // pass A, then the keys and the label count per source tile.
 void launch_packed_pb(const RoundArgs &a, hipStream_t s);

@@ -326,6 +326,7 @@ __global__ __launch_bounds__(kBlock) void k_direct_end(DirectArgs a, uint32_t la
     ctl->last_claims = 0;
     ctl->active_sum = active;
     ctl->pb_rounds = 0;
+    ctl->part_rounds = 0;
 }
 
 // The general path goes on after `rounds` rounds: the singleton bits, and as

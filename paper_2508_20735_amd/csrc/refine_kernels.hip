@@ -214,6 +214,14 @@ __device__ __forceinline__ bool pb_round(const PbArgs &pb, const RoundCtl &c, si
     return 4ull * c.prev_count < 3ull * N;
 }
 
+// Whether this round is one to group by buckets of the key hash instead of
+// the table: the first table round, its keys gathered through the slices.
+// `over` is the overflow flag (nullptr without buckets), which decides it once
+// the scatter pass has ended.
+__device__ __forceinline__ bool part_round(const uint32_t *over, const RoundCtl &c, size_t N) {
+    return over && !c.done && c.round == c.all_active_until && 4ull * c.prev_count < 3ull * N;
+}
+
 struct SigParams {
     const uint32_t *cols;
     const uint32_t *colmap;
@@ -1517,6 +1525,7 @@ __global__ __launch_bounds__(NT) void k_signature_pb(SigParams p) {
     __shared__ PbRunsLds<KC, NT> runs;
     if (!pb_round(p.pb, *p.ctl, p.N)) return;
     const PbArgs &pb = p.pb;
+    if (part_round(pb.gover, *p.ctl, p.N) && *pb.gover == 0) return;  // (grouped by buckets)
     const uint32_t r = p.ctl->round;
     const uint32_t *__restrict__ X = (r & 1u) ? p.blockB : p.blockA;
     uint32_t *__restrict__ Y = (r & 1u) ? p.blockA : p.blockB;
@@ -1577,6 +1586,198 @@ __global__ __launch_bounds__(NT) void k_signature_pb(SigParams p) {
     wg_add_spread<NT>(p.counters, 3, claims);
 }
 
+// ---------------------------------------------------------------- grouping by buckets
+//
+// The first table round groups every state, and its keys are spread: with the
+// hash table, each state probes a random slot of 2N, and each duplicate reads
+// its representative's row at random as well.  Here the keys are partitioned
+// by hash instead: the pass that assembles a tile's keys writes each state's
+// entry (key row, state) to the bucket of its hash, and one workgroup per
+// bucket groups the entries in an LDS table, comparing rows that it has just
+// streamed.  What stays random are the id and the block mark of a duplicate;
+// a state with a key of its own keeps the id that the first pass stored.
+//
+// A bucket's room is a quarter more than its mean.  Keys shared by a large
+// part of the states overflow it; the flag stops both passes, and the table
+// does the round.  Measured on MI355X (k_signature_pb and k_insert_lds2
+// before, both passes here): 2^22 random states, 4 letters, 330 -> 151 us; a
+// union of 2^23, every state with a twin, 774 -> 536 us.
+
+// Bucket and LDS hash of a key row.
+template <int KC>
+__device__ __forceinline__ uint64_t part_hash(const uint32_t *w) {
+    uint32_t a = 0x85EBCA6Bu, b = 0xC2B2AE35u;
+#pragma unroll
+    for (int j = 0; j <= KC; ++j) {
+        a = (a ^ w[j]) * 0x9E3779B1u;
+        a ^= a >> 15;
+        b = (b + w[j]) * 0x85EBCA77u;
+        b ^= b >> 13;
+    }
+    a *= 0x27D4EB2Fu;
+    b = (b ^ a) * 0x165667B1u;
+    return (static_cast<uint64_t>(a ^ (a >> 15)) << 32) | (b ^ (b >> 16));
+}
+
+template <int KC, uint32_t NT>
+__global__ __launch_bounds__(NT) void k_signature_part(SigParams p) {
+    __shared__ uint32_t key[kPbTile * KC];
+    __shared__ PbRunsLds<KC, NT> runs;
+    __shared__ uint32_t hist[kGroupMaxBuckets];
+    const PbArgs &pb = p.pb;
+    if (!part_round(pb.gover, *p.ctl, p.N)) return;
+    // (one thread reads the flag: the workgroup stays or goes as a whole)
+    const bool stopped =
+        threadIdx.x == 0 &&
+        __hip_atomic_load(pb.gover, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+    if (__syncthreads_or(stopped)) return;
+    const uint32_t r = p.ctl->round;
+    const uint32_t *__restrict__ X = (r & 1u) ? p.blockB : p.blockA;
+    uint32_t *__restrict__ Y = (r & 1u) ? p.blockA : p.blockB;
+    constexpr uint32_t W = KC + 1;
+    constexpr int EP = kPbTile / NT;
+    const uint32_t tx = threadIdx.x;
+    const uint32_t shift = 64 - (31 - __clz(pb.gbuckets));
+    for (uint32_t t = blockIdx.x; t < pb.ntiles; t += gridDim.x) {
+        const size_t base = static_cast<size_t>(t) * kPbTile;
+        uint32_t w0s[EP];
+#pragma unroll
+        for (int e = 0; e < EP; ++e) {
+            const size_t q = base + e * NT + tx;
+            w0s[e] = q < p.N ? X[q] : 0u;
+        }
+        for (uint32_t b = tx; b < pb.gbuckets; b += NT) hist[b] = 0;
+        pb_tile_keys<KC, NT>(pb, t, key, runs);  // (ends with a barrier)
+        uint32_t bucket[EP], rank[EP];
+#pragma unroll
+        for (int e = 0; e < EP; ++e) {
+            const uint32_t i = e * NT + tx;
+            const size_t q = base + i;
+            bucket[e] = 0;
+            rank[e] = ~0u;
+            const size_t first = q - lane_id();
+            const unsigned long long am = __ballot(q < p.N);
+            if (lane_id() == 0 && first < p.N) p.active[first >> 6] = am;
+            if (q >= p.N) continue;
+            Y[q] = static_cast<uint32_t>(q);
+            uint32_t w[W];
+            w[0] = w0s[e];
+#pragma unroll
+            for (int a = 0; a < KC; ++a) w[1 + a] = key[i * KC + a];
+            const uint64_t h = part_hash<KC>(w);
+            bucket[e] = pb.gbuckets > 1 ? static_cast<uint32_t>(h >> shift) : 0u;
+            rank[e] = atomicAdd(hist + bucket[e], 1u);
+        }
+        __syncthreads();
+        // the tile's place in every bucket (hist becomes the first position)
+        for (uint32_t b = tx; b < pb.gbuckets; b += NT) {
+            const uint32_t c = hist[b];
+            hist[b] = c ? atomicAdd(pb.gfill + b * kGroupStride, c) : 0u;
+        }
+        __syncthreads();
+        bool over = false;
+#pragma unroll
+        for (int e = 0; e < EP; ++e) {
+            if (rank[e] == ~0u) continue;
+            const uint32_t i = e * NT + tx;
+            const uint32_t at = hist[bucket[e]] + rank[e];
+            if (at >= pb.gcap) {
+                over = true;
+                continue;
+            }
+            uint32_t *ent = pb.gent + (static_cast<size_t>(bucket[e]) * pb.gcap + at) * (W + 1);
+            ent[0] = w0s[e];
+#pragma unroll
+            for (int a = 0; a < KC; ++a) ent[1 + a] = key[i * KC + a];
+            ent[W] = static_cast<uint32_t>(base + i);
+        }
+        // (another tile may read the flag while it is set: it then only does
+        // work that nobody uses)
+        const bool stop = __syncthreads_or(over) != 0;
+        if (stop) {
+            if (tx == 0)
+                __hip_atomic_store(pb.gover, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return;
+        }
+    }
+}
+
+constexpr uint32_t kGroupThreads = 1024;
+
+// One workgroup per bucket.
+template <int KC>
+__global__ __launch_bounds__(kGroupThreads) void k_group_part(SigParams p, uint32_t *multi) {
+    extern __shared__ uint32_t tab[];  // kGroupSlots: tag << 14 | entry
+    const PbArgs &pb = p.pb;
+    if (!part_round(pb.gover, *p.ctl, p.N) || *pb.gover) return;
+    const uint32_t r = p.ctl->round;
+    uint32_t *__restrict__ Y = (r & 1u) ? p.blockA : p.blockB;
+    constexpr uint32_t W = KC + 1;
+    const uint32_t tx = threadIdx.x;
+    const uint32_t n = pb.gfill[blockIdx.x * kGroupStride];  // (<= gcap < kGroupSlots)
+    const uint32_t *__restrict__ ent =
+        pb.gent + static_cast<size_t>(blockIdx.x) * pb.gcap * (W + 1);
+    for (uint32_t i = tx; i < kGroupSlots; i += kGroupThreads) tab[i] = ~0u;
+    if (blockIdx.x == 0 && tx == 0) const_cast<RoundCtl *>(p.ctl)->part_rounds |= 1ull << (r % 64);
+    __syncthreads();
+    uint32_t blocks = 0;
+    // two entries per thread at a time: both rows are loaded before either is
+    // looked up
+    constexpr int S = 2;
+    for (uint32_t i0 = 0; i0 < n; i0 += S * kGroupThreads) {
+        uint32_t w[S][W + 1];
+#pragma unroll
+        for (int u = 0; u < S; ++u) {
+            const uint32_t i = i0 + u * kGroupThreads + tx;
+            const uint32_t *e = ent + static_cast<size_t>(i < n ? i : 0u) * (W + 1);
+#pragma unroll
+            for (uint32_t j = 0; j <= W; ++j) w[u][j] = e[j];
+        }
+#pragma unroll
+        for (int u = 0; u < S; ++u) {
+            const uint32_t i = i0 + u * kGroupThreads + tx;
+            if (i >= n) continue;
+            // (the bucket took the top bits of the hash; the slot and tag
+            // take low ones)
+            const uint64_t h = part_hash<KC>(w[u]);
+            const uint32_t tag = static_cast<uint32_t>(h >> 14) & 0x3FFFFu;
+            const uint32_t want = (tag << 14) | i;
+            uint32_t s = static_cast<uint32_t>(h) & (kGroupSlots - 1);
+            for (;;) {
+                uint32_t e = __hip_atomic_load(tab + s, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_WORKGROUP);
+                if (e == ~0u) {
+                    e = atomicCAS(tab + s, ~0u, want);
+                    if (e == ~0u) {
+                        ++blocks;
+                        break;
+                    }
+                }
+                if ((e >> 14) == tag) {
+                    const uint32_t *o = ent + static_cast<size_t>(e & 0x3FFFu) * (W + 1);
+                    uint32_t v[W + 1];
+#pragma unroll
+                    for (uint32_t j = 0; j <= W; ++j) v[j] = o[j];
+                    bool eq = true;
+#pragma unroll
+                    for (uint32_t j = 0; j < W; ++j) eq &= v[j] == w[u][j];
+                    if (eq) {
+                        Y[w[u][W]] = v[W];
+                        multi[v[W]] = r + 1;
+                        break;
+                    }
+                }
+                s = (s + 1) & (kGroupSlots - 1);
+            }
+        }
+    }
+    // every state is refined, and counts as changed (the ids before were
+    // labels, not states): the next round is not incremental
+    wg_add_spread<kGroupThreads>(p.counters, 0, blocks);
+    wg_add_spread<kGroupThreads>(p.counters, 2, tx == 0 ? n : 0u);
+    wg_add_spread<kGroupThreads>(p.counters, 3, blocks);
+}
+
 // ---------------------------------------------------------------- grouping
 
 struct InsParams {
@@ -1596,7 +1797,13 @@ struct InsParams {
     unsigned long long *chg;
     unsigned long long *chg_sum;
     const uint8_t *tile_dead;  // segmented refinements: decided tiles (else null)
+    const uint32_t *gover;     // grouping by buckets: its overflow flag (else null)
 };
+
+// Whether the round has been grouped by buckets already.
+__device__ __forceinline__ bool grouped_already(const InsParams &p) {
+    return part_round(p.gover, *p.ctl, p.N) && *p.gover == 0;
+}
 
 // Stores a wave's changed-id mask and sets the summary bits of its groups
 // with a changed state (lane 0 only).
@@ -1622,7 +1829,7 @@ __device__ __forceinline__ bool stage_in_lds(const InsParams &p) {
 // [2] states whose id changed, [3] blocks formed by claims.  The signature
 // kernel adds the unrefined block holders and its own claims.
 __device__ __forceinline__ void insert_body(const InsParams &p) {
-    if (p.ctl->done || stage_in_lds(p)) return;
+    if (p.ctl->done || stage_in_lds(p) || grouped_already(p)) return;
     const uint32_t r = p.ctl->round;
     const uint32_t epoch = r % kEpochs + 1;
     const bool all = r <= p.ctl->all_active_until;
@@ -1681,7 +1888,7 @@ __device__ __forceinline__ void insert_lds_body(const InsParams &p) {
     __shared__ unsigned long long ltab[kLdsSlots];
     __shared__ uint32_t gid[kBlock];
     __shared__ uint32_t lsize[kBlock];
-    if (p.ctl->done || !stage_in_lds(p)) return;
+    if (p.ctl->done || !stage_in_lds(p) || grouped_already(p)) return;
     const uint32_t r = p.ctl->round;
     const uint32_t epoch = r % kEpochs + 1;
     const bool all = r <= p.ctl->all_active_until;
@@ -1806,7 +2013,7 @@ __device__ __forceinline__ void insert_lds2_body(const InsParams &p) {
     __shared__ unsigned long long ltab[kSlots2];
     __shared__ uint32_t gid[kTile];
     __shared__ uint32_t lsize[kTile];
-    if (p.ctl->done || !stage_in_lds(p)) return;
+    if (p.ctl->done || !stage_in_lds(p) || grouped_already(p)) return;
     const uint32_t r = p.ctl->round;
     const uint32_t epoch = r % kEpochs + 1;
     const bool all = r <= p.ctl->all_active_until;
@@ -2783,7 +2990,7 @@ InsParams ins_params(const RoundArgs &a) {
     return InsParams{a.sig,    a.hash,   a.N,     a.k_eff + 1, a.table,    a.table_cap - 1,
                      a.blockA, a.blockB, a.multi, a.active,    a.counters, a.ctl,
                      a.cached_probe, a.lds_stage, a.chg, a.chg_sum,
-                     a.seg.nseg ? a.seg.tile_dead : nullptr};
+                     a.seg.nseg ? a.seg.tile_dead : nullptr, a.pb.gover};
 }
 
 // Workgroups of the persistent loop: no more than fit on the device at once.
@@ -3003,6 +3210,36 @@ void launch_packed_pb(const RoundArgs &a, hipStream_t s) {
         default: break;  // packed labels only for k_eff <= 4
     }
     launch_kernel(k_count_labels, dim3(1024), dim3(kBlock), 0, s, sp);
+}
+
+void launch_signature_part(const RoundArgs &a, hipStream_t s) {
+    if (!a.pb.gbuckets) return;
+    const SigParams sp = sig_params(a);
+    constexpr uint32_t NT = kPbSigThreads;
+    const dim3 grid(a.pb.ntiles), block(NT);
+    switch (a.k_eff) {
+        case 1: launch_kernel(k_signature_part<1, NT>, grid, block, 0, s, sp); break;
+        case 2: launch_kernel(k_signature_part<2, NT>, grid, block, 0, s, sp); break;
+        case 3: launch_kernel(k_signature_part<3, NT>, grid, block, 0, s, sp); break;
+        case 4: launch_kernel(k_signature_part<4, NT>, grid, block, 0, s, sp); break;
+        case 8: launch_kernel(k_signature_part<8, NT>, grid, block, 0, s, sp); break;
+        default: break;  // the host makes buckets for these widths only
+    }
+}
+
+void launch_group_part(const RoundArgs &a, hipStream_t s) {
+    if (!a.pb.gbuckets) return;
+    const SigParams sp = sig_params(a);
+    const dim3 grid(a.pb.gbuckets), block(kGroupThreads);
+    constexpr uint32_t lds = kGroupSlots * 4;
+    switch (a.k_eff) {
+        case 1: launch_kernel(k_group_part<1>, grid, block, lds, s, sp, a.multi); break;
+        case 2: launch_kernel(k_group_part<2>, grid, block, lds, s, sp, a.multi); break;
+        case 3: launch_kernel(k_group_part<3>, grid, block, lds, s, sp, a.multi); break;
+        case 4: launch_kernel(k_group_part<4>, grid, block, lds, s, sp, a.multi); break;
+        case 8: launch_kernel(k_group_part<8>, grid, block, lds, s, sp, a.multi); break;
+        default: break;
+    }
 }
 
 void launch_signature_pb(const RoundArgs &a, hipStream_t s) {
