@@ -213,6 +213,7 @@ struct Ctx {
     Buffer group_fill;  // grouping by buckets: counters and overflow flag
     Buffer direct_cnt;                // round counters of direct rounds
     Buffer segd_plan, segd_state, segd_table;  // batches, one launch per round
+    Buffer staged_rows, staged_entries, staged_offs;  // batches, ids staged in LDS
     uint32_t segd_epoch = 0;          // last epoch used in segd_table (0: cleared)
     uint64_t segd_epoch_in = 0;       // the allocation it counts in
     Buffer segpat_table, segpat;  // round 0 of segmented refinements by acceptance patterns
@@ -2256,17 +2257,42 @@ int refine_batch_direct(Ctx &c, const std::vector<Part> &parts, uint32_t nseg, b
     for (const Part &p : parts) tiles64 += (static_cast<uint64_t>(p.n) + kBlock - 1) / kBlock;
     const uint32_t tiles = static_cast<uint32_t>(tiles64);
     const size_t N = static_cast<size_t>(tiles) * kBlock;
+    // staged rounds hold the ids of a part in LDS; a workgroup takes up to
+    // 8,192 states, fewer if the batch would not give every CU two of them
+    bool staged = kmax <= kStagedMaxK && N < (size_t(1) << 31);
+    for (const Part &p : parts) staged = staged && p.n <= kStagedWindow;
+    const uint32_t chunk_groups = static_cast<uint32_t>(
+        std::min<size_t>(4, std::max<size_t>(1, N / (512 * size_t(kStagedGroup)))));
+    const uint32_t chunk_states = chunk_groups * kStagedGroup;
+    uint32_t chunks = 0, buckets = 0;
+    auto buckets_of = [](uint64_t states) {
+        return static_cast<uint32_t>((states + kStagedMean - 1) / kStagedMean);
+    };
+    if (staged) {
+        for (size_t p = 0; p < nparts; ++p) {
+            chunks += (parts[p].n + chunk_states - 1) / chunk_states;
+            if (!pairs)
+                buckets += buckets_of(parts[p].n);
+            else if (p & 1u)
+                buckets += buckets_of(uint64_t(parts[p - 1].n) + parts[p].n);
+        }
+    }
     // the plan, built in page-locked memory and uploaded in one copy
     const size_t segs_at = nparts * sizeof(SegdPart);
-    const size_t tiles_at = segs_at + nseg * sizeof(SegdSeg);
+    const size_t chunks_at = segs_at + nseg * sizeof(SegdSeg);
+    const size_t buckets_at = chunks_at + chunks * sizeof(SegdChunk);
+    const size_t tiles_at = buckets_at + buckets * sizeof(SegdBucket);
     const size_t plan_bytes = tiles_at + tiles * sizeof(uint32_t);
     const size_t state_words = 9 * static_cast<size_t>(nseg);  // cnt, classes, done, changing, blocks, verdicts
     const size_t state_bytes = sizeof(SegdCtl) + state_words * sizeof(uint32_t);
     DFA_TRY(ensure_pinned_batch(c, std::max(plan_bytes, state_bytes)));
     SegdPart *hp = reinterpret_cast<SegdPart *>(c.pinned_batch);
     SegdSeg *hs = reinterpret_cast<SegdSeg *>(c.pinned_batch + segs_at);
+    SegdChunk *hc = reinterpret_cast<SegdChunk *>(c.pinned_batch + chunks_at);
+    SegdBucket *hb = reinterpret_cast<SegdBucket *>(c.pinned_batch + buckets_at);
     uint32_t *ht = reinterpret_cast<uint32_t *>(c.pinned_batch + tiles_at);
-    uint32_t tile = 0;
+    uint32_t tile = 0, max_n = 0, max_states = 0, runs = 0;
+    uint64_t row_words = 0;
     for (uint32_t p = 0; p < nparts; ++p) {
         const Part &v = parts[p];
         SegdPart &d = hp[p];
@@ -2280,21 +2306,41 @@ int refine_batch_direct(Ctx &c, const std::vector<Part> &parts, uint32_t nseg, b
                  (reinterpret_cast<uintptr_t>(v.delta) & 15u) == 0;
         d.pad = 0;
         d.out = v.out;
+        d.rows = row_words;
+        const uint32_t padded = (v.n + kBlock - 1) / kBlock * kBlock;
         const bool second = pairs && (p & 1u);
         SegdSeg &g = hs[v.seg];
         if (!second) {
             const uint64_t states = v.n + (pairs ? static_cast<uint64_t>(parts[p + 1].n) : 0);
-            const uint64_t cap = next_pow2(std::max<uint64_t>(2 * states, 64));
             g.table = slots;
-            g.mask = static_cast<uint32_t>(cap - 1);
             g.first_tile = tile;
             g.eq_a = d.off + v.start;
             g.eq_b = 0;
-            slots += cap;
+            g.offs = runs;
+            g.groups = 0;
+            if (staged) {
+                g.mask = buckets_of(states);
+                for (uint32_t i = 0; i < g.mask; ++i) *hb++ = SegdBucket{v.seg, i};
+                max_states = std::max(max_states, static_cast<uint32_t>(states));
+            } else {
+                const uint64_t cap = next_pow2(std::max<uint64_t>(2 * states, 64));
+                g.mask = static_cast<uint32_t>(cap - 1);
+                slots += cap;
+            }
         } else {
             g.eq_b = d.off + v.start;
         }
-        for (uint32_t t = (v.n + kBlock - 1) / kBlock; t > 0; --t) ht[tile++] = p;
+        if (staged) {
+            for (uint32_t q = 0; q < v.n; q += chunk_states)
+                *hc++ = SegdChunk{p, d.off + q, g.groups + q / kStagedGroup};
+            const uint32_t groups = (v.n + kStagedGroup - 1) / kStagedGroup;
+            g.groups += groups;
+            runs += groups * (g.mask + 1);
+            slots += static_cast<uint64_t>(padded) * staged_words(v.k);  // (entry words)
+            row_words += static_cast<uint64_t>(padded) * direct_width(v.k);
+            max_n = std::max(max_n, v.n);
+        }
+        for (uint32_t t = padded / kBlock; t > 0; --t) ht[tile++] = p;
     }
     DFA_TRY(c.segd_plan.ensure(plan_bytes, "batch plan"));
     DFA_TRY(c.segd_state.ensure(state_bytes, "segment state"));
@@ -2302,7 +2348,14 @@ int refine_batch_direct(Ctx &c, const std::vector<Part> &parts, uint32_t nseg, b
     DFA_TRY(c.blockB.ensure(N * sizeof(uint32_t), "blocks"));
     DFA_TRY(c.multi.ensure((N + 1) * sizeof(uint32_t), "block marks"));
     if (out_dev) DFA_TRY(c.canon.ensure(N * sizeof(uint32_t), "canonical ids"));
-    DFA_TRY(c.segd_table.ensure(slots * sizeof(unsigned long long), "segment tables"));
+    const size_t pattern_bytes = nseg * size_t(kStagedPatterns) * sizeof(uint32_t);
+    if (staged) {
+        DFA_TRY(c.staged_rows.ensure(row_words * sizeof(uint16_t), "rows"));
+        DFA_TRY(c.staged_entries.ensure(slots * sizeof(uint32_t), "key entries"));
+        DFA_TRY(c.staged_offs.ensure(pattern_bytes + runs * sizeof(uint16_t), "key runs"));
+    } else {
+        DFA_TRY(c.segd_table.ensure(slots * sizeof(unsigned long long), "segment tables"));
+    }
     HIP_TRY(hipMemcpyAsync(c.segd_plan.p, c.pinned_batch, plan_bytes, hipMemcpyHostToDevice,
                            c.stream));
     auto clear_table = [&c]() -> int {
@@ -2313,11 +2366,12 @@ int refine_batch_direct(Ctx &c, const std::vector<Part> &parts, uint32_t nseg, b
         c.segd_epoch_in = c.segd_table.allocation;
         return DFA_OK;
     };
-    if (c.segd_epoch_in != c.segd_table.allocation) DFA_TRY(clear_table());
+    if (!staged && c.segd_epoch_in != c.segd_table.allocation) DFA_TRY(clear_table());
     {
         ZeroList z{};
         DFA_TRY(zero_add(z, c.segd_state, state_bytes));
-        DFA_TRY(zero_add(z, c.multi, N * sizeof(uint32_t)));
+        DFA_TRY(zero_add(z, c.multi, N * (staged ? sizeof(uint8_t) : sizeof(uint32_t))));
+        if (staged) DFA_TRY(zero_add(z, c.staged_offs, pattern_bytes));
         if (out_dev) DFA_TRY(zero_add(z, c.canon, N * sizeof(uint32_t)));
         launch_zero(z, c.stream);
     }
@@ -2326,6 +2380,19 @@ int refine_batch_direct(Ctx &c, const std::vector<Part> &parts, uint32_t nseg, b
     a.parts = reinterpret_cast<const SegdPart *>(plan);
     a.segs = reinterpret_cast<const SegdSeg *>(plan + segs_at);
     a.tile_part = reinterpret_cast<const uint32_t *>(plan + tiles_at);
+    a.chunks = reinterpret_cast<const SegdChunk *>(plan + chunks_at);
+    a.buckets = reinterpret_cast<const SegdBucket *>(plan + buckets_at);
+    a.nchunks = chunks;
+    a.chunk_groups = chunk_groups;
+    a.nbuckets = buckets;
+    a.window = (max_n + 15) & ~15u;
+    a.max_n = max_n;
+    a.max_states = max_states;
+    a.rows = c.staged_rows.as<uint16_t>();
+    a.shared = c.multi.as<uint8_t>();
+    a.entries = c.staged_entries.as<uint32_t>();
+    a.patterns = c.staged_offs.as<uint32_t>();
+    a.offs = reinterpret_cast<uint16_t *>(c.staged_offs.as<uint8_t>() + pattern_bytes);
     a.tiles = tiles;
     a.nseg = nseg;
     a.pairs = pairs ? 1u : 0u;
@@ -2347,6 +2414,10 @@ int refine_batch_direct(Ctx &c, const std::vector<Part> &parts, uint32_t nseg, b
         uint32_t stop = launched + chunk;
         if (o.max_rounds) stop = std::min(stop, o.max_rounds);
         while (launched < stop) {
+            if (staged) {
+                launch_staged_round(a, launched++, c.stream);
+                continue;
+            }
             if (c.segd_epoch + 1 >= kSegdEpochs) DFA_TRY(clear_table());
             launch_segd_round(a, launched++, ++c.segd_epoch, kmax > 8, c.stream);
         }
@@ -2923,7 +2994,8 @@ void for_each_buffer(Ctx &c, F &&f) {
                       &c.sort_m, &c.serve_in, &c.small_jobs, &c.small_results,
                       &c.small_ctl, &c.pb_tl, &c.pb_src, &c.pb_val, &c.pb_off,
                       &c.pb_partials, &c.segpat_table, &c.segpat, &c.tile_dead,
-                      &c.direct_cnt, &c.group_fill, &c.segd_plan, &c.segd_state, &c.segd_table};
+                      &c.direct_cnt, &c.group_fill, &c.segd_plan, &c.segd_state, &c.segd_table,
+                      &c.staged_rows, &c.staged_entries, &c.staged_offs};
     for (Buffer *b : bufs) f(*b);
 }
 

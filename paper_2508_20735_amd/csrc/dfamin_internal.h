@@ -412,13 +412,35 @@ struct SegdPart {
     uint32_t wide;  // k = direct_width(k) is a multiple of 4, 16-byte aligned rows
     uint32_t pad;
     uint64_t out;   // offset of its block ids in the output
+    uint64_t rows;  // staged rounds: first word of its 16-bit rows
 };
 struct SegdSeg {
-    uint64_t table;       // first slot of its table
-    uint32_t mask;        // slots - 1 (a power of two, at least twice its states)
+    uint64_t table;       // first slot of its table; staged rounds: first word of its entries
+    uint32_t mask;        // slots - 1 (a power of two, at least twice its states); staged
+                          // rounds: its buckets
     uint32_t first_tile;
     uint32_t eq_a, eq_b;  // pairs: the start states in the union
+    uint32_t offs, groups;  // staged rounds: first run start, groups of states
 };
+// Staged rounds: a workgroup's states are `first` .. of part `part`, up to
+// SegdArgs::chunk_groups groups of them; `group` is the first one's number in
+// the segment.
+struct SegdChunk {
+    uint32_t part, first, group;
+};
+struct SegdBucket {
+    uint32_t seg, bucket;
+};
+constexpr uint32_t kStagedThreads = 1024;
+constexpr uint32_t kStagedGroup = 2048;       // states whose entries are sorted together
+constexpr uint32_t kStagedWindow = 1u << 16;  // ids that a workgroup holds in LDS
+constexpr uint32_t kStagedMaxK = 8;
+constexpr uint32_t kStagedPatterns = 2u << kStagedMaxK;
+constexpr uint32_t kStagedSlots = 12288;      // LDS slots that group a bucket
+constexpr uint32_t kStagedMean = kStagedSlots / 2;  // a bucket's share of the states
+constexpr uint32_t kStagedMaxBuckets = 32;
+// Words of an entry: the state and letters + 1 ids of 17 bits.
+constexpr uint32_t staged_words(uint32_t k) { return (17 * (k + 2) + 31) / 32; }
 constexpr uint32_t kSegdEpochs = 1u << 20;  // epoch 0 is the cleared table's
 constexpr uint32_t kSegdSpread = 16;        // counters of refined states
 constexpr uint32_t kSegdStride = 8;         // 8-byte words between two counters
@@ -431,6 +453,16 @@ struct SegdArgs {
     const SegdPart *parts;
     const SegdSeg *segs;
     const uint32_t *tile_part;  // part of each tile of kBlock states
+    // staged rounds: the work of both launches, the largest window staged (a
+    // multiple of 16), part and segment
+    const SegdChunk *chunks;
+    const SegdBucket *buckets;
+    uint32_t nchunks, chunk_groups, nbuckets, window, max_n, max_states;
+    uint16_t *rows;      // the parts' targets, direct_width(k) to a state
+    uint8_t *shared;     // block marks (multi's)
+    uint32_t *entries;
+    uint16_t *offs;      // run starts: per group and bucket, and the group's end
+    uint32_t *patterns;  // kStagedPatterns words per segment, zero before round 0
     uint32_t tiles, nseg, pairs;
     uint32_t *blockA, *blockB;  // round r reads A (even) or B (odd), writes the other
     uint32_t *multi;            // zero before round 0
@@ -446,6 +478,8 @@ struct SegdArgs {
 // wide_letters: some part has more than 8 letters (at most kDirectMaxK).
 void launch_segd_round(const SegdArgs &a, uint32_t r, uint32_t epoch, bool wide_letters,
                        hipStream_t s);
+// The same for parts of at most kStagedWindow states and kStagedMaxK letters.
+void launch_staged_round(const SegdArgs &a, uint32_t r, hipStream_t s);
 void launch_segd_decide(const SegdArgs &a, uint32_t r, bool last, hipStream_t s);
 // Canonical ids of every DFA (scratch_max: a zeroed word per state of the
 // union); verdicts of the pairs.
