@@ -208,7 +208,7 @@ struct Ctx {
     bool blocking_sync = false;
     hipEvent_t ev_sync = nullptr;
     Buffer parts, tile_part, seg_words, batch_in, batch_out, tile_dead;
-    Buffer small_jobs, small_results, small_ctl;  // batched small DFAs (one workgroup each)
+    Buffer small_jobs, small_ctl;  // batched small DFAs (one workgroup each)
     Buffer pb_tl, pb_src, pb_val, pb_off, pb_partials;  // edges bucketed by target slice
     Buffer group_fill;  // grouping by buckets: counters and overflow flag
     Buffer direct_cnt;                // round counters of direct rounds
@@ -223,6 +223,8 @@ struct Ctx {
     hipEvent_t ring_ev[2] = {nullptr, nullptr};
     bool ring_recorded[2] = {false, false};  // ring_ev[i] has been recorded
     size_t pinned_batch_cap = 0;
+    uint8_t *pinned_small = nullptr;  // results of batched small DFAs, stored by the kernel
+    size_t pinned_small_cap = 0;
     // chunk graphs, one per chunk length in use (automatic chunks grow
     // 4, 8, ..., 256 within one call), replaced round-robin
     static constexpr int kGraphSlots = 8;
@@ -2162,23 +2164,26 @@ void parallel_copies(const std::vector<CopyJob> &jobs) {
     parallel_for(cut.size() - 1, [&](size_t t) { run(cut[t], cut[t + 1]); });
 }
 
-int ensure_pinned_batch(Ctx &c, size_t bytes) {
-    if (c.pinned_batch && bytes <= c.pinned_batch_cap) return DFA_OK;
-    if (c.pinned_batch) {
+int ensure_pinned(Ctx &c, uint8_t *&p, size_t &cap, size_t bytes) {
+    if (p && bytes <= cap) return DFA_OK;
+    if (p) {
         HIP_TRY(stream_sync(c));
-        (void)hipHostFree(c.pinned_batch);
-        c.pinned_batch = nullptr;
-        c.pinned_batch_cap = 0;
+        (void)hipHostFree(p);
+        p = nullptr;
+        cap = 0;
     }
-    const size_t want = std::max<size_t>(bytes, 1 << 20);
-    if (hipHostMalloc(reinterpret_cast<void **>(&c.pinned_batch), want, hipHostMallocDefault) !=
-        hipSuccess) {
+    const size_t want = std::max<size_t>(bytes, 64 << 10);
+    if (hipHostMalloc(reinterpret_cast<void **>(&p), want, hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
-        c.pinned_batch = nullptr;
+        p = nullptr;
         return fail(DFA_ENOMEM, "pinned host allocation of %zu bytes failed", want);
     }
-    c.pinned_batch_cap = want;
+    cap = want;
     return DFA_OK;
+}
+
+int ensure_pinned_batch(Ctx &c, size_t bytes) {
+    return ensure_pinned(c, c.pinned_batch, c.pinned_batch_cap, std::max<size_t>(bytes, 1 << 20));
 }
 
 // parts (host vector, device pointers inside) -> device SegArgs.
@@ -2601,37 +2606,43 @@ int launch_small_jobs(Ctx &c, std::vector<SmallJob> &jobs, uint32_t slots, uint3
     std::sort(jobs.begin(), jobs.end(), [](const SmallJob &x, const SmallJob &y) {
         return x.na + x.nb > y.na + y.nb;
     });
-    const uint32_t nmax = jobs.front().na + jobs.front().nb;
-    const uint32_t lds = small_refine_lds_bytes(nmax);
-    int cus = 0;
+    // LDS for every job with its transitions, as far as a workgroup can have it
+    uint32_t lds = 0;
+    int cus = 0, limit = 0;
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c.device));
+    HIP_TRY(hipDeviceGetAttribute(&limit, hipDeviceAttributeMaxSharedMemoryPerBlock, c.device));
+    for (const SmallJob &j : jobs) {
+        const uint32_t n = j.na + j.nb, ids = small_refine_lds_bytes(n);
+        lds = std::max(lds, ids);
+        const uint32_t all = ids + small_rows_lds_bytes(n, j.k);
+        if (static_cast<int>(all) + 256 <= limit) lds = std::max(lds, all);
+    }
     const int fit = small_refine_max_groups(lds, cus);
     if (fit <= 0) return fail(DFA_EDEVICE, "no workgroup of %u LDS bytes fits the device", lds);
     const uint32_t groups = std::min<uint32_t>(static_cast<uint32_t>(jobs.size()),
                                                static_cast<uint32_t>(fit));
     DFA_TRY(c.small_jobs.ensure(jobs.size() * sizeof(SmallJob), "small jobs"));
-    DFA_TRY(c.small_results.ensure(static_cast<size_t>(slots) * sizeof(SmallResult),
-                                   "small results"));
-    DFA_TRY(c.small_ctl.ensure(2 * sizeof(uint32_t), "small job counter"));
+    DFA_TRY(c.small_ctl.ensure(sizeof(uint32_t), "small job counter"));
+    // (the kernel stores the results and the target check into host memory)
+    DFA_TRY(ensure_pinned(c, c.pinned_small, c.pinned_small_cap,
+                          static_cast<size_t>(slots) * sizeof(SmallResult) + sizeof(uint32_t)));
+    SmallResult *results = reinterpret_cast<SmallResult *>(c.pinned_small);
+    uint32_t *err = reinterpret_cast<uint32_t *>(results + slots);
     HIP_TRY(hipMemcpyAsync(c.small_jobs.p, jobs.data(), jobs.size() * sizeof(SmallJob),
                            hipMemcpyHostToDevice, c.stream));
-    uint32_t *ctl = c.small_ctl.as<uint32_t>();
     launch_small_refine(c.small_jobs.as<SmallJob>(), static_cast<uint32_t>(jobs.size()), groups,
-                        lds, ctl, out_dev, c.small_results.as<SmallResult>(), max_rounds, ctl + 1,
+                        lds, c.small_ctl.as<uint32_t>(), out_dev, results, max_rounds, err,
                         c.stream);
     HIP_TRY(hipGetLastError());
     return DFA_OK;
 }
 
 // After the stream has been synchronised: the small jobs' results (indexed
-// by DFA / pair) and their target check.
-int finish_small_jobs(Ctx &c, uint32_t slots, std::vector<SmallResult> &res) {
-    res.resize(slots);
-    HIP_TRY(hipMemcpy(res.data(), c.small_results.p, slots * sizeof(SmallResult),
-                      hipMemcpyDeviceToHost));
-    uint32_t err = 0;
-    HIP_TRY(hipMemcpy(&err, c.small_ctl.as<uint32_t>() + 1, sizeof err, hipMemcpyDeviceToHost));
-    if (err) return fail(DFA_EINVAL, "a transition target is >= n");
+// by DFA / pair), or the failure of their target check.
+int finish_small_jobs(Ctx &c, uint32_t slots, const SmallResult *&res) {
+    res = reinterpret_cast<const SmallResult *>(c.pinned_small);
+    if (*reinterpret_cast<const uint32_t *>(res + slots))
+        return fail(DFA_EINVAL, "a transition target is >= n");
     return DFA_OK;
 }
 
@@ -2688,7 +2699,7 @@ int minimise_batch_impl(Ctx &c, uint32_t count, const dfa_view *views, uint32_t 
         HIP_TRY(hipEventRecord(c.ev_stop, c.stream));
         HIP_TRY(stream_sync(c));
     }
-    std::vector<SmallResult> sres;
+    const SmallResult *sres = nullptr;
     if (!small.empty()) DFA_TRY(finish_small_jobs(c, count, sres));
     uint64_t transitions = 0, small_bytes = 0;
     uint32_t joint_rounds = r.rounds;
@@ -2778,7 +2789,7 @@ int equivalent_batch_impl(Ctx &c, uint32_t count, const dfa_view *a, const dfa_v
         HIP_TRY(hipEventRecord(c.ev_stop, c.stream));
         HIP_TRY(stream_sync(c));
     }
-    std::vector<SmallResult> sres;
+    const SmallResult *sres = nullptr;
     if (!small.empty()) DFA_TRY(finish_small_jobs(c, count, sres));
     uint64_t transitions = 0, small_bytes = 0;
     uint32_t joint_rounds = r.rounds;
@@ -2991,8 +3002,7 @@ void for_each_buffer(Ctx &c, F &&f) {
                       &c.reach_qb, &c.reach_dense, &c.reach_orig, &c.sub_delta,
                       &c.sub_acc, &c.sub_block, &c.sort_keys0, &c.sort_keys1, &c.sort_vals0,
                       &c.sort_vals1, &c.sort_hist, &c.sort_partials, &c.sort_runhead,
-                      &c.sort_m, &c.serve_in, &c.small_jobs, &c.small_results,
-                      &c.small_ctl, &c.pb_tl, &c.pb_src, &c.pb_val, &c.pb_off,
+                      &c.sort_m, &c.serve_in, &c.small_jobs, &c.small_ctl, &c.pb_tl, &c.pb_src, &c.pb_val, &c.pb_off,
                       &c.pb_partials, &c.segpat_table, &c.segpat, &c.tile_dead,
                       &c.direct_cnt, &c.group_fill, &c.segd_plan, &c.segd_state, &c.segd_table,
                       &c.staged_rows, &c.staged_entries, &c.staged_offs};
@@ -3028,6 +3038,7 @@ void release_ctx(Ctx &c) {
     if (c.host_progress) (void)hipHostFree(c.host_progress);
     c.host_progress = nullptr;
     if (c.pinned_batch) (void)hipHostFree(c.pinned_batch);
+    if (c.pinned_small) (void)hipHostFree(c.pinned_small);
     for (int i = 0; i < 2; ++i) {
         if (c.ring[i]) (void)hipHostFree(c.ring[i]);
         if (c.ring_ev[i]) (void)hipEventDestroy(c.ring_ev[i]);
@@ -3041,6 +3052,8 @@ void release_ctx(Ctx &c) {
     c.pinned = nullptr;
     c.pinned_batch = nullptr;
     c.pinned_batch_cap = 0;
+    c.pinned_small = nullptr;
+    c.pinned_small_cap = 0;
     c.stream = nullptr;
     c.inited = false;
 }

@@ -5,11 +5,15 @@
 // Section 3.3 (Algorithm 4: signature = own block id and the successors'
 // block ids; equal signatures form the next blocks; stop when the block
 // count does not grow) on the device.  Block ids and the grouping table sit
-// in LDS, so every successor-id gather and every probe is an LDS access;
-// rounds are separated by workgroup barriers, with no launch and no host
-// round trip per round.  The transition rows are read from the caller's
-// row-major arrays (L2-resident for DFAs of this size).  Workgroups take jobs
-// from a counter, largest first.
+// in LDS, and the transitions too where they fit (16 bits a target), so
+// every access of a round is an LDS access; rounds are separated by workgroup
+// barriers, with no launch and no host round trip per round.  Workgroups take
+// jobs from a counter, largest first.
+//
+// Bound by the longest job, a chain of rounds that each wait for LDS.  1,024
+// threads and transitions in LDS, instead of 256 that read them from the L2,
+// measured on MI355X: 589 DFAs of 64 to 4,096 states 198 -> 59 us, 272 pairs
+// 550 -> 152 us.
 //
 // Ids inside a round are the index of the state that first claimed its
 // signature's slot; the final ids are made canonical (smallest member) in
@@ -21,78 +25,178 @@
 namespace dfamin {
 namespace {
 
-constexpr uint32_t kEmptySlot = 0xFFFFFFFFu;
+constexpr uint32_t kEpochBits = 4;
+constexpr uint32_t kRoundsPerClear = (1u << kEpochBits) - 1;  // epochs 1 .. 15
 
-__device__ __forceinline__ uint32_t small_table_slots(uint32_t n) {
+__host__ __device__ __forceinline__ uint32_t small_table_slots(uint32_t n) {
     uint32_t t = 64;
     while (t < 2 * n) t <<= 1;
     return t;
 }
 
-// Local state i of a job: its row and the offset of its targets.
-struct JobView {
-    const uint32_t *da, *db;
-    const uint8_t *aa, *ab;
-    uint32_t na, n, k;
-    __device__ __forceinline__ const uint32_t *row(uint32_t i) const {
-        return i < na ? da + static_cast<size_t>(i) * k : db + static_cast<size_t>(i - na) * k;
+template <int KC>
+struct alignas(2 * KC) SmallRow {
+    uint16_t t[KC];
+};
+
+// The transitions of a job's states, numbered in the union: in LDS, or read
+// from the caller's arrays.  A target outside its DFA becomes the DFA's state
+// 0 and sets `bad` (the call then fails; no access leaves the job's arrays);
+// with fewer letters than KC the first one fills up.
+template <int KC>
+struct SmallRows {
+    const SmallJob &J;
+    const SmallRow<KC> *staged;  // nullptr: not in LDS
+
+    __device__ __forceinline__ SmallRow<KC> load(uint32_t i, bool &bad) const {
+        const bool in_b = i >= J.na;
+        const uint32_t off = in_b ? J.na : 0u, lim = in_b ? J.nb : J.na;
+        const uint32_t *r = (in_b ? J.delta_b : J.delta_a) + static_cast<size_t>(i - off) * J.k;
+        uint32_t t[KC];
+#pragma unroll
+        for (int j = 0; j < KC; ++j) t[j] = r[j < static_cast<int>(J.k) ? j : 0];
+        SmallRow<KC> row;
+#pragma unroll
+        for (int j = 0; j < KC; ++j) {
+            const bool out = t[j] >= lim;
+            bad |= out;
+            row.t[j] = static_cast<uint16_t>(off + (out ? 0u : t[j]));
+        }
+        return row;
     }
-    __device__ __forceinline__ uint32_t base(uint32_t i) const { return i < na ? 0u : na; }
-    __device__ __forceinline__ bool accepting(uint32_t i) const {
-        return (i < na ? aa[i] : ab[i - na]) != 0;
+    __device__ __forceinline__ SmallRow<KC> operator[](uint32_t i) const {
+        bool bad = false;
+        return staged ? staged[i] : load(i, bad);
     }
 };
 
-// Signature of local state i from the ids in `cur` (LDS): w0 and w[0..k).
-// A target outside its DFA sets `bad` and reads state 0 of that DFA instead
-// (the call then fails; no access leaves the job's arrays).
-__device__ __forceinline__ void small_key(const JobView &v, const uint16_t *cur, uint32_t i,
-                                          uint32_t &w0, uint32_t *w, bool &bad) {
-    const uint32_t *r = v.row(i);
-    const uint32_t b = v.base(i);
-    const uint32_t lim = i < v.na ? v.na : v.n - v.na;
-    w0 = cur[i];
-    uint32_t t[kSmallMaxK];
-#pragma unroll
-    for (uint32_t a = 0; a < kSmallMaxK; ++a)
-        if (a < v.k) t[a] = r[a];
-#pragma unroll
-    for (uint32_t a = 0; a < kSmallMaxK; ++a)
-        if (a < v.k) {
-            if (t[a] >= lim) {
-                bad = true;
-                t[a] = 0;
-            }
-            w[a] = cur[b + t[a]];
-        }
-}
-
-// Whether local state j's signature is (w0, w).  j already passed through
-// small_key in this round, so its targets are in range or `bad` is set;
-// they are clamped the same way here.
-__device__ __forceinline__ bool small_key_equal(const JobView &v, const uint16_t *cur, uint32_t j,
-                                                uint32_t w0, const uint32_t *w) {
-    if (cur[j] != w0) return false;
-    const uint32_t *r = v.row(j);
-    const uint32_t b = v.base(j);
-    const uint32_t lim = j < v.na ? v.na : v.n - v.na;
-    for (uint32_t a = 0; a < v.k; ++a) {
-        const uint32_t t = r[a];
-        if (cur[b + (t < lim ? t : 0u)] != w[a]) return false;
+template <int KC>
+__device__ __forceinline__ void small_job(const SmallJob &J, uint8_t *lds, uint32_t lds_bytes,
+                                          uint32_t *claims, uint32_t max_rounds,
+                                          uint32_t *out_blocks, SmallResult *results,
+                                          uint32_t *err) {
+    constexpr uint32_t NT = kSmallThreads;
+    const uint32_t tx = threadIdx.x, n = J.na + J.nb, T = small_table_slots(n);
+    // LDS: table (T words), two id arrays of n halves, the rows
+    uint32_t *table = reinterpret_cast<uint32_t *>(lds);
+    const uint32_t halves = (n + 7) & ~7u;
+    uint16_t *ida = reinterpret_cast<uint16_t *>(table + T);
+    uint16_t *idb = ida + halves;
+    SmallRow<KC> *rows = reinterpret_cast<SmallRow<KC> *>(idb + halves);
+    const bool staged = 4 * T + 4 * halves + n * sizeof(SmallRow<KC>) <= lds_bytes;
+    const SmallRows<KC> R{J, staged ? rows : nullptr};
+    bool bad = false, acc = false, rej = false;
+    for (uint32_t i = tx; i < n; i += NT) {
+        const SmallRow<KC> row = R.load(i, bad);
+        if (staged) rows[i] = row;
+        const bool f = (i < J.na ? J.acc_a[i] : J.acc_b[i - J.na]) != 0;
+        ida[i] = f ? 1 : 0;
+        acc |= f;
+        rej |= !f;
     }
-    return true;
-}
-
-__device__ __forceinline__ uint32_t wg_sum(uint32_t v, uint32_t *red) {
+    for (uint32_t s = tx; s < T; s += NT) table[s] = 0;
+    if (tx == 0) claims[0] = claims[1] = 0;
+    uint32_t prev = (__syncthreads_or(acc) ? 1u : 0u) + (__syncthreads_or(rej) ? 1u : 0u);
+    if (__syncthreads_or(bad) && tx == 0) *err = 1u;
+    uint16_t *cur = ida, *nxt = idb;
+    uint32_t round = 0, changing = 0, limit = 0;
+    for (;;) {
+        // entry = (epoch:4 | tag:12 | representative:16); entries of older
+        // epochs are empty, and the table is cleared when the epochs run out
+        if (round && round % kRoundsPerClear == 0) {
+            for (uint32_t s = tx; s < T; s += NT) table[s] = 0;
+            __syncthreads();
+        }
+        const uint32_t epoch = round % kRoundsPerClear + 1;
+        uint32_t mine = 0;
+        for (uint32_t i = tx; i < n; i += NT) {
+            const SmallRow<KC> row = R[i];
+            const uint32_t w0 = cur[i];
+            uint32_t w[KC];
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-    __syncthreads();
-    if (lane_id() == 0) red[threadIdx.x / 64] = v;
-    __syncthreads();
-    uint32_t s = 0;
+            for (int j = 0; j < KC; ++j) w[j] = cur[row.t[j]];
+            uint64_t h = mix_step(kHashSeed, w0);
 #pragma unroll
-    for (uint32_t w = 0; w < kSmallThreads / 64; ++w) s += red[w];
-    return s;
+            for (int j = 0; j < KC; ++j) h = mix_step(h, w[j]);
+            h = mix_final(h);
+            const uint32_t tag = (epoch << 12) | static_cast<uint32_t>(h >> 52);
+            const uint32_t want = (tag << 16) | i;
+            uint32_t s = static_cast<uint32_t>(h) & (T - 1);
+            uint32_t id = i;
+            uint32_t e =
+                __hip_atomic_load(table + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            // (at least half of the slots stay empty: the probe ends)
+            for (;;) {
+                if ((e >> (32 - kEpochBits)) != epoch) {
+                    const uint32_t was = atomicCAS(table + s, e, want);
+                    if (was == e) {
+                        ++mine;
+                        break;
+                    }
+                    e = was;
+                    continue;
+                }
+                if ((e >> 16) == tag) {
+                    const uint32_t o = e & 0xFFFFu;
+                    const SmallRow<KC> ro = R[o];
+                    bool eq = cur[o] == w0;
+#pragma unroll
+                    for (int j = 0; j < KC; ++j) eq &= cur[ro.t[j]] == w[j];
+                    if (eq) {
+                        id = o;
+                        break;
+                    }
+                }
+                s = (s + 1) & (T - 1);
+                e = __hip_atomic_load(table + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+            nxt[i] = static_cast<uint16_t>(id);
+        }
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) mine += __shfl_xor(mine, d, 64);
+        if (lane_id() == 0 && mine) atomicAdd(claims + (round & 1u), mine);
+        __syncthreads();  // ids and count of the round
+        const uint32_t count = claims[round & 1u];
+        // the next round's counter: last read before the barrier of this
+        // round, next added to after the barrier below
+        if (tx == 0) claims[(round + 1) & 1u] = 0;
+        __syncthreads();
+        ++round;
+        uint16_t *sw = cur;
+        cur = nxt;
+        nxt = sw;
+        // stable: the same partition as before, with state ids
+        if (count == prev) break;
+        prev = count;
+        ++changing;
+        // a pair is decided once its start states are separated (the
+        // refinement never merges them again)
+        if (J.nb && cur[J.start_a] != cur[J.na + J.start_b]) break;
+        if (max_rounds && round >= max_rounds) {
+            limit = 1;
+            break;
+        }
+    }
+    if (J.nb == 0) {
+        // canonical ids (smallest member) in the table's words
+        uint32_t *minof = table;
+        for (uint32_t i = tx; i < n; i += NT) minof[i] = ~0u;
+        __syncthreads();
+        for (uint32_t i = tx; i < n; i += NT) atomicMin(minof + cur[i], i);
+        __syncthreads();
+        uint32_t *out = out_blocks + J.out;
+        for (uint32_t i = tx; i < n; i += NT) out[i] = minof[cur[i]];
+    }
+    if (tx == 0) {
+        SmallResult r;
+        r.num_blocks = prev;
+        r.rounds = round;
+        r.changing = changing;
+        r.verdict = J.nb ? (cur[J.start_a] == cur[J.na + J.start_b] ? 1u : 0u) : 0u;
+        r.limit = limit;
+        results[J.index] = r;
+    }
+    __syncthreads();
 }
 
 __global__ __launch_bounds__(kSmallThreads) void k_small_refine(const SmallJob *__restrict__ jobs,
@@ -100,118 +204,25 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_refine(const SmallJob *
                                                                 uint32_t *out_blocks,
                                                                 SmallResult *results,
                                                                 uint32_t max_rounds,
-                                                                uint32_t *err) {
+                                                                uint32_t *err,
+                                                                uint32_t lds_bytes) {
     extern __shared__ __align__(16) uint8_t lds[];
-    __shared__ uint32_t red[kSmallThreads / 64];
-    __shared__ uint32_t job_id;
-    const uint32_t tx = threadIdx.x;
+    __shared__ uint32_t job_id, claims[2];
     for (;;) {
-        if (tx == 0) job_id = atomicAdd(next_job, 1u);
+        if (threadIdx.x == 0) job_id = atomicAdd(next_job, 1u);
         __syncthreads();
         const uint32_t j = job_id;
         __syncthreads();  // every thread has read job_id before it changes
         if (j >= njobs) return;
         const SmallJob J = jobs[j];
-        const JobView v{J.delta_a, J.delta_b, J.acc_a, J.acc_b, J.na, J.na + J.nb, J.k};
-        const uint32_t n = v.n;
-        const uint32_t T = small_table_slots(n);
-        // LDS: table (T words), then two id arrays of n halves
-        uint32_t *table = reinterpret_cast<uint32_t *>(lds);
-        uint16_t *ida = reinterpret_cast<uint16_t *>(table + T);
-        uint16_t *idb = ida + ((n + 1) & ~1u);
-        // initial partition {F, Q \ F}: labels 1 / 0
-        uint32_t has_acc = 0, has_rej = 0;
-        for (uint32_t i = tx; i < n; i += kSmallThreads) {
-            const bool f = v.accepting(i);
-            ida[i] = f ? 1 : 0;
-            has_acc |= f ? 1u : 0u;
-            has_rej |= f ? 0u : 1u;
-        }
-        uint32_t prev = (wg_sum(has_acc, red) ? 1u : 0u);
-        prev += (wg_sum(has_rej, red) ? 1u : 0u);
-        uint16_t *cur = ida, *nxt = idb;
-        uint32_t round = 0, changing = 0, limit = 0;
-        bool bad = false;
-        for (;;) {
-            for (uint32_t s = tx; s < T; s += kSmallThreads) table[s] = kEmptySlot;
-            __syncthreads();
-            uint32_t claims = 0;
-            for (uint32_t i = tx; i < n; i += kSmallThreads) {
-                uint32_t w0, w[kSmallMaxK];
-                small_key(v, cur, i, w0, w, bad);
-                uint64_t h = mix_step(kHashSeed, w0);
-#pragma unroll
-                for (uint32_t a = 0; a < kSmallMaxK; ++a)
-                    if (a < v.k) h = mix_step(h, w[a]);
-                h = mix_final(h);
-                const uint32_t tag = static_cast<uint32_t>(h >> 48);
-                const uint32_t want = (tag << 16) | i;
-                uint32_t s = static_cast<uint32_t>(h) & (T - 1);
-                uint32_t id;
-                for (;;) {
-                    uint32_t e = __hip_atomic_load(table + s, __ATOMIC_RELAXED,
-                                                   __HIP_MEMORY_SCOPE_WORKGROUP);
-                    if (e == kEmptySlot) {
-                        const uint32_t prevs = atomicCAS(table + s, kEmptySlot, want);
-                        if (prevs == kEmptySlot) {
-                            id = i;
-                            ++claims;
-                            break;
-                        }
-                        e = prevs;
-                    }
-                    if ((e >> 16) == tag && small_key_equal(v, cur, e & 0xFFFFu, w0, w)) {
-                        id = e & 0xFFFFu;
-                        break;
-                    }
-                    s = (s + 1) & (T - 1);
-                }
-                nxt[i] = static_cast<uint16_t>(id);
-            }
-            const uint32_t count = wg_sum(claims, red);  // (its barriers order nxt too)
-            ++round;
-            // stable: nxt holds the same partition as cur, with state ids
-            if (count == prev) break;
-            prev = count;
-            ++changing;
-            uint16_t *t = cur;
-            cur = nxt;
-            nxt = t;
-            // a pair is decided once its start states are separated (the
-            // refinement never merges them again)
-            if (J.nb && cur[J.start_a] != cur[J.na + J.start_b]) {
-                nxt = cur;
-                break;
-            }
-            if (max_rounds && round >= max_rounds) {
-                limit = 1;
-                nxt = cur;  // the last round's ids
-                break;
-            }
-        }
-        if (__syncthreads_or(bad) && tx == 0) *err = 1u;
-        // canonical ids (smallest member) in the table's words; the ids in
-        // nxt are state indices (< n)
-        const uint16_t *fin = nxt;
-        uint32_t *minof = table;
-        for (uint32_t i = tx; i < n; i += kSmallThreads) minof[i] = kEmptySlot;
-        __syncthreads();
-        for (uint32_t i = tx; i < n; i += kSmallThreads) atomicMin(minof + fin[i], i);
-        __syncthreads();
-        if (J.nb == 0) {
-            uint32_t *out = out_blocks + J.out;
-            for (uint32_t i = tx; i < n; i += kSmallThreads) out[i] = minof[fin[i]];
-        }
-        if (tx == 0) {
-            SmallResult r;
-            r.num_blocks = prev;
-            r.rounds = round;
-            r.changing = changing;
-            r.verdict = J.nb ? (fin[J.start_a] == fin[J.na + J.start_b] ? 1u : 0u) : 0u;
-            r.limit = limit;
-            results[J.index] = r;
-        }
-        __syncthreads();
+        if (J.k <= 2)
+            small_job<2>(J, lds, lds_bytes, claims, max_rounds, out_blocks, results, err);
+        else if (J.k <= 4)
+            small_job<4>(J, lds, lds_bytes, claims, max_rounds, out_blocks, results, err);
+        else if (J.k <= 8)
+            small_job<8>(J, lds, lds_bytes, claims, max_rounds, out_blocks, results, err);
+        else
+            small_job<16>(J, lds, lds_bytes, claims, max_rounds, out_blocks, results, err);
     }
 }
 
@@ -225,9 +236,11 @@ __global__ void k_small_counter_reset(uint32_t *next_job, uint32_t *err) {
 }  // namespace
 
 uint32_t small_refine_lds_bytes(uint32_t n) {
-    uint32_t t = 64;
-    while (t < 2 * n) t <<= 1;
-    return t * 4u + 2u * ((n + 1) & ~1u) * 2u;
+    return small_table_slots(n) * 4u + 2u * ((n + 7) & ~7u) * 2u;
+}
+
+uint32_t small_rows_lds_bytes(uint32_t n, uint32_t k) {
+    return n * 2u * (k <= 2 ? 2u : k <= 4 ? 4u : k <= 8 ? 8u : 16u);
 }
 
 int small_refine_max_groups(uint32_t lds_bytes, int device_cus) {
@@ -244,7 +257,7 @@ void launch_small_refine(const SmallJob *jobs, uint32_t njobs, uint32_t groups, 
                          uint32_t max_rounds, uint32_t *err, hipStream_t s) {
     launch_kernel(k_small_counter_reset, dim3(1), dim3(64), 0, s, next_job, err);
     launch_kernel(k_small_refine, dim3(groups), dim3(kSmallThreads), lds_bytes, s, jobs, njobs,
-                  next_job, out_blocks, results, max_rounds, err);
+                  next_job, out_blocks, results, max_rounds, err, lds_bytes);
 }
 
 }  // namespace dfamin
