@@ -508,6 +508,14 @@ int launch_full_round(Ctx &c, const RoundArgs &args, uint32_t round) {
         a.pb.gover = nullptr;
     }
     DFA_TRY(launch_kern(c, Kern::Mark, a, round));
+    // closure rounds keep their keys in LDS, up to 48 KB of them (three
+    // workgroups a CU); kernels that are timed keep the two passes' names
+    const bool fixed_width = a.k_eff <= 8 || a.k_eff == 16;
+    if (a.spread && !fixed_width && a.k_eff <= kClosureMaxK && a.lds_stage != 0 && !a.grouping &&
+        !a.seg.nseg && !a.pb.nb && !c.profiling) {
+        launch_closure_round(a, c.stream);
+        return launch_kern(c, Kern::RoundEnd, a, round);
+    }
     if (a.pb.nb) {
         DFA_TRY(launch_kern(c, Kern::PbGather, a, round));
         if (a.pb.gbuckets) {

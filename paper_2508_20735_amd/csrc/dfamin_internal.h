@@ -311,6 +311,10 @@ void launch_seg_round(const RoundArgs &a, hipStream_t s);
 // nothing in rounds that gather directly.
 void launch_pb_gather(const RoundArgs &a, hipStream_t s);
 void launch_signature_pb(const RoundArgs &a, hipStream_t s);
+// A closure round (a.spread) in place of launch_signature and launch_insert:
+// no segments, slices or sort grouping, at most kClosureMaxK columns.
+constexpr uint32_t kClosureMaxK = 47;
+void launch_closure_round(const RoundArgs &a, hipStream_t s);
 // The first table round by buckets (pb.gbuckets > 0): the keys of every
 // source tile into the buckets of their hashes, then the buckets' grouping.
 // Both, or (a bucket overflowed) launch_signature_pb and launch_insert, which
