@@ -327,10 +327,12 @@ __global__ __launch_bounds__(kBlock) void k_segd_round(SegdArgs a, uint32_t r, u
 // A bucket's runs lie in the groups of its segment, so entries of one key can
 // overflow nothing: they only make that bucket longer.
 //
-// Measured on MI355X (the batches above, whole calls): 2.83 -> 1.26 ms, and
-// 6.17 -> 2.88 ms for the pairs.  A round that refines all 9.87 million states
-// takes 158 + 153 us, the tile rounds' 988 us; of the keys' 158 us a sixth is
-// staging, the rest the latency of one workgroup a CU.
+// Measured on MI355X (the batches above, whole calls): 2.83 -> 1.24 ms, and
+// 6.17 -> 2.80 ms for the pairs.  A round that refines all 9.87 million states
+// takes 147 + 153 us, the tile rounds' 988 us.  Of the keys' time a sixth is
+// staging, the rest latency with one workgroup a CU (loading a group's rows
+// while the one before it is sorted: 158 -> 147 us); more entries in flight in
+// the groups' launch change nothing.
 //
 // Round 0 gathers acceptance bytes instead: a key is a pattern of letters + 1
 // bits, grouped by direct index, in LDS and then (once per pattern) in a
@@ -420,6 +422,19 @@ __device__ __forceinline__ void staged_keys(const SegdArgs &a, const SegdPart &P
     const uint32_t seg0 = S.first_tile * kBlock;
     StagedEntry<K> *out = reinterpret_cast<StagedEntry<K> *>(a.entries + S.table);
     uint32_t group = C.group;
+    // rows and marks of a group are loaded while the one before it is sorted
+    StagedRow<K> next_row[U];
+    uint8_t next_mark[U];
+    auto fetch = [&](uint32_t q0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t q = q0 + u * kStagedThreads + tx;
+            const uint32_t qs = q < end ? q : C.first;
+            next_mark[u] = a.shared[qs];
+            next_row[u] = *staged_row<K>(a, P, qs);
+        }
+    };
+    fetch(C.first);
     for (uint32_t q0 = C.first; q0 < end; q0 += kStagedGroup, ++group) {
         if (tx < nb) hist[tx] = 0;
         StagedEntry<K> e[U];
@@ -430,11 +445,10 @@ __device__ __forceinline__ void staged_keys(const SegdArgs &a, const SegdPart &P
             uint8_t m[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const uint32_t q = q0 + u * kStagedThreads + tx;
-                const uint32_t qs = q < end ? q : q0;
-                m[u] = a.shared[qs];
-                row[u] = *staged_row<K>(a, P, qs);
+                row[u] = next_row[u];
+                m[u] = next_mark[u];
             }
+            if (q0 + kStagedGroup < end) fetch(q0 + kStagedGroup);
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const uint32_t q = q0 + u * kStagedThreads + tx;
