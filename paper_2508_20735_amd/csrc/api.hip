@@ -921,7 +921,8 @@ int make_buckets(Ctx &c, size_t N, uint32_t k_eff, PbArgs &pb) {
     uint32_t buckets = 0, cap = 0;
     const size_t entries = bucket_entries(N, buckets, cap);
     if (c.arena.base || c.blocking_sync || buckets > kGroupMaxBuckets || cap >= kGroupSlots) return DFA_OK;
-    const size_t fill_bytes = (static_cast<size_t>(buckets) * kGroupStride + 2) * sizeof(uint32_t);
+    const size_t fills = static_cast<size_t>(buckets + 3) / 4 * kGroupStride;
+    const size_t fill_bytes = (fills + 1) * sizeof(unsigned long long);
     if (c.sig.ensure(entries * (k_eff + 2) * sizeof(uint32_t), "key buckets") != DFA_OK ||
         c.group_fill.ensure(fill_bytes, "bucket counters") != DFA_OK) {
         g_last_error.clear();
@@ -933,8 +934,8 @@ int make_buckets(Ctx &c, size_t N, uint32_t k_eff, PbArgs &pb) {
     pb.gbuckets = buckets;
     pb.gcap = cap;
     pb.gent = c.sig.as<uint32_t>();
-    pb.gfill = c.group_fill.as<uint32_t>();
-    pb.gover = pb.gfill + static_cast<size_t>(buckets) * kGroupStride;
+    pb.gfill = c.group_fill.as<unsigned long long>();
+    pb.gover = reinterpret_cast<uint32_t *>(pb.gfill + fills);
     return DFA_OK;
 }
 

@@ -207,14 +207,14 @@ struct PbArgs {
     // (key row, state), their numbers, and a flag set when one overflows
     uint32_t gbuckets, gcap;
     uint32_t *gent;
-    uint32_t *gfill;  // gbuckets words, kGroupStride apart
+    unsigned long long *gfill;  // four 16-bit fills to a word, kGroupStride words apart
     uint32_t *gover;
 };
 // Grouping by buckets: a bucket's entries are grouped by one workgroup in an
 // LDS table of kGroupSlots slots, so it holds on average at most kGroupMean.
 constexpr uint32_t kGroupSlots = 16384;
 constexpr uint32_t kGroupMean = 8192;
-constexpr uint32_t kGroupStride = 16;  // counters on 64-byte lines of their own
+constexpr uint32_t kGroupStride = 8;  // counters on 64-byte lines of their own
 constexpr uint32_t kGroupMaxBuckets = 1024;
 struct SortPlan {
     uint32_t sort_tiles, compact_tiles, hist_blocks, run_blocks;

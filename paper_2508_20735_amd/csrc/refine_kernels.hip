@@ -1601,7 +1601,7 @@ __global__ __launch_bounds__(NT) void k_signature_pb(SigParams p) {
 // part of the states overflow it; the flag stops both passes, and the table
 // does the round.  Measured on MI355X (k_signature_pb and k_insert_lds2
 // before, both passes here): 2^22 random states, 4 letters, 330 -> 151 us; a
-// union of 2^23, every state with a twin, 774 -> 536 us.
+// union of 2^23, every state with a twin, 774 -> 514 us.
 
 // Bucket and LDS hash of a key row.
 template <int KC>
@@ -1646,7 +1646,7 @@ __global__ __launch_bounds__(NT) void k_signature_part(SigParams p) {
             const size_t q = base + e * NT + tx;
             w0s[e] = q < p.N ? X[q] : 0u;
         }
-        for (uint32_t b = tx; b < pb.gbuckets; b += NT) hist[b] = 0;
+        for (uint32_t b = tx; b < ((pb.gbuckets + 3) & ~3u); b += NT) hist[b] = 0;
         pb_tile_keys<KC, NT>(pb, t, key, runs);  // (ends with a barrier)
         uint32_t bucket[EP], rank[EP];
 #pragma unroll
@@ -1669,10 +1669,21 @@ __global__ __launch_bounds__(NT) void k_signature_part(SigParams p) {
             rank[e] = atomicAdd(hist + bucket[e], 1u);
         }
         __syncthreads();
-        // the tile's place in every bucket (hist becomes the first position)
-        for (uint32_t b = tx; b < pb.gbuckets; b += NT) {
-            const uint32_t c = hist[b];
-            hist[b] = c ? atomicAdd(pb.gfill + b * kGroupStride, c) : 0u;
+        // the tile's place in every bucket (hist becomes the first position),
+        // four buckets to an atomic: with 1,024 buckets a tile has two states
+        // for each, and an atomic costs its L2 channel about 9 ns (one a
+        // bucket: 251 us for a union of 2^23 states; one for four: 227).  A
+        // fill that leaves its 16 bits has been past gcap before (a tile adds
+        // at most 2,048), so the flag is set by then.
+        for (uint32_t g = tx; 4 * g < pb.gbuckets; g += NT) {
+            unsigned long long c = 0;
+#pragma unroll
+            for (uint32_t i = 0; i < 4; ++i)
+                c |= static_cast<unsigned long long>(hist[4 * g + i]) << (16 * i);
+            if (c) c = atomicAdd(pb.gfill + g * kGroupStride, c);
+#pragma unroll
+            for (uint32_t i = 0; i < 4; ++i)
+                hist[4 * g + i] = static_cast<uint32_t>(c >> (16 * i)) & 0xFFFFu;
         }
         __syncthreads();
         bool over = false;
@@ -1714,7 +1725,9 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_part(SigParams p, uint3
     uint32_t *__restrict__ Y = (r & 1u) ? p.blockA : p.blockB;
     constexpr uint32_t W = KC + 1;
     const uint32_t tx = threadIdx.x;
-    const uint32_t n = pb.gfill[blockIdx.x * kGroupStride];  // (<= gcap < kGroupSlots)
+    const uint32_t n =  // (<= gcap < kGroupSlots)
+        static_cast<uint32_t>(pb.gfill[blockIdx.x / 4 * kGroupStride] >> (16 * (blockIdx.x % 4))) &
+        0xFFFFu;
     const uint32_t *__restrict__ ent =
         pb.gent + static_cast<size_t>(blockIdx.x) * pb.gcap * (W + 1);
     for (uint32_t i = tx; i < kGroupSlots; i += kGroupThreads) tab[i] = ~0u;

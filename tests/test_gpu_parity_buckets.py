@@ -29,7 +29,7 @@ def check(d):
         (nb, rounds, changing)
 
 
-@pytest.mark.parametrize("n", [1024, 2047, 2049, 8192, 8193, 16_385, 100_001])
+@pytest.mark.parametrize("n", [1024, 2047, 2049, 8192, 8193, 16_385, 100_001, 131_073, 200_001])
 @pytest.mark.parametrize("k", [1, 2, 3, 4, 8])
 def test_sizes_and_widths(n, k):
     check(W.random_dfa(n, k, 0.3, n + k))
