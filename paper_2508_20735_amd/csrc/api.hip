@@ -913,16 +913,16 @@ RoundArgs make_round_args(Ctx &c, const uint32_t *cols, size_t N, uint32_t k_eff
 size_t bucket_entries(size_t N, uint32_t &buckets, uint32_t &cap) {
     buckets = static_cast<uint32_t>(next_pow2((N + kGroupMean - 1) / kGroupMean));
     const size_t mean = (N + buckets - 1) / buckets;
-    cap = static_cast<uint32_t>(mean + mean / 4 + 512);
+    cap = static_cast<uint32_t>(std::min<size_t>(2 * mean + 512, kGroupSlots - 1));
     return static_cast<size_t>(buckets) * cap;
 }
 
 int make_buckets(Ctx &c, size_t N, uint32_t k_eff, PbArgs &pb) {
     uint32_t buckets = 0, cap = 0;
     const size_t entries = bucket_entries(N, buckets, cap);
-    if (c.arena.base || c.blocking_sync || buckets > kGroupMaxBuckets || cap >= kGroupSlots) return DFA_OK;
+    if (c.arena.base || c.blocking_sync || buckets > kGroupMaxBuckets) return DFA_OK;
     const size_t fills = static_cast<size_t>(buckets + 3) / 4 * kGroupStride;
-    const size_t fill_bytes = (fills + 1) * sizeof(unsigned long long);
+    const size_t fill_bytes = (fills + 1 + (buckets + 1) / 2) * sizeof(unsigned long long);
     if (c.sig.ensure(entries * (k_eff + 2) * sizeof(uint32_t), "key buckets") != DFA_OK ||
         c.group_fill.ensure(fill_bytes, "bucket counters") != DFA_OK) {
         g_last_error.clear();
@@ -936,6 +936,7 @@ int make_buckets(Ctx &c, size_t N, uint32_t k_eff, PbArgs &pb) {
     pb.gent = c.sig.as<uint32_t>();
     pb.gfill = c.group_fill.as<unsigned long long>();
     pb.gover = reinterpret_cast<uint32_t *>(pb.gfill + fills);
+    pb.gsample = pb.gover + 2;
     return DFA_OK;
 }
 
@@ -947,8 +948,12 @@ int build_slices(Ctx &c, const uint32_t *cols, size_t N, uint32_t k_eff, const d
                  bool excluded, bool group, PbArgs &pb) {
     pb = PbArgs{};
     const bool width = k_eff >= 1 && (k_eff <= 8 || k_eff == 16);
-    if (excluded || !width || o.loop_mode == DFA_LOOP_PERSISTENT || !c.tune.slice_min_states ||
-        N < c.tune.slice_min_states || N > (static_cast<size_t>(kPbMaxBuckets) << kPbSliceLog))
+    if (excluded || !width || o.loop_mode == DFA_LOOP_PERSISTENT) return DFA_OK;
+    // (with one or two letters the first table round still has few keys, which
+    // share buckets: no faster at 3 million states)
+    group = group && (k_eff == 3 || k_eff == 4 || k_eff == 8);
+    if (!c.tune.slice_min_states || N < c.tune.slice_min_states ||
+        N > (static_cast<size_t>(kPbMaxBuckets) << kPbSliceLog))
         return DFA_OK;
     const uint32_t nb = static_cast<uint32_t>((N + (1u << kPbSliceLog) - 1) >> kPbSliceLog);
     const uint32_t ntiles = static_cast<uint32_t>((N + kPbTile - 1) / kPbTile);
@@ -970,7 +975,7 @@ int build_slices(Ctx &c, const uint32_t *cols, size_t N, uint32_t k_eff, const d
     pb.bstart = pb.off + L;
     pb.nb = nb;
     pb.ntiles = ntiles;
-    if (group && (k_eff <= 4 || k_eff == 8)) DFA_TRY(make_buckets(c, N, k_eff, pb));
+    if (group) DFA_TRY(make_buckets(c, N, k_eff, pb));
     uint32_t *csum = c.pb_partials.as<uint32_t>();
     launch_pb_build(cols, c.colmap.as<uint32_t>(), N, k_eff, pb, csum,
                     csum + pb_chunk_words(nb, ntiles), c.stream);

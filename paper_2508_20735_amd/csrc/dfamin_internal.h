@@ -209,9 +209,11 @@ struct PbArgs {
     uint32_t *gent;
     unsigned long long *gfill;  // four 16-bit fills to a word, kGroupStride words apart
     uint32_t *gover;
+    uint32_t *gsample;  // gbuckets words: a sample's states in each bucket
 };
 // Grouping by buckets: a bucket's entries are grouped by one workgroup in an
-// LDS table of kGroupSlots slots, so it holds on average at most kGroupMean.
+// LDS table of kGroupSlots slots, so it holds fewer, and on average at most
+// kGroupMean.
 constexpr uint32_t kGroupSlots = 16384;
 constexpr uint32_t kGroupMean = 8192;
 constexpr uint32_t kGroupStride = 8;  // counters on 64-byte lines of their own

@@ -215,11 +215,11 @@ __device__ __forceinline__ bool pb_round(const PbArgs &pb, const RoundCtl &c, si
 }
 
 // Whether this round is one to group by buckets of the key hash instead of
-// the table: the first table round, its keys gathered through the slices.
+// the table: the first table round.
 // `over` is the overflow flag (nullptr without buckets), which decides it once
 // the scatter pass has ended.
-__device__ __forceinline__ bool part_round(const uint32_t *over, const RoundCtl &c, size_t N) {
-    return over && !c.done && c.round == c.all_active_until && 4ull * c.prev_count < 3ull * N;
+__device__ __forceinline__ bool part_round(const uint32_t *over, const RoundCtl &c) {
+    return over && !c.done && c.round == c.all_active_until;
 }
 
 struct SigParams {
@@ -566,10 +566,75 @@ __device__ __forceinline__ void wave_mark_bit(unsigned long long *T, uint32_t xi
     if ((pending >> lane_id()) & 1ull) atomicOr(T + w, bit);
 }
 
+// Bucket and LDS hash of a key row.
+template <int KC>
+__device__ __forceinline__ uint64_t part_hash(const uint32_t *w) {
+    uint32_t a = 0x85EBCA6Bu, b = 0xC2B2AE35u;
+#pragma unroll
+    for (int j = 0; j <= KC; ++j) {
+        a = (a ^ w[j]) * 0x9E3779B1u;
+        a ^= a >> 15;
+        b = (b + w[j]) * 0x85EBCA77u;
+        b ^= b >> 13;
+    }
+    a *= 0x27D4EB2Fu;
+    b = (b ^ a) * 0x165667B1u;
+    return (static_cast<uint64_t>(a ^ (a >> 15)) << 32) | (b ^ (b >> 16));
+}
+
+// Whether buckets are worth it: the marking kernel of the first table round,
+// which has nothing to mark, hashes 16,384 states spread over the index space
+// into their buckets, and one that has the share of the sample that would
+// overflow it stops the pass before it starts.  (The sample has 32 states for
+// a bucket of the mean size, so this takes 5 standard deviations; with a
+// quarter of the sample, equal buckets were stopped too.)  Without it inputs
+// with a few frequent keys paid for most of a pass: 3 million states, 4
+// letters, one state in 20 accepting, 870 -> 930 us; 881 with it.
+constexpr uint32_t kPartSample = 16384, kPartSampleGroups = 64;
+
+template <int KC>
+__device__ __forceinline__ void part_sample(const SigParams &p) {
+    const PbArgs &pb = p.pb;
+    __shared__ uint32_t hist[kGroupMaxBuckets];  // (a frequent key is one atomic then)
+    const uint32_t groups = gridDim.x < kPartSampleGroups ? gridDim.x : kPartSampleGroups;
+    if (blockIdx.x >= groups) return;
+    for (uint32_t b = threadIdx.x; b < pb.gbuckets; b += kBlock) hist[b] = 0;
+    __syncthreads();
+    const uint32_t *__restrict__ X = (p.ctl->round & 1u) ? p.blockB : p.blockA;
+    const uint32_t shift = 64 - (31 - __clz(pb.gbuckets));
+    const ColPtrs<KC> colp(p.cols, p.colmap, p.N);
+    for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < kPartSample; i += groups * kBlock) {
+        const size_t q = i * p.N / kPartSample;
+        uint32_t t[KC], w[KC + 1];
+        w[0] = X[q];
+#pragma unroll
+        for (int j = 0; j < KC; ++j) t[j] = colp.c[j][q];
+#pragma unroll
+        for (int j = 0; j < KC; ++j) w[1 + j] = X[t[j]];
+        atomicAdd(hist + (pb.gbuckets > 1 ? part_hash<KC>(w) >> shift : 0u), 1u);
+    }
+    __syncthreads();
+    for (uint32_t b = threadIdx.x; b < pb.gbuckets; b += kBlock)
+        if (hist[b]) atomicAdd(pb.gsample + b, hist[b]);
+}
+
+// One workgroup, between the marking kernel and the pass: sets the overflow
+// flag if the sample says so.
+__device__ __forceinline__ void part_judge(const PbArgs &pb, size_t N) {
+    bool over = false;
+    for (uint32_t b = threadIdx.x; b < pb.gbuckets; b += blockDim.x)
+        over |= pb.gsample[b] * static_cast<uint64_t>(N) >
+                static_cast<uint64_t>(kPartSample) * pb.gcap;
+    if (over) *pb.gover = 1;  // (every writer stores the same)
+}
+
 template <int KC>
 __device__ __forceinline__ void mark_body(const SigParams &p) {
     if (p.ctl->done) return;
     const uint32_t r = p.ctl->round;
+    if constexpr (KC == 3 || KC == 4 || KC == 8) {
+        if (part_round(p.pb.gover, *p.ctl)) part_sample<KC>(p);
+    }
     // the table is cleared every kEpochs rounds (its entries carry the epoch)
     if (r > 0 && r % kEpochs == 0) {
         for (size_t i = global_tid(); i < p.table_cap; i += grid_stride()) p.table[i] = 0ull;
@@ -1264,6 +1329,7 @@ __global__ __launch_bounds__(kPbGatherThreads) void k_pb_gather(SigParams p, uin
     // (the round end reads the record only after this kernel has finished)
     if (blockIdx.x == 0 && threadIdx.x == 0)
         const_cast<RoundCtl *>(p.ctl)->pb_rounds |= 1ull << (r % 64);
+    if (blockIdx.x == 0 && part_round(pb.gover, *p.ctl)) part_judge(pb, p.N);
     for (uint32_t job = blockIdx.x; job < pb.nb * per_bucket; job += gridDim.x) {
         const uint32_t b = job / per_bucket, part = job % per_bucket;
         const size_t s0 = static_cast<size_t>(b) * S;
@@ -1525,7 +1591,7 @@ __global__ __launch_bounds__(NT) void k_signature_pb(SigParams p) {
     __shared__ PbRunsLds<KC, NT> runs;
     if (!pb_round(p.pb, *p.ctl, p.N)) return;
     const PbArgs &pb = p.pb;
-    if (part_round(pb.gover, *p.ctl, p.N) && *pb.gover == 0) return;  // (grouped by buckets)
+    if (part_round(pb.gover, *p.ctl) && *pb.gover == 0) return;  // (grouped by buckets)
     const uint32_t r = p.ctl->round;
     const uint32_t *__restrict__ X = (r & 1u) ? p.blockB : p.blockA;
     uint32_t *__restrict__ Y = (r & 1u) ? p.blockA : p.blockB;
@@ -1597,26 +1663,30 @@ __global__ __launch_bounds__(NT) void k_signature_pb(SigParams p) {
 // streamed.  What stays random are the id and the block mark of a duplicate;
 // a state with a key of its own keeps the id that the first pass stored.
 //
-// A bucket's room is a quarter more than its mean.  Keys shared by a large
-// part of the states overflow it; the flag stops both passes, and the table
-// does the round.  Measured on MI355X (k_signature_pb and k_insert_lds2
+// A bucket has room for twice its mean.  Keys shared by a large part of
+// the states overflow it; the flag, set by a sample or by the pass, stops both
+// passes, and the table does the round.  Measured on MI355X (k_signature_pb and k_insert_lds2
 // before, both passes here): 2^22 random states, 4 letters, 330 -> 151 us; a
 // union of 2^23, every state with a twin, 774 -> 514 us.
 
-// Bucket and LDS hash of a key row.
-template <int KC>
-__device__ __forceinline__ uint64_t part_hash(const uint32_t *w) {
-    uint32_t a = 0x85EBCA6Bu, b = 0xC2B2AE35u;
+// A tile's place in every bucket, from its counts in hist (a multiple of four
+// of them), which become the first positions.  Four buckets to an atomic: with
+// 1,024 buckets a tile of 2,048 states has two for each, and an atomic costs
+// its L2 channel about 9 ns (one a bucket: 251 us for a union of 2^23 states;
+// one for four: 227).  A fill that leaves its 16 bits has been past gcap
+// before (a tile adds at most 2,048), so the overflow flag is set by then.
+template <uint32_t NT>
+__device__ __forceinline__ void part_reserve(const PbArgs &pb, uint32_t *hist) {
+    for (uint32_t g = threadIdx.x; 4 * g < pb.gbuckets; g += NT) {
+        unsigned long long c = 0;
 #pragma unroll
-    for (int j = 0; j <= KC; ++j) {
-        a = (a ^ w[j]) * 0x9E3779B1u;
-        a ^= a >> 15;
-        b = (b + w[j]) * 0x85EBCA77u;
-        b ^= b >> 13;
+        for (uint32_t i = 0; i < 4; ++i)
+            c |= static_cast<unsigned long long>(hist[4 * g + i]) << (16 * i);
+        if (c) c = atomicAdd(pb.gfill + g * kGroupStride, c);
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i)
+            hist[4 * g + i] = static_cast<uint32_t>(c >> (16 * i)) & 0xFFFFu;
     }
-    a *= 0x27D4EB2Fu;
-    b = (b ^ a) * 0x165667B1u;
-    return (static_cast<uint64_t>(a ^ (a >> 15)) << 32) | (b ^ (b >> 16));
 }
 
 template <int KC, uint32_t NT>
@@ -1625,7 +1695,7 @@ __global__ __launch_bounds__(NT) void k_signature_part(SigParams p) {
     __shared__ PbRunsLds<KC, NT> runs;
     __shared__ uint32_t hist[kGroupMaxBuckets];
     const PbArgs &pb = p.pb;
-    if (!part_round(pb.gover, *p.ctl, p.N)) return;
+    if (!part_round(pb.gover, *p.ctl)) return;
     // (one thread reads the flag: the workgroup stays or goes as a whole)
     const bool stopped =
         threadIdx.x == 0 &&
@@ -1669,22 +1739,7 @@ __global__ __launch_bounds__(NT) void k_signature_part(SigParams p) {
             rank[e] = atomicAdd(hist + bucket[e], 1u);
         }
         __syncthreads();
-        // the tile's place in every bucket (hist becomes the first position),
-        // four buckets to an atomic: with 1,024 buckets a tile has two states
-        // for each, and an atomic costs its L2 channel about 9 ns (one a
-        // bucket: 251 us for a union of 2^23 states; one for four: 227).  A
-        // fill that leaves its 16 bits has been past gcap before (a tile adds
-        // at most 2,048), so the flag is set by then.
-        for (uint32_t g = tx; 4 * g < pb.gbuckets; g += NT) {
-            unsigned long long c = 0;
-#pragma unroll
-            for (uint32_t i = 0; i < 4; ++i)
-                c |= static_cast<unsigned long long>(hist[4 * g + i]) << (16 * i);
-            if (c) c = atomicAdd(pb.gfill + g * kGroupStride, c);
-#pragma unroll
-            for (uint32_t i = 0; i < 4; ++i)
-                hist[4 * g + i] = static_cast<uint32_t>(c >> (16 * i)) & 0xFFFFu;
-        }
+        part_reserve<NT>(pb, hist);
         __syncthreads();
         bool over = false;
 #pragma unroll
@@ -1720,7 +1775,7 @@ template <int KC>
 __global__ __launch_bounds__(kGroupThreads) void k_group_part(SigParams p, uint32_t *multi) {
     extern __shared__ uint32_t tab[];  // kGroupSlots: tag << 14 | entry
     const PbArgs &pb = p.pb;
-    if (!part_round(pb.gover, *p.ctl, p.N) || *pb.gover) return;
+    if (!part_round(pb.gover, *p.ctl) || *pb.gover) return;
     const uint32_t r = p.ctl->round;
     uint32_t *__restrict__ Y = (r & 1u) ? p.blockA : p.blockB;
     constexpr uint32_t W = KC + 1;
@@ -1815,7 +1870,7 @@ struct InsParams {
 
 // Whether the round has been grouped by buckets already.
 __device__ __forceinline__ bool grouped_already(const InsParams &p) {
-    return part_round(p.gover, *p.ctl, p.N) && *p.gover == 0;
+    return part_round(p.gover, *p.ctl) && *p.gover == 0;
 }
 
 // Stores a wave's changed-id mask and sets the summary bits of its groups
@@ -3433,8 +3488,6 @@ void launch_signature_part(const RoundArgs &a, hipStream_t s) {
     constexpr uint32_t NT = kPbSigThreads;
     const dim3 grid(a.pb.ntiles), block(NT);
     switch (a.k_eff) {
-        case 1: launch_kernel(k_signature_part<1, NT>, grid, block, 0, s, sp); break;
-        case 2: launch_kernel(k_signature_part<2, NT>, grid, block, 0, s, sp); break;
         case 3: launch_kernel(k_signature_part<3, NT>, grid, block, 0, s, sp); break;
         case 4: launch_kernel(k_signature_part<4, NT>, grid, block, 0, s, sp); break;
         case 8: launch_kernel(k_signature_part<8, NT>, grid, block, 0, s, sp); break;
@@ -3448,8 +3501,6 @@ void launch_group_part(const RoundArgs &a, hipStream_t s) {
     const dim3 grid(a.pb.gbuckets), block(kGroupThreads);
     constexpr uint32_t lds = kGroupSlots * 4;
     switch (a.k_eff) {
-        case 1: launch_kernel(k_group_part<1>, grid, block, lds, s, sp, a.multi); break;
-        case 2: launch_kernel(k_group_part<2>, grid, block, lds, s, sp, a.multi); break;
         case 3: launch_kernel(k_group_part<3>, grid, block, lds, s, sp, a.multi); break;
         case 4: launch_kernel(k_group_part<4>, grid, block, lds, s, sp, a.multi); break;
         case 8: launch_kernel(k_group_part<8>, grid, block, lds, s, sp, a.multi); break;
