@@ -91,7 +91,10 @@ extern "C" {
 #define DFA_LOOP_CHUNK 1 /* rounds are enqueued in chunks; kernels turn into no-ops
                             on the device once the partition is stable; the host
                             checks once per chunk */
-#define DFA_LOOP_GRAPH 2 /* like CHUNK, each chunk replayed from a hipGraph (built once per chunk shape) */
+#define DFA_LOOP_GRAPH 2 /* like CHUNK, each chunk replayed from a hipGraph (built once per chunk shape).
+                            CHUNK and GRAPH queue a few rounds ahead of the device instead where
+                            the host can watch the rounds' progress (no kernel timing, no server
+                            lane), and small inputs run whole or in one launch per round */
 #define DFA_LOOP_PERSISTENT 3 /* each chunk is one cooperative launch that loops over
                                  the rounds on the device, its phases separated by grid
                                  barriers, and stops as soon as the partition is stable

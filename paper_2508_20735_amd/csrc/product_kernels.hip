@@ -69,7 +69,7 @@ __global__ __launch_bounds__(64) void k_product_reset(ProductCtl *ctl, unsigned 
 // probe per pair and letter.  A workgroup appends its new pairs of up to
 // kLetters letters with one atomic: one atomic per wave and letter on the
 // single counter made a level of 806,000 pairs and 4 letters 608 us (50,000
-// atomics, about 12 ns each); this one takes about 140.
+// atomics, about 12 ns each); this one takes about 120.
 constexpr uint32_t kLetters = 4;
 
 __global__ __launch_bounds__(kBlock) void k_product_level(ProductArgs a,
