@@ -913,7 +913,7 @@ RoundArgs make_round_args(Ctx &c, const uint32_t *cols, size_t N, uint32_t k_eff
 size_t bucket_entries(size_t N, uint32_t &buckets, uint32_t &cap) {
     buckets = static_cast<uint32_t>(next_pow2((N + kGroupMean - 1) / kGroupMean));
     const size_t mean = (N + buckets - 1) / buckets;
-    cap = static_cast<uint32_t>(std::min<size_t>(2 * mean + 512, kGroupSlots - 1));
+    cap = static_cast<uint32_t>(std::min<size_t>(mean + mean / 4 + 512, kGroupSlots - 1));
     return static_cast<size_t>(buckets) * cap;
 }
 

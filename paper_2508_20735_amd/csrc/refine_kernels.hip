@@ -584,10 +584,9 @@ __device__ __forceinline__ uint64_t part_hash(const uint32_t *w) {
 
 // Whether buckets are worth it: the marking kernel of the first table round,
 // which has nothing to mark, hashes 16,384 states spread over the index space
-// into their buckets, and one that has the share of the sample that would
-// overflow it stops the pass before it starts.  (The sample has 32 states for
-// a bucket of the mean size, so this takes 5 standard deviations; with a
-// quarter of the sample, equal buckets were stopped too.)  Without it inputs
+// into their buckets, and one with twice its share of the sample stops the
+// pass before it starts.  (The sample has 16 or more states for a bucket of
+// the mean size; twice that is 4 standard deviations and more.)  Without it inputs
 // with a few frequent keys paid for most of a pass: 3 million states, 4
 // letters, one state in 20 accepting, 870 -> 930 us; 881 with it.
 constexpr uint32_t kPartSample = 16384, kPartSampleGroups = 64;
@@ -620,11 +619,10 @@ __device__ __forceinline__ void part_sample(const SigParams &p) {
 
 // One workgroup, between the marking kernel and the pass: sets the overflow
 // flag if the sample says so.
-__device__ __forceinline__ void part_judge(const PbArgs &pb, size_t N) {
+__device__ __forceinline__ void part_judge(const PbArgs &pb) {
     bool over = false;
     for (uint32_t b = threadIdx.x; b < pb.gbuckets; b += blockDim.x)
-        over |= pb.gsample[b] * static_cast<uint64_t>(N) >
-                static_cast<uint64_t>(kPartSample) * pb.gcap;
+        over |= pb.gsample[b] * static_cast<uint64_t>(pb.gbuckets) > 2 * kPartSample;
     if (over) *pb.gover = 1;  // (every writer stores the same)
 }
 
@@ -1329,7 +1327,7 @@ __global__ __launch_bounds__(kPbGatherThreads) void k_pb_gather(SigParams p, uin
     // (the round end reads the record only after this kernel has finished)
     if (blockIdx.x == 0 && threadIdx.x == 0)
         const_cast<RoundCtl *>(p.ctl)->pb_rounds |= 1ull << (r % 64);
-    if (blockIdx.x == 0 && part_round(pb.gover, *p.ctl)) part_judge(pb, p.N);
+    if (blockIdx.x == 0 && part_round(pb.gover, *p.ctl)) part_judge(pb);
     for (uint32_t job = blockIdx.x; job < pb.nb * per_bucket; job += gridDim.x) {
         const uint32_t b = job / per_bucket, part = job % per_bucket;
         const size_t s0 = static_cast<size_t>(b) * S;
@@ -1663,11 +1661,13 @@ __global__ __launch_bounds__(NT) void k_signature_pb(SigParams p) {
 // streamed.  What stays random are the id and the block mark of a duplicate;
 // a state with a key of its own keeps the id that the first pass stored.
 //
-// A bucket has room for twice its mean.  Keys shared by a large part of
-// the states overflow it; the flag, set by a sample or by the pass, stops both
-// passes, and the table does the round.  Measured on MI355X (k_signature_pb and k_insert_lds2
-// before, both passes here): 2^22 random states, 4 letters, 330 -> 151 us; a
-// union of 2^23, every state with a twin, 774 -> 514 us.
+// A bucket has room for a quarter more than its mean (twice the mean, its
+// entries spread over more memory, made a call on a union of 2^23 states 3%
+// slower).  Keys shared by a large part of the states overflow it; the flag,
+// set by a sample or by the pass, stops both passes, and the table does the
+// round.  Measured on MI355X (k_signature_pb and k_insert_lds2 before, both
+// passes here): 2^22 random states, 4 letters, 330 -> 151 us; a union of 2^23,
+// every state with a twin, 774 -> 514 us.
 
 // A tile's place in every bucket, from its counts in hist (a multiple of four
 // of them), which become the first positions.  Four buckets to an atomic: with
