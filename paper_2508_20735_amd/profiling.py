@@ -27,14 +27,18 @@ from collections import defaultdict
 ROUND_KERNELS = ("k_mark", "k_signature", "k_insert", "k_insert_lds", "k_insert_lds2",
                  "k_round_end", "k_pattern_round", "k_packed_round", "k_pb_gather",
                  "k_signature_pb", "k_pb_count", "k_pb_scatter", "k_pb_gather8",
-                 "k_packed_pb", "k_count_labels")
+                 "k_packed_pb", "k_count_labels", "k_signature_part", "k_group_part")
 # The library's per-kernel timing names a launch of the grouping step
 # "k_insert": one dispatch of an LDS-staged variant and one of the plain
 # kernel, of which exactly one does the round's work.  "k_packed_pb" is the
 # packed label round through slices: the byte gather, the round, and the
 # count of the labels it marked.
-LIBRARY_GROUPS = {"k_insert": ("k_insert_lds2", "k_insert_lds", "k_insert"),
+# The two passes of the grouping by buckets go by the names of the kernels that
+# they replace in that round, as launches of their own.
+LIBRARY_GROUPS = {"k_insert": ("k_insert_lds2", "k_insert_lds", "k_insert", "k_group_part"),
+                  "k_signature_pb": ("k_signature_pb", "k_signature_part"),
                   "k_packed_pb": ("k_pb_gather8", "k_packed_pb", "k_count_labels")}
+OWN_LAUNCH = ("k_group_part", "k_signature_part")
 COPY_KERNEL = "__amd_rocclr_copyBuffer"
 
 
@@ -129,10 +133,12 @@ def traffic(fetch_dir: str, write_dir: str, copy_bytes: int) -> dict:
         if not any(b in members for members in LIBRARY_GROUPS.values()):
             lib[b] = dict(e)
     for name, members in LIBRARY_GROUPS.items():
-        parts = [out["kernels"][m] for m in members if m in out["kernels"]]
+        found = {m: out["kernels"][m] for m in members if m in out["kernels"]}
+        parts = list(found.values())
         if not parts:
             continue
-        launches = max(p["launches"] for p in parts)
+        launches = max([e["launches"] for m, e in found.items() if m not in OWN_LAUNCH] + [0]) + \
+            sum(e["launches"] for m, e in found.items() if m in OWN_LAUNCH)
         f_tot = sum(p["fetch_bytes_per_launch"] * p["launches"] for p in parts)
         w_tot = sum(p["write_bytes_per_launch"] * p["launches"] for p in parts)
         lib[name] = {"launches": launches, "fetch_bytes_per_launch": f_tot / launches,
