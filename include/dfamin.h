@@ -45,8 +45,11 @@
  *   - Host-pointer calls (dfa_minimise, dfa_equivalent, dfa_included) copy the
  *     inputs to the device and the results back.  The *_device variants take
  *     device pointers (memory of the current HIP device) and a hipStream_t
- *     (passed as void*, NULL = the library's own stream); their inputs must
- *     stay unchanged until the call returns.
+ *     (passed as void*, NULL = the legacy default stream): the call's work
+ *     starts behind what is queued on that stream, and is complete when the
+ *     call returns.  It runs on streams of the library, but a refinement that
+ *     one workgroup takes (some thousand states) runs on the given stream
+ *     itself.  The inputs must stay unchanged until the call returns.
  */
 #ifndef DFAMIN_H
 #define DFAMIN_H

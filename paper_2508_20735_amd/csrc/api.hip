@@ -178,10 +178,6 @@ struct Ctx {
     hipEvent_t ev_start = nullptr, ev_stop = nullptr, ev_in = nullptr;
     int lds_bytes = -1;          // LDS a workgroup may have (asked once)
     int clock_khz = 0;           // rate of the device's wall clock
-    // device-pointer calls: the caller's stream, and whether its work is
-    // ordered before the library's stream yet
-    hipStream_t caller = nullptr;
-    bool joined = true;
     uint32_t *pinned = nullptr;  // host staging for small transfers
     HostProgress *host_progress = nullptr;  // page-locked: written by the device
     Buffer cols, tc_cols, colmap, blockA, blockB, sig, hash, table, ctl, flags, canon, dense,
@@ -383,12 +379,23 @@ int join_stream(Ctx &c, void *stream) {
     return DFA_OK;
 }
 
-// The same for the caller's stream of a call that has not needed it yet (a
-// refinement that one workgroup takes runs on the caller's stream itself).
-int join_caller(Ctx &c) {
-    if (c.joined) return DFA_OK;
-    c.joined = true;
-    return join_stream(c, c.caller);
+// The caller's stream of one device-pointer call, and whether the work queued
+// there is ordered before the library's stream yet (a refinement that one
+// workgroup takes runs on the caller's stream itself and needs no such order).
+// It lives as long as the call: nothing outlives it in the context, whose next
+// call may come when the stream is gone.  Host-pointer calls and server lanes
+// have none.
+struct Caller {
+    hipStream_t stream = nullptr;
+    bool joined = true;
+    Caller() = default;
+    explicit Caller(void *s) : stream(static_cast<hipStream_t>(s)), joined(false) {}
+};
+
+int join_caller(Ctx &c, Caller &caller) {
+    if (caller.joined) return DFA_OK;
+    caller.joined = true;
+    return join_stream(c, caller.stream);
 }
 
 // ---- kernel timing ----
@@ -1619,8 +1626,14 @@ int refine_direct(Ctx &c, const dfa_view &a, const dfa_view *b, bool canon, cons
 // A refinement small enough for one workgroup's LDS; done: it is decided, res
 // is complete and the outputs are written.  Otherwise (more rounds than the
 // general path runs before it looks for a stall) another path starts anew.
-int refine_whole(Ctx &c, const dfa_view &a, const dfa_view *b, const Outputs *out,
+int refine_whole(Ctx &c, Caller &caller, const dfa_view &a, const dfa_view *b, const Outputs *out,
                  RefineResult &res, bool &done) {
+    // (a stream of another device is refused where it is joined)
+    hipDevice_t on = c.device;
+    if (caller.stream && (hipStreamGetDevice(caller.stream, &on) != hipSuccess || on != c.device)) {
+        (void)hipGetLastError();
+        DFA_TRY(join_caller(c, caller));
+    }
     const uint32_t k = a.k, n = a.n + (b ? b->n : 0u);
     WholeArgs w{};
     w.da = a.delta;
@@ -1648,10 +1661,10 @@ int refine_whole(Ctx &c, const dfa_view &a, const dfa_view *b, const Outputs *ou
     w.result = reinterpret_cast<WholeResult *>(c.pinned);
     // no workspace: the kernel runs on the caller's stream, behind the work
     // that is queued there, and times itself
-    hipStream_t s = c.joined ? c.stream : c.caller;
+    hipStream_t s = caller.joined ? c.stream : caller.stream;
     launch_whole(w, s);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(c.joined ? stream_sync(c) : hipStreamSynchronize(s));
+    HIP_TRY(caller.joined ? stream_sync(c) : hipStreamSynchronize(s));
     WholeResult r;
     std::memcpy(&r, c.pinned, sizeof r);
     if (r.err) return fail(DFA_EINVAL, "a transition target is >= n");
@@ -1681,8 +1694,8 @@ int refine_whole(Ctx &c, const dfa_view &a, const dfa_view *b, const Outputs *ou
 // Refines one DFA, or the union of two (equivalence: until their start
 // states separate), by the algorithm of the options.  canon: the scratch of
 // the canonical ids is cleared too.
-int refine_any(Ctx &c, const dfa_view &a, const dfa_view *b, const dfa_options &o, bool canon,
-               const Outputs *out, RefineResult &res) {
+int refine_any(Ctx &c, Caller &caller, const dfa_view &a, const dfa_view *b, const dfa_options &o,
+               bool canon, const Outputs *out, RefineResult &res) {
     const uint32_t k = a.k;
     const size_t N = static_cast<size_t>(a.n) + (b ? b->n : 0);
     Resume resume;
@@ -1690,10 +1703,10 @@ int refine_any(Ctx &c, const dfa_view &a, const dfa_view *b, const dfa_options &
     const bool direct = direct_applies(c, N, k, b != nullptr, o);
     if (direct && whole_applies(c, N, k)) {
         bool done = false;
-        DFA_TRY(refine_whole(c, a, b, out, res, done));
+        DFA_TRY(refine_whole(c, caller, a, b, out, res, done));
         if (done) return DFA_OK;
     }
-    DFA_TRY(join_caller(c));
+    DFA_TRY(join_caller(c, caller));
     // (a context without events, the allocation-free one, times on the host)
     if (c.ev_start) HIP_TRY(hipEventRecord(c.ev_start, c.stream));
     if (direct) {
@@ -1728,8 +1741,8 @@ int refine_any(Ctx &c, const dfa_view &a, const dfa_view *b, const dfa_options &
     return refine(c, N, k, o, check_eq, eq_a, eq_b, !b, res, nullptr, resumed ? &resume : nullptr);
 }
 
-int minimise_pruned(Ctx &c, uint32_t n, uint32_t k, const uint32_t *delta, const uint8_t *acc,
-                    uint32_t *block_out, dfa_quotient *q, const dfa_options &o, dfa_stats *st);
+int minimise_pruned(Ctx &c, Caller &caller, uint32_t n, uint32_t k, const uint32_t *delta,
+                    const uint8_t *acc, uint32_t *block_out, dfa_quotient *q, const dfa_options &o, dfa_stats *st);
 
 // Canonical ids and the quotient of a finished refinement.
 int write_outputs(Ctx &c, uint32_t n, uint32_t k, const uint32_t *delta, const uint8_t *acc,
@@ -1776,9 +1789,9 @@ int write_outputs(Ctx &c, uint32_t n, uint32_t k, const uint32_t *delta, const u
     return DFA_OK;
 }
 
-int minimise_impl(Ctx &c, uint32_t n, uint32_t k, const uint32_t *delta, const uint8_t *acc,
-                  uint32_t *block_out, dfa_quotient *q, const dfa_options &o, dfa_stats *st) {
-    if (o.prune) return minimise_pruned(c, n, k, delta, acc, block_out, q, o, st);
+int minimise_impl(Ctx &c, Caller &caller, uint32_t n, uint32_t k, const uint32_t *delta,
+                  const uint8_t *acc, uint32_t *block_out, dfa_quotient *q, const dfa_options &o, dfa_stats *st) {
+    if (o.prune) return minimise_pruned(c, caller, n, k, delta, acc, block_out, q, o, st);
     // (the leaders of leader rounds are canonical ids already)
     const bool canon = o.algorithm != DFA_ALGO_LEADER;
     if (canon || q) DFA_TRY(c.canon.ensure(static_cast<size_t>(n) * sizeof(uint32_t), "canonical ids"));
@@ -1791,7 +1804,7 @@ int minimise_impl(Ctx &c, uint32_t n, uint32_t k, const uint32_t *delta, const u
     RefineResult r;
     const dfa_view view{n, k, o.start, delta, acc};
     const Outputs out{block_out, q};
-    int rc = refine_any(c, view, nullptr, o, canon, &out, r);
+    int rc = refine_any(c, caller, view, nullptr, o, canon, &out, r);
     if (rc != DFA_OK) return rc;
     if (!r.outputs_done) DFA_TRY(write_outputs(c, n, k, delta, acc, block_out, q, o, r));
     if (r.ctl.limit) {
@@ -1816,10 +1829,10 @@ int minimise_impl(Ctx &c, uint32_t n, uint32_t k, const uint32_t *delta, const u
 // dense renumbering of the reachable states (in increasing order), the
 // sub-automaton, its minimisation, and the ids mapped back (smallest
 // reachable member of each block; DFA_UNREACHABLE elsewhere).
-int minimise_pruned(Ctx &c, uint32_t n, uint32_t k, const uint32_t *delta, const uint8_t *acc,
-                    uint32_t *block_out, dfa_quotient *q, const dfa_options &o, dfa_stats *st) {
+int minimise_pruned(Ctx &c, Caller &caller, uint32_t n, uint32_t k, const uint32_t *delta,
+                    const uint8_t *acc, uint32_t *block_out, dfa_quotient *q, const dfa_options &o, dfa_stats *st) {
     if (o.start >= n) return fail(DFA_EINVAL, "start (%u) >= n (%u)", o.start, n);
-    DFA_TRY(join_caller(c));
+    DFA_TRY(join_caller(c, caller));
     const size_t ntiles = (static_cast<size_t>(n) + kScanTile - 1) / kScanTile;
     DFA_TRY(c.flags.ensure(4 * sizeof(uint32_t), "flags"));
     DFA_TRY(c.scalars.ensure(16 * sizeof(uint32_t), "scalars"));
@@ -1904,7 +1917,7 @@ int minimise_pruned(Ctx &c, uint32_t n, uint32_t k, const uint32_t *delta, const
     dfa_options o2 = o;
     o2.prune = 0;
     o2.start = sub_start;
-    int rc = minimise_impl(c, m, k, c.sub_delta.as<uint32_t>(), c.sub_acc.as<uint8_t>(),
+    int rc = minimise_impl(c, caller, m, k, c.sub_delta.as<uint32_t>(), c.sub_acc.as<uint8_t>(),
                            c.sub_block.as<uint32_t>(), q, o2, st);
     if (rc != DFA_OK && rc != DFA_ELIMIT) return rc;
     launch_reach_expand(ra.mark, n, c.reach_dense.as<uint32_t>(), c.reach_orig.as<uint32_t>(),
@@ -1921,16 +1934,17 @@ int minimise_pruned(Ctx &c, uint32_t n, uint32_t k, const uint32_t *delta, const
     return rc;
 }
 
-int included_impl(Ctx &c, const dfa_view &a, const dfa_view &b, int *verdict, uint64_t *visited,
-                  dfa_stats *st, int mode);
+int included_impl(Ctx &c, Caller &caller, const dfa_view &a, const dfa_view &b, int *verdict,
+                  uint64_t *visited, dfa_stats *st, int mode);
 
-int equivalent_impl(Ctx &c, const dfa_view &a, const dfa_view &b, int *verdict,
+int equivalent_impl(Ctx &c, Caller &caller, const dfa_view &a, const dfa_view &b, int *verdict,
                     const dfa_options &o, dfa_stats *st) {
-    if (o.equiv_method == DFA_EQ_PRODUCT) return included_impl(c, a, b, verdict, nullptr, st, 1);
+    if (o.equiv_method == DFA_EQ_PRODUCT)
+        return included_impl(c, caller, a, b, verdict, nullptr, st, 1);
     const size_t N = static_cast<size_t>(a.n) + b.n;
     if (N >= 0xFFFFFFFFull) return fail(DFA_EINVAL, "nA + nB must be < 2^32 - 1");
     RefineResult r;
-    DFA_TRY(refine_any(c, a, &b, o, false, nullptr, r));
+    DFA_TRY(refine_any(c, caller, a, &b, o, false, nullptr, r));
     if (r.device_ms < 0) {
         HIP_TRY(hipEventRecord(c.ev_stop, c.stream));
         HIP_TRY(stream_sync(c));
@@ -1959,9 +1973,9 @@ int equivalent_impl(Ctx &c, const dfa_view &a, const dfa_view &b, int *verdict,
 // equivalence (refuted by exactly one accepting side).  The host queues a
 // batch at a time (a narrow launch, then wide levels that stop by themselves
 // when they have no work or no room) and waits once per batch.
-int included_impl(Ctx &c, const dfa_view &a, const dfa_view &b, int *verdict, uint64_t *visited,
-                  dfa_stats *st, int mode = 0) {
-    DFA_TRY(join_caller(c));
+int included_impl(Ctx &c, Caller &caller, const dfa_view &a, const dfa_view &b, int *verdict,
+                  uint64_t *visited, dfa_stats *st, int mode = 0) {
+    DFA_TRY(join_caller(c, caller));
     const uint32_t k = a.k;
     const size_t N = static_cast<size_t>(a.n) + b.n;
     uint64_t cap = next_pow2(std::max<uint64_t>(4 * N, 4096));
@@ -2938,7 +2952,8 @@ int minimise_host(Ctx &c_, uint32_t n, uint32_t k, const uint32_t *delta, const 
         dq.delta = c->stage_qdelta.as<uint32_t>();
         dq.accepting = c->stage_qacc.as<uint8_t>();
     }
-    int rc = minimise_impl(*c, n, k, c->stage_delta.as<uint32_t>(), c->stage_acc.as<uint8_t>(),
+    Caller none;
+    int rc = minimise_impl(*c, none, n, k, c->stage_delta.as<uint32_t>(), c->stage_acc.as<uint8_t>(),
                            c->stage_block.as<uint32_t>(), q_out ? &dq : nullptr, o, stats);
     if (rc != DFA_OK && rc != DFA_ELIMIT) return rc;
     t0 = std::chrono::steady_clock::now();
@@ -2982,7 +2997,8 @@ int equivalent_host(Ctx &c, const dfa_view *a, const dfa_view *b, int *verdict,
     DFA_TRY(stage_view(c, c.stage_delta_b, c.stage_acc_b, b, db));
     HIP_TRY(stream_sync(c));
     const double h2d = ms_since(t0);
-    int rc = equivalent_impl(c, da, db, verdict, o, stats);
+    Caller none;
+    int rc = equivalent_impl(c, none, da, db, verdict, o, stats);
     if (stats) stats->h2d_ms = h2d;
     return rc;
 }
@@ -3263,11 +3279,12 @@ void run_solo(Server &s, Ctx &c, ServedRequest *r) {
     o.tc_mode = s.cfg.tc_mode;
     o.loop_mode = DFA_LOOP_CHUNK;
     dfa_stats st{};
+    Caller none;
     if (r->kind == DFA_REQ_MINIMISE) {
         const size_t n = r->a.n;
         r->status = c.stage_block.ensure(n * sizeof(uint32_t), "output copy");
         if (r->status == DFA_OK)
-            r->status = minimise_impl(c, r->a.n, r->a.k, r->a.delta, r->a.accepting,
+            r->status = minimise_impl(c, none, r->a.n, r->a.k, r->a.delta, r->a.accepting,
                                       c.stage_block.as<uint32_t>(), nullptr, o, &st);
         if (r->status == DFA_OK) {
             r->blocks = static_cast<uint32_t *>(s.pinned.get(n * sizeof(uint32_t), r->blocks_cls));
@@ -3285,7 +3302,7 @@ void run_solo(Server &s, Ctx &c, ServedRequest *r) {
         r->rounds = st.rounds;
     } else {
         int v = 0;
-        r->status = equivalent_impl(c, r->a, r->b, &v, o, &st);
+        r->status = equivalent_impl(c, none, r->a, r->b, &v, o, &st);
         r->verdict = v;
         r->rounds = st.rounds;
     }
@@ -3717,10 +3734,9 @@ int dfa_minimise_device(uint32_t n, uint32_t k, const uint32_t *delta, const uin
         DFA_TRY(get_ctx(c));
         CallScope lock(c->mu);
         DFA_TRY(init_ctx(*c));
-        c->caller = static_cast<hipStream_t>(stream);
-        c->joined = false;
+        Caller caller(stream);
         if (stats) std::memset(stats, 0, sizeof *stats);
-        return minimise_impl(*c, n, k, delta, accepting, block_out, q_out, o, stats);
+        return minimise_impl(*c, caller, n, k, delta, accepting, block_out, q_out, o, stats);
     });
 }
 
@@ -3758,8 +3774,9 @@ int dfa_minimise_device_fixed(uint32_t n, uint32_t k, const uint32_t *delta,
         c.arena.used = 0;
         ++c.arena.generation;
         DFA_TRY(join_stream(c, stream));
+        Caller none;
         if (stats) std::memset(stats, 0, sizeof *stats);
-        return minimise_impl(c, n, k, delta, accepting, block_out, q_out, o, stats);
+        return minimise_impl(c, none, n, k, delta, accepting, block_out, q_out, o, stats);
     });
 }
 
@@ -3790,10 +3807,9 @@ int dfa_equivalent_device(const dfa_view *a, const dfa_view *b, int *verdict,
         DFA_TRY(get_ctx(c));
         CallScope lock(c->mu);
         DFA_TRY(init_ctx(*c));
-        c->caller = static_cast<hipStream_t>(stream);
-        c->joined = false;
+        Caller caller(stream);
         if (stats) std::memset(stats, 0, sizeof *stats);
-        return equivalent_impl(*c, *a, *b, verdict, o, stats);
+        return equivalent_impl(*c, caller, *a, *b, verdict, o, stats);
     });
 }
 
@@ -3826,8 +3842,8 @@ int dfa_included_device(const dfa_view *a, const dfa_view *b, int *verdict,
         DFA_TRY(get_ctx(c));
         CallScope lock(c->mu);
         DFA_TRY(init_ctx(*c));
-        DFA_TRY(join_stream(*c, stream));
-        return included_impl(*c, *a, *b, verdict, pairs_visited, stats);
+        Caller caller(stream);
+        return included_impl(*c, caller, *a, *b, verdict, pairs_visited, stats);
     });
 }
 
@@ -3849,7 +3865,8 @@ int dfa_included(const dfa_view *a, const dfa_view *b, int *verdict, uint64_t *p
         DFA_TRY(stage_view(*c, c->stage_delta_b, c->stage_acc_b, b, db));
         HIP_TRY(stream_sync(*c));
         const double h2d = ms_since(t0);
-        int rc = included_impl(*c, da, db, verdict, pairs_visited, stats);
+        Caller none;
+        int rc = included_impl(*c, none, da, db, verdict, pairs_visited, stats);
         if (stats) stats->h2d_ms = h2d;
         return rc;
     });
