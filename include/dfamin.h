@@ -253,7 +253,9 @@ int dfa_profile_read(dfa_kernel_time *out, int cap, int *count);
  * dfa_kernel_time.name, e.g. "k_signature"): the other kernels run without
  * events, so the timed region is barely disturbed.  NULL or "" times every
  * round kernel again.  Kept across dfa_profile_enable calls.  DFA_EINVAL for
- * a name of 32 characters or more. */
+ * a name of 32 characters or more.  "k_group_part" is the grouping by buckets
+ * of the first table round, otherwise reported within "k_insert": its states
+ * are those that buckets grouped, zero if the table did the round. */
 int dfa_profile_only(const char *name);
 
 /*

@@ -443,6 +443,8 @@ uint32_t kern_bytes(Kern kind, uint32_t k_eff) {
     }
 }
 
+constexpr const char *kGroupPartName = "k_group_part";
+
 const char *kern_name(Kern kind) {
     switch (kind) {
         case Kern::Mark: return "k_mark";
@@ -465,11 +467,20 @@ const char *kern_name(Kern kind) {
     }
 }
 
+// The name that a timed kernel is reported by: kern_name, but for the bucket
+// grouping timed by itself, which tells it from the table that it stands in
+// for (launches without work count no states there).
+const char *timed_name(const Ctx &c, Kern kind) {
+    if (kind == Kern::GroupPart && c.prof_only == kGroupPartName) return kGroupPartName;
+    return kern_name(kind);
+}
+
 // Launches one round kernel, bracketed by events when timing is on.
 template <class Args>
 int launch_kern(Ctx &c, Kern kind, const Args &a, uint32_t round) {
     size_t e0 = 0, e1 = 0;
-    const bool timed = c.profiling && (c.prof_only.empty() || c.prof_only == kern_name(kind));
+    const char *name = timed_name(c, kind);
+    const bool timed = c.profiling && (c.prof_only.empty() || c.prof_only == name);
     if (timed) {
         DFA_TRY(prof_event(c, e0));
         HIP_TRY(hipEventRecord(c.evpool[e0], c.stream));
@@ -502,7 +513,7 @@ int launch_kern(Ctx &c, Kern kind, const Args &a, uint32_t round) {
     if (timed) {
         DFA_TRY(prof_event(c, e1));
         HIP_TRY(hipEventRecord(c.evpool[e1], c.stream));
-        c.pending.push_back({kern_name(kind), e0, e1, round, kern_bytes(kind, a.k_eff), a.k_eff,
+        c.pending.push_back({name, e0, e1, round, kern_bytes(kind, a.k_eff), a.k_eff,
                              kind == Kern::SignaturePart || kind == Kern::GroupPart});
     }
     return DFA_OK;
@@ -560,7 +571,8 @@ int prof_collect(Ctx &c, const RoundCtl &ctl) {
         // (and so do the two ways of grouping the first table round)
         const bool part = ((ctl.part_rounds >> (p.round % 64)) & 1ull) != 0;
         const bool grouping = std::strcmp(p.name, "k_signature_pb") == 0 ||
-                              std::strcmp(p.name, "k_insert") == 0;
+                              std::strcmp(p.name, "k_insert") == 0 ||
+                              std::strcmp(p.name, kGroupPartName) == 0;
         const bool did_work =
             !((sig && pb) || (pass && !pb) || (grouping && p.buckets != part));
         if (did_work && p.round < ctl.round && ctl.round - p.round <= kActiveHist) {
