@@ -210,6 +210,7 @@ struct PbArgs {
     unsigned long long *gfill;  // four 16-bit fills to a word, kGroupStride words apart
     uint32_t *gover;
     uint32_t *gsample;  // gbuckets words: a sample's states in each bucket
+    uint32_t gskew;     // more of them in one: the table does the round
 };
 // Grouping by buckets: a bucket's entries are grouped by one workgroup in an
 // LDS table of kGroupSlots slots, so it holds fewer, and on average at most
@@ -218,6 +219,7 @@ constexpr uint32_t kGroupSlots = 16384;
 constexpr uint32_t kGroupMean = 8192;
 constexpr uint32_t kGroupStride = 8;  // counters on 64-byte lines of their own
 constexpr uint32_t kGroupMaxBuckets = 1024;
+constexpr uint32_t kPartSample = 16384;  // states that are hashed beforehand
 struct SortPlan {
     uint32_t sort_tiles, compact_tiles, hist_blocks, run_blocks;
     uint64_t hist_words, partial_words;

@@ -584,12 +584,11 @@ __device__ __forceinline__ uint64_t part_hash(const uint32_t *w) {
 
 // Whether buckets are worth it: the marking kernel of the first table round,
 // which has nothing to mark, hashes 16,384 states spread over the index space
-// into their buckets, and one with twice its share of the sample stops the
-// pass before it starts.  (The sample has 16 or more states for a bucket of
-// the mean size; twice that is 4 standard deviations and more.)  Without it inputs
+// into their buckets, and one with more than gskew of them (see
+// group_sample_limit) stops the pass before it starts.  Without it inputs
 // with a few frequent keys paid for most of a pass: 3 million states, 4
 // letters, one state in 20 accepting, 870 -> 930 us; 881 with it.
-constexpr uint32_t kPartSample = 16384, kPartSampleGroups = 64;
+constexpr uint32_t kPartSampleGroups = 64;
 
 template <int KC>
 __device__ __forceinline__ void part_sample(const SigParams &p) {
@@ -622,7 +621,7 @@ __device__ __forceinline__ void part_sample(const SigParams &p) {
 __device__ __forceinline__ void part_judge(const PbArgs &pb) {
     bool over = false;
     for (uint32_t b = threadIdx.x; b < pb.gbuckets; b += blockDim.x)
-        over |= pb.gsample[b] * static_cast<uint64_t>(pb.gbuckets) > 2 * kPartSample;
+        over |= pb.gsample[b] > pb.gskew;
     if (over) *pb.gover = 1;  // (every writer stores the same)
 }
 

@@ -93,3 +93,18 @@ def test_a_fill_outgrows_its_16_bits():
     d.delta[at] = rows
     d.accepting[at] = accepting
     assert grouped_by_buckets(d) == 0
+
+
+@pytest.mark.parametrize("n,k,seed", [(4_200_000, 4, 3), (4_200_000, 4, 6), (4_200_000, 4, 29),
+                                      (4_300_007, 3, 5), (4_300_007, 3, 39)])
+def test_the_sample_lets_spread_keys_through(n, k, seed):
+    """1,024 buckets have 16 states of the sample each: some bucket of these
+    inputs has more than twice that by chance."""
+    d = W.random_dfa(n, k, 0.3, seed)
+    assert grouped_by_buckets(d, check=False) == n
+    buckets = B.minimise(d.delta, d.accepting, tc="off")
+    B.set_tuning(slice_min_states=0)
+    table = B.minimise(d.delta, d.accepting, tc="off")
+    np.testing.assert_array_equal(buckets.block, table.block)
+    assert [buckets.stats[s] for s in ("num_blocks", "rounds", "changing_rounds")] == \
+        [table.stats[s] for s in ("num_blocks", "rounds", "changing_rounds")]
