@@ -2653,6 +2653,17 @@ uint32_t small_cutoff(Ctx &c) {
     return cut;
 }
 
+// Jobs of few states per CU from which workgroups of few threads take them.
+// Up to that, large workgroups have the jobs done in few turns, and a second
+// launch would wait for the first; beyond, the jobs that share a CU count.
+// Measured on MI355X, large against small workgroups, minimisation of jobs of
+// 64 states: 300 jobs 84 us against 113, 1,400 jobs 151 against 124, 20,000
+// jobs 1,490 against 770; 3,000 jobs of 500 states 317 against 195.  20,000
+// jobs took 795 us before large workgroups; a job of 4,096 states beside
+// 10,000 of 64 (whose LDS every workgroup had): 742 us in one launch, 445 in
+// two, 466 before.
+constexpr uint32_t kSmallFewJobs = 4;
+
 // Queues the small jobs (one workgroup each, largest first); their results
 // are read back by finish_small_jobs after the stream is synchronised.
 int launch_small_jobs(Ctx &c, std::vector<SmallJob> &jobs, uint32_t slots, uint32_t *out_dev,
@@ -2660,23 +2671,42 @@ int launch_small_jobs(Ctx &c, std::vector<SmallJob> &jobs, uint32_t slots, uint3
     std::sort(jobs.begin(), jobs.end(), [](const SmallJob &x, const SmallJob &y) {
         return x.na + x.nb > y.na + y.nb;
     });
-    // LDS for every job with its transitions, as far as a workgroup can have it
-    uint32_t lds = 0;
     int cus = 0, limit = 0;
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c.device));
     HIP_TRY(hipDeviceGetAttribute(&limit, hipDeviceAttributeMaxSharedMemoryPerBlock, c.device));
-    for (const SmallJob &j : jobs) {
-        const uint32_t n = j.na + j.nb, ids = small_refine_lds_bytes(n);
-        lds = std::max(lds, ids);
-        const uint32_t all = ids + small_rows_lds_bytes(n, j.k);
-        if (static_cast<int>(all) + 256 <= limit) lds = std::max(lds, all);
+    // the jobs for small workgroups, if there are enough of them
+    struct Launch {
+        uint32_t first, count, threads, lds, groups;
+    } launches[2];
+    const uint32_t all = static_cast<uint32_t>(jobs.size());
+    uint32_t few = static_cast<uint32_t>(
+        std::partition_point(jobs.begin(), jobs.end(),
+                             [](const SmallJob &j) { return j.na + j.nb > kSmallFewStates; }) -
+        jobs.begin());
+    if (all - few <= kSmallFewJobs * static_cast<uint32_t>(cus)) few = all;
+    launches[0] = {0, few, kSmallThreads, 0, 0};
+    launches[1] = {few, all - few, kSmallFewThreads, 0, 0};
+    for (Launch &l : launches) {
+        // LDS for every job with its transitions, as far as a workgroup can
+        // have it (a small one: a sixth, as six share a CU)
+        const uint32_t most =
+            static_cast<uint32_t>(l.threads == kSmallThreads ? limit : limit / 6);
+        // (sorted by size: the first job of k letters that fits takes most)
+        for (uint32_t i = l.first, seen = 0; i < l.first + l.count; ++i) {
+            if ((seen >> jobs[i].k) & 1u) continue;
+            const uint32_t n = jobs[i].na + jobs[i].nb, ids = small_refine_lds_bytes(n);
+            const uint32_t rows = ids + small_rows_lds_bytes(n, jobs[i].k);
+            if (rows + 256 <= most) seen |= 1u << jobs[i].k;
+            l.lds = std::max(l.lds, rows + 256 <= most ? rows : ids);
+        }
+        if (!l.count) continue;
+        const int fit = small_refine_max_groups(l.threads, l.lds, cus);
+        if (fit <= 0)
+            return fail(DFA_EDEVICE, "no workgroup of %u LDS bytes fits the device", l.lds);
+        l.groups = std::min<uint32_t>(l.count, static_cast<uint32_t>(fit));
     }
-    const int fit = small_refine_max_groups(lds, cus);
-    if (fit <= 0) return fail(DFA_EDEVICE, "no workgroup of %u LDS bytes fits the device", lds);
-    const uint32_t groups = std::min<uint32_t>(static_cast<uint32_t>(jobs.size()),
-                                               static_cast<uint32_t>(fit));
     DFA_TRY(c.small_jobs.ensure(jobs.size() * sizeof(SmallJob), "small jobs"));
-    DFA_TRY(c.small_ctl.ensure(sizeof(uint32_t), "small job counter"));
+    DFA_TRY(c.small_ctl.ensure(2 * sizeof(uint32_t), "small job counters"));
     // (the kernel stores the results and the target check into host memory)
     DFA_TRY(ensure_pinned(c, c.pinned_small, c.pinned_small_cap,
                           static_cast<size_t>(slots) * sizeof(SmallResult) + sizeof(uint32_t)));
@@ -2684,19 +2714,25 @@ int launch_small_jobs(Ctx &c, std::vector<SmallJob> &jobs, uint32_t slots, uint3
     uint32_t *err = reinterpret_cast<uint32_t *>(results + slots);
     HIP_TRY(hipMemcpyAsync(c.small_jobs.p, jobs.data(), jobs.size() * sizeof(SmallJob),
                            hipMemcpyHostToDevice, c.stream));
-    launch_small_refine(c.small_jobs.as<SmallJob>(), static_cast<uint32_t>(jobs.size()), groups,
-                        lds, c.small_ctl.as<uint32_t>(), out_dev, results, max_rounds, err,
-                        c.stream);
+    uint32_t *next_job = c.small_ctl.as<uint32_t>();
+    launch_small_reset(next_job, err, c.stream);
+    for (const Launch &l : launches)
+        if (l.count)
+            launch_small_refine(c.small_jobs.as<SmallJob>() + l.first, l.count, l.threads, l.groups,
+                                l.lds, next_job + (&l - launches), out_dev, results, max_rounds,
+                                err, c.stream);
     HIP_TRY(hipGetLastError());
     return DFA_OK;
 }
 
 // After the stream has been synchronised: the small jobs' results (indexed
-// by DFA / pair), or the failure of their target check.
-int finish_small_jobs(Ctx &c, uint32_t slots, const SmallResult *&res) {
-    res = reinterpret_cast<const SmallResult *>(c.pinned_small);
-    if (*reinterpret_cast<const uint32_t *>(res + slots))
+// by DFA / pair), or the failure of their target check.  Copied in order: the
+// jobs go by size, and the lines that the device has written are in no cache.
+int finish_small_jobs(Ctx &c, uint32_t slots, std::vector<SmallResult> &res) {
+    const SmallResult *from = reinterpret_cast<const SmallResult *>(c.pinned_small);
+    if (*reinterpret_cast<const uint32_t *>(from + slots))
         return fail(DFA_EINVAL, "a transition target is >= n");
+    res.assign(from, from + slots);
     return DFA_OK;
 }
 
@@ -2753,7 +2789,7 @@ int minimise_batch_impl(Ctx &c, uint32_t count, const dfa_view *views, uint32_t 
         HIP_TRY(hipEventRecord(c.ev_stop, c.stream));
         HIP_TRY(stream_sync(c));
     }
-    const SmallResult *sres = nullptr;
+    std::vector<SmallResult> sres;
     if (!small.empty()) DFA_TRY(finish_small_jobs(c, count, sres));
     uint64_t transitions = 0, small_bytes = 0;
     uint32_t joint_rounds = r.rounds;
@@ -2843,7 +2879,7 @@ int equivalent_batch_impl(Ctx &c, uint32_t count, const dfa_view *a, const dfa_v
         HIP_TRY(hipEventRecord(c.ev_stop, c.stream));
         HIP_TRY(stream_sync(c));
     }
-    const SmallResult *sres = nullptr;
+    std::vector<SmallResult> sres;
     if (!small.empty()) DFA_TRY(finish_small_jobs(c, count, sres));
     uint64_t transitions = 0, small_bytes = 0;
     uint32_t joint_rounds = r.rounds;

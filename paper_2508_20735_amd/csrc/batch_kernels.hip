@@ -13,7 +13,8 @@
 // Bound by the longest job, a chain of rounds that each wait for LDS.  1,024
 // threads and transitions in LDS, instead of 256 that read them from the L2,
 // measured on MI355X: 589 DFAs of 64 to 4,096 states 198 -> 59 us, 272 pairs
-// 550 -> 152 us.
+// 550 -> 152 us.  Thousands of jobs of at most 1,024 states go to workgroups of
+// 256 threads instead, six to a CU (kSmallFewJobs in api.hip).
 //
 // Ids inside a round are the index of the state that first claimed its
 // signature's slot; the final ids are made canonical (smallest member) in
@@ -70,12 +71,11 @@ struct SmallRows {
     }
 };
 
-template <int KC>
+template <int KC, uint32_t NT>
 __device__ __forceinline__ void small_job(const SmallJob &J, uint8_t *lds, uint32_t lds_bytes,
                                           uint32_t *claims, uint32_t max_rounds,
                                           uint32_t *out_blocks, SmallResult *results,
                                           uint32_t *err) {
-    constexpr uint32_t NT = kSmallThreads;
     const uint32_t tx = threadIdx.x, n = J.na + J.nb, T = small_table_slots(n);
     // LDS: table (T words), two id arrays of n halves, the rows
     uint32_t *table = reinterpret_cast<uint32_t *>(lds);
@@ -199,13 +199,14 @@ __device__ __forceinline__ void small_job(const SmallJob &J, uint8_t *lds, uint3
     __syncthreads();
 }
 
-__global__ __launch_bounds__(kSmallThreads) void k_small_refine(const SmallJob *__restrict__ jobs,
-                                                                uint32_t njobs, uint32_t *next_job,
-                                                                uint32_t *out_blocks,
-                                                                SmallResult *results,
-                                                                uint32_t max_rounds,
-                                                                uint32_t *err,
-                                                                uint32_t lds_bytes) {
+// (1,024 threads: registers for two workgroups a CU, with a few words spilled;
+// small workgroups have six a CU without that)
+template <uint32_t NT>
+__global__ __launch_bounds__(NT, NT == kSmallThreads ? 8 : 1) void k_small_refine(const SmallJob *__restrict__ jobs,
+                                                     uint32_t njobs, uint32_t *next_job,
+                                                     uint32_t *out_blocks, SmallResult *results,
+                                                     uint32_t max_rounds, uint32_t *err,
+                                                     uint32_t lds_bytes) {
     extern __shared__ __align__(16) uint8_t lds[];
     __shared__ uint32_t job_id, claims[2];
     for (;;) {
@@ -216,19 +217,19 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_refine(const SmallJob *
         if (j >= njobs) return;
         const SmallJob J = jobs[j];
         if (J.k <= 2)
-            small_job<2>(J, lds, lds_bytes, claims, max_rounds, out_blocks, results, err);
+            small_job<2, NT>(J, lds, lds_bytes, claims, max_rounds, out_blocks, results, err);
         else if (J.k <= 4)
-            small_job<4>(J, lds, lds_bytes, claims, max_rounds, out_blocks, results, err);
+            small_job<4, NT>(J, lds, lds_bytes, claims, max_rounds, out_blocks, results, err);
         else if (J.k <= 8)
-            small_job<8>(J, lds, lds_bytes, claims, max_rounds, out_blocks, results, err);
+            small_job<8, NT>(J, lds, lds_bytes, claims, max_rounds, out_blocks, results, err);
         else
-            small_job<16>(J, lds, lds_bytes, claims, max_rounds, out_blocks, results, err);
+            small_job<16, NT>(J, lds, lds_bytes, claims, max_rounds, out_blocks, results, err);
     }
 }
 
-__global__ void k_small_counter_reset(uint32_t *next_job, uint32_t *err) {
+__global__ void k_small_reset(uint32_t *next_job, uint32_t *err) {
     if (threadIdx.x == 0 && blockIdx.x == 0) {
-        *next_job = 0;
+        next_job[0] = next_job[1] = 0;
         *err = 0;
     }
 }
@@ -243,21 +244,31 @@ uint32_t small_rows_lds_bytes(uint32_t n, uint32_t k) {
     return n * 2u * (k <= 2 ? 2u : k <= 4 ? 4u : k <= 8 ? 8u : 16u);
 }
 
-int small_refine_max_groups(uint32_t lds_bytes, int device_cus) {
+int small_refine_max_groups(uint32_t threads, uint32_t lds_bytes, int device_cus) {
     int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_small_refine, kSmallThreads,
-                                                     lds_bytes) != hipSuccess ||
-        per_cu <= 0)
-        return 0;
-    return per_cu * device_cus;
+    const hipError_t e =
+        threads == kSmallThreads
+            ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_small_refine<kSmallThreads>,
+                                                           kSmallThreads, lds_bytes)
+            : hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                  &per_cu, k_small_refine<kSmallFewThreads>, kSmallFewThreads, lds_bytes);
+    return e == hipSuccess && per_cu > 0 ? per_cu * device_cus : 0;
 }
 
-void launch_small_refine(const SmallJob *jobs, uint32_t njobs, uint32_t groups, uint32_t lds_bytes,
-                         uint32_t *next_job, uint32_t *out_blocks, SmallResult *results,
+void launch_small_reset(uint32_t *next_job, uint32_t *err, hipStream_t s) {
+    launch_kernel(k_small_reset, dim3(1), dim3(64), 0, s, next_job, err);
+}
+
+void launch_small_refine(const SmallJob *jobs, uint32_t njobs, uint32_t threads, uint32_t groups,
+                         uint32_t lds_bytes, uint32_t *next_job, uint32_t *out_blocks, SmallResult *results,
                          uint32_t max_rounds, uint32_t *err, hipStream_t s) {
-    launch_kernel(k_small_counter_reset, dim3(1), dim3(64), 0, s, next_job, err);
-    launch_kernel(k_small_refine, dim3(groups), dim3(kSmallThreads), lds_bytes, s, jobs, njobs,
-                  next_job, out_blocks, results, max_rounds, err, lds_bytes);
+    if (threads == kSmallThreads)
+        launch_kernel(k_small_refine<kSmallThreads>, dim3(groups), dim3(kSmallThreads), lds_bytes,
+                      s, jobs, njobs, next_job, out_blocks, results, max_rounds, err, lds_bytes);
+    else
+        launch_kernel(k_small_refine<kSmallFewThreads>, dim3(groups), dim3(kSmallFewThreads),
+                      lds_bytes, s, jobs, njobs, next_job, out_blocks, results, max_rounds, err,
+                      lds_bytes);
 }
 
 }  // namespace dfamin

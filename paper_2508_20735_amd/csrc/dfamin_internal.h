@@ -643,6 +643,11 @@ void launch_quotient_identity(const uint32_t *delta, const uint8_t *acc, uint32_
 // the disjoint union of two DFAs with the same k (equivalence: the verdict).
 // States are local: DFA a's are 0 .. na-1, DFA b's follow.
 constexpr uint32_t kSmallThreads = 1024;  // threads of a job's workgroup
+// The same where jobs of at most kSmallFewStates states fill the device: a
+// round of such a job has work for few waves, and smaller workgroups leave a
+// CU room for six jobs instead of one or two.
+constexpr uint32_t kSmallFewThreads = 256;
+constexpr uint32_t kSmallFewStates = 1024;
 constexpr uint32_t kSmallMaxK = 16;      // letters of a job
 constexpr uint32_t kSmallMaxStates = 16384;  // states of a job (ids are 16-bit)
 struct SmallJob {
@@ -661,13 +666,16 @@ uint32_t small_refine_lds_bytes(uint32_t n);
 // What its transitions take there besides (they are read from memory where a
 // job's total is more than the launch has).
 uint32_t small_rows_lds_bytes(uint32_t n, uint32_t k);
-// Workgroups that fit on the device at once with that much LDS (0: none).
-int small_refine_max_groups(uint32_t lds_bytes, int device_cus);
+// Workgroups (of kSmallThreads or kSmallFewThreads) that fit on the device at
+// once with that much LDS (0: none).
+int small_refine_max_groups(uint32_t threads, uint32_t lds_bytes, int device_cus);
+// Clears two job counters and *err.
+void launch_small_reset(uint32_t *next_job, uint32_t *err, hipStream_t s);
 // Refines every job (largest first: jobs sorted by size, taken from a
-// counter); *err = 1 if some target is out of range; results[job.index].  The
-// results and *err may lie in page-locked host memory.
-void launch_small_refine(const SmallJob *jobs, uint32_t njobs, uint32_t groups, uint32_t lds_bytes,
-                         uint32_t *next_job, uint32_t *out_blocks, SmallResult *results,
+// counter, zero before); *err = 1 if some target is out of range;
+// results[job.index].  The results and *err may lie in page-locked host memory.
+void launch_small_refine(const SmallJob *jobs, uint32_t njobs, uint32_t threads, uint32_t groups,
+                         uint32_t lds_bytes, uint32_t *next_job, uint32_t *out_blocks, SmallResult *results,
                          uint32_t max_rounds, uint32_t *err, hipStream_t s);
 
 // ---- product exploration (product_kernels.hip) ----
