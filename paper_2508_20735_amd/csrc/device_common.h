@@ -95,14 +95,17 @@ __device__ __forceinline__ bool rows_equal(const uint32_t *__restrict__ sig, siz
                                            size_t b) {
     const uint32_t *ra = sig + a * W;
     const uint32_t *rb = sig + b * W;
-    // eight words at a time: their loads are in flight together
+    // eight words at a time: their loads are in flight together, and none
+    // is past the row (W is uniform)
     for (size_t i = 0; i < W; i += 8) {
         uint32_t va[8], vb[8];
 #pragma unroll
         for (size_t j = 0; j < 8; ++j) {
-            const size_t at = i + j < W ? i + j : W - 1;
-            va[j] = ra[at];
-            vb[j] = rb[at];
+            va[j] = vb[j] = 0;
+            if (i + j < W) {
+                va[j] = ra[i + j];
+                vb[j] = rb[i + j];
+            }
         }
         bool eq = true;
 #pragma unroll

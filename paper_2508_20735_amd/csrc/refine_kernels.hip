@@ -153,6 +153,30 @@ __device__ __forceinline__ unsigned long long load_entry(const unsigned long lon
                   : __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The same grouping with two states per thread (tiles of 2 * kBlock
+// states) and the signature width known at compile time (KC = k_eff > 0):
+// the reads of both states' rows, their holders' rows and their hashes are
+// in flight together, and the probes of the two states' tile leaders are
+// issued one after the other without waiting in between (the kernel is
+// bound by the latency of these dependent random reads).
+template <int KC>
+__device__ __forceinline__ bool rows_equal_fixed(const uint32_t *__restrict__ sig, size_t a,
+                                                 size_t b) {
+    constexpr int W = KC + 1;
+    const uint32_t *ra = sig + a * W;
+    const uint32_t *rb = sig + b * W;
+    uint32_t va[W], vb[W];
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+        va[i] = ra[i];
+        vb[i] = rb[i];
+    }
+    bool eq = true;
+#pragma unroll
+    for (int i = 0; i < W; ++i) eq &= va[i] == vb[i];
+    return eq;
+}
+
 // Finds the slot holding q's signature or claims an empty one for it.
 // Entry = (epoch:8 | tag:24) << 32 | representative; entries of older
 // epochs count as empty.  Lock-free: a slot only ever changes from "empty" to
@@ -161,6 +185,7 @@ __device__ __forceinline__ unsigned long long load_entry(const unsigned long lon
 // value; the CAS then fails and returns the value actually stored, which is
 // examined next without reading the cache again.  The load factor stays
 // <= 1/2, so the probe always reaches an empty slot.
+template <int KC>
 __device__ __forceinline__ uint32_t find_or_claim(unsigned long long *table, uint64_t mask,
                                                   uint32_t epoch, uint64_t h, uint32_t self,
                                                   const uint32_t *sig, size_t W, bool cached,
@@ -181,7 +206,7 @@ __device__ __forceinline__ uint32_t find_or_claim(unsigned long long *table, uin
         }
         if (static_cast<uint32_t>(e >> 32) == tag) {
             const uint32_t rep = static_cast<uint32_t>(e);
-            if (rows_equal(sig, W, self, rep)) {
+            if (KC > 0 ? rows_equal_fixed<KC>(sig, self, rep) : rows_equal(sig, W, self, rep)) {
                 claimed = false;
                 return rep;
             }
@@ -1925,7 +1950,7 @@ __device__ __forceinline__ void insert_body(const InsParams &p) {
                 mark_multi(p.multi, x, r + 1);
             } else if (all || x != q) {
                 bool claimed = false;
-                const uint32_t id = find_or_claim(p.table, p.mask, epoch, p.hash[q],
+                const uint32_t id = find_or_claim<0>(p.table, p.mask, epoch, p.hash[q],
                                                   static_cast<uint32_t>(q), p.sig, p.W,
                                                   p.cached_probe != 0, claimed);
                 Y[q] = id;
@@ -2024,7 +2049,7 @@ __device__ __forceinline__ void insert_lds_body(const InsParams &p) {
         __syncthreads();
         if (grp && lead == tx) {
             bool claimed = false;
-            const uint32_t id = find_or_claim(p.table, p.mask, epoch, h, static_cast<uint32_t>(q),
+            const uint32_t id = find_or_claim<0>(p.table, p.mask, epoch, h, static_cast<uint32_t>(q),
                                               p.sig, p.W, p.cached_probe != 0, claimed);
             gid[tx] = id;
             if (claimed) ++blocks;
@@ -2046,30 +2071,6 @@ __device__ __forceinline__ void insert_lds_body(const InsParams &p) {
     wg_add_spread(p.counters, 1, idle);
     wg_add_spread(p.counters, 2, changed);
     wg_add_spread(p.counters, 3, blocks);
-}
-
-// The same grouping with two states per thread (tiles of 2 * kBlock
-// states) and the signature width known at compile time (KC = k_eff > 0):
-// the reads of both states' rows, their holders' rows and their hashes are
-// in flight together, and the probes of the two states' tile leaders are
-// issued one after the other without waiting in between (the kernel is
-// bound by the latency of these dependent random reads).
-template <int KC>
-__device__ __forceinline__ bool rows_equal_fixed(const uint32_t *__restrict__ sig, size_t a,
-                                                 size_t b) {
-    constexpr int W = KC + 1;
-    const uint32_t *ra = sig + a * W;
-    const uint32_t *rb = sig + b * W;
-    uint32_t va[W], vb[W];
-#pragma unroll
-    for (int i = 0; i < W; ++i) {
-        va[i] = ra[i];
-        vb[i] = rb[i];
-    }
-    bool eq = true;
-#pragma unroll
-    for (int i = 0; i < W; ++i) eq &= va[i] == vb[i];
-    return eq;
 }
 
 template <int KC>
@@ -2172,7 +2173,7 @@ __device__ __forceinline__ void insert_lds2_body(const InsParams &p) {
         for (int i = 0; i < S; ++i) {
             if (!grp[i] || lead[i] != loc[i]) continue;
             bool claimed = false;
-            const uint32_t id = find_or_claim(p.table, p.mask, epoch, h[i],
+            const uint32_t id = find_or_claim<KC>(p.table, p.mask, epoch, h[i],
                                               static_cast<uint32_t>(q[i]), p.sig, p.W,
                                               p.cached_probe != 0, claimed);
             gid[loc[i]] = id;
