@@ -812,14 +812,19 @@ int run_chunk(Ctx &c, const RoundArgs &ra, uint32_t rounds, int mode, uint32_t f
 // reports the rounds that have ended, and nothing is queued once the
 // refinement has stopped.  known: ctl holds what the device reported, without
 // a wait for the stream: the final state if the refinement has stopped (at
-// most two rounds that do nothing are still queued), else the
-// rounds so far, after all of them (drain), with their blocks, gains and
-// refined states, or as far as they have been reported.  Not known: the
-// caller reads the state back.
+// most two rounds that do nothing are still queued), else the number of
+// rounds queued; after all of them (drain), with their blocks, gains and
+// refined states, which the last one reports (launch's second argument).  Not
+// known: the caller reads the state back.
 // Rounds of 2^20 states and more are longer than the host needs to queue one,
 // so two in flight keep the device busy; of the shorter ones three.
 constexpr size_t kLongRoundStates = size_t(1) << 20;
-constexpr uint32_t kPipelinedRounds = 64;  // longer chunks are replayed from a graph
+// Longer chunks are replayed from a graph (or launched at once): what the host
+// queues ahead saves the rounds that a chunk has too many, but of a long run of
+// short rounds it costs a launch per kernel.  Measured on MI355X, 377 leader
+// rounds of 233 states: 1,910 us with 16 here, 2,050 with 64 (1,910 with chunks
+// alone); 15 rounds of 16,384 states 293 us with either (383).
+constexpr uint32_t kPipelinedRounds = 16;
 
 template <class Launch>
 int run_pipelined(Ctx &c, size_t N, uint32_t rounds, uint32_t &launched, bool drain,
@@ -845,7 +850,7 @@ int run_pipelined(Ctx &c, size_t N, uint32_t rounds, uint32_t &launched, bool dr
     for (uint32_t i = 0; i < rounds; ++i) {
         if (launched >= ahead && !reached(launched - ahead + 1)) return DFA_OK;
         if (p & kProgressDone) break;
-        DFA_TRY(launch(launched));
+        DFA_TRY(launch(launched, drain && i + 1 == rounds));
         ++launched;
     }
     HIP_TRY(hipGetLastError());
@@ -857,6 +862,7 @@ int run_pipelined(Ctx &c, size_t N, uint32_t rounds, uint32_t &launched, bool dr
     }
     ctl.round = launched;
     ctl.done = 0;
+    if (!drain) return DFA_OK;
     ctl.prev_count = host->blocks;
     ctl.active_sum = host->active_sum;
     std::memcpy(ctl.gain_hist, host->gain_hist, sizeof ctl.gain_hist);
@@ -1212,7 +1218,11 @@ int refine(Ctx &c, size_t N, uint32_t k, const dfa_options &o, uint32_t check_eq
                     (res.tc_used && !rejudged);
                 DFA_TRY(run_pipelined(
                     c, N, chunk, launched, drain,
-                    [&](uint32_t round) { return launch_full_round(c, ra, round); }, res.ctl,
+                    [&](uint32_t round, bool details) {
+                        ra.host_details = details ? 1u : 0u;
+                        return launch_full_round(c, ra, round);
+                    },
+                    res.ctl,
                     known));
             } else {
                 DFA_TRY(run_chunk(c, ra, mode == DFA_LOOP_HOST ? 1u : chunk, mode, next_round));
@@ -1361,7 +1371,11 @@ int refine_leader(Ctx &c, size_t N, uint32_t k, const dfa_options &o, uint32_t c
                                launched + chunk >= kStallRounds;
             DFA_TRY(run_pipelined(
                 c, N, chunk, launched, drain,
-                [&](uint32_t round) { return launch_full_round(c, la, round); }, res.ctl, known));
+                [&](uint32_t round, bool details) {
+                    la.host_details = details ? 1u : 0u;
+                    return launch_full_round(c, la, round);
+                },
+                res.ctl, known));
         } else {
             DFA_TRY(run_chunk(c, none, mode == DFA_LOOP_HOST ? 1u : chunk, mode, last_round, &la));
         }

@@ -127,39 +127,51 @@ struct ColPtrs {
     }
 };
 
-// Tells the host (page-locked memory) that a round has ended: the number of
-// rounds, blocks and the round's gain, and once the refinement has stopped
-// also the whole round state.
-// Every thread of the workgroup calls it, after ctl has been written by
-// thread 0 (behind a barrier).  The stores bypass the caches, so waiting for
-// them orders them; a system-scope release would write back the XCD's L2 as
-// well, which cost 5 us a round.
+// What the end of a round leaves: whether the round ran, and (in thread 0) the
+// rounds so far and whether the refinement has stopped.
+struct RoundOutcome {
+    bool ran, done;
+    uint32_t rounds;
+};
+
 __device__ __forceinline__ void wait_for_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-__device__ __forceinline__ void report_round(const RoundCtl *ctl, HostProgress *host) {
+// Tells the host (page-locked memory) that a round has ended: the number of
+// rounds; with details, first the blocks and gains so far; once the refinement
+// has stopped, the whole round state.
+// Every thread of the workgroup calls it, after ctl has been written by
+// thread 0.  The stores bypass the caches, so waiting for them orders them; a
+// system-scope release would write back the XCD's L2 as well, which cost 5 us
+// a round.  The wait itself is a round trip to the host's memory, 1.5 us: it is
+// left to the rounds that have something to order.
+__device__ __forceinline__ void report_round(const RoundCtl *ctl, HostProgress *host,
+                                             uint32_t details, const RoundOutcome &o) {
     if (!host) return;
-    const bool done = ctl->done != 0;
+    const bool done = __syncthreads_or(o.done) != 0;
     if (done) {
         constexpr uint32_t words = sizeof(RoundCtl) / sizeof(uint32_t);
         const uint32_t *src = reinterpret_cast<const uint32_t *>(ctl);
         uint32_t *dst = reinterpret_cast<uint32_t *>(&host->ctl);
         for (uint32_t i = threadIdx.x; i < words; i += blockDim.x)
             __hip_atomic_store(dst + i, src[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    } else if (details) {
+        for (uint32_t i = threadIdx.x; i < kActiveHist; i += blockDim.x)
+            __hip_atomic_store(&host->gain_hist[i], ctl->gain_hist[i], __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_SYSTEM);
+        if (threadIdx.x == 0) {
+            __hip_atomic_store(&host->blocks, ctl->prev_count, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_SYSTEM);
+            __hip_atomic_store(&host->active_sum, ctl->active_sum, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+    }
+    if (done || details) {
         wait_for_stores();
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        const uint32_t last = (ctl->round - 1) % kActiveHist;
-        __hip_atomic_store(&host->blocks, ctl->prev_count, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_SYSTEM);
-        __hip_atomic_store(&host->active_sum, ctl->active_sum, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_SYSTEM);
-        __hip_atomic_store(&host->gain_hist[last], ctl->gain_hist[last], __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_SYSTEM);
-        wait_for_stores();
-        __hip_atomic_store(&host->progress, ctl->round | (done ? kProgressDone : 0u),
+    if (threadIdx.x == 0)
+        __hip_atomic_store(&host->progress, o.rounds | (done ? kProgressDone : 0u),
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    }
 }
 
 // Marks block `id` as having two or more members after round r.

@@ -86,13 +86,14 @@ struct RoundCtl {
 };
 
 // What the device tells the host while rounds run, in page-locked host memory:
-// the rounds that have ended, with what the host's decisions between rounds
-// need, kProgressDone with the last one, and then the whole round state.  The
-// host queues rounds a few ahead of it and stops when the refinement has.
+// the rounds that have ended, kProgressDone with the last one, and then the
+// whole round state.  The host queues rounds a few ahead of it and stops when
+// the refinement has.  A round before a decision of the host's (host_details)
+// first stores what that needs.
 constexpr uint32_t kProgressDone = 1u << 31;
 struct HostProgress {
     uint32_t progress;
-    uint32_t blocks;                 // after the last round
+    uint32_t blocks;                 // after the last round with details
     unsigned long long active_sum;   // refined states over the rounds
     uint32_t gain_hist[kActiveHist]; // blocks added by round r, at r % kActiveHist
     RoundCtl ctl;
@@ -269,6 +270,8 @@ struct RoundArgs {
     uint16_t *segpat;
     uint32_t segpat_bits;
     HostProgress *host;  // nullptr: rounds end without telling the host
+    uint32_t host_details;  // 1: the round also reports what decisions between rounds need
+    uint32_t pad;
     uint32_t first_table_round;  // the round that pb's buckets group
     uint32_t spread;     // 1: signature tiles go round the XCDs instead of in eighths
 };
@@ -514,6 +517,7 @@ struct LeaderArgs {
     uint32_t *counters;  // kSpread * kSpreadStride words, zero between rounds
     RoundCtl *ctl;
     HostProgress *host;  // nullptr: rounds end without telling the host
+    uint32_t host_details, pad2;  // (as in RoundArgs)
 };
 // Initial leaders: block[q] = smallest accepting or smallest rejecting state
 // of q's class, from the acceptance bits; lead: 2 words preset to all ones.

@@ -172,10 +172,11 @@ __device__ __forceinline__ void leader_move_body(const LeaderArgs &a) {
     wg_add_spread(a.counters, 1, moved);
 }
 
-__device__ __forceinline__ void leader_end_body(RoundCtl *ctl, const uint32_t *block,
-                                                uint32_t *counters) {
+// (every thread has read the flag when thread 0 comes to write it)
+__device__ __forceinline__ RoundOutcome leader_end_body(RoundCtl *ctl, const uint32_t *block,
+                                                        uint32_t *counters) {
     __shared__ uint32_t red[3][kBlock / 64];
-    if (ctl->done) return;
+    if (ctl->done) return {};
     uint32_t v[3] = {0, 0, 0};
     for (uint32_t i = threadIdx.x; i < kSpread; i += kBlock)
         for (int w = 0; w < 3; ++w) {
@@ -188,7 +189,8 @@ __device__ __forceinline__ void leader_end_body(RoundCtl *ctl, const uint32_t *b
     if (lane_id() == 0)
         for (int w = 0; w < 3; ++w) red[w][threadIdx.x / 64] = v[w];
     __syncthreads();
-    if (threadIdx.x != 0) return;
+    RoundOutcome o{true, false, 0};
+    if (threadIdx.x != 0) return o;
     for (int w = 0; w < 3; ++w) {
         v[w] = 0;
         for (int i = 0; i < kBlock / 64; ++i) v[w] += red[w][i];
@@ -203,20 +205,23 @@ __device__ __forceinline__ void leader_end_body(RoundCtl *ctl, const uint32_t *b
     ctl->gain_hist[r % kActiveHist] = fresh;
     if (moved == 0) {
         ctl->stable = 1;
-        ctl->done = 1;
+        o.done = true;
     } else {
         ctl->changing += 1;
         ctl->prev_count += fresh;
     }
     if (ctl->check_eq && block[ctl->eq_a] != block[ctl->eq_b]) {
         ctl->separated = 1;
-        ctl->done = 1;
+        o.done = true;
     }
     ctl->round = r + 1;
-    if (!ctl->done && ctl->max_rounds && r + 1 >= ctl->max_rounds) {
+    if (!o.done && ctl->max_rounds && r + 1 >= ctl->max_rounds) {
         ctl->limit = 1;
-        ctl->done = 1;
+        o.done = true;
     }
+    if (o.done) ctl->done = 1;
+    o.rounds = r + 1;
+    return o;
 }
 
 __global__ __launch_bounds__(kBlock) void k_leader_elect(LeaderArgs a) { leader_elect_body(a); }
@@ -224,13 +229,10 @@ __global__ __launch_bounds__(kBlock) void k_leader_elect(LeaderArgs a) { leader_
 __global__ __launch_bounds__(kBlock) void k_leader_move(LeaderArgs a) { leader_move_body(a); }
 
 __global__ __launch_bounds__(kBlock) void k_leader_end(RoundCtl *ctl, const uint32_t *block,
-                                                       uint32_t *counters, HostProgress *host) {
-    const bool over = ctl->done != 0;
-    __syncthreads();  // every thread has read the flag before it is written
-    if (over) return;
-    leader_end_body(ctl, block, counters);
-    __syncthreads();
-    report_round(ctl, host);
+                                                       uint32_t *counters, HostProgress *host,
+                                                       uint32_t details) {
+    const RoundOutcome o = leader_end_body(ctl, block, counters);
+    if (o.ran) report_round(ctl, host, details, o);
 }
 
 // Persistent loop of leader rounds: the three phases of a round separated by
@@ -288,7 +290,7 @@ void launch_leader_move(const LeaderArgs &a, hipStream_t s) {
 
 void launch_leader_end(const LeaderArgs &a, hipStream_t s) {
     launch_kernel(k_leader_end, dim3(1), dim3(kBlock), 0, s, a.ctl, a.block, a.counters,
-                  a.host);
+                  a.host, a.host_details);
 }
 
 void launch_leader_round(const LeaderArgs &a, hipStream_t s) {

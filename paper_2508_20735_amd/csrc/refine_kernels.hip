@@ -2405,12 +2405,13 @@ __global__ __launch_bounds__(kBlock) void k_closure_round(SigParams p, InsParams
 
 // One workgroup: the round's block count (spread counters), the stop tests,
 // and the counter reset.
-__device__ __forceinline__ void round_end_body(RoundCtl *ctl, const uint32_t *blockA,
-                                               const uint32_t *blockB, uint32_t *counters,
-                                               uint32_t N) {
+// (every thread has read the flag when thread 0 comes to write it)
+__device__ __forceinline__ RoundOutcome round_end_body(RoundCtl *ctl, const uint32_t *blockA,
+                                                       const uint32_t *blockB, uint32_t *counters,
+                                                       uint32_t N) {
     constexpr int kWords = 4;  // blocks, idle states, changed ids, claims
     __shared__ uint32_t red[kWords][kBlock / 64];
-    if (ctl->done) return;
+    if (ctl->done) return {};
     const uint32_t r = ctl->round;
     uint32_t v[kWords] = {0, 0, 0, 0};
     for (uint32_t i = threadIdx.x; i < kSpread; i += kBlock)
@@ -2424,7 +2425,8 @@ __device__ __forceinline__ void round_end_body(RoundCtl *ctl, const uint32_t *bl
     if (lane_id() == 0)
         for (int w = 0; w < kWords; ++w) red[w][threadIdx.x / 64] = v[w];
     __syncthreads();
-    if (threadIdx.x != 0) return;
+    RoundOutcome o{true, false, 0};
+    if (threadIdx.x != 0) return o;
     for (int w = 0; w < kWords; ++w) {
         v[w] = 0;
         for (int i = 0; i < kBlock / 64; ++i) v[w] += red[w][i];
@@ -2440,20 +2442,23 @@ __device__ __forceinline__ void round_end_body(RoundCtl *ctl, const uint32_t *bl
     ctl->gain_hist[r % kActiveHist] = c - ctl->prev_count;
     if (c == ctl->prev_count) {
         ctl->stable = 1;
-        ctl->done = 1;
+        o.done = true;
     } else {
         ctl->changing += 1;
         ctl->prev_count = c;
     }
     if (ctl->check_eq && out[ctl->eq_a] != out[ctl->eq_b]) {
         ctl->separated = 1;
-        ctl->done = 1;
+        o.done = true;
     }
     ctl->round = r + 1;
-    if (!ctl->done && ctl->max_rounds && r + 1 >= ctl->max_rounds) {
+    if (!o.done && ctl->max_rounds && r + 1 >= ctl->max_rounds) {
         ctl->limit = 1;
-        ctl->done = 1;
+        o.done = true;
     }
+    if (o.done) ctl->done = 1;
+    o.rounds = r + 1;
+    return o;
 }
 
 // The round kernels: one launch per phase (host, chunk and graph loops).
@@ -2476,13 +2481,10 @@ __global__ __launch_bounds__(kBlock) void k_insert_lds2(InsParams p) { insert_ld
 
 __global__ __launch_bounds__(kBlock) void k_round_end(RoundCtl *ctl, const uint32_t *blockA,
                                                        const uint32_t *blockB, uint32_t *counters,
-                                                       uint32_t N, HostProgress *host) {
-    const bool over = ctl->done != 0;
-    __syncthreads();  // every thread has read the flag before it is written
-    if (over) return;
-    round_end_body(ctl, blockA, blockB, counters, N);
-    __syncthreads();
-    report_round(ctl, host);
+                                                       uint32_t N, HostProgress *host,
+                                                       uint32_t details) {
+    const RoundOutcome o = round_end_body(ctl, blockA, blockB, counters, N);
+    if (o.ran) report_round(ctl, host, details, o);
 }
 
 
@@ -3353,7 +3355,7 @@ void launch_ctl_resume(RoundCtl *ctl, hipStream_t s) {
 
 void launch_round_end(const RoundArgs &a, hipStream_t s) {
     launch_kernel(k_round_end, dim3(1), dim3(kBlock), 0, s, a.ctl, a.blockA, a.blockB,
-                       a.counters, static_cast<uint32_t>(a.N), a.host);
+                       a.counters, static_cast<uint32_t>(a.N), a.host, a.host_details);
 }
 
 void launch_pattern_kernel(const RoundArgs &a, hipStream_t s) {
