@@ -1025,9 +1025,26 @@ constexpr uint32_t kPbScatterThreads = 2 * kBlock;
 template <int KC>
 constexpr int kPbScatterBatch = kPbBatch<KC> / 2;
 
+// Whether the wave's first states have a letter that takes all of them to one
+// bucket (inputs whose targets sit together, chains above all).  Their edges
+// are then added by wave_bucket_add: 64 atomics on one LDS word take turns.
+// The test is made once a batch, since those of each edge would keep the
+// batch's atomics from being in flight together (inputs whose targets are
+// spread, union of 2^21 states, 4 letters: scatter 26 us, 39 with a test an
+// edge).
+template <int KC>
+__device__ __forceinline__ bool wave_together(const uint32_t (&tg)[KC]) {
+    bool one = false;
+#pragma unroll
+    for (int a = 0; a < KC; ++a) {
+        const uint32_t b = tg[a] >> kPbSliceLog;
+        one |= __ballot(tg[a] == ~0u || b != __builtin_amdgcn_readfirstlane(b)) == 0;
+    }
+    return one;
+}
+
 // atomicAdd(cnt + b, 1) for the lanes with `on`, returning each one's old
-// value; when the whole wave shares a bucket (inputs whose targets sit
-// together), one atomic instead of 64 on one word.  Every lane calls it.
+// value; when the whole wave shares a bucket, one atomic.  Every lane calls it.
 __device__ __forceinline__ uint32_t wave_bucket_add(uint32_t *cnt, uint32_t b, bool on) {
     const uint32_t first = __builtin_amdgcn_readfirstlane(b);
     if (__ballot(!on || b != first) == 0) {
@@ -1059,11 +1076,19 @@ __global__ __launch_bounds__(kBlock) void k_pb_count(const uint32_t *cols, const
 #pragma unroll
                 for (int a = 0; a < KC; ++a) tg[u][a] = q < N ? colp.c[a][q] : ~0u;
             }
+            if (wave_together<KC>(tg[0])) {
+#pragma unroll
+                for (int u = 0; u < kPbBatch<KC>; ++u)
+#pragma unroll
+                    for (int a = 0; a < KC; ++a)
+                        (void)wave_bucket_add(hist, tg[u][a] >> kPbSliceLog, tg[u][a] != ~0u);
+                continue;
+            }
 #pragma unroll
             for (int u = 0; u < kPbBatch<KC>; ++u)
 #pragma unroll
                 for (int a = 0; a < KC; ++a)
-                    (void)wave_bucket_add(hist, tg[u][a] >> kPbSliceLog, tg[u][a] != ~0u);
+                    if (tg[u][a] != ~0u) atomicAdd(hist + (tg[u][a] >> kPbSliceLog), 1u);
         }
         __syncthreads();
         for (uint32_t b = threadIdx.x; b < nb; b += kBlock)
@@ -1225,12 +1250,14 @@ __device__ __forceinline__ uint32_t pb_tile_run_ids(const PbArgs &pb, uint32_t t
             delta[b] = at - start;
             if (lpos) lpos[b] = start;
         }
-        // short runs by their own thread; long ones (inputs whose targets sit
-        // together, chains above all) by the whole wave, run by run
-        constexpr uint32_t kLong = 64;
-        if (len <= kLong)
-            for (uint32_t l = 0; l < len; ++l) rid[start + l] = static_cast<uint16_t>(b);
+        // a run by its own thread; long ones (inputs whose targets sit
+        // together, chains above all) by the whole wave, run by run.  Spread
+        // targets have runs of tens to some hundreds, and those of a wave's 64
+        // threads are filled side by side.
+        constexpr uint32_t kLong = 512;
         unsigned long long lng = __ballot(len > kLong);
+        if (!lng || len <= kLong)
+            for (uint32_t l = 0; l < len; ++l) rid[start + l] = static_cast<uint16_t>(b);
         while (lng) {
             const int src = __ffsll(lng) - 1;
             lng &= lng - 1;
@@ -1301,18 +1328,27 @@ __global__ __launch_bounds__(kPbScatterThreads) void k_pb_scatter(const uint32_t
 #pragma unroll
                 for (int a = 0; a < KC; ++a) tg[u][a] = q < N ? colp.c[a][q] : ~0u;
             }
-#pragma unroll
-            for (int u = 0; u < kPbScatterBatch<KC>; ++u) {
+            auto put = [&](uint32_t e, int u, int a) {
                 const uint32_t i = i0 + u * kPbScatterThreads + tx;
+                ltl[e] = static_cast<uint16_t>(tg[u][a] & ((1u << kPbSliceLog) - 1u));
+                lsrc[e] = static_cast<uint16_t>(i * KC + a);
+            };
+            if (wave_together<KC>(tg[0])) {
 #pragma unroll
-                for (int a = 0; a < KC; ++a) {
-                    const uint32_t e =
-                        wave_bucket_add(lpos, tg[u][a] >> kPbSliceLog, tg[u][a] != ~0u);
-                    if (tg[u][a] == ~0u) continue;
-                    ltl[e] = static_cast<uint16_t>(tg[u][a] & ((1u << kPbSliceLog) - 1u));
-                    lsrc[e] = static_cast<uint16_t>(i * KC + a);
-                }
+                for (int u = 0; u < kPbScatterBatch<KC>; ++u)
+#pragma unroll
+                    for (int a = 0; a < KC; ++a) {
+                        const uint32_t e =
+                            wave_bucket_add(lpos, tg[u][a] >> kPbSliceLog, tg[u][a] != ~0u);
+                        if (tg[u][a] != ~0u) put(e, u, a);
+                    }
+                continue;
             }
+#pragma unroll
+            for (int u = 0; u < kPbScatterBatch<KC>; ++u)
+#pragma unroll
+                for (int a = 0; a < KC; ++a)
+                    if (tg[u][a] != ~0u) put(atomicAdd(lpos + (tg[u][a] >> kPbSliceLog), 1u), u, a);
         }
         __syncthreads();
         for (uint32_t j = tx; j < total; j += kPbScatterThreads) {
