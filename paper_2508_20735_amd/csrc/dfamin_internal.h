@@ -630,7 +630,7 @@ void launch_dense_marks(const uint8_t *mark, size_t n, uint32_t start, uint32_t 
 // with room for one more word): leaders numbered in increasing order
 // (dense[l], leader_of[b] = l), *num_blocks, qdelta[b*k + a] = dense id of
 // delta(l, a), qacc[b] = acc[l] as 0/1, *qstart = dense id of start.  dq: n
-// words of scratch.  With ctl (at most kScanTile tiles): only if ctl->done.
+// words of scratch.  With ctl (at most 2^19 states): only if ctl->done.
 void launch_quotient_from_tiles(const uint32_t *delta, const uint8_t *acc, uint32_t k,
                                 const uint32_t *block, uint32_t *partials, uint32_t n,
                                 uint32_t start, uint32_t *dense, uint32_t *leader_of, uint32_t *dq,
