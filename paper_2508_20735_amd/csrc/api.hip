@@ -816,9 +816,12 @@ int run_chunk(Ctx &c, const RoundArgs &ra, uint32_t rounds, int mode, uint32_t f
 // rounds queued; after all of them (drain), with their blocks, gains and
 // refined states, which the last one reports (launch's second argument).  Not
 // known: the caller reads the state back.
-// Rounds of 2^20 states and more are longer than the host needs to queue one,
-// so two in flight keep the device busy; of the shorter ones three.
-constexpr size_t kLongRoundStates = size_t(1) << 20;
+// Rounds of 2^17 states and more are longer (25 us) than the host needs to
+// queue one, so two in flight keep the device busy; of the shorter ones three.
+// One more in flight is one more that does nothing behind the last (measured on
+// MI355X with the line at 2^20, us a call: 600,000 states, 3 letters 311
+// against 303, 300,000 by sort grouping 1,680 against 1,308).
+constexpr size_t kLongRoundStates = size_t(1) << 17;
 // Longer chunks are replayed from a graph (or launched at once): what the host
 // queues ahead saves the rounds that a chunk has too many, but of a long run of
 // short rounds it costs a launch per kernel.  Measured on MI355X, 377 leader
