@@ -826,8 +826,9 @@ constexpr size_t kLongRoundStates = size_t(1) << 17;
 // queues ahead saves the rounds that a chunk has too many, but of a long run of
 // short rounds it costs a launch per kernel.  Measured on MI355X, 377 leader
 // rounds of 233 states: 1,910 us with 16 here, 2,050 with 64 (1,910 with chunks
-// alone); 15 rounds of 16,384 states 293 us with either (383).
-constexpr uint32_t kPipelinedRounds = 16;
+// alone); 15 rounds of 16,384 states 293 us with either (383); 31 rounds of 2^21
+// states, 17 of them over closure columns, 3,095 us with 16, 2,820 with 64.
+constexpr uint32_t kPipelinedRounds = 16, kPipelinedLongRounds = 64;
 
 template <class Launch>
 int run_pipelined(Ctx &c, size_t N, uint32_t rounds, uint32_t &launched, bool drain,
@@ -874,8 +875,9 @@ int run_pipelined(Ctx &c, size_t N, uint32_t rounds, uint32_t &launched, bool dr
 
 // Whether a chunk is queued round by round (run_pipelined).  Server lanes
 // wait asleep, so they do not watch the device.
-bool pipelined(const Ctx &c, uint32_t rounds, int mode) {
-    return (mode == DFA_LOOP_GRAPH || mode == DFA_LOOP_CHUNK) && rounds <= kPipelinedRounds &&
+bool pipelined(const Ctx &c, size_t N, uint32_t rounds, int mode) {
+    const uint32_t most = N >= kLongRoundStates ? kPipelinedLongRounds : kPipelinedRounds;
+    return (mode == DFA_LOOP_GRAPH || mode == DFA_LOOP_CHUNK) && rounds <= most &&
            !c.profiling && !c.blocking_sync && c.host_progress;
 }
 
@@ -1172,7 +1174,7 @@ int refine(Ctx &c, size_t N, uint32_t k, const dfa_options &o, uint32_t check_eq
             // gather directly, so a long refinement pays nothing for the passes
             if (first_chunk) ra.pb = pb;
             // (rounds replayed from a graph do not know their number)
-            if (mode == DFA_LOOP_GRAPH && !pipelined(c, chunk, mode) && !c.profiling) {
+            if (mode == DFA_LOOP_GRAPH && !pipelined(c, N, chunk, mode) && !c.profiling) {
                 ra.pb.gbuckets = 0;
                 ra.pb.gover = nullptr;
             }
@@ -1185,7 +1187,7 @@ int refine(Ctx &c, size_t N, uint32_t k, const dfa_options &o, uint32_t check_eq
                 ra.segpat = c.segpat.as<uint16_t>();
                 ra.segpat_bits = segpat_bits;
             }
-            if (watch && pipelined(c, chunk, mode)) ra.host = c.host_progress;
+            if (watch && pipelined(c, N, chunk, mode)) ra.host = c.host_progress;
             if (first) {
                 // rounds 0 (and 1) run on their own: label rounds when the
                 // signatures are short enough
@@ -1211,7 +1213,7 @@ int refine(Ctx &c, size_t N, uint32_t k, const dfa_options &o, uint32_t check_eq
             // rounds launched so far: the label rounds, then last_round onwards
             const uint32_t next_round = std::max(last_round, res.label_rounds ? res.label_rounds : 1u);
             bool known = false;
-            if (watch && pipelined(c, chunk, mode)) {
+            if (watch && pipelined(c, N, chunk, mode)) {
                 uint32_t launched = next_round;
                 // the rounds need have ended only where a decision follows:
                 // the closure switched on, or its columns judged again
@@ -1367,7 +1369,7 @@ int refine_leader(Ctx &c, size_t N, uint32_t k, const dfa_options &o, uint32_t c
         la.counters = c.counters.as<uint32_t>();
         la.ctl = ctl;
         bool known = false;
-        if (pipelined(c, chunk, mode)) {
+        if (pipelined(c, N, chunk, mode)) {
             la.host = c.host_progress;
             uint32_t launched = last_round;
             const bool drain = o.tc_mode == DFA_TC_AUTO && !res.tc_used && !tc_failed &&
