@@ -2323,14 +2323,31 @@ struct BatchResult {
 };
 
 // Whether a batch's segments may run one launch per round: the options and
-// tuning of direct_applies, without its size limit.
+// tuning of direct_applies, without its size limit.  Every part takes whole
+// tiles there: where that is more than eight times the states, and not few
+// tiles, the general path takes them (measured on MI355X, with no DFA left to
+// workgroups of its own: 20,000 pairs of 16 states 1.40 ms there, 1.81 in
+// tiles; 1,000 pairs 0.80 against 0.27; 20,000 pairs of 70 states, 3.7 times
+// padded, 2.66 against 2.19).
+constexpr uint64_t kSegdMaxPadding = 8, kSegdFewTiles = 8192;
+
+// States of a part on average from which parts are staged: below, a workgroup
+// with the ids of one part in LDS has little to do with them.  Measured on
+// MI355X, tiles against staged, minimisation of 5,000 parts of 700 states 0.84
+// ms against 1.06, 3,000 of 1,000 0.76 against 0.77, 3,000 of 1,500 1.03
+// against 0.82; pairs 3.12 against 3.13, 2.80 against 2.24, 4.33 against 2.72.
+// (20,000 pairs of 70 states 2.19 against 7.7, 2.66 in the general path.)
+constexpr uint64_t kStagedMeanStates = 896;
+
 bool batch_direct_applies(const Ctx &c, const std::vector<Part> &parts, uint32_t kmax,
                           const dfa_options &o) {
-    uint64_t tiles = 0;
+    uint64_t tiles = 0, states = 0;
     for (const Part &p : parts) {
+        states += p.n;
         tiles += (static_cast<uint64_t>(p.n) + kBlock - 1) / kBlock;
         if (p.n > (1u << 29)) return false;  // (a segment's slots are 32-bit)
     }
+    if (tiles > kSegdFewTiles && tiles * kBlock > kSegdMaxPadding * states) return false;
     return kmax <= kDirectMaxK && tiles * kBlock < 0xFFFFFFFFull &&
            o.algorithm == DFA_ALGO_SIGNATURE && o.tc_mode != DFA_TC_ON &&
            (o.loop_mode == DFA_LOOP_GRAPH || o.loop_mode == DFA_LOOP_CHUNK) && !o.chunk &&
@@ -2345,12 +2362,17 @@ int refine_batch_direct(Ctx &c, const std::vector<Part> &parts, uint32_t nseg, b
                         BatchResult &res) {
     const uint32_t nparts = static_cast<uint32_t>(parts.size());
     uint64_t tiles64 = 0, slots = 0;
-    for (const Part &p : parts) tiles64 += (static_cast<uint64_t>(p.n) + kBlock - 1) / kBlock;
+    uint64_t states = 0;
+    for (const Part &p : parts) {
+        states += p.n;
+        tiles64 += (static_cast<uint64_t>(p.n) + kBlock - 1) / kBlock;
+    }
     const uint32_t tiles = static_cast<uint32_t>(tiles64);
     const size_t N = static_cast<size_t>(tiles) * kBlock;
     // staged rounds hold the ids of a part in LDS; a workgroup takes up to
     // 8,192 states, fewer if the batch would not give every CU two of them
-    bool staged = kmax <= kStagedMaxK && N < (size_t(1) << 31);
+    bool staged = kmax <= kStagedMaxK && N < (size_t(1) << 31) &&
+                  states >= kStagedMeanStates * nparts;
     for (const Part &p : parts) staged = staged && p.n <= kStagedWindow;
     const uint32_t chunk_groups = static_cast<uint32_t>(
         std::min<size_t>(4, std::max<size_t>(1, N / (512 * size_t(kStagedGroup)))));
