@@ -2331,6 +2331,20 @@ struct BatchResult {
 // padded, 2.66 against 2.19).
 constexpr uint64_t kSegdMaxPadding = 8, kSegdFewTiles = 8192;
 
+// The largest union of a pair, and the states of a batch of few DFAs with eight
+// letters, for which tile rounds are faster than the general path, which skips
+// blocks whose members' successors kept their ids and has grouping kernels for
+// that width.  Measured on MI355X, general against tiles: one pair (renamed
+// copy) of 2 x 400,000 states, 5 to 8 letters, 1.02 to 1.13 times as long, of 2
+// x 500,000 0.97 to 1.03, of 2 x 10^6 0.69 to 0.74; with 3 and 4 letters 1.10 and
+// 1.22 of 2 x 500,000, 0.89 and 0.92 of 2 x 10^6; with 2 letters 1.08 there.
+// Minimisation, eight letters: two DFAs of 500,000 states 1.06, four 0.89, five
+// 0.90; with six or more, every XCD's tiles are of one or two segments, whose
+// tables then stay in its L2: 1.13, 1.98 for seven.
+constexpr uint64_t kSegdMaxUnion = 7u << 17, kSegdMaxUnion2 = 1u << 21;
+constexpr uint64_t kSegdFewStates = 1u << 20;
+constexpr uint32_t kSegdFewSegments = 6;
+
 // States of a part on average from which parts are staged: below, a workgroup
 // with the ids of one part in LDS has little to do with them.  Measured on
 // MI355X, tiles against staged, minimisation of 5,000 parts of 700 states 0.84
@@ -2339,15 +2353,19 @@ constexpr uint64_t kSegdMaxPadding = 8, kSegdFewTiles = 8192;
 // (20,000 pairs of 70 states 2.19 against 7.7, 2.66 in the general path.)
 constexpr uint64_t kStagedMeanStates = 896;
 
-bool batch_direct_applies(const Ctx &c, const std::vector<Part> &parts, uint32_t kmax,
-                          const dfa_options &o) {
-    uint64_t tiles = 0, states = 0;
+bool batch_direct_applies(const Ctx &c, const std::vector<Part> &parts, uint32_t nseg, bool pairs,
+                          uint32_t kmax, const dfa_options &o) {
+    uint64_t tiles = 0, states = 0, largest = 0;
     for (const Part &p : parts) {
         states += p.n;
+        if (pairs && (&p - parts.data()) % 2)
+            largest = std::max(largest, static_cast<uint64_t>(p.n) + (&p)[-1].n);
         tiles += (static_cast<uint64_t>(p.n) + kBlock - 1) / kBlock;
         if (p.n > (1u << 29)) return false;  // (a segment's slots are 32-bit)
     }
     if (tiles > kSegdFewTiles && tiles * kBlock > kSegdMaxPadding * states) return false;
+    if (largest > (kmax <= 2 ? kSegdMaxUnion2 : kSegdMaxUnion)) return false;
+    if (kmax == 8 && nseg < kSegdFewSegments && states > kSegdFewStates) return false;
     return kmax <= kDirectMaxK && tiles * kBlock < 0xFFFFFFFFull &&
            o.algorithm == DFA_ALGO_SIGNATURE && o.tc_mode != DFA_TC_ON &&
            (o.loop_mode == DFA_LOOP_GRAPH || o.loop_mode == DFA_LOOP_CHUNK) && !o.chunk &&
@@ -2598,7 +2616,7 @@ int refine_segments(Ctx &c, const std::vector<Part> &parts, uint32_t nseg, bool 
 // ev_stop recorded and the stream synchronised.
 int refine_batch(Ctx &c, const std::vector<Part> &parts, uint32_t nseg, bool pairs, uint32_t kmax,
                  const dfa_options &o, uint32_t *out_dev, BatchResult &res) {
-    if (batch_direct_applies(c, parts, kmax, o))
+    if (batch_direct_applies(c, parts, nseg, pairs, kmax, o))
         return refine_batch_direct(c, parts, nseg, pairs, kmax, o, out_dev, res);
     RefineResult r;
     SegArgs g{};

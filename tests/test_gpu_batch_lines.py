@@ -64,3 +64,20 @@ def test_padding(n, count):
     check_minimise([made[i % 40] for i in range(count)])
     pairs = [(d, other(d, i)) for i, d in enumerate(made)]
     check_pairs([pairs[i % 40] for i in range(count // 2 + 1)])
+
+
+@pytest.mark.parametrize("n", [458_752, 458_753])
+@pytest.mark.parametrize("k", [2, 3])
+def test_largest_unions(n, k):
+    """Unions of 7 * 2^17 states and two more."""
+    d = W.random_dfa(n, k, 0.3, n + k)
+    small = W.random_dfa(3000, k, 0.3, 5)
+    check_pairs([(d, W.permuted_copy(d, 3)[0]), (small, W.mutate_one(small, 4)[0]),
+                 (d, W.mutate_one(d, 5)[0])])
+
+
+@pytest.mark.parametrize("last", [209_716, 209_717])
+def test_few_large_dfas_with_eight_letters(last):
+    """2^20 states in five DFAs, and one more."""
+    check_minimise([W.random_dfa(209_715, 8, 0.3, i) for i in range(4)] +
+                   [W.random_dfa(last, 8, 0.3, 9)])
