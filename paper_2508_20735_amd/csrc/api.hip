@@ -1917,7 +1917,9 @@ int minimise_pruned(Ctx &c, Caller &caller, uint32_t n, uint32_t k, const uint32
     launch_check_targets(delta, static_cast<uint64_t>(n) * k, n, err, c.stream);
     // small frontiers: a queue expanded in one workgroup; large ones: dense
     // levels over the marks (frontier mark f, alternating 2 / 3), queued
-    // kBfsBatch at a time
+    // kBfsBatch at a time.  None behind the first launch: a search that it ends
+    // would wait for ten launches without work (2^18 states of which few are
+    // reached, 17 letters, 295 us a call against 248; others are the same)
     const uint64_t cap = bfs_narrow_cap();
     const bool never_dense = static_cast<uint64_t>(n) * k <= cap;
     bool init = true, dense = false;
@@ -1925,7 +1927,7 @@ int minimise_pruned(Ctx &c, Caller &caller, uint32_t n, uint32_t k, const uint32
     for (;;) {
         const bool from_list = !dense;
         if (from_list) launch_bfs_narrow(ra, o.start, init, c.stream);
-        if (!never_dense) {
+        if (!never_dense && !init) {
             launch_bfs_reset(ra, false, c.stream);
             if (from_list) launch_bfs_list_to_marks(ra, f, c.stream);
             uint8_t fl = f;
@@ -1940,9 +1942,12 @@ int minimise_pruned(Ctx &c, Caller &caller, uint32_t n, uint32_t k, const uint32
         DFA_TRY(read_back(c, stored, (kBfsBatch * kBfsSetWords + 1) * sizeof(uint32_t)));
         if (init && c.pinned[kBfsBatch * kBfsSetWords + 1])
             return fail(DFA_EINVAL, "a transition target is >= n");
-        init = false;
         // a narrow launch ends with an empty frontier or one that is too large
         if (from_list && c.pinned[kBfsBatch * kBfsSetWords] == 0) break;
+        if (init) {
+            init = false;
+            continue;
+        }
         uint64_t last = 0;  // marks stored by the last level that ran (>= its new states)
         for (uint32_t l = 0; l < kBfsBatch; ++l) {
             last = 0;
