@@ -891,9 +891,7 @@ bool pipelined(const Ctx &c, size_t N, uint32_t rounds, int mode) {
            !c.profiling && !c.blocking_sync && c.host_progress;
 }
 
-// Signature rounds over N states whose level-0 columns are in c.cols and
-// whose initial labels are in c.blockA (flags already written by the ingest
-// and init kernels).
+// The arguments of signature rounds over N states with the context's buffers.
 RoundArgs make_round_args(Ctx &c, const uint32_t *cols, size_t N, uint32_t k_eff, uint64_t cap,
                           int lds_stage, bool packed, const SegArgs *seg, uint32_t grouping) {
     RoundArgs ra;
@@ -941,11 +939,6 @@ RoundArgs make_round_args(Ctx &c, const uint32_t *cols, size_t N, uint32_t k_eff
     return ra;
 }
 
-// Signature rounds over N states whose level-0 columns are in c.cols and
-// whose initial labels are in c.blockA (flags already written by the ingest
-// and init kernels).  With state_ids, a partition that ends in label ids
-// (a stable partition found by a label round) gets one more table round,
-// which keeps the partition and turns the labels into state ids.
 // Buckets for the grouping of the first table round: their entries lie in the
 // buffer of the signature rows, which that round does not write then.  A
 // context that cannot allocate keeps the table, and so does a server's lane
@@ -1004,7 +997,9 @@ int build_slices(Ctx &c, const uint32_t *cols, size_t N, uint32_t k_eff, const d
     const bool width = k_eff >= 1 && (k_eff <= 8 || k_eff == 16);
     if (excluded || !width || o.loop_mode == DFA_LOOP_PERSISTENT) return DFA_OK;
     // (with one or two letters the first table round still has few keys, which
-    // share buckets: no faster at 3 million states)
+    // share buckets: no faster at 3 million states.  The passes are built for 3,
+    // 4 and 8 letters only; 5 to 7 and 16 have not been measured and keep the
+    // table.)
     group = group && (k_eff == 3 || k_eff == 4 || k_eff == 8);
     if (!c.tune.slice_min_states || N < c.tune.slice_min_states ||
         N > (static_cast<size_t>(kPbMaxBuckets) << kPbSliceLog))
@@ -1037,6 +1032,11 @@ int build_slices(Ctx &c, const uint32_t *cols, size_t N, uint32_t k_eff, const d
     return DFA_OK;
 }
 
+// Signature rounds over N states whose level-0 columns are in c.cols and
+// whose initial labels are in c.blockA (flags already written by the ingest
+// and init kernels).  With state_ids, a partition that ends in label ids
+// (a stable partition found by a label round) gets one more table round,
+// which keeps the partition and turns the labels into state ids.
 // With `resume`, the refinement goes on after res.ctl.round rounds (see
 // refine_direct) instead of starting.
 int refine(Ctx &c, size_t N, uint32_t k, const dfa_options &o, uint32_t check_eq, uint32_t eq_a,
@@ -2724,8 +2724,6 @@ int check_views(uint32_t count, const dfa_view *v, const char *name) {
     return DFA_OK;
 }
 
-// Batched minimisation on device views; out_dev receives the block ids,
-// part i at out_off[i].
 // Largest job (states) that goes to the one-workgroup path: the tuning's
 // limit, lowered to what one workgroup's LDS holds on this device.
 uint32_t small_cutoff(Ctx &c) {
@@ -2825,6 +2823,8 @@ int finish_small_jobs(Ctx &c, uint32_t slots, std::vector<SmallResult> &res) {
     return DFA_OK;
 }
 
+// Batched minimisation on device views; out_dev receives the block ids,
+// part i at out_off[i].
 int minimise_batch_impl(Ctx &c, uint32_t count, const dfa_view *views, uint32_t *out_dev,
                         const uint64_t *out_off, uint32_t *num_blocks, uint32_t *rounds,
                         const dfa_options &o, dfa_batch_stats *st) {

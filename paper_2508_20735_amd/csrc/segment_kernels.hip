@@ -13,7 +13,8 @@
 //   - a segment's block count goes to a ring of four counters; a round that
 //     finds the last two equal (stable), or a pair's start states separated,
 //     does nothing for the segment, and the segment's first tile records it.
-//     A decided segment costs its tiles one load a round.
+//     A decided segment costs its tiles three loads a round, one behind the
+//     other: the tile's part, its segment, the segment's end.
 //
 // Table entries carry a 20-bit epoch that the workspace counts on from call
 // to call, so the tables are cleared once in a million rounds.
@@ -22,9 +23,9 @@
 // table.  Measured on MI355X, 1,024 random DFAs of 64 to 65,536 states and 2 to
 // 8 letters, 9.87 million states in the segments: the call takes 2.83 ms, 3.81
 // in the general path's five passes over signature rows; 512 pairs 6.17 ms,
-// 7.29.  Batches whose parts have at most 65,536 states and 8 letters are
-// faster with their ids in LDS (staged rounds, below); these rounds remain for
-// the others.
+// 7.29.  Batches whose parts have at most 65,536 states and 8 letters, and 896
+// states on average, are faster with their ids in LDS (staged rounds, below);
+// these rounds remain for the others.
 #include "device_common.h"
 
 namespace dfamin {

@@ -5,7 +5,7 @@
 // chain of launches and host waits.  Here one workgroup of 1,024 threads
 // keeps everything in LDS: the transitions (16-bit), two id arrays (16-bit)
 // and the grouping table, so every access of a round is an LDS access and a
-// round costs one barrier.  The same launch writes the canonical ids and the
+// round costs two barriers.  The same launch writes the canonical ids and the
 // quotient, and its figures go to page-locked host memory, so the call is
 // one launch and one wait.  Measured on MI355X, a call that minimises 1,009
 // states, 4 letters, with the quotient: 116 us with a launch per round, 43 us
