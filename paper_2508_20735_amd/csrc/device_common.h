@@ -148,6 +148,7 @@ __device__ __forceinline__ void report_round(const RoundCtl *ctl, HostProgress *
                                              uint32_t details, const RoundOutcome &o) {
     if (!host) return;
     const bool done = __syncthreads_or(o.done) != 0;
+    if (done || details) __syncthreads();  // (thread 0's stores to ctl)
     if (done) {
         constexpr uint32_t words = sizeof(RoundCtl) / sizeof(uint32_t);
         const uint32_t *src = reinterpret_cast<const uint32_t *>(ctl);
